@@ -143,7 +143,12 @@ typedef struct kf_options {
   int32_t want_vectors;  /* kf_result.vectors is filled when nonzero */
   int32_t index_bytes;   /* column-index width of the device operator:
                             0 = automatic (2 when every |col - row| < 32768),
-                            2 or 4 */
+                            2 or 4.  With 0 here, nt_loads 0, gather_unroll 0
+                            and block_band 0 or -1, an operator whose rows
+                            repeat (in every 64 consecutive rows the entries
+                            at one offset col - row have one value, as on
+                            uniform meshes) is stepped as stencils instead of
+                            stored entries, with the same results */
   int32_t xcd_remap;     /* 1: map consecutive row slices to the same XCD */
   int32_t nt_loads;      /* 1: stream the operator with non-temporal loads in
                             the fused time step */

@@ -1723,7 +1723,7 @@ int tune_block(kf_problem* p, SellOp& A, StepBufs& sb, int bk) {
   int best_l = 1, best_b = 0;
   // lanes per row, each with the gathers from the caches and (unless the
   // caller fixed it, and where the band copy fits) from LDS
-  const bool try_band = p->opt.block_band == 0;
+  const bool try_band = p->opt.block_band == 0 && A.st.width == 0;
   for (int l = 1; l <= std::min(bk, 4); l *= 2) {
     for (int band = 0; band <= 1; ++band) {
       if (band && (!try_band || band_lds_bytes(A, bk, l) > kBandLdsBytes)) continue;
@@ -1748,6 +1748,14 @@ int tune_block(kf_problem* p, SellOp& A, StepBufs& sb, int bk) {
 // index width (2 and 4 bytes when 2 fits) of the fused step, timed on this
 // operator; the fastest is kept.
 int autotune(kf_problem* p, DevCsr& dc, const double* d_scale) {
+  if (p->A.st.width > 0) {
+    // stencil slices: only the XCD mapping is left to choose
+    double us[2] = {0.0, 0.0};
+    for (int remap = 0; remap <= 1; ++remap) KF_TRY(time_variant_min(p, p->A, p->sb, remap, 20, &us[remap]));
+    p->opt.xcd_remap = us[1] < us[0] ? 1 : 0;
+    p->tuned_us = std::min(us[0], us[1]);
+    return KF_OK;
+  }
   SellOp alt;
   const bool try_alt = p->A.idx_bytes == 2;
   if (try_alt) {
@@ -1807,6 +1815,13 @@ int autotune(kf_problem* p, DevCsr& dc, const double* d_scale) {
   }
   p->tuned_us = best;
   return KF_OK;
+}
+
+// The stencil form of the slices replaces the stored entries unless the
+// caller fixed a choice that only those have (index width, non-temporal
+// loads, unroll factor, LDS band copy).
+bool layout_is_free(const kf_options& o) {
+  return o.index_bytes == 0 && o.nt_loads == 0 && o.gather_unroll == 0 && o.block_band != 1;
 }
 
 void free_problem(kf_problem* p) {
@@ -1956,9 +1971,10 @@ int kf_create(const kf_csr* S, const double* m_diag, double omega_min, double om
       break;
     }
     const int vb = o.precision == KF_MIXED ? 4 : 8;
-    rc = build_sell(p->n, p->nnz, dc.rowptr, dc.col, dc.val, d_scale, vb, o.index_bytes, p->st, p->A);
+    const bool stencil = layout_is_free(o);
+    rc = build_sell(p->n, p->nnz, dc.rowptr, dc.col, dc.val, d_scale, vb, o.index_bytes, p->st, p->A, stencil);
     if (!rc && o.precision == KF_MIXED && o.refine)
-      rc = build_sell(p->n, p->nnz, dc.rowptr, dc.col, dc.val, d_scale, 8, o.index_bytes, p->st, p->A64);
+      rc = build_sell(p->n, p->nnz, dc.rowptr, dc.col, dc.val, d_scale, 8, o.index_bytes, p->st, p->A64, stencil);
     if (!rc) rc = build_sell(p->n, p->nnz, dc.rowptr, dc.col, dc.val, nullptr, 8, o.index_bytes, p->st, p->S);
     if (rc) {
       dfree(d_scale);

@@ -33,6 +33,20 @@ void set_error(const std::string& msg);
 
 constexpr int kSlice = 64;  // SELL slice height = wavefront width
 
+// The slices of an operator whose rows repeat: in every slice the stored
+// entries with the same offset col - row have the same value (uniform meshes
+// and materials, any ordering).  A slice is then the list of its offsets in
+// ascending order, each with one value and a 64-bit mask of the rows that
+// store it: `width` entries per slice at [slice * stride], the tail with empty
+// masks.  Lossless: value, order of summation and result are the row's own.
+struct StencilOp {
+  int width = 0;   // entries of the longest slice; 0: not built
+  int stride = 0;  // entries stored per slice
+  void* val = nullptr;  // in the operator's precision
+  int32_t* off = nullptr;
+  uint64_t* mask = nullptr;
+};
+
 // Sliced-ELLPACK operator (slice height 64, one row per lane, entries of a
 // slice stored column by column so that lane l reads entry k of its row at
 // slice_ptr[s] + 64*k + l).  Column indices are either int32 absolute or
@@ -53,6 +67,7 @@ struct SellOp {
   int unroll = 0;                // single vectors: unroll of the loop over a slice's entries (2, 3, 4, 6; 0: 4)
   int32_t max_off = 0;           // largest |col - row| of a stored entry
   int band[5] = {0, 0, 0, 0, 0}; // blocks 2..16: 1 = gather from an LDS copy of the workgroup's band of rows
+  StencilOp st;                  // the slices as stencils (width 0: the operator has no such form)
 };
 
 // LDS available to the band copy of one workgroup of the fused step.
@@ -80,9 +95,12 @@ void free_sell(SellOp& op);
 // Build a SELL operator from a device CSR: values scaled per row by
 // row_scale[i] (device array, or nullptr for 1), stored as float64
 // (val_bytes 8) or float32 (val_bytes 4).  want_idx_bytes 0 chooses 2 when
-// every |col - row| < 32768.
+// every |col - row| < 32768.  stencil: also build out.st when every slice is
+// a stencil of at most kStencilMax offsets.
+constexpr int kStencilMax = 32;
 int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
-               const double* d_row_scale, int val_bytes, int want_idx_bytes, hipStream_t st, SellOp& out);
+               const double* d_row_scale, int val_bytes, int want_idx_bytes, hipStream_t st, SellOp& out,
+               bool stencil = false);
 
 // ---- fused leapfrog step ----------------------------------------------------
 enum StepMode { kMid = 0, kFirst = 1, kLast = 2, kFirstLast = 3, kMidAcc = 4 };

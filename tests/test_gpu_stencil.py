@@ -1,0 +1,80 @@
+"""Operators whose slices are stencils (every stored offset of a 64-row slice
+has one value) against the same operator in its stored-entry form
+(index_bytes fixed), bit for bit: the stencil form keeps the values and the
+order of summation of every row, so no tolerance is needed."""
+
+import numpy as np
+import pytest
+import scipy.sparse as sp
+
+from synth import start_block
+from synth.grids import grid_problem
+
+pytestmark = pytest.mark.gpu
+
+
+def _band(n, offsets):
+    """Symmetric constant-band matrix: value 1/(1+o) at offset +-o, diagonal
+    dominant; offsets past the matrix are dropped."""
+    offs = [o for o in offsets if 0 < o < n]
+    diags = [np.full(n, 4.0)] + [np.full(n - o, -1.0 / (1 + o)) for o in offs] * 2
+    return sp.csr_matrix(sp.diags(diags, [0] + offs + [-o for o in offs], shape=(n, n), format="csr"))
+
+
+def _matrix(kind):
+    if kind.startswith("grid"):
+        S, m, _ = grid_problem(int(kind[4]), int(kind[6:]))
+        return S, m
+    if kind == "broken":  # one row of one slice has a value of its own: no stencil
+        S = _band(200, [1, 9])
+        S[70, 70] = 5.0
+        return S, np.full(200, 0.5)
+    if kind == "mass":  # uneven row scaling
+        S = _band(200, [1, 9])
+        return S, np.linspace(0.5, 1.0, 200)
+    n, k = (int(v) for v in kind.split("x"))
+    return _band(n, list(range(1, k + 1))), np.full(n, 0.5)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("b", [1, 2, 3, 8, 16])
+@pytest.mark.parametrize(
+    "kind",
+    # rows x neighbours on one side: slice widths 1, 3, 5, 7 (the unrolled
+    # lengths), 9, 31 and 33 (one past the longest stencil); less than a
+    # slice, one slice, one row more, several
+    ["1x1", "63x1", "64x2", "65x3", "130x4", "200x15", "200x16", "grid2_23", "grid3_9", "broken", "mass"],
+)
+def test_stencil_slices_match_stored_entries_bitwise(kind, b, precision):
+    import torch
+
+    from paper_2402_08515_amd import kf
+
+    print(f"case stencil kind={kind} b={b} {precision}", flush=True)
+    S, m = _matrix(kind)
+    n = S.shape[0]
+    lam = np.abs(S).sum(1).max() / m.min()
+    tau = 1.8 / np.sqrt(lam)
+    x = torch.from_numpy(start_block(n, b, 7)).cuda()
+    for L in (2, 3, 8):  # first = last step, one middle step, steps with and without the sum
+        out = []
+        for ib in (0, 4):
+            P = kf.Problem(S, m, 0.3 / tau, 0.6 / tau, tau, L, precision=precision, index_bytes=ib)
+            out.append(P.apply_filter(x))
+        assert torch.equal(out[0], out[1]), (L, (out[0] - out[1]).abs().max())
+
+
+@pytest.mark.parametrize("lpr", [1, 2, 4])
+@pytest.mark.parametrize("b", [2, 4, 16])
+def test_stencil_lanes_per_row_bitwise(b, lpr):
+    import torch
+
+    from paper_2402_08515_amd import kf
+
+    S, m, _ = grid_problem(3, 11)
+    tau = 1.8 / np.sqrt(12.0 * 11 * 11)
+    x = torch.from_numpy(start_block(S.shape[0], b, 8)).cuda()
+    for precision in ("fp64", "mixed"):
+        out = [kf.Problem(S, m, 4.0, 8.0, tau, 7, precision=precision, index_bytes=ib, lanes_per_row=lpr).apply_filter(x)
+               for ib in (0, 2)]
+        assert torch.equal(out[0], out[1])
