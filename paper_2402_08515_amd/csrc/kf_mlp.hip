@@ -62,111 +62,78 @@ __device__ __forceinline__ short to_bf16(float f) {
   return (short)(u >> 16);
 }
 
-// C[M x N] (row-major, ldc) (+)= op(A)[M x K] * op(B)[K x N]
-//   TA = 0: A[m*lda + k]; TA = 1: A[k*lda + m]
-//   TB = 0: B[k*ldb + n]; TB = 1: B[n*ldb + k]
-// 64 x 64 tile per workgroup of 4 wavefronts, 32 x 32 per wavefront.
-// Requires M % 64 == 0, N % 64 == 0, K % 16 == 0.
-template <int TA, int TB, bool BF16>
-__global__ __launch_bounds__(256) void k_gemm(int M, int N, int K, const float* __restrict__ A, int lda,
-                                              const float* __restrict__ B, int ldb, float* __restrict__ C, int ldc,
-                                              int accumulate) {
-  __shared__ float As[64][17];
-  __shared__ float Bs[16][65];
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  f32x4 acc[2][2];
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int t = tid; t < 64 * 16; t += 256) {
-      const int mm = t >> 4, kk = t & 15;
-      As[mm][kk] = TA ? A[(int64_t)(k0 + kk) * lda + m0 + mm] : A[(int64_t)(m0 + mm) * lda + k0 + kk];
-    }
-    for (int t = tid; t < 16 * 64; t += 256) {
-      const int kk = t >> 6, nn = t & 63;
-      Bs[kk][nn] = TB ? B[(int64_t)(n0 + nn) * ldb + k0 + kk] : B[(int64_t)(k0 + kk) * ldb + n0 + nn];
-    }
-    __syncthreads();
-    const int r16 = lane & 15, q4 = lane >> 4;
-    for (int i = 0; i < 2; ++i) {
-      for (int j = 0; j < 2; ++j) {
-        const int r = wm + 16 * i + r16;
-        const int cc = wn + 16 * j + r16;
-        if (BF16) {
-          // lane holds A[r][4*q4 .. 4*q4+3] and B[4*q4 .. 4*q4+3][cc]
-          bf16x4 a, b;
-          for (int q = 0; q < 4; ++q) {
-            a[q] = to_bf16(As[r][4 * q4 + q]);
-            b[q] = to_bf16(Bs[4 * q4 + q][cc]);
-          }
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[i][j], 0, 0, 0);
-        } else {
-          // four k-slices of 4: lane holds A[r][4s + q4] and B[4s + q4][cc]
-          for (int sl = 0; sl < 4; ++sl)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(As[r][4 * sl + q4], Bs[4 * sl + q4][cc], acc[i][j], 0, 0, 0);
-        }
-      }
-    }
-    __syncthreads();
-  }
-  // lane holds D[4*q4 + q][r16] of each 16 x 16 tile
-  const int r16 = lane & 15, q4 = lane >> 4;
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j)
-      for (int q = 0; q < 4; ++q) {
-        const int row = m0 + wm + 16 * i + 4 * q4 + q;
-        const int col = n0 + wn + 16 * j + r16;
-        float* cp = C + (int64_t)row * ldc + col;
-        *cp = accumulate ? *cp + acc[i][j][q] : acc[i][j][q];
-      }
+// A training step of 256 samples is five launches: k_forward (all layers of a
+// row group in one workgroup, the Fourier weights beside them), k_response for
+// beta~ and for dw, k_backward, and k_update (weight gradients, biases, losses
+// and Adam).  Its products take 0.4 GFLOP: what bounds it is the latency of
+// five dependent launches, 5 to 9 us each; 43 us a step against 678 us with a
+// launch per product, bias, activation and reduction and a host wait per step.
+// The gradient of 1024 samples: 67 us of kernels instead of 1.8 ms.  The
+// float32 products alone (k_response) would take 1.7 us of matrix cores at 256
+// samples and cannot be split along k without changing their rounding.
+
+// ---- operand fragments
+// A matrix instruction takes 16 x 16 tiles: lane (r16 = lane % 16, q4 =
+// lane / 16) supplies four consecutive k = 4 q4 + q of row (or column) r16 and
+// receives D[4 q4 + q][r16].  Everything one kernel hands to another for such
+// a product is stored tile by tile in that lane order, one 8-byte run of four
+// bfloat16 per lane and tile, so that an operand is one contiguous load: the
+// weights in both orientations (forward: k = layer input; backward: k = layer
+// output), and activations and their gradients for the weight gradients
+// (k = sample).  All products take their k tiles in ascending order with one
+// accumulator per output, whatever the launch shape.
+constexpr int kFwd1 = 0;                                  // [128/16][64/16] tiles of 64 fragments
+constexpr int kFwd2 = kFwd1 + (kH / 16) * (kNF / 16) * 64;
+constexpr int kFwd3 = kFwd2 + (kH / 16) * (kH / 16) * 64;
+constexpr int kFwd4 = kFwd3 + (kH / 16) * (kH / 16) * 64;
+constexpr int kBwd2 = kFwd4 + (kLM / 16) * (kH / 16) * 64;
+constexpr int kBwd3 = kBwd2 + (kH / 16) * (kH / 16) * 64;
+constexpr int kBwd4 = kBwd3 + (kH / 16) * (kH / 16) * 64;
+constexpr int kNFrag = kBwd4 + (kH / 16) * (kLM / 16) * 64;
+constexpr int kPrm = 8;  // per sample: the two float4 of Band
+
+// layer i = 0..3: parameter offset, inputs, outputs, fragment offsets
+struct Layer {
+  int off, bias, in, out, fwd, bwd;
+};
+__host__ __device__ constexpr Layer layer_of(int i) {
+  return i == 0   ? Layer{kOffW1, kOffB1, kNF, kH, kFwd1, -1}
+         : i == 1 ? Layer{kOffW2, kOffB2, kH, kH, kFwd2, kBwd2}
+         : i == 2 ? Layer{kOffW3, kOffB3, kH, kH, kFwd3, kBwd3}
+                  : Layer{kOffW4, kOffB4, kH, kLM, kFwd4, kBwd4};
 }
 
-// per sample: features, (a, c, L, x_max), Fourier weights
-__global__ void k_prepare(int B, const double* __restrict__ smp, const int32_t* __restrict__ idx,
-                          const int32_t* __restrict__ Lover, float* __restrict__ feat, float* __restrict__ prm,
-                          float* __restrict__ wF) {
-  const int s = blockIdx.x;
-  if (s >= B) return;
-  const double* r = smp + 4 * (int64_t)(idx ? idx[s] : s);
-  const double a = r[2] * r[0], c = r[2] * r[1];
-  int L = (int)ceil(2.0 * kPi / a);
-  if (Lover) L = Lover[0];
-  if (L > kLM) L = kLM;
-  if (L < 1) L = 1;
-  const double xm = 0.5 * r[2] * sqrt(r[3]);
-  if (threadIdx.x == 0) {
-    prm[4 * s + 0] = (float)a;
-    prm[4 * s + 1] = (float)c;
-    prm[4 * s + 2] = (float)L;
-    prm[4 * s + 3] = (float)xm;
-  }
-  if (threadIdx.x < kNF) {
-    const int t = threadIdx.x;
-    float v = 0.f;
-    if (t == 0) v = (float)(a / kPi);
-    if (t == 1) v = (float)(c / kPi);
-    if (t == 2) v = (float)xm;
-    if (t == 3) v = (float)L / kLM;
-    feat[(int64_t)s * kNF + t] = v;
-  }
-  for (int l = threadIdx.x; l < kLM; l += blockDim.x) {
-    double w = 0.0;
-    if (l == 0)
-      w = 2.0 * (c - a) / kPi;
-    else if (l < L)
-      w = 4.0 / (kPi * l) * sin(0.5 * l * (c - a)) * cos(0.5 * l * (c + a));
-    wF[(int64_t)s * kLM + l] = (float)w;
+// the weight W[row][col] of layer L into its fragments
+__device__ __forceinline__ void put_fragments(const Layer L, int row, int col, float v, short* __restrict__ frag) {
+  const short h = to_bf16(v);
+  const int kt = row >> 4, nt = col >> 4;
+  frag[((int64_t)(L.fwd + (nt * (L.in >> 4) + kt) * 64 + ((row & 15) >> 2) * 16 + (col & 15))) * 4 + (row & 3)] = h;
+  if (L.bwd >= 0)
+    frag[((int64_t)(L.bwd + (kt * (L.out >> 4) + nt) * 64 + ((col & 15) >> 2) * 16 + (row & 15))) * 4 + (col & 3)] = h;
+}
+
+__global__ __launch_bounds__(256) void k_pack(const float* __restrict__ theta, short* __restrict__ frag) {
+  const int p = blockIdx.x * 256 + threadIdx.x;
+  for (int i = 0; i < 4; ++i) {
+    const Layer L = layer_of(i);
+    const int t = p - L.off;
+    if (t >= 0 && t < L.in * L.out) put_fragments(L, t / L.out, t % L.out, theta[p], frag);
   }
 }
 
-__global__ void k_qmat(float* __restrict__ Q) {
+// Q[l][g] = q_l(x_g) for the float32 products beta~ = w Q (k = l) and dw =
+// dbeta Q^T (k = g), tile by tile: lane (r16, q4) of tile (n tile, k tile)
+// holds the four k = 4 sl + q4, sl < 4, of column r16 (v_mfma_f32_16x16x4
+// takes one k per lane group).
+__global__ void k_qmat(float* __restrict__ Qf, float* __restrict__ Qt) {
   const int l = blockIdx.x;
   for (int g = threadIdx.x; g < kG; g += blockDim.x) {
     const double x = kXmaxGrid * g / (kG - 1);
     const double phi = 2.0 * asin(x);
-    Q[(int64_t)l * kG + g] = (float)(cos((l + 0.5) * phi) / cos(0.5 * phi));
+    const float v = (float)(cos((l + 0.5) * phi) / cos(0.5 * phi));
+    auto at = [](int n, int k) { return (((n >> 4) * 32 + (k >> 4)) * 64 + (k & 3) * 16 + (n & 15)) * 4 + ((k >> 2) & 3); };
+    Qf[at(g, l)] = v;
+    Qt[at(l, g)] = v;
   }
 }
 
@@ -175,123 +142,506 @@ __device__ __forceinline__ float gelu_g(float z) {
   return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
 }
 
-// Z += bias; H = gelu(Z)
-__global__ void k_bias_gelu(int M, int N, float* __restrict__ Z, const float* __restrict__ b, float* __restrict__ H) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)M * N) return;
-  const float z = Z[t] + b[t % N];
-  Z[t] = z;
-  H[t] = gelu_f(z);
+// A sample's constants: the band [a/2, c/2] of the loss grid and its edges
+// widened by pi/(2L), x_max, the number of weights, and the numbers of grid
+// points in the band and outside (x <= x_max, beyond the widened band).
+struct Band {
+  float lo, hi, wlo, whi, xm, L, ni, no;
+  __device__ __forceinline__ Band(float a, float c, float Lf, float xm_) : xm(xm_), L(Lf), ni(1.f), no(1.f) {
+    lo = 0.5f * a;
+    hi = 0.5f * c;
+    const float d = (float)(kPi / (2.0 * Lf));
+    wlo = lo - d;
+    whi = hi + d;
+  }
+  __device__ __forceinline__ Band(const float* __restrict__ prm, int64_t s) {
+    const float4 u = reinterpret_cast<const float4*>(prm)[2 * s], v = reinterpret_cast<const float4*>(prm)[2 * s + 1];
+    lo = u.x, hi = u.y, wlo = u.z, whi = u.w;
+    xm = v.x, L = v.y, ni = v.z, no = v.w;
+  }
+  __device__ __forceinline__ void store(float* __restrict__ prm, int64_t s) const {
+    reinterpret_cast<float4*>(prm)[2 * s] = make_float4(lo, hi, wlo, whi);
+    reinterpret_cast<float4*>(prm)[2 * s + 1] = make_float4(xm, L, ni, no);
+  }
+  static __device__ __forceinline__ float x(int g) { return kXmaxGrid * g / (kG - 1); }
+  __device__ __forceinline__ bool in(float v) const { return v >= lo && v <= hi; }
+  __device__ __forceinline__ bool out(float v) const { return v <= xm && (v < wlo || v > whi); }
+};
+
+struct Sample {
+  double a, c, xm;
+  int L;
+  __device__ __forceinline__ Sample(const double* __restrict__ r, const int32_t* __restrict__ Lover) {
+    a = r[2] * r[0];
+    c = r[2] * r[1];
+    L = (int)ceil(2.0 * kPi / a);
+    if (Lover) L = Lover[0];
+    if (L > kLM) L = kLM;
+    if (L < 1) L = 1;
+    xm = 0.5 * r[2] * sqrt(r[3]);
+  }
+};
+
+// One 16 x 16 tile: A (16 x 16 KT, bfloat16 rows in LDS, row stride ld) times
+// the KT fragments of a column tile, which the caller loads long before (a
+// kernel's weights do not depend on its rows, so their latency overlaps the
+// staging and the layers before).
+template <int KT>
+__device__ __forceinline__ void load_tiles(const bf16x4* __restrict__ b, int lane, bf16x4 (&f)[KT]) {
+#pragma unroll
+  for (int u = 0; u < KT; ++u) f[u] = b[u * 64 + lane];
+}
+template <int KT>
+__device__ __forceinline__ f32x4 tile_product(const short* A, int ld, const bf16x4 (&f)[KT], int lane) {
+  const short* ap = A + (lane & 15) * ld + 4 * (lane >> 4);
+  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int u = 0; u < KT; ++u)
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*reinterpret_cast<const bf16x4*>(ap + u * 16), f[u], acc, 0, 0, 0);
+  return acc;
 }
 
-// w = (wF + s * (out + b4)) * [l < L]
+__device__ __forceinline__ bf16x4 pack4(const float (&v)[4]) {
+  return bf16x4{to_bf16(v[0]), to_bf16(v[1]), to_bf16(v[2]), to_bf16(v[3])};
+}
+
+// Forward through the four layers, 16 samples per group of four workgroups
+// (the hidden layers are computed by all four, the output layer's 512 columns
+// are divided; one wavefront per 16 columns), and beside them one workgroup
+// per sample for what does not depend on the parameters: the Fourier weights,
+// the sample's constants and its grid-point counts.  The hidden rows stay in
+// LDS between the layers; the first workgroup of a group stores what the
+// backward pass needs.
+constexpr int kHs = kH + 8;  // LDS row stride (bfloat16)
+__global__ __launch_bounds__(512) void k_forward(int B, int nnet, const double* __restrict__ smp,
+                                                 const int32_t* __restrict__ idx, const int32_t* __restrict__ Lover,
+                                                 const float* __restrict__ theta, const bf16x4* __restrict__ frag,
+                                                 bf16x4* __restrict__ xf, float* __restrict__ z,
+                                                 bf16x4* __restrict__ hf, float* __restrict__ out,
+                                                 float* __restrict__ prm, float* __restrict__ wF) {
+  __shared__ __align__(16) short hs[2][16][kHs];
+  __shared__ int cnt[2][8];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int r16 = lane & 15, q4 = lane >> 4;
+  if ((int)blockIdx.x >= nnet) {
+    const int s = blockIdx.x - nnet;
+    const double* r = smp + 4 * (int64_t)(idx ? idx[s] : s);
+    const Sample S(r, Lover);
+    Band band((float)S.a, (float)S.c, (float)S.L, (float)S.xm);
+    const float x = Band::x(tid);
+    const bool in = band.in(x);
+    const bool ou = !in && band.out(x);
+    const int ni = __popcll(__ballot(in)), no = __popcll(__ballot(ou));
+    if (lane == 0) {
+      cnt[0][wave] = ni;
+      cnt[1][wave] = no;
+    }
+    double w = 0.0;
+    if (tid == 0)
+      w = 2.0 * (S.c - S.a) / kPi;
+    else if (tid < S.L)
+      w = 4.0 / (kPi * tid) * sin(0.5 * tid * (S.c - S.a)) * cos(0.5 * tid * (S.c + S.a));
+    wF[(int64_t)s * kLM + tid] = (float)w;
+    __syncthreads();
+    if (tid == 0) {
+      int n0 = 0, n1 = 0;
+      for (int i = 0; i < 8; ++i) {
+        n0 += cnt[0][i];
+        n1 += cnt[1][i];
+      }
+      band.ni = fmaxf((float)n0, 1.f);
+      band.no = fmaxf((float)n1, 1.f);
+      band.store(prm, s);
+    }
+    return;
+  }
+  const int st = blockIdx.x >> 2, part = blockIdx.x & 3, nst = B >> 4;
+  const bool keep = part == 0;
+  const int nt = part * 8 + wave;
+  bf16x4 f1[kNF / 16], f2[kH / 16], f3[kH / 16], f4[kH / 16];
+  load_tiles(frag + kFwd1 + wave * (kNF / 16) * 64, lane, f1);
+  load_tiles(frag + kFwd2 + wave * (kH / 16) * 64, lane, f2);
+  load_tiles(frag + kFwd3 + wave * (kH / 16) * 64, lane, f3);
+  load_tiles(frag + kFwd4 + nt * (kH / 16) * 64, lane, f4);
+  for (int t = tid; t < 16 * kNF; t += 512) hs[0][t / kNF][t % kNF] = 0;
+  __syncthreads();
+  if (tid < 16) {
+    const int s = st * 16 + tid;
+    const Sample S(smp + 4 * (int64_t)(idx ? idx[s] : s), Lover);
+    hs[0][tid][0] = to_bf16((float)(S.a / kPi));
+    hs[0][tid][1] = to_bf16((float)(S.c / kPi));
+    hs[0][tid][2] = to_bf16((float)S.xm);
+    hs[0][tid][3] = to_bf16((float)S.L / kLM);
+  }
+  __syncthreads();
+  if (keep && wave < kNF / 16) {
+    bf16x4 v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = hs[0][4 * q4 + q][wave * 16 + r16];
+    xf[((int64_t)wave * nst + st) * 64 + lane] = v;
+  }
+  int src = 0;
+  const int n = wave * 16 + r16;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const Layer L = layer_of(i);
+    const float bias = theta[L.bias + n];
+    const f32x4 acc = i == 0   ? tile_product(&hs[src][0][0], kHs, f1, lane)
+                      : i == 1 ? tile_product(&hs[src][0][0], kHs, f2, lane)
+                               : tile_product(&hs[src][0][0], kHs, f3, lane);
+    float h[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float zv = acc[q] + bias;
+      h[q] = gelu_f(zv);
+      if (keep) z[((int64_t)i * B + st * 16 + 4 * q4 + q) * kH + n] = zv;
+      hs[src ^ 1][4 * q4 + q][n] = to_bf16(h[q]);
+    }
+    if (keep) hf[((int64_t)(i * (kH / 16) + wave) * nst + st) * 64 + lane] = pack4(h);
+    __syncthreads();
+    src ^= 1;
+  }
+  const f32x4 acc = tile_product(&hs[src][0][0], kHs, f4, lane);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) out[(int64_t)(st * 16 + 4 * q4 + q) * kLM + nt * 16 + r16] = acc[q];
+}
+
+// w = (wF + s (out + b4)) [l < L], the correction left out without the network
+__device__ __forceinline__ float weight_of(float out, float b4, float wF, int l, float Lf, int use_net) {
+#pragma clang fp contract(off)
+  const float d = use_net ? kOut * (out + b4) : 0.f;
+  return l < (int)Lf ? wF + d : 0.f;
+}
+
 __global__ void k_out_weights(int B, const float* __restrict__ out, const float* __restrict__ b4,
                               const float* __restrict__ wF, const float* __restrict__ prm, float* __restrict__ w,
                               int use_net) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (int64_t)B * kLM) return;
   const int s = (int)(t / kLM), l = (int)(t % kLM);
-  const int L = (int)prm[4 * s + 2];
-  const float d = use_net ? kOut * (out[t] + b4[l]) : 0.f;
-  w[t] = l < L ? wF[t] + d : 0.f;
+  w[t] = weight_of(use_net ? out[t] : 0.f, b4[l], wF[t], l, Band(prm, s).L, use_net);
 }
 
-// per sample (one workgroup): loss J and dJ/dbeta (scaled by 1/B)
-__global__ __launch_bounds__(256) void k_loss(int B, const float* __restrict__ beta, const float* __restrict__ prm,
-                                              float* __restrict__ dbeta, float* __restrict__ J, float scale) {
-  __shared__ float red[4][4];
-  const int s = blockIdx.x;
-  const float a = prm[4 * s], c = prm[4 * s + 1], Lf = prm[4 * s + 2], xm = prm[4 * s + 3];
-  const float lo = 0.5f * a, hi = 0.5f * c, d = (float)(kPi / (2.0 * Lf));
-  float ni = 0.f, no = 0.f, ji = 0.f, jo = 0.f;
-  for (int g = threadIdx.x; g < kG; g += blockDim.x) {
-    const float x = kXmaxGrid * g / (kG - 1);
-    const float bt = beta[(int64_t)s * kG + g];
-    if (x >= lo && x <= hi) {
-      ni += 1.f;
-      ji += (bt - 1.f) * (bt - 1.f);
-    } else if (x <= xm && (x < lo - d || x > hi + d)) {
-      no += 1.f;
-      jo += bt * bt;
+// The two float32 products with the response matrix, 16 rows x 64 columns
+// per workgroup, one wavefront per 16 columns (the k order is fixed, so the
+// work is spread over rows and columns only).  BACK = 0: beta~ = w Q with w
+// formed while the rows are staged; writes w, beta~ and (grad) dJ/dbeta~.
+// BACK = 1: dw = dbeta~ Q^T, and from it the output layer's gradient dz =
+// s dw [l < L] as rows and as fragments.
+constexpr int kRs = kG + 4;  // LDS row stride (float32)
+template <int BACK>
+__global__ __launch_bounds__(256) void k_response(int B, const float* __restrict__ src, const float* __restrict__ b4,
+                                                  const float* __restrict__ wF, const float* __restrict__ prm,
+                                                  const float4* __restrict__ Q, int use_net, float scale,
+                                                  float* __restrict__ w, float* __restrict__ res,
+                                                  float* __restrict__ dbeta, bf16x4* __restrict__ dzf) {
+  __shared__ __align__(16) float xs[16][kRs];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int r16 = lane & 15, q4 = lane >> 4;
+  const int st = blockIdx.y, nt = blockIdx.x * 4 + wave;
+  const float4* __restrict__ qp = Q + (int64_t)nt * 32 * 64 + lane;
+  constexpr int U = 8;
+  float4 cur[U], nxt[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) cur[u] = qp[u * 64];
+  const Band band[4] = {Band(prm, st * 16 + 4 * q4), Band(prm, st * 16 + 4 * q4 + 1), Band(prm, st * 16 + 4 * q4 + 2),
+                        Band(prm, st * 16 + 4 * q4 + 3)};
+  // a thread stages columns tid and tid + 256 of the 16 rows, eight rows of
+  // loads at a time; k = 4 sl + q4 of a 16-block sits at 4 q4 + sl, so that a
+  // lane's four are one read
+#pragma unroll
+  for (int r0 = 0; r0 < 16; r0 += 8) {
+    float va[8][2], vf[8][2];
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int64_t g = (int64_t)(st * 16 + r0 + r) * kG + tid + 256 * h;
+        va[r][h] = BACK || use_net ? src[g] : 0.f;
+        vf[r][h] = BACK ? 0.f : wF[g];
+      }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = tid + 256 * h;
+      const float bias = BACK ? 0.f : b4[k];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        float v = va[r][h];
+        if (!BACK) {
+          v = weight_of(v, bias, vf[r][h], k, prm[(int64_t)(st * 16 + r0 + r) * kPrm + 5], use_net);
+          if (blockIdx.x == 0) w[(int64_t)(st * 16 + r0 + r) * kG + k] = v;
+        }
+        xs[r0 + r][(k & ~15) + (k & 3) * 4 + ((k >> 2) & 3)] = v;
+      }
     }
   }
-  float v[4] = {ni, no, ji, jo};
-  for (int q = 0; q < 4; ++q)
-    for (int off = 32; off > 0; off >>= 1) v[q] += __shfl_xor(v[q], off);
-  if ((threadIdx.x & 63) == 0)
-    for (int q = 0; q < 4; ++q) red[q][threadIdx.x >> 6] = v[q];
   __syncthreads();
-  for (int q = 0; q < 4; ++q) v[q] = red[q][0] + red[q][1] + red[q][2] + red[q][3];
-  const float NI = fmaxf(v[0], 1.f), NO = fmaxf(v[1], 1.f);
-  if (threadIdx.x == 0 && J) J[s] = v[2] / NI + v[3] / NO;
-  if (!dbeta) return;
-  for (int g = threadIdx.x; g < kG; g += blockDim.x) {
-    const float x = kXmaxGrid * g / (kG - 1);
-    const float bt = beta[(int64_t)s * kG + g];
-    float gr = 0.f;
-    if (x >= lo && x <= hi)
-      gr = 2.f * (bt - 1.f) / NI;
-    else if (x <= xm && (x < lo - d || x > hi + d))
-      gr = 2.f * bt / NO;
-    dbeta[(int64_t)s * kG + g] = gr * scale;
+  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k0 = 0; k0 < 32; k0 += U) {
+    if (k0 + U < 32) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) nxt[u] = qp[(k0 + U + u) * 64];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float4 a = *reinterpret_cast<const float4*>(&xs[r16][(k0 + u) * 16 + 4 * q4]);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, cur[u].x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, cur[u].y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, cur[u].z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, cur[u].w, acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) cur[u] = nxt[u];
+  }
+  const int n = nt * 16 + r16;
+  if (BACK) {
+    float d[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int s = st * 16 + 4 * q4 + q;
+      d[q] = n < (int)band[q].L ? kOut * acc[q] : 0.f;
+      res[(int64_t)s * kLM + n] = d[q];
+    }
+    dzf[((int64_t)nt * (B >> 4) + st) * 64 + lane] = pack4(d);
+  } else {
+    const float x = Band::x(n);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int s = st * 16 + 4 * q4 + q;
+      const float bt = acc[q];
+      res[(int64_t)s * kG + n] = bt;
+      if (dbeta) {
+        float gr = 0.f;
+        if (band[q].in(x))
+          gr = 2.f * (bt - 1.f) / band[q].ni;
+        else if (band[q].out(x))
+          gr = 2.f * bt / band[q].no;
+        dbeta[(int64_t)s * kG + n] = gr * scale;
+      }
+    }
   }
 }
 
-// dout = s * dw * [l < L]
-__global__ void k_mask_scale(int B, const float* __restrict__ dw, const float* __restrict__ prm,
-                             float* __restrict__ dout) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)B * kLM) return;
-  const int s = (int)(t / kLM), l = (int)(t % kLM);
-  dout[t] = l < (int)prm[4 * s + 2] ? kOut * dw[t] : 0.f;
+// The loss of sample s by one wavefront: lane l takes g = 64 p + l and
+// 64 p + l + 256 for p = 0..3, the four parts are summed in order.
+__device__ __forceinline__ float sample_loss(const float* __restrict__ beta, const float* __restrict__ prm, int s,
+                                             int lane) {
+  const Band band(prm, s);
+  float bt[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) bt[i] = beta[(int64_t)s * kG + 64 * (i >> 1) + lane + 256 * (i & 1)];
+  float ji = 0.f, jo = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float a = 0.f, b = 0.f;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const float v = bt[2 * i + h], x = Band::x(64 * i + lane + 256 * h);
+      if (band.in(x))
+        a = fmaf(v - 1.f, v - 1.f, a);
+      else if (band.out(x))
+        b = fmaf(v, v, b);
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      a += __shfl_xor(a, off);
+      b += __shfl_xor(b, off);
+    }
+    ji = i ? ji + a : a;
+    jo = i ? jo + b : b;
+  }
+  return ji / band.ni + jo / band.no;
 }
 
-// D = D * gelu'(Z)
-__global__ void k_gelu_back(int64_t n, float* __restrict__ D, const float* __restrict__ Z) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < n) D[t] *= gelu_g(Z[t]);
+__global__ __launch_bounds__(256) void k_loss(int B, const float* __restrict__ beta, const float* __restrict__ prm,
+                                              float* __restrict__ J) {
+  const int s = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (s >= B) return;
+  const float v = sample_loss(beta, prm, s, lane);
+  if (lane == 0) J[s] = v;
 }
 
-// out[n] = sum over rows (fixed order)
-__global__ void k_colsum(int M, int N, const float* __restrict__ X, float* __restrict__ out) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= N) return;
-  float s = 0.f;
-  for (int m = 0; m < M; ++m) s += X[(int64_t)m * N + n];
-  out[n] = s;
-}
-
-__global__ void k_adam(int n, float* __restrict__ th, const float* __restrict__ g, float* __restrict__ m1,
-                       float* __restrict__ m2, float lr, float b1, float b2, float eps, float c1, float c2) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n) return;
-  const float gg = g[t];
-  const float a = b1 * m1[t] + (1.f - b1) * gg;
-  const float b = b2 * m2[t] + (1.f - b2) * gg * gg;
-  m1[t] = a;
-  m2[t] = b;
-  th[t] -= lr * (a / c1) / (sqrtf(b / c2) + eps);
-}
-
-__global__ void k_mean(int B, const float* __restrict__ J, float* __restrict__ out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    double s = 0.0;
-    for (int i = 0; i < B; ++i) s += J[i];
-    out[0] = (float)(s / B);
+// Backward through the hidden layers, 16 samples per workgroup: each of the
+// eight wavefronts carries one 16-column tile through the three products
+// (rows in LDS as bfloat16 between them).
+__global__ __launch_bounds__(512) void k_backward(int B, const float* __restrict__ dz4, const float* __restrict__ z,
+                                                  const bf16x4* __restrict__ frag, float* __restrict__ dz,
+                                                  bf16x4* __restrict__ dzf) {
+  __shared__ __align__(16) short d4[16][kLM + 8];
+  __shared__ __align__(16) short ds[2][16][kHs];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int r16 = lane & 15, q4 = lane >> 4;
+  const int st = blockIdx.x, nst = B >> 4;
+  const int n = wave * 16 + r16;
+  float dv[16];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) dv[u] = dz4[(int64_t)(st * 16) * kLM + tid + 512 * u];
+  bf16x4 f4[kLM / 16], f3[kH / 16], f2[kH / 16];
+  load_tiles(frag + kBwd4 + wave * (kLM / 16) * 64, lane, f4);
+  load_tiles(frag + kBwd3 + wave * (kH / 16) * 64, lane, f3);
+  load_tiles(frag + kBwd2 + wave * (kH / 16) * 64, lane, f2);
+  float zv[3][4];
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) zv[i][q] = z[((int64_t)i * B + st * 16 + 4 * q4 + q) * kH + n];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) d4[u][tid] = to_bf16(dv[u]);
+  __syncthreads();
+#pragma unroll
+  for (int i = 2; i >= 0; --i) {
+    const f32x4 acc = i == 2   ? tile_product(&d4[0][0], kLM + 8, f4, lane)
+                      : i == 1 ? tile_product(&ds[i & 1][0][0], kHs, f3, lane)
+                               : tile_product(&ds[i & 1][0][0], kHs, f2, lane);
+    float d[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      d[q] = acc[q] * gelu_g(zv[i][q]);
+      dz[((int64_t)i * B + st * 16 + 4 * q4 + q) * kH + n] = d[q];
+      ds[(i & 1) ^ 1][4 * q4 + q][n] = to_bf16(d[q]);
+    }
+    dzf[((int64_t)(i * (kH / 16) + wave) * nst + st) * 64 + lane] = pack4(d);
+    __syncthreads();
   }
 }
 
-template <int TA, int TB, bool BF16>
-int gemm(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc, int acc,
-         hipStream_t st) {
-  if (M % 64 || N % 64 || K % 16) {
-    set_error("mlp gemm: shapes must be multiples of 64 / 64 / 16");
-    return KF_EINVAL;
+struct AdamStep {
+  float lr, c1, c2;  // c1 = 0: no update (the gradient is stored instead)
+};
+
+__device__ __forceinline__ float adam(int p, float g, float th, float* __restrict__ m1, float* __restrict__ m2,
+                                      const AdamStep& o) {
+  const float a = fmaf(1.f - 0.9f, g, 0.9f * m1[p]);
+  const float b = fmaf(g, (1.f - 0.999f) * g, 0.999f * m2[p]);
+  m1[p] = a;
+  m2[p] = b;
+  return th - o.lr * (a / o.c1) / (sqrtf(b / o.c2) + 1e-8f);
+}
+
+// Gradients of all parameters, and in training the Adam step on the spot (the
+// gradient is never stored).  One wavefront per 16 x 16 tile of a weight
+// matrix (416 tiles, both operands one contiguous run per 16 samples), then
+// one workgroup per 64 biases: four wavefronts stage rows, the first sums
+// them in row order; then the samples' losses, one wavefront each.
+constexpr int kTiles4 = (kH / 16) * (kLM / 16), kTilesH = (kH / 16) * (kH / 16), kTiles1 = (kNF / 16) * (kH / 16);
+constexpr int kTileBlocks = (kTiles4 + 2 * kTilesH + kTiles1) / 4;
+constexpr int kBiasBlocks = (kLM + 3 * kH) / 64;
+__global__ __launch_bounds__(256) void k_update(int B, const bf16x4* __restrict__ xf, const bf16x4* __restrict__ hf,
+                                                const bf16x4* __restrict__ dzf, const bf16x4* __restrict__ dzf4,
+                                                const float* __restrict__ dz, const float* __restrict__ dz4,
+                                                float* __restrict__ theta, float* __restrict__ m1,
+                                                float* __restrict__ m2, float* __restrict__ grad,
+                                                short* __restrict__ frag, const float* __restrict__ beta,
+                                                const float* __restrict__ prm, float* __restrict__ J, AdamStep o) {
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int nst = B >> 4;
+  if ((int)blockIdx.x >= kTileBlocks + kBiasBlocks) {
+    const int s = (blockIdx.x - kTileBlocks - kBiasBlocks) * 4 + wave;
+    const float v = sample_loss(beta, prm, s, lane);
+    if (lane == 0) J[s] = v;
+    return;
   }
-  hipLaunchKernelGGL((k_gemm<TA, TB, BF16>), dim3(N / 64, M / 64), dim3(256), 0, st, M, N, K, A, lda, B, ldb, C, ldc,
-                     acc);
-  KF_HIP(hipGetLastError());
-  return KF_OK;
+  if ((int)blockIdx.x >= kTileBlocks) {
+    __shared__ float rows[64][64];
+    int c = (blockIdx.x - kTileBlocks) * 64;  // first of this workgroup's biases, counted b4, b3, b2, b1
+    int i = 3;
+    const float* src = dz4;
+    int ld = kLM;
+    if (c >= kLM) {
+      c -= kLM;
+      i = 2 - c / kH;
+      c %= kH;
+      src = dz + (int64_t)i * B * kH;
+      ld = kH;
+    }
+    src += c + lane;
+    float s = 0.f;
+    float v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = src[(int64_t)(wave + 4 * u) * ld];
+    for (int r0 = 0; r0 < B; r0 += 64) {
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < 16; ++u) rows[wave + 4 * u][lane] = v[u];
+      __syncthreads();
+      if (r0 + 64 < B) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = src[(int64_t)(r0 + 64 + wave + 4 * u) * ld];
+      }
+      if (wave == 0) {
+#pragma unroll
+        for (int r = 0; r < 64; ++r) s += rows[r][lane];
+      }
+    }
+    if (wave != 0) return;
+    const int p = layer_of(i).bias + c + lane;
+    if (o.c1 == 0.f)
+      grad[p] = s;
+    else
+      theta[p] = adam(p, s, theta[p], m1, m2, o);
+    return;
+  }
+  int t = blockIdx.x * 4 + wave, i = 3;
+  if (t >= kTiles4) {
+    t -= kTiles4;
+    i = t < kTilesH ? 2 : (t < 2 * kTilesH ? 1 : 0);
+    t -= (2 - i) * kTilesH;
+  }
+  const Layer L = layer_of(i);
+  const int mt = t / (L.out >> 4), nt = t % (L.out >> 4);
+  const bf16x4* __restrict__ ap = (i == 0 ? xf + (int64_t)mt * nst * 64
+                                          : hf + (int64_t)((i - 1) * (kH / 16) + mt) * nst * 64) + lane;
+  const bf16x4* __restrict__ bp = (i == 3 ? dzf4 + (int64_t)nt * nst * 64
+                                          : dzf + (int64_t)(i * (kH / 16) + nt) * nst * 64) + lane;
+  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+  constexpr int U = 4;  // B is a multiple of 64
+  bf16x4 a[U], b[U], an[U], bn[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    a[u] = ap[u * 64];
+    b[u] = bp[u * 64];
+  }
+  for (int k = 0; k < nst; k += U) {
+    if (k + U < nst) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        an[u] = ap[(k + U + u) * 64];
+        bn[u] = bp[(k + U + u) * 64];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[u], b[u], acc, 0, 0, 0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      a[u] = an[u];
+      b[u] = bn[u];
+    }
+  }
+  const int r16 = lane & 15, q4 = lane >> 4;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int row = mt * 16 + 4 * q4 + q, col = nt * 16 + r16;
+    const int p = L.off + row * L.out + col;
+    if (o.c1 == 0.f) {
+      grad[p] = acc[q];
+    } else {
+      const float th = adam(p, acc[q], theta[p], m1, m2, o);
+      theta[p] = th;
+      put_fragments(L, row, col, th, frag);
+    }
+  }
+}
+
+// mean of J in double
+__global__ __launch_bounds__(256) void k_mean(int B, const float* __restrict__ J, float* __restrict__ out) {
+  __shared__ double red[4];
+  double s = 0.0;
+  for (int i = threadIdx.x; i < B; i += 256) s += J[i];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) out[0] = (float)(((red[0] + red[1]) + (red[2] + red[3])) / B);
 }
 
 inline int nblk(int64_t n, int b = 256) { return (int)((n + b - 1) / b); }
@@ -308,15 +658,18 @@ struct kf_mlp {
   float* grad = nullptr;
   float* m1 = nullptr;
   float* m2 = nullptr;
-  float* Q = nullptr;  // kLM x kG
-  // activations (cap rows)
-  float *feat = nullptr, *prm = nullptr, *wF = nullptr, *z1 = nullptr, *h1 = nullptr, *z2 = nullptr, *h2 = nullptr,
-        *z3 = nullptr, *h3 = nullptr, *out = nullptr, *w = nullptr, *beta = nullptr, *dbeta = nullptr, *dw = nullptr,
-        *dh = nullptr, *dz = nullptr, *J = nullptr, *scal = nullptr;
+  short* frag = nullptr;  // the weights as bfloat16 fragments (kept with theta)
+  float *Qf = nullptr, *Qt = nullptr;  // the response matrix and its transpose, tile by tile
+  // activations (cap rows): z, dz and their fragments for the three hidden layers
+  float *prm = nullptr, *wF = nullptr, *z = nullptr, *out = nullptr, *w = nullptr, *beta = nullptr, *dbeta = nullptr,
+        *dz4 = nullptr, *dz = nullptr, *J = nullptr, *scal = nullptr;
+  bf16x4 *xf = nullptr, *hf = nullptr, *dzf4 = nullptr, *dzf = nullptr;
   double* smp = nullptr;  // device samples
   int nsmp_cap = 0;
   int32_t* idx = nullptr;
   int idx_cap = 0;
+  float* Jrun = nullptr;  // the losses of a training run's steps
+  int64_t Jrun_cap = 0;
   int32_t* Lover = nullptr;
   int64_t adam_t = 0;
 };
@@ -343,30 +696,32 @@ void mfree(void* p) {
 
 int ensure_batch(kf_mlp* net, int B) {
   if (net->cap >= B) return KF_OK;
-  float** bufs[] = {&net->feat, &net->prm, &net->wF, &net->z1, &net->h1, &net->z2, &net->h2, &net->z3,
-                    &net->h3,   &net->out, &net->w,  &net->beta, &net->dbeta, &net->dw, &net->dh, &net->dz, &net->J};
+  float** bufs[] = {&net->prm, &net->wF, &net->z, &net->out, &net->w, &net->beta, &net->dbeta, &net->dz4, &net->dz, &net->J};
+  bf16x4** frags[] = {&net->xf, &net->hf, &net->dzf4, &net->dzf};
+  net->cap = 0;
   for (float** b : bufs) {
     mfree(*b);
     *b = nullptr;
   }
+  for (bf16x4** b : frags) {
+    mfree(*b);
+    *b = nullptr;
+  }
   const size_t Bn = (size_t)B;
-  KF_TRY(dalloc_m(&net->feat, Bn * kNF));
-  KF_TRY(dalloc_m(&net->prm, Bn * 4));
+  KF_TRY(dalloc_m(&net->prm, Bn * kPrm));
   KF_TRY(dalloc_m(&net->wF, Bn * kLM));
-  KF_TRY(dalloc_m(&net->z1, Bn * kH));
-  KF_TRY(dalloc_m(&net->h1, Bn * kH));
-  KF_TRY(dalloc_m(&net->z2, Bn * kH));
-  KF_TRY(dalloc_m(&net->h2, Bn * kH));
-  KF_TRY(dalloc_m(&net->z3, Bn * kH));
-  KF_TRY(dalloc_m(&net->h3, Bn * kH));
+  KF_TRY(dalloc_m(&net->z, Bn * 3 * kH));
   KF_TRY(dalloc_m(&net->out, Bn * kLM));
   KF_TRY(dalloc_m(&net->w, Bn * kLM));
   KF_TRY(dalloc_m(&net->beta, Bn * kG));
   KF_TRY(dalloc_m(&net->dbeta, Bn * kG));
-  KF_TRY(dalloc_m(&net->dw, Bn * kLM));
-  KF_TRY(dalloc_m(&net->dh, Bn * kLM));
-  KF_TRY(dalloc_m(&net->dz, Bn * kLM));
+  KF_TRY(dalloc_m(&net->dz4, Bn * kLM));
+  KF_TRY(dalloc_m(&net->dz, Bn * 3 * kH));
   KF_TRY(dalloc_m(&net->J, Bn));
+  KF_TRY(dalloc_m(&net->xf, Bn * kNF / 4));
+  KF_TRY(dalloc_m(&net->hf, Bn * 3 * kH / 4));
+  KF_TRY(dalloc_m(&net->dzf4, Bn * kLM / 4));
+  KF_TRY(dalloc_m(&net->dzf, Bn * 3 * kH / 4));
   net->cap = B;
   return KF_OK;
 }
@@ -389,60 +744,58 @@ int upload_samples(kf_mlp* net, const double* samples, int n) {
   return KF_OK;
 }
 
-// forward (use_net: network correction on) and loss; grad: backpropagation
-int fwd_bwd(kf_mlp* net, int B, const int32_t* d_idx, bool use_net, bool grad, const int32_t* d_Lover) {
-  hipStream_t st = net->st;
-  const float* th = net->theta;
-  hipLaunchKernelGGL(k_prepare, dim3(B), dim3(256), 0, st, B, net->smp, d_idx, d_Lover, net->feat, net->prm, net->wF);
-  KF_HIP(hipGetLastError());
-  if (use_net) {
-    KF_TRY((gemm<0, 0, true>(B, kH, kNF, net->feat, kNF, th + kOffW1, kH, net->z1, kH, 0, st)));
-    hipLaunchKernelGGL(k_bias_gelu, dim3(nblk((int64_t)B * kH)), dim3(256), 0, st, B, kH, net->z1, th + kOffB1, net->h1);
-    KF_TRY((gemm<0, 0, true>(B, kH, kH, net->h1, kH, th + kOffW2, kH, net->z2, kH, 0, st)));
-    hipLaunchKernelGGL(k_bias_gelu, dim3(nblk((int64_t)B * kH)), dim3(256), 0, st, B, kH, net->z2, th + kOffB2, net->h2);
-    KF_TRY((gemm<0, 0, true>(B, kH, kH, net->h2, kH, th + kOffW3, kH, net->z3, kH, 0, st)));
-    hipLaunchKernelGGL(k_bias_gelu, dim3(nblk((int64_t)B * kH)), dim3(256), 0, st, B, kH, net->z3, th + kOffB3, net->h3);
-    KF_TRY((gemm<0, 0, true>(B, kLM, kH, net->h3, kH, th + kOffW4, kLM, net->out, kLM, 0, st)));
-  }
-  hipLaunchKernelGGL(k_out_weights, dim3(nblk((int64_t)B * kLM)), dim3(256), 0, st, B, net->out, th + kOffB4, net->wF,
-                     net->prm, net->w, use_net ? 1 : 0);
-  KF_TRY((gemm<0, 0, false>(B, kG, kLM, net->w, kLM, net->Q, kG, net->beta, kG, 0, st)));
-  hipLaunchKernelGGL(k_loss, dim3(B), dim3(256), 0, st, B, net->beta, net->prm, grad ? net->dbeta : nullptr, net->J,
-                     1.0f / B);
-  KF_HIP(hipGetLastError());
-  if (!grad) return KF_OK;
-  float* g = net->grad;
-  // dw = dbeta Q^T ; dout = s * dw * mask
-  KF_TRY((gemm<0, 1, false>(B, kLM, kG, net->dbeta, kG, net->Q, kG, net->dw, kLM, 0, st)));
-  hipLaunchKernelGGL(k_mask_scale, dim3(nblk((int64_t)B * kLM)), dim3(256), 0, st, B, net->dw, net->prm, net->dz);
-  // layer 4
-  KF_TRY((gemm<1, 0, true>(kH, kLM, B, net->h3, kH, net->dz, kLM, g + kOffW4, kLM, 0, st)));
-  hipLaunchKernelGGL(k_colsum, dim3(nblk(kLM)), dim3(256), 0, st, B, kLM, net->dz, g + kOffB4);
-  KF_TRY((gemm<0, 1, true>(B, kH, kLM, net->dz, kLM, th + kOffW4, kLM, net->dh, kH, 0, st)));
-  hipLaunchKernelGGL(k_gelu_back, dim3(nblk((int64_t)B * kH)), dim3(256), 0, st, (int64_t)B * kH, net->dh, net->z3);
-  // layer 3
-  KF_TRY((gemm<1, 0, true>(kH, kH, B, net->h2, kH, net->dh, kH, g + kOffW3, kH, 0, st)));
-  hipLaunchKernelGGL(k_colsum, dim3(nblk(kH)), dim3(256), 0, st, B, kH, net->dh, g + kOffB3);
-  KF_TRY((gemm<0, 1, true>(B, kH, kH, net->dh, kH, th + kOffW3, kH, net->dw, kH, 0, st)));
-  hipLaunchKernelGGL(k_gelu_back, dim3(nblk((int64_t)B * kH)), dim3(256), 0, st, (int64_t)B * kH, net->dw, net->z2);
-  // layer 2
-  KF_TRY((gemm<1, 0, true>(kH, kH, B, net->h1, kH, net->dw, kH, g + kOffW2, kH, 0, st)));
-  hipLaunchKernelGGL(k_colsum, dim3(nblk(kH)), dim3(256), 0, st, B, kH, net->dw, g + kOffB2);
-  KF_TRY((gemm<0, 1, true>(B, kH, kH, net->dw, kH, th + kOffW2, kH, net->dh, kH, 0, st)));
-  hipLaunchKernelGGL(k_gelu_back, dim3(nblk((int64_t)B * kH)), dim3(256), 0, st, (int64_t)B * kH, net->dh, net->z1);
-  // layer 1
-  KF_TRY((gemm<1, 0, true>(kNF, kH, B, net->feat, kNF, net->dh, kH, g + kOffW1, kH, 0, st)));
-  hipLaunchKernelGGL(k_colsum, dim3(nblk(kH)), dim3(256), 0, st, B, kH, net->dh, g + kOffB1);
+// the network's output and the samples' constants (B a multiple of 64)
+int forward(kf_mlp* net, int B, const int32_t* d_idx, bool use_net, const int32_t* d_Lover) {
+  const int nnet = use_net ? B / 4 : 0;
+  hipLaunchKernelGGL(k_forward, dim3(nnet + B), dim3(512), 0, net->st, B, nnet, net->smp, d_idx, d_Lover, net->theta,
+                     reinterpret_cast<const bf16x4*>(net->frag), net->xf, net->z, net->hf, net->out, net->prm, net->wF);
   KF_HIP(hipGetLastError());
   return KF_OK;
+}
+
+// the weights of the forward pass, their filter response and, without a
+// backward pass to follow, the losses into net->J
+int response(kf_mlp* net, int B, bool use_net, bool grad) {
+  hipLaunchKernelGGL(k_response<0>, dim3(kG / 64, B / 16), dim3(256), 0, net->st, B, net->out, net->theta + kOffB4,
+                     net->wF, net->prm, reinterpret_cast<const float4*>(net->Qf), use_net ? 1 : 0, 1.0f / B, net->w,
+                     net->beta, grad ? net->dbeta : nullptr, (bf16x4*)nullptr);
+  KF_HIP(hipGetLastError());
+  if (grad) return KF_OK;
+  hipLaunchKernelGGL(k_loss, dim3(nblk(B, 4)), dim3(256), 0, net->st, B, net->beta, net->prm, net->J);
+  KF_HIP(hipGetLastError());
+  return KF_OK;
+}
+
+// losses into J, and the gradient into net->grad (step.c1 = 0) or an Adam step
+int backward(kf_mlp* net, int B, float* J, const AdamStep& step) {
+  hipStream_t st = net->st;
+  hipLaunchKernelGGL(k_response<1>, dim3(kLM / 64, B / 16), dim3(256), 0, st, B, net->dbeta, (const float*)nullptr,
+                     (const float*)nullptr, net->prm, reinterpret_cast<const float4*>(net->Qt), 0, 0.f,
+                     (float*)nullptr, net->dz4, (float*)nullptr, net->dzf4);
+  KF_HIP(hipGetLastError());
+  hipLaunchKernelGGL(k_backward, dim3(B / 16), dim3(512), 0, st, B, net->dz4, net->z,
+                     reinterpret_cast<const bf16x4*>(net->frag), net->dz, net->dzf);
+  KF_HIP(hipGetLastError());
+  hipLaunchKernelGGL(k_update, dim3(kTileBlocks + kBiasBlocks + B / 4), dim3(256), 0, st, B, net->xf, net->hf,
+                     net->dzf, net->dzf4, net->dz, net->dz4, net->theta, net->m1, net->m2, net->grad, net->frag,
+                     net->beta, net->prm, J, step);
+  KF_HIP(hipGetLastError());
+  return KF_OK;
+}
+
+// forward (use_net: network correction on) and loss; grad: backpropagation
+int fwd_bwd(kf_mlp* net, int B, const int32_t* d_idx, bool use_net, bool grad, const int32_t* d_Lover) {
+  KF_TRY(forward(net, B, d_idx, use_net, d_Lover));
+  KF_TRY(response(net, B, use_net, grad));
+  return grad ? backward(net, B, net->J, AdamStep{0.f, 0.f, 0.f}) : KF_OK;
 }
 
 void free_mlp(kf_mlp* net) {
   if (!net) return;
   if (net->st) (void)hipStreamSynchronize(net->st);
-  void* ps[] = {net->theta, net->grad, net->m1, net->m2, net->Q, net->feat, net->prm, net->wF, net->z1, net->h1,
-                net->z2, net->h2, net->z3, net->h3, net->out, net->w, net->beta, net->dbeta, net->dw, net->dh, net->dz,
-                net->J, net->scal, net->smp, net->idx, net->Lover};
+  void* ps[] = {net->theta, net->grad, net->m1, net->m2, net->frag, net->Qf, net->Qt, net->prm, net->wF, net->z,
+                net->out, net->w, net->beta, net->dbeta, net->dz4, net->dz, net->J, net->scal, net->xf, net->hf,
+                net->dzf4, net->dzf, net->smp, net->idx, net->Jrun, net->Lover};
   for (void* p : ps) mfree(p);
   if (net->st) (void)hipStreamDestroy(net->st);
   delete net;
@@ -469,7 +822,8 @@ int kf_mlp_create(const float* params, kf_mlp** out) {
     }
     if ((rc = dalloc_m(&net->theta, kNParams)) || (rc = dalloc_m(&net->grad, kNParams)) ||
         (rc = dalloc_m(&net->m1, kNParams)) || (rc = dalloc_m(&net->m2, kNParams)) ||
-        (rc = dalloc_m(&net->Q, (size_t)kLM * kG)) || (rc = dalloc_m(&net->scal, 4)) ||
+        (rc = dalloc_m(&net->frag, (size_t)kNFrag * 4)) || (rc = dalloc_m(&net->Qf, (size_t)kLM * kG)) ||
+        (rc = dalloc_m(&net->Qt, (size_t)kLM * kG)) || (rc = dalloc_m(&net->scal, 4)) ||
         (rc = dalloc_m(&net->Lover, 1)))
       break;
     if (hipMemcpy(net->theta, params, sizeof(float) * kNParams, hipMemcpyHostToDevice) != hipSuccess ||
@@ -478,7 +832,8 @@ int kf_mlp_create(const float* params, kf_mlp** out) {
       rc = mfail(KF_EHIP, "kf_mlp_create: upload");
       break;
     }
-    hipLaunchKernelGGL(k_qmat, dim3(kLM), dim3(256), 0, net->st, net->Q);
+    hipLaunchKernelGGL(k_pack, dim3(nblk(kNParams)), dim3(256), 0, net->st, net->theta, net->frag);
+    hipLaunchKernelGGL(k_qmat, dim3(kLM), dim3(256), 0, net->st, net->Qf, net->Qt);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(net->st) != hipSuccess) rc = mfail(KF_EHIP, "kf_mlp_create: Q");
   } while (false);
   if (rc) {
@@ -506,7 +861,7 @@ int kf_mlp_loss_grad(kf_mlp* net, const double* samples, int32_t n, double* loss
   KF_TRY(ensure_batch(net, n));
   KF_TRY(upload_samples(net, samples, n));
   KF_TRY(fwd_bwd(net, n, nullptr, true, grad != nullptr, nullptr));
-  hipLaunchKernelGGL(k_mean, dim3(1), dim3(64), 0, net->st, n, net->J, net->scal);
+  hipLaunchKernelGGL(k_mean, dim3(1), dim3(256), 0, net->st, n, net->J, net->scal);
   float lf = 0.f;
   KF_HIP(hipMemcpyAsync(&lf, net->scal, sizeof(float), hipMemcpyDeviceToHost, net->st));
   if (grad) KF_HIP(hipMemcpyAsync(grad, net->grad, sizeof(float) * kNParams, hipMemcpyDeviceToHost, net->st));
@@ -533,28 +888,37 @@ int kf_mlp_train(kf_mlp* net, const double* samples, int32_t n, const int32_t* o
   }
   KF_HIP(hipMemcpyAsync(net->idx, order, sizeof(int32_t) * total, hipMemcpyHostToDevice, net->st));
   const int steps = n / batch;
-  std::vector<float> Jh((size_t)batch);
+  const int64_t nJ = (int64_t)epochs * steps * batch;
+  if (nJ > net->Jrun_cap) {
+    mfree(net->Jrun);
+    net->Jrun = nullptr;
+    net->Jrun_cap = 0;
+    KF_TRY(dalloc_m(&net->Jrun, (size_t)nJ));
+    net->Jrun_cap = nJ;
+  }
   for (int e = 0; e < epochs; ++e) {
-    double acc = 0.0;
     for (int s = 0; s < steps; ++s) {
       const int32_t* d_idx = net->idx + (int64_t)e * n + (int64_t)s * batch;
-      KF_TRY(fwd_bwd(net, batch, d_idx, true, true, nullptr));
+      KF_TRY(forward(net, batch, d_idx, true, nullptr));
+      KF_TRY(response(net, batch, true, true));
       ++net->adam_t;
       // cosine decay from lr to lr/100 over the run
       const double prog = (double)(e * steps + s) / std::max(1, epochs * steps - 1);
       const double lrt = lr * (0.01 + 0.99 * 0.5 * (1.0 + std::cos(kPi * prog)));
       const float c1 = (float)(1.0 - std::pow(0.9, (double)net->adam_t));
       const float c2 = (float)(1.0 - std::pow(0.999, (double)net->adam_t));
-      hipLaunchKernelGGL(k_adam, dim3(nblk(kNParams)), dim3(256), 0, net->st, kNParams, net->theta, net->grad, net->m1,
-                         net->m2, (float)lrt, 0.9f, 0.999f, 1e-8f, c1, c2);
-      KF_HIP(hipGetLastError());
-      if (epoch_loss) {
-        KF_HIP(hipMemcpyAsync(Jh.data(), net->J, sizeof(float) * batch, hipMemcpyDeviceToHost, net->st));
-        KF_HIP(hipStreamSynchronize(net->st));
-        for (float v : Jh) acc += v;
-      }
+      KF_TRY(backward(net, batch, net->Jrun + ((int64_t)e * steps + s) * batch, AdamStep{(float)lrt, c1, c2}));
     }
-    if (epoch_loss) epoch_loss[e] = acc / ((double)steps * batch);
+  }
+  if (epoch_loss) {
+    std::vector<float> Jh((size_t)nJ);
+    KF_HIP(hipMemcpyAsync(Jh.data(), net->Jrun, sizeof(float) * (size_t)nJ, hipMemcpyDeviceToHost, net->st));
+    KF_HIP(hipStreamSynchronize(net->st));
+    for (int e = 0; e < epochs; ++e) {
+      double acc = 0.0;
+      for (int64_t i = 0; i < (int64_t)steps * batch; ++i) acc += Jh[(size_t)((int64_t)e * steps * batch + i)];
+      epoch_loss[e] = acc / ((double)steps * batch);
+    }
   }
   KF_HIP(hipStreamSynchronize(net->st));
   return KF_OK;
@@ -569,7 +933,10 @@ int kf_mlp_weights(kf_mlp* net, const double* samples, int32_t n, double* w_out)
   for (int i = n; i < np; ++i) std::memcpy(&rep[4 * (size_t)i], samples + 4 * (size_t)(n - 1), sizeof(double) * 4);
   KF_TRY(ensure_batch(net, np));
   KF_TRY(upload_samples(net, rep.data(), np));
-  KF_TRY(fwd_bwd(net, np, nullptr, true, false, nullptr));
+  KF_TRY(forward(net, np, nullptr, true, nullptr));
+  hipLaunchKernelGGL(k_out_weights, dim3(nblk((int64_t)np * kLM)), dim3(256), 0, net->st, np, net->out,
+                     net->theta + kOffB4, net->wF, net->prm, net->w, 1);
+  KF_HIP(hipGetLastError());
   std::vector<float> wl((size_t)n * kLM);
   KF_HIP(hipMemcpyAsync(wl.data(), net->w, sizeof(float) * wl.size(), hipMemcpyDeviceToHost, net->st));
   KF_HIP(hipStreamSynchronize(net->st));
