@@ -205,7 +205,10 @@ typedef struct kf_options {
                             gives): each workgroup keeps its rows, the rows
                             the next s steps reach and its part of the
                             weighted sum in LDS and advances s steps per
-                            launch.  0 = one step per launch (default);
+                            launch.  0 = one step per launch (default),
+                            except that operators stepped as stencils (see
+                            index_bytes) take several, for blocks too, where
+                            that is faster; the results are the same;
                             s > 0 = s steps per launch; -1 = the whole filter
                             in one launch.  KF_EINVAL from the solve or
                             filter call when the band does not fit;

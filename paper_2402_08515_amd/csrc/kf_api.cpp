@@ -322,9 +322,9 @@ void dfree(void* p) {
   if (p) (void)hipFree(p);
 }
 
-int ensure_step_buffers(kf_problem* p, StepBufs& sb, int bk, int vb) {
+int ensure_step_buffers(kf_problem* p, StepBufs& sb, int bk, int vb, bool second_pair = false) {
   const bool needz = p->opt.stepper == 4;
-  const bool need23 = p->opt.multistep != 0 && bk == 1;
+  const bool need23 = second_pair || (p->opt.multistep != 0 && bk == 1);
   if (sb.cap >= bk && sb.vb == vb && (!needz || sb.Z) && (!need23 || sb.Y3)) return KF_OK;
   dfree(sb.Y0);
   dfree(sb.Y1);
@@ -370,9 +370,10 @@ int scratch_address(void** out) {
   return KF_OK;
 }
 
-// The n x bk time-stepping blocks (three, four for the fourth-order
-// stepper) carved out of the scratch array.
-int scratch_step_buffers(int32_t n, int bk, int vb, StepBufs& sb, int nbuf = 3) {
+// The n x bk time-stepping blocks (three, four for the fourth-order stepper,
+// and two more for several steps per launch where they fit as well) carved
+// out of the scratch array.
+int scratch_step_buffers(int32_t n, int bk, int vb, StepBufs& sb, int nbuf, bool second_pair) {
   const size_t one = ((size_t)n * bk * vb + 255) / 256 * 256;
   if (nbuf * one > kScratchBytes)
     return fail(KF_EINVAL, "kf_apply_filter_noalloc: " + std::to_string(nbuf) + " x n x " + std::to_string(bk) +
@@ -385,6 +386,10 @@ int scratch_step_buffers(int32_t n, int bk, int vb, StepBufs& sb, int nbuf = 3) 
   sb.Y1 = c + one;
   sb.R = c + 2 * one;
   sb.Z = nbuf > 3 ? c + 3 * one : nullptr;
+  if (second_pair && (size_t)(nbuf + 2) * one <= kScratchBytes) {
+    sb.Y2 = c + nbuf * one;
+    sb.Y3 = c + (nbuf + 1) * one;
+  }
   sb.cap = bk;
   sb.vb = vb;
   return KF_OK;
@@ -442,8 +447,10 @@ int run_filter(kf_problem* p, const SellOp& A, StepBufs& sb, const double* src, 
   const int L = (int)w.size();
   hipStream_t st = p->st;
   if (L == 1) return launch_scale_copy(p->n, bout, std::min(bsrc, bout), src, srs, scs, w[0], dst, drs, dcs, st);
+  StepsPlan steps;
+  if (p->opt.multistep == 0 && p->opt.stepper != 4 && A.st.width > 0) steps = plan_steps(A, bk, L, lds_per_workgroup());
   if (may_alloc) {
-    KF_TRY(ensure_step_buffers(p, sb, bk, A.val_bytes));
+    KF_TRY(ensure_step_buffers(p, sb, bk, A.val_bytes, steps.s > 0 && steps.own < A.nslices && steps.s < L - 1));
   } else if (sb.cap < bk || sb.vb != A.val_bytes || !sb.Y0 || !sb.Y1 || !sb.R || (p->opt.stepper == 4 && !sb.Z)) {
     return fail(KF_EINVAL, "kf: time-stepping buffers too small");
   }
@@ -474,6 +481,22 @@ int run_filter(kf_problem* p, const SellOp& A, StepBufs& sb, const double* src, 
       KF_TRY(launch_leapfrog_mp(A, pl, l, cnt, l == 0, last, y0, in[0], in[1], outp[0], outp[1], sb.R, dst, drs, dw, st));
       l += cnt;
       ping ^= 1;
+    }
+    return KF_OK;
+  }
+  if (steps.s > 0 && (steps.own >= A.nslices || steps.s >= L - 1 || sb.Y3)) {
+    // (one workgroup reads every level before it writes, so one pair serves)
+    void* P0[2] = {sb.Y0, sb.Y1};
+    void* P1[2] = {steps.own >= A.nslices ? sb.Y0 : sb.Y2, steps.own >= A.nslices ? sb.Y1 : sb.Y3};
+    for (int l = 0, ping = 0; l < L - 1; ping ^= 1) {
+      const int cnt = std::min(steps.s, L - 1 - l);
+      StepWeights sw;
+      for (int j = 0; j <= cnt; ++j) sw.w[j] = w[(size_t)(l + j)];
+      void** in = ping ? P1 : P0;
+      void** outp = ping ? P0 : P1;
+      KF_TRY(launch_steps(A, steps, bk, cnt, l == 0, l + cnt == L - 1, y0, in[0], in[1], outp[0], outp[1], sb.R, dst, drs,
+                          dcs, bout, sw, st));
+      l += cnt;
     }
     return KF_OK;
   }
@@ -1719,6 +1742,10 @@ int tune_block(kf_problem* p, SellOp& A, StepBufs& sb, int bk) {
   int lb = 0;
   while ((1 << lb) < bk && lb < 4) ++lb;
   if (A.lpr_tuned & (1 << lb)) return KF_OK;
+  // (several steps per launch have no such choice)
+  if (p->opt.multistep == 0 && p->opt.stepper != 4 && A.st.width > 0 &&
+      plan_steps(A, bk, p->L, lds_per_workgroup()).s > 0)
+    return KF_OK;
   double best = 1e300;
   int best_l = 1, best_b = 0;
   // lanes per row, each with the gathers from the caches and (unless the
@@ -2420,7 +2447,7 @@ int kf_apply_filter_noalloc(kf_problem* p, const double* x, double* y, int32_t b
                                ", the current device is " + std::to_string(dev));
   const int bk = pow2ceil(b);
   StepBufs sb;
-  KF_TRY(scratch_step_buffers(p->n, bk, p->A.val_bytes, sb, p->opt.stepper == 4 ? 4 : 3));
+  KF_TRY(scratch_step_buffers(p->n, bk, p->A.val_bytes, sb, p->opt.stepper == 4 ? 4 : 3, p->opt.multistep == 0));
   return run_filter(p, p->A, sb, x, b, 1, b, bk, y, b, 1, b, p->w, false);
 }
 

@@ -151,6 +151,27 @@ int launch_leapfrog_mp(const SellOp& A, const MultiStepPlan& pl, int l0, int s, 
                        const void* i0, const void* i1, void* o0, void* o1, void* acc, double* rout, int64_t rs,
                        const double* w, hipStream_t st);
 
+// Several steps per launch over stencil slices (k_steps_st): each workgroup
+// owns `own` slices and advances them s steps, hb slices of halo per step.
+// plan_steps picks s and own for blocks of b vectors and L - 1 steps; s = 0:
+// one step per launch is the better or the only choice.  launch_steps advances
+// y_{l0} to y_{l0+s} (s <= the plan's); the weights of y_{l0} .. y_{l0+s}
+// travel as a kernel argument.
+constexpr int kStepsMax = 64;  // steps of one launch
+// row slices per wavefront for rows of rb bytes (16: LDS ends before more, and
+// their registers would spill)
+constexpr int steps_max_r(size_t rb) { return rb > 8 ? 5 : 8; }
+struct StepWeights {
+  double w[kStepsMax + 1];
+};
+struct StepsPlan {
+  int s = 0, own = 0, hb = 0;
+};
+StepsPlan plan_steps(const SellOp& A, int b, int L, size_t lds_bytes);
+int launch_steps(const SellOp& A, const StepsPlan& pl, int b, int s, bool first, bool last, const void* ysrc,
+                 const void* i0, const void* i1, void* o0, void* o1, void* acc, double* rout, int64_t rs, int64_t cs,
+                 int bout, const StepWeights& w, hipStream_t st);
+
 // The accumulation schedule of one filter application (L - 1 steps): for
 // step l, the mode and the weights (wp, wc, wn) of prev, cur and nxt.  Every
 // y_j enters once: y_0 and y_1 at step 1, then three at a time at steps

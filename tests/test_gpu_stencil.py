@@ -78,3 +78,51 @@ def test_stencil_lanes_per_row_bitwise(b, lpr):
         out = [kf.Problem(S, m, 4.0, 8.0, tau, 7, precision=precision, index_bytes=ib, lanes_per_row=lpr).apply_filter(x)
                for ib in (0, 2)]
         assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("b", [1, 2, 16])
+def test_stencil_one_step_per_launch_bitwise(b, precision):
+    """A cube whose band is too wide for several steps per launch."""
+    import torch
+
+    from paper_2402_08515_amd import kf
+
+    S, m, _ = grid_problem(3, 48)
+    tau = 1.8 / np.sqrt(12.0 * 48 * 48)
+    x = torch.from_numpy(start_block(S.shape[0], b, 9)).cuda()
+    for L in (2, 3, 8):
+        out = [kf.Problem(S, m, 8.0, 16.0, tau, L, precision=precision, index_bytes=ib).apply_filter(x) for ib in (0, 4)]
+        assert torch.equal(out[0], out[1]), L
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("b", [1, 2, 3, 8])
+@pytest.mark.parametrize(
+    "dim,n",
+    # one slice; one workgroup with few and many slices per wavefront; several
+    # workgroups with halos of one, a few and many slices (ragged last ones)
+    [(2, 5), (2, 33), (2, 64), (2, 91), (2, 140), (2, 257), (3, 5), (3, 17), (3, 20), (3, 27), (3, 34)],
+)
+def test_several_steps_per_launch_bitwise(dim, n, b, precision):
+    """The library's own choice of several steps per launch (and the
+    allocation-free entry point, which has fewer buffers) against one step per
+    launch: the same operations in the same order."""
+    import torch
+
+    from paper_2402_08515_amd import kf
+
+    print(f"case steps dim={dim} n={n} b={b} {precision}", flush=True)
+    S, m, _ = grid_problem(dim, n)
+    tau = 1.8 / np.sqrt(4.0 * dim * n * n)
+    x = torch.from_numpy(start_block(S.shape[0], b, 11)).cuda()
+    for L in (3, 24, 65, 130):  # one launch, several, exactly 64 steps, a remainder after 128
+        out = []
+        for ib in (0, 4):
+            P = kf.Problem(S, m, 0.3 / tau, 0.5 / tau, tau, L, precision=precision, index_bytes=ib)
+            out.append(P.apply_filter(x))
+            if ib == 0:
+                y = torch.empty_like(x)
+                P.apply_filter_noalloc(x, y)
+                assert torch.equal(y, out[0]), L
+        assert torch.equal(out[0], out[1]), (L, (out[0] - out[1]).abs().max())
