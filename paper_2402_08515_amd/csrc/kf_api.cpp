@@ -1998,7 +1998,7 @@ int kf_create(const kf_csr* S, const double* m_diag, double omega_min, double om
       break;
     }
     const int vb = o.precision == KF_MIXED ? 4 : 8;
-    const bool stencil = layout_is_free(o);
+    const int stencil = layout_is_free(o) ? kStencilExact : kStencilNone;
     rc = build_sell(p->n, p->nnz, dc.rowptr, dc.col, dc.val, d_scale, vb, o.index_bytes, p->st, p->A, stencil);
     if (!rc && o.precision == KF_MIXED && o.refine)
       rc = build_sell(p->n, p->nnz, dc.rowptr, dc.col, dc.val, d_scale, 8, o.index_bytes, p->st, p->A64, stencil);
@@ -3292,7 +3292,7 @@ int ensure_batch_graph(kf_batch* bt, BatchStack& k, int bk) {
     KF_HIP(hipMemsetAsync(k.sb.Y1, 0, bytes, st));
     double best = 1e300;
     int best_remap = k.remap, best_nt = k.A.nt_loads;
-    for (int nt = 0; nt <= 1; ++nt)
+    for (int nt = 0; nt <= (k.A.st.width > 0 ? 0 : 1); ++nt)
       for (int remap = 0; remap <= 1; ++remap) {
         k.A.nt_loads = nt;
         for (int rep = 0; rep < 2; ++rep) {  // warm-up, then the timing
@@ -3495,7 +3495,7 @@ int kf_create_batch(int32_t P, const kf_problem_desc* descs, const kf_options* o
       BatchStack& k = bt->stk[ks];
       const int vb = (mixed && ks == 0) ? 4 : 8;
       rc = build_sell((int32_t)bt->rows, (int64_t)hs.col.size(), dc.rowptr, dc.col, dc.val, nullptr, vb, o.index_bytes,
-                      bt->st, k.A);
+                      bt->st, k.A, layout_is_free(o) ? kStencilPadded : kStencilNone);
       if (rc) break;
       k.A.nt_loads = o.nt_loads ? 1 : 0;
       if ((rc = dalloc(&k.d_tb, 1))) break;

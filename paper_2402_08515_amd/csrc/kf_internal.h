@@ -96,11 +96,14 @@ void free_sell(SellOp& op);
 // row_scale[i] (device array, or nullptr for 1), stored as float64
 // (val_bytes 8) or float32 (val_bytes 4).  want_idx_bytes 0 chooses 2 when
 // every |col - row| < 32768.  stencil: also build out.st when every slice is
-// a stencil of at most kStencilMax offsets.
+// a stencil of at most kStencilMax offsets; its stride is a multiple of 4, or
+// with kStencilExact the width itself for the lengths that have kernels of
+// their own (5 and 7).
 constexpr int kStencilMax = 32;
+enum StencilForm { kStencilNone = 0, kStencilPadded = 1, kStencilExact = 2 };
 int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
                const double* d_row_scale, int val_bytes, int want_idx_bytes, hipStream_t st, SellOp& out,
-               bool stencil = false);
+               int stencil = kStencilNone);
 
 // ---- fused leapfrog step ----------------------------------------------------
 enum StepMode { kMid = 0, kFirst = 1, kLast = 2, kFirstLast = 3, kMidAcc = 4 };

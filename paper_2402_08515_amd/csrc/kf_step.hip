@@ -578,6 +578,66 @@ __global__ __launch_bounds__(256) void k_leapfrog_batch(int32_t nslices, const i
   }
 }
 
+// The batched step over stencil slices (see stencil_product).  The tables of
+// the slice's problem are scalar loads, as the slice's entries are.
+template <typename T, int B>
+__global__ __launch_bounds__(256) void k_leapfrog_batch_st(int32_t nslices, const T* __restrict__ val,
+                                                           const int32_t* __restrict__ soff,
+                                                           const uint64_t* __restrict__ mask, int stride,
+                                                           const int32_t* __restrict__ sp,
+                                                           const BatchTables* __restrict__ tb,
+                                                           const T* __restrict__ wtab, int lmax, int ell,
+                                                           const T* __restrict__ cur, const T* prev, T* out,
+                                                           T* __restrict__ acc, int remap) {
+  using V = Row<T, B>;
+  const int wg = remap ? xcd_map(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const int slice = __builtin_amdgcn_readfirstlane(wg * 4 + (int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63;
+  if (slice >= nslices) return;
+  const int p = sp[slice];
+  const int Lp = tb->L[p];
+  if (!tb->active[p] || ell > Lp - 1) return;
+  const int row = slice * 64 + lane;
+  const int local = row - (int)tb->row0[p];
+  if (local >= tb->n[p]) return;
+  const bool first = ell == 1, last = ell == Lp - 1;
+  // the accumulation schedule of the single-problem steps (step_plan)
+  const int u = ell >= 2 ? 1 + 3 * ((ell - 2) / 3) : 1;  // latest update before this step
+  const bool sums = first || last || ell - u == 3;
+  const V yc = reinterpret_cast<const V*>(cur)[row];
+  V yp = yc, r = yc;
+  if (!first) yp = reinterpret_cast<const V*>(prev)[row];
+  if (sums && !first) r = reinterpret_cast<const V*>(acc)[row];
+  T sum[B];
+#pragma unroll
+  for (int j = 0; j < B; ++j) sum[j] = (T)0;
+  stencil_product<T, B, B, 1, 0>(val, soff, mask, stride, slice, lane, row, cur, 0, sum);
+  V nx;
+#pragma unroll
+  for (int j = 0; j < B; ++j) nx.v[j] = (T)2 * yc.v[j] - yp.v[j] - sum[j];
+  if (!last) reinterpret_cast<V*>(out)[row] = nx;
+  if (!sums) return;
+  const T* __restrict__ wq = wtab + (int64_t)p * lmax;
+  if (first) {
+#pragma unroll
+    for (int j = 0; j < B; ++j) r.v[j] = fma(wq[1], nx.v[j], wq[0] * yc.v[j]);
+  } else {
+    const T wp = ell - 2 > u ? wq[ell - 2] : (T)0, wc = ell - 1 > u ? wq[ell - 1] : (T)0, wn = wq[ell];
+#pragma unroll
+    for (int j = 0; j < B; ++j) r.v[j] = fma(wn, nx.v[j], fma(wc, yc.v[j], fma(wp, yp.v[j], r.v[j])));
+  }
+  if (last) {
+    double* __restrict__ dst = tb->dst[p];
+    const int64_t ld = tb->ld[p];
+    const int bout = tb->bout[p];
+#pragma unroll
+    for (int j = 0; j < B; ++j)
+      if (j < bout) dst[local + (int64_t)j * ld] = (double)r.v[j];
+  } else {
+    reinterpret_cast<V*>(acc)[row] = r;
+  }
+}
+
 // Batched start of a filter application: Y1 <- the problem's source columns
 // (zero beyond bsrc or for inactive problems); L_p = 1 problems get C = w0 I
 // written straight to their destination.
@@ -1174,7 +1234,7 @@ namespace {
 // stays 0).
 template <typename VT>
 int build_stencil(int32_t n, int32_t ns, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
-                  const double* d_row_scale, hipStream_t st, StencilOp& out) {
+                  const double* d_row_scale, bool exact, hipStream_t st, StencilOp& out) {
   const int grid = ceil_div64(ns, 4);
   int32_t* d_w = nullptr;
   if (hipMalloc(&d_w, sizeof(int32_t) * (size_t)ns) != hipSuccess) {
@@ -1196,7 +1256,7 @@ int build_stencil(int32_t n, int32_t ns, const int32_t* d_rowptr, const int32_t*
   if (width < 1 || width > kStencilMax) return KF_OK;
   // 5 and 7 entries (the 2D and 3D point stencils) have kernels of their own
   // length; other lengths are padded to the loop's four entries
-  const int stride = width == 5 || width == 7 ? width : (width + 3) / 4 * 4;
+  const int stride = exact && (width == 5 || width == 7) ? width : (width + 3) / 4 * 4;
   const size_t tot = (size_t)ns * stride;
   StencilOp s;
   if (hipMalloc(&s.val, tot * sizeof(VT)) != hipSuccess || hipMalloc(&s.off, tot * sizeof(int32_t)) != hipSuccess ||
@@ -1217,7 +1277,7 @@ int build_stencil(int32_t n, int32_t ns, const int32_t* d_rowptr, const int32_t*
 }  // namespace
 
 int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
-               const double* d_row_scale, int val_bytes, int want_idx_bytes, hipStream_t st, SellOp& out, bool stencil) {
+               const double* d_row_scale, int val_bytes, int want_idx_bytes, hipStream_t st, SellOp& out, int stencil) {
   free_sell(out);
   if (n <= 0) {
     set_error("build_sell: empty matrix");
@@ -1291,9 +1351,9 @@ int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d
   KF_HIP(hipGetLastError());
   if (stencil) {
     if (val_bytes == 8)
-      KF_TRY(build_stencil<double>(n, ns, d_rowptr, d_col, d_val, d_row_scale, st, out.st));
+      KF_TRY(build_stencil<double>(n, ns, d_rowptr, d_col, d_val, d_row_scale, stencil == kStencilExact, st, out.st));
     else
-      KF_TRY(build_stencil<float>(n, ns, d_rowptr, d_col, d_val, d_row_scale, st, out.st));
+      KF_TRY(build_stencil<float>(n, ns, d_rowptr, d_col, d_val, d_row_scale, stencil == kStencilExact, st, out.st));
   }
   KF_HIP(hipStreamSynchronize(st));
   (void)nnz;
@@ -1594,10 +1654,37 @@ int launch_lfb_t(const SellOp& A, int b, const int32_t* sp, const BatchTables* t
 }
 }  // namespace
 
+namespace {
+template <typename T>
+int launch_lfb_st(const SellOp& A, int b, const int32_t* sp, const BatchTables* tb, const void* wtab, int lmax, int ell,
+                  const void* cur, const void* prev, void* out, void* acc, int nslices, int remap, hipStream_t st) {
+#define KF_LFS(B)                                                                                                  \
+  hipLaunchKernelGGL((k_leapfrog_batch_st<T, B>), dim3(ceil_div64(nslices, 4)), dim3(256), 0, st, nslices,          \
+                     static_cast<const T*>(A.st.val), A.st.off, A.st.mask, A.st.stride, sp, tb,                     \
+                     static_cast<const T*>(wtab), lmax, ell, static_cast<const T*>(cur), static_cast<const T*>(prev), \
+                     static_cast<T*>(out), static_cast<T*>(acc), remap)
+  switch (b) {
+    case 1: KF_LFS(1); break;
+    case 2: KF_LFS(2); break;
+    case 4: KF_LFS(4); break;
+    case 8: KF_LFS(8); break;
+    case 16: KF_LFS(16); break;
+    default: set_error("batched leapfrog: block width must be 1, 2, 4, 8 or 16"); return KF_EINVAL;
+  }
+#undef KF_LFS
+  KF_HIP(hipGetLastError());
+  return KF_OK;
+}
+}  // namespace
+
 int launch_leapfrog_batch(const SellOp& A, int b, const int32_t* sp, const BatchTables* tb, const void* wtab, int lmax,
                           int ell, const void* cur, const void* prev, void* out, void* acc, int nslices, int remap,
                           hipStream_t st) {
   if (nslices <= 0 || nslices > A.nslices) nslices = A.nslices;
+  if (A.st.width > 0)
+    return A.val_bytes == 8
+               ? launch_lfb_st<double>(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, nslices, remap, st)
+               : launch_lfb_st<float>(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, nslices, remap, st);
 #define KF_LFB(T, IT)                                                                                               \
   return A.nt_loads ? launch_lfb_t<T, IT, true>(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, nslices, remap, \
                                                 st)                                                                 \
