@@ -473,6 +473,70 @@ __global__ __launch_bounds__(256) void k_leapfrog4(int32_t n, int32_t nslices, c
   }
 }
 
+// The two launches of a fourth-order step over stencil slices: MODE < 0 forms
+// z = A cur, else the update (see stencil_product).
+template <typename T, int B, int MODE, int LPR, int W>
+__global__ __launch_bounds__(256) void k_leapfrog4_st(int32_t n, int32_t nslices, const T* __restrict__ val,
+                                                      const int32_t* __restrict__ soff,
+                                                      const uint64_t* __restrict__ mask, int stride,
+                                                      const T* __restrict__ cur, const T* prev, T* out,
+                                                      T* __restrict__ acc, T* __restrict__ z,
+                                                      double* __restrict__ rout, int64_t rs, int64_t cs, int bout, T wp,
+                                                      T wc, T wn, int remap) {
+  constexpr int BL = B / LPR;
+  constexpr int RW = 64 / LPR;
+  using V = Row<T, BL>;
+  const int wg = remap ? xcd_map(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const int gw = __builtin_amdgcn_readfirstlane(wg * 4 + (int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63;
+  const int slice = (gw * RW) >> 6;
+  if (slice >= nslices) return;
+  const int rin = ((gw * RW) & 63) + lane / LPR;
+  const int row = slice * 64 + rin;
+  if (row >= n) return;
+  const int col0 = (lane % LPR) * BL;
+  const int64_t off = (int64_t)row * B + col0;
+  V yc, yp, zc, r;
+  if (MODE >= 0) {
+    yc = *reinterpret_cast<const V*>(cur + off);
+    zc = *reinterpret_cast<const V*>(z + off);
+    if (!(MODE & kFirst)) yp = *reinterpret_cast<const V*>(prev + off);
+    if (MODE == kMidAcc || MODE == kLast) r = *reinterpret_cast<const V*>(acc + off);
+  }
+  T sum[BL];
+#pragma unroll
+  for (int j = 0; j < BL; ++j) sum[j] = (T)0;
+  stencil_product<T, B, BL, LPR, W>(val, soff, mask, stride, slice, rin, row, MODE < 0 ? cur : z, col0, sum);
+  if (MODE < 0) {
+    V o;
+#pragma unroll
+    for (int j = 0; j < BL; ++j) o.v[j] = sum[j];
+    *reinterpret_cast<V*>(z + off) = o;
+    return;
+  }
+  if (MODE & kFirst) yp = yc;
+  constexpr T twelfth = (T)(1.0 / 12.0);
+  V nx;
+#pragma unroll
+  for (int j = 0; j < BL; ++j) nx.v[j] = fma(twelfth, sum[j], (T)2 * yc.v[j] - yp.v[j] - zc.v[j]);
+  if (!(MODE & kLast)) *reinterpret_cast<V*>(out + off) = nx;
+  if (MODE == kMid) return;
+  if (MODE & kFirst) {
+#pragma unroll
+    for (int j = 0; j < BL; ++j) r.v[j] = fma(wn, nx.v[j], wc * yc.v[j]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < BL; ++j) r.v[j] = fma(wn, nx.v[j], fma(wc, yc.v[j], fma(wp, yp.v[j], r.v[j])));
+  }
+  if (MODE & kLast) {
+#pragma unroll
+    for (int j = 0; j < BL; ++j)
+      if (col0 + j < bout) rout[(int64_t)row * rs + (int64_t)(col0 + j) * cs] = (double)r.v[j];
+  } else {
+    *reinterpret_cast<V*>(acc + off) = r;
+  }
+}
+
 // ------------------------------------------------------- batched leapfrog
 // Many independent problems stacked into one block-diagonal operator: every
 // problem owns whole 64-row slices (rows padded to a multiple of 64), slice s
@@ -870,6 +934,55 @@ int launch_lf4_b(const SellOp& A, int mode, const void* cur, const void* prev, v
 #undef KF_LF4
   KF_HIP(hipGetLastError());
   return KF_OK;
+}
+
+template <typename T, int B, int LPR, int W>
+int launch_st4_w(const SellOp& A, int mode, const void* cur, const void* prev, void* out, void* acc, void* z,
+                 double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap,
+                 hipStream_t st) {
+#define KF_ST4(M)                                                                                                   \
+  hipLaunchKernelGGL((k_leapfrog4_st<T, B, M, LPR, W>), dim3(ceil_div64((int64_t)A.nslices * LPR, 4)), dim3(256), 0,  \
+                     st, A.n, A.nslices, static_cast<const T*>(A.st.val), A.st.off, A.st.mask, A.st.stride,            \
+                     static_cast<const T*>(cur), static_cast<const T*>(prev), static_cast<T*>(out),                    \
+                     static_cast<T*>(acc), static_cast<T*>(z), rout, rs, cs, bout, (T)wp, (T)wc, (T)wn, remap)
+  KF_ST4(-1);
+  switch (mode) {
+    case kMid: KF_ST4(kMid); break;
+    case kFirst: KF_ST4(kFirst); break;
+    case kMidAcc: KF_ST4(kMidAcc); break;
+    case kLast: KF_ST4(kLast); break;
+    default: KF_ST4(kFirstLast); break;
+  }
+#undef KF_ST4
+  KF_HIP(hipGetLastError());
+  return KF_OK;
+}
+
+// (16 bytes of a row per lane; as many lanes share it)
+template <typename T, int B>
+int launch_st4_b(const SellOp& A, int mode, const void* cur, const void* prev, void* out, void* acc, void* z,
+                 double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap,
+                 hipStream_t st) {
+  constexpr int LPR = B * sizeof(T) >= 64 ? 4 : (B * sizeof(T) >= 32 ? 2 : 1);
+  if (A.st.stride == 5)
+    return launch_st4_w<T, B, LPR, 5>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+  if (A.st.stride == 7)
+    return launch_st4_w<T, B, LPR, 7>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+  return launch_st4_w<T, B, LPR, 0>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+}
+
+template <typename T>
+int launch_st4(const SellOp& A, int b, int mode, const void* cur, const void* prev, void* out, void* acc, void* z,
+               double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap,
+               hipStream_t st) {
+  switch (b) {
+    case 1: return launch_st4_b<T, 1>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    case 2: return launch_st4_b<T, 2>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    case 4: return launch_st4_b<T, 4>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    case 8: return launch_st4_b<T, 8>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    case 16: return launch_st4_b<T, 16>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    default: set_error("fourth-order step: block width must be 1, 2, 4, 8 or 16"); return KF_EINVAL;
+  }
 }
 
 template <typename T, typename IT>
@@ -1490,6 +1603,11 @@ int launch_leapfrog_mp(const SellOp& A, const MultiStepPlan& pl, int l0, int s, 
 int launch_leapfrog4(const SellOp& A, int b, int mode, const void* cur, const void* prev, void* out, void* acc, void* z,
                      double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int xcd_remap,
                      hipStream_t st) {
+  if (A.st.width > 0) {
+    if (A.val_bytes == 8)
+      return launch_st4<double>(A, b, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, xcd_remap, st);
+    return launch_st4<float>(A, b, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, xcd_remap, st);
+  }
   if (A.val_bytes == 8) {
     if (A.idx_bytes == 2)
       return launch_lf4_t<double, int16_t>(A, b, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn,

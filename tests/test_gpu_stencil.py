@@ -126,3 +126,20 @@ def test_several_steps_per_launch_bitwise(dim, n, b, precision):
                 P.apply_filter_noalloc(x, y)
                 assert torch.equal(y, out[0]), L
         assert torch.equal(out[0], out[1]), (L, (out[0] - out[1]).abs().max())
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("kind", ["63x1", "65x3", "200x15", "grid2_23", "grid3_9", "broken"])
+def test_fourth_order_step_over_stencils_bitwise(kind, precision):
+    import torch
+
+    from paper_2402_08515_amd import kf
+
+    S, m = _matrix(kind)
+    tau = 1.8 / np.sqrt(np.abs(S).sum(1).max() / m.min())
+    for b in (1, 3, 8, 16):
+        x = torch.from_numpy(start_block(S.shape[0], b, 12)).cuda()
+        for L in (2, 3, 8):
+            out = [kf.Problem(S, m, 0.3 / tau, 0.6 / tau, tau, L, precision=precision, index_bytes=ib, stepper=4)
+                   .apply_filter(x) for ib in (0, 4)]
+            assert torch.equal(out[0], out[1]), (b, L)
