@@ -4,7 +4,8 @@
 // G = I up to rounding; the solver works on the symmetric H (its distance
 // from the generalized problem is bounded by |G - I| |theta|, reported as the
 // orthogonality error).  Steps:
-//   1. Householder reduction of H to tridiagonal form (one workgroup; the
+//   1. Householder reduction of H to tridiagonal form (one launch per
+//      reflector, the last 128 and small matrices in one workgroup; the
 //      reflectors stay in the lower triangle of the work matrix);
 //   2. all eigenvalues by Sturm-count bisection, one lane per eigenvalue;
 //   3. eigenvectors for the selected eigenvalues only, by inverse iteration
@@ -35,6 +36,47 @@ __device__ __forceinline__ double wave_sum_e(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
   return v;
+}
+
+// Sum over the wavefront through the DPP paths of the vector unit (row shifts,
+// then the two row broadcasts), the same value in every lane: six dependent
+// adds instead of six trips through the LDS permute unit.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, true);
+  return v + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+__device__ __forceinline__ double wave_total(double v) {
+  v = dpp_add<0x111, 0xF>(v);  // row_shr:1, 2, 4, 8
+  v = dpp_add<0x112, 0xF>(v);
+  v = dpp_add<0x114, 0xF>(v);
+  v = dpp_add<0x118, 0xF>(v);
+  v = dpp_add<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+  v = dpp_add<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+  return lane_value(v, 63);
+}
+
+// The same sum as wave_sum_e, bit for bit (lanes 32 apart first, then 16, 8,
+// 4, 2, 1), without its trips through the LDS permute unit: half-wave and row
+// swaps, then row rotations (after the step for 8 a row repeats every 8 lanes,
+// so a rotation by 4 reads the lane an exchange by 4 would, and so on).
+__device__ __forceinline__ double wave_butterfly(double v) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  u32x2 lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+  u32x2 hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+  v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+  lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+  hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+  v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+  v = dpp_add<0x128, 0xF>(v);  // row_ror:8, 4, 2, 1
+  v = dpp_add<0x124, 0xF>(v);
+  v = dpp_add<0x122, 0xF>(v);
+  return dpp_add<0x121, 0xF>(v);
 }
 
 // Sum over the workgroup, same value and summation order in every thread.
@@ -299,23 +341,299 @@ __global__ __launch_bounds__(256) void k_tri_step(int m, int k, double* __restri
   }
 }
 
-__device__ int sturm_count(int m, const double* __restrict__ d, const double* __restrict__ e2, double x,
-                           double pivmin) {
+// The same step, bit for bit, in registers, one column per wavefront.  The
+// four wavefronts form the two sums of k_tri_step exactly as it does (element
+// tid + 256 u per thread, rows from base = k rounded down to 256), and each
+// holds the rows k + 1 + lane + 64 u of w_{k-1}, v_{k-1} and reflector k, where
+// its own column j > k is updated.  Every load of the launch (p, v and column k
+// in both arrangements, the owned column) is issued at once, so a launch is its
+// own latency, one trip to memory and three sums: 6.0 -> 4.5 us at order 440.
+// MT: 64 MT rows cover base .. m.
+template <int MT>
+__global__ __launch_bounds__(256) void k_tri_wave(int m, int k, double* __restrict__ A, double* __restrict__ d,
+                                                  double* __restrict__ e, double* __restrict__ tau,
+                                                  double* __restrict__ pv) {
+  __shared__ double red[2][4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int gw = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + wave));
+  const int j = min(k + 1 + gw, m - 1);
+  const bool own = k + 1 + gw < m;
+  const int base = k & ~255;
+  const double* __restrict__ pprev = pv + (int64_t)((k + 1) & 1) * m;
+  const double* __restrict__ vprev = pv + (int64_t)(2 + ((k + 1) & 1)) * m;
+  double* __restrict__ pcur = pv + (int64_t)(k & 1) * m;
+  double* __restrict__ vcur = pv + (int64_t)(2 + (k & 1)) * m;
+  const double* __restrict__ colk = A + (int64_t)k * m;
+  double* __restrict__ colj = A + (int64_t)j * m;
+  const bool some = k > 0;
+  constexpr int MA = (MT + 3) / 4;
+  double pa[MA], va[MA], ca[MA], w[MT], v[MT], c[MT], x[MT];
+#pragma unroll
+  for (int t = 0; t < MA; ++t) {
+    const int i = base + (int)threadIdx.x + 256 * t;
+    const bool ok = i >= k && i < m;
+    pa[t] = ok && some ? pprev[i] : 0.0;
+    va[t] = ok && some ? vprev[i] : 0.0;
+    ca[t] = ok ? colk[i] : 0.0;
+  }
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    const int i = k + 1 + lane + 64 * t;
+    const bool ok = i < m;
+    w[t] = ok && some ? pprev[i] : 0.0;
+    v[t] = ok && some ? vprev[i] : 0.0;
+    c[t] = ok ? colk[i] : 0.0;
+    x[t] = ok ? colj[i] : 0.0;
+  }
+  const double pk = some ? pprev[k] : 0.0, vpk = some ? vprev[k] : 0.0, ck = colk[k];
+  const double pj = some ? pprev[j] : 0.0, vj = some ? vprev[j] : 0.0;
+  const double tprev = some ? tau[k - 1] : 0.0;
+  auto total = [&](double part, double* r) -> double {
+    part = wave_butterfly(part);
+    if (lane == 0) r[wave] = part;
+    __syncthreads();
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s += r[q];
+    return s;
+  };
+  // w_{k-1} = p - (tau/2)(p.v) v
+  double part = 0.0;
+#pragma unroll
+  for (int t = 0; t < MA; ++t) part = fma(pa[t], va[t], part);
+  const double K = 0.5 * tprev * total(part, red[0]);
+  const double wk = pk - K * vpk, wj = pj - K * vj;
+  // column k after reflector k-1, and reflector k
+  part = 0.0;
+#pragma unroll
+  for (int t = 0; t < MA; ++t) {
+    const double wa = pa[t] - K * va[t];
+    const double a = ca[t] - va[t] * wk - wa * vpk;
+    if (base + (int)threadIdx.x + 256 * t >= k + 2) part = fma(a, a, part);
+  }
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    w[t] = w[t] - K * v[t];
+    c[t] = c[t] - v[t] * wk - w[t] * vpk;
+  }
+  const double s = total(part, red[1]);
+  const double dk = ck - vpk * wk - wk * vpk;
+  const double alpha = lane_value(c[0], 0);
+  double beta = alpha, tk = 0.0, v0 = 1.0;
+  if (s > 0.0) {
+    const double mu = sqrt(alpha * alpha + s);
+    beta = alpha <= 0.0 ? mu : -mu;
+    v0 = alpha - beta;
+    tk = (beta - alpha) / beta;
+  }
+#pragma unroll
+  for (int t = 0; t < MT; ++t) c[t] = (t == 0 && lane == 0) ? 1.0 : (tk == 0.0 ? 0.0 : c[t] / v0);
+  if (gw == 0) {
+    if (lane == 0) {
+      d[k] = dk;
+      e[k] = beta;
+      tau[k] = tk;
+    }
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const int i = k + 1 + lane + 64 * t;
+      if (i < m) {
+        vcur[i] = c[t];
+        if (some) A[i + (int64_t)(k - 1) * m] = v[t];
+      }
+    }
+  }
+  if (!own) return;
+  double dot = 0.0;
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    const int i = k + 1 + lane + 64 * t;
+    if (i < m) {
+      const double a = x[t] - v[t] * wj - w[t] * vj;
+      colj[i] = a;
+      dot = fma(a, c[t], dot);
+      if (k == m - 2) d[m - 1] = a;
+    }
+  }
+  dot = wave_butterfly(dot);
+  if (lane == 0) pcur[j] = tk * dot;
+}
+
+// The last reflectors (trailing order n = m - k0 <= kTriTail, k0 >= 1) in one
+// workgroup with the trailing matrix in LDS, again with every sum and product
+// of k_tri_step: the rows are elements (i mod 256) of the four parts of its
+// sums.  Three barriers and the LDS traffic of the matrix per reflector, 2.6 us
+// on average, against 3.6 us for a launch of k_tri_wave.
+constexpr int kTriTail = 128;
+__global__ __launch_bounds__(1024) void k_tri_tail(int m, int k0, double* __restrict__ A, double* __restrict__ d,
+                                                   double* __restrict__ e, double* __restrict__ tau,
+                                                   const double* __restrict__ pv) {
+  extern __shared__ double sh[];
+  const int n = m - k0, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  double* a = sh;               // a[c * n + r], columns and rows k0 ..
+  double* p = a + n * n;        // p_{k-1}, then p_k
+  double* v = p + kTriTail;     // v_{k-1}
+  double* w = v + kTriTail;
+  double* y = w + kTriTail;     // column k after reflector k-1
+  double* vn = y + kTriTail;    // v_k
+  double* red = vn + kTriTail;  // 2 x 4
+  {
+    const double* __restrict__ pp = pv + (int64_t)((k0 + 1) & 1) * m;
+    const double* __restrict__ vp = pv + (int64_t)(2 + ((k0 + 1) & 1)) * m;
+    for (int c = wave; c < n; c += 16)
+      for (int r = lane; r < n; r += 64) a[c * n + r] = A[(k0 + r) + (int64_t)(k0 + c) * m];
+    for (int r = tid; r < n; r += 1024) {
+      p[r] = pp[k0 + r];
+      v[r] = vp[k0 + r];
+    }
+  }
+  double tprev = tau[k0 - 1];
+  // the row of this thread's element of the four-part sums (threads 0 .. 255)
+  const int row = ((tid - k0) & 255);  // (k0 + row) mod 256 == tid
+  __syncthreads();
+  for (int k = 0; k + 2 <= n; ++k) {
+    const bool mine = tid < 256 && row >= k && row < n;
+    double part = mine ? fma(p[row], v[row], 0.0) : 0.0;
+    if (tid < 256) {
+      part = wave_butterfly(part);
+      if (lane == 0) red[wave] = part;
+    }
+    __syncthreads();
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s += red[q];
+    const double K = 0.5 * tprev * s;
+    const double vpk = v[k], wk = p[k] - K * vpk;
+    if (tid < 256) {
+      part = 0.0;
+      if (mine) {
+        const double wr = p[row] - K * v[row];
+        const double b = a[k * n + row] - v[row] * wk - wr * vpk;
+        w[row] = wr;
+        y[row] = b;
+        if (row >= k + 2) part = fma(b, b, part);
+      }
+      part = wave_butterfly(part);
+      if (lane == 0) red[4 + wave] = part;
+    }
+    __syncthreads();
+    s = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s += red[4 + q];
+    const double alpha = y[k + 1];
+    double beta = alpha, tk = 0.0, v0 = 1.0;
+    if (s > 0.0) {
+      const double mu = sqrt(alpha * alpha + s);
+      beta = alpha <= 0.0 ? mu : -mu;
+      v0 = alpha - beta;
+      tk = (beta - alpha) / beta;
+    }
+    double c[2], vv[2], ww[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int r = k + 1 + lane + 64 * u;
+      const bool ok = r < n;
+      vv[u] = ok ? v[r] : 0.0;
+      ww[u] = ok ? w[r] : 0.0;
+      c[u] = (u == 0 && lane == 0) ? 1.0 : (tk == 0.0 || !ok ? 0.0 : y[r] / v0);
+      if (ok && wave == 15) {
+        vn[r] = c[u];
+        A[(k0 + r) + (int64_t)(k0 + k - 1) * m] = vv[u];
+      }
+    }
+    if (tid == 0) {
+      d[k0 + k] = y[k];
+      e[k0 + k] = beta;
+      tau[k0 + k] = tk;
+    }
+    for (int j = k + 1 + wave; j < n; j += 16) {
+      const double wj = w[j], vj = v[j];
+      double dot = 0.0;
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int r = k + 1 + lane + 64 * u;
+        if (r < n) {
+          const double b = a[j * n + r] - vv[u] * wj - ww[u] * vj;
+          a[j * n + r] = b;
+          dot = fma(b, c[u], dot);
+          if (k == n - 2) d[m - 1] = b;
+        }
+      }
+      dot = wave_butterfly(dot);
+      if (lane == 0) p[j] = tk * dot;
+    }
+    tprev = tk;
+    __syncthreads();
+    double* t = v;
+    v = vn;
+    vn = t;
+  }
+}
+
+// Number of eigenvalues of the tridiagonal matrix below x, the pairs (d_j,
+// e_{j-1}^2) in LDS, padded to a multiple of kSturmB rows: negative ratios q_j =
+// (d_j - x) - e_{j-1}^2 / q_{j-1}, a chain of divisions.
+constexpr int kSturmB = 8;
+__device__ __forceinline__ int sturm_count(int m, const double2* __restrict__ de, double x, double pivmin) {
   int c = 0;
-  double q = d[0] - x;
-  if (fabs(q) < pivmin) q = -pivmin;
-  if (q < 0.0) ++c;
-  for (int j = 1; j < m; ++j) {
-    q = (d[j] - x) - e2[j - 1] / q;
-    if (fabs(q) < pivmin) q = -pivmin;
-    if (q < 0.0) ++c;
+  double q = 1.0;
+  double2 cur[kSturmB], nxt[kSturmB];
+#pragma unroll
+  for (int u = 0; u < kSturmB; ++u) cur[u] = de[u];
+  for (int j0 = 0; j0 < m; j0 += kSturmB) {
+#pragma unroll
+    for (int u = 0; u < kSturmB; ++u) nxt[u] = de[j0 + kSturmB + u];
+#pragma unroll
+    for (int u = 0; u < kSturmB; ++u) {
+      // (row 0: e_{-1} = 0 over q = 1; rows past m count nothing)
+      q = (cur[u].x - x) - cur[u].y / q;
+      if (fabs(q) < pivmin) q = -pivmin;
+      if (q < 0.0 && j0 + u < m) ++c;
+    }
+#pragma unroll
+    for (int u = 0; u < kSturmB; ++u) cur[u] = nxt[u];
   }
   return c;
 }
 
+// The same count from the sign changes of p_j = (d_j - x) p_{j-1} -
+// e_{j-1}^2 p_{j-2}, one dependent multiply-add per row; entries and x scaled by
+// a power of two to at most one (`scale` for x and d), so that in eight rows
+// |p| grows at most by 3^8, and brought back by a power of two every eight rows.
+// Rounds differently from the ratios, so it is for points many roundings
+// away from the eigenvalue sought, where the counts agree.
+__device__ __forceinline__ int sturm_count_far(int m, const double2* __restrict__ de, double x, double scale) {
+  int cnt = 0;
+  double p1 = 1.0, p2 = 0.0;
+  x *= scale;
+  const double scale2 = scale * scale;
+  double2 cur[kSturmB], nxt[kSturmB];
+#pragma unroll
+  for (int u = 0; u < kSturmB; ++u) cur[u] = de[u];
+  for (int j0 = 0; j0 < m; j0 += kSturmB) {
+#pragma unroll
+    for (int u = 0; u < kSturmB; ++u) nxt[u] = de[j0 + kSturmB + u];
+#pragma unroll
+    for (int u = 0; u < kSturmB; ++u) {
+      double p = fma(fma(cur[u].x, scale, -x), p1, -(cur[u].y * scale2) * p2);
+      p = p == 0.0 ? -0x1p-200 * p1 : p;
+      if (j0 + u < m) cnt += (int)((uint32_t)(__double2hiint(p) ^ __double2hiint(p1)) >> 31);
+      p2 = p1;
+      p1 = p;
+    }
+    const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p1), fabs(p2)));
+    p1 = ldexp(p1, ex);
+    p2 = ldexp(p2, ex);
+#pragma unroll
+    for (int u = 0; u < kSturmB; ++u) cur[u] = nxt[u];
+  }
+  return cnt;
+}
+
 __global__ __launch_bounds__(256) void k_tri_prep(int m, const double* __restrict__ d, const double* __restrict__ e,
-                                                  double* __restrict__ e2, double* __restrict__ bounds) {
-  // e2 = e^2; bounds = {gershgorin lo, hi, pivmin}
+                                                  double* __restrict__ bounds) {
+  // bounds = {gershgorin lo, hi, pivmin, scale}
   __shared__ double red[3][4];
   double lo = INFINITY, hi = -INFINITY, emax2 = 0.0;
   for (int j = threadIdx.x; j < m; j += blockDim.x) {
@@ -323,8 +641,7 @@ __global__ __launch_bounds__(256) void k_tri_prep(int m, const double* __restric
     lo = fmin(lo, d[j] - r);
     hi = fmax(hi, d[j] + r);
     if (j < m - 1) {
-      e2[j] = e[j] * e[j];
-      emax2 = fmax(emax2, e2[j]);
+      emax2 = fmax(emax2, e[j] * e[j]);
     }
   }
 #pragma unroll
@@ -355,24 +672,39 @@ __global__ __launch_bounds__(256) void k_tri_prep(int m, const double* __restric
     bounds[0] = lo - 2.0 * DBL_EPSILON * tn - pivmin;
     bounds[1] = hi + 2.0 * DBL_EPSILON * tn + pivmin;
     bounds[2] = pivmin;
+    // the power of two that scales the matrix and its bracket to at most one
+    int ex = 0;
+    (void)frexp(fmax(tn, DBL_MIN), &ex);
+    bounds[3] = ldexp(1.0, -min(max(ex + 1, -1000), 1000));
   }
 }
 
 // Eigenvalue i by 65-section: the 64 lanes of a wavefront evaluate Sturm
 // counts at 64 interior points of the bracket, which shrinks 65-fold per
-// round until it is a few ulps wide.
-__global__ __launch_bounds__(256) void k_bisect(int m, const double* __restrict__ d, const double* __restrict__ e2,
+// round until it is a few ulps wide.  The counts are chains of m dependent
+// steps, ten times.  While the points are at least 2^-20 of the spectrum's
+// scale apart, one of them lies within rounding (some 2^-45) of the eigenvalue
+// only once in 2^25 rounds, and the division-free count serves; the others
+// use the ratios.  440 eigenvalues: 486 us with ratios from global memory
+// throughout, 286 us so.
+__global__ __launch_bounds__(256) void k_bisect(int m, const double* __restrict__ d, const double* __restrict__ e,
                                                 const double* __restrict__ bounds, double* __restrict__ theta) {
+  extern __shared__ double2 de[];
+  for (int j = threadIdx.x; j < (m + kSturmB - 1) / kSturmB * kSturmB + kSturmB; j += blockDim.x) {
+    const double ej = j > 0 && j < m ? e[j - 1] : 0.0;
+    de[j] = make_double2(j < m ? d[j] : 0.0, ej * ej);
+  }
+  __syncthreads();
   const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (i >= m) return;
   double lo = bounds[0], hi = bounds[1];
-  const double pivmin = bounds[2];
+  const double pivmin = bounds[2], scale = bounds[3];
   for (int it = 0; it < 64; ++it) {
     if (hi - lo <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + pivmin) break;
     const double h = (hi - lo) / 65.0;
     const double x = lo + (lane + 1) * h;
-    const bool above = sturm_count(m, d, e2, x, pivmin) > i;
+    const bool above = (h * scale >= 0x1p-20 ? sturm_count_far(m, de, x, scale) : sturm_count(m, de, x, pivmin)) > i;
     const unsigned long long mask = __ballot(above);
     double nlo, nhi;
     if (mask == 0ull) {
@@ -390,181 +722,202 @@ __global__ __launch_bounds__(256) void k_bisect(int m, const double* __restrict_
   if (lane == 0) theta[i] = 0.5 * (lo + hi);
 }
 
-// Inverse iteration, one lane per selected eigenvalue; the recurrences carry
-// their running values in registers.  Within a cluster of (nearly) equal
-// values the shifts are kept 10 eps apart and each member starts from its own
-// vector (its position in the cluster sets the phase), so the members
-// converge to different directions of the eigenspace; k_cluster_orth then
-// orthonormalises each cluster's vectors.  The lane's work
-// arrays (LU factors and the iterate) are interleaved across lanes, element i
-// of lane c at [i * ldw + c], so that at every step the lanes of a wavefront
-// touch consecutive addresses.  Finished vectors go to Z (m x nsel).
-// LDS: the work arrays of the wavefront's first ldw lanes live in LDS (the
-// recurrences are chains of dependent steps, and LDS answers in a fraction of
-// the time of the cache hierarchy); otherwise in `scratch` (global memory).
-constexpr int kIvB = 8;  // rows loaded ahead of the running values
-constexpr int kIvLdsBytes = 65536;  // LDS for the work arrays of one wavefront
-template <bool LDS>
+// Inverse iteration, one selected eigenvalue per workgroup of one wavefront.
+// Within a cluster of (nearly) equal values the shifts are kept 10 eps apart
+// and each member starts from its own vector (its position in the cluster
+// sets the phase), so the members converge to different directions of the
+// eigenspace; k_cluster_orth then orthonormalises each cluster's vectors.  The
+// recurrences run in one lane, their running values in registers, the LU
+// factors and the iterate in LDS; what is independent along m (start vector,
+// the pivots' inverses, the result) is done by all lanes.  Bound by the issue
+// and latency of a single wavefront's chain: one division per row in the
+// factorisation, one multiply-add per row forward and two operations backward;
+// the rows are read kIvB ahead, with the normalisation of an iterate applied
+// by the next sweep's reads.  110 vectors of order 440: 560 us with two
+// divisions per row, several lanes' arrays interleaved and separate passes for
+// the norms, 232 us so.
+constexpr int kIvB = 8;
+// doubles of LDS: five arrays and one flag word per kIvB rows
+__host__ __device__ constexpr int invit_doubles(int m) { return 5 * m + (m / kIvB + 2) / 2 + 1; }
 __global__ __launch_bounds__(64) void k_invit(int m, const double* __restrict__ d, const double* __restrict__ e,
                                               const double* __restrict__ bounds, int ncl,
                                               const int32_t* __restrict__ cstart, const double* __restrict__ sel,
-                                              double* __restrict__ Z, double* __restrict__ scratch, int ldw) {
+                                              double* __restrict__ Z) {
   extern __shared__ double ivs[];
-  if (LDS && (int)threadIdx.x >= ldw) return;
-  const int s = LDS ? blockIdx.x * ldw + threadIdx.x : blockIdx.x * blockDim.x + threadIdx.x;
-  const int nsel = cstart[ncl];
-  if (s >= nsel) return;
+  const int lane = threadIdx.x, s = blockIdx.x;
   const double tn = fmax(fabs(bounds[0]), fabs(bounds[1]));
   const double tiny = DBL_EPSILON * fmax(tn, DBL_MIN);
-  const int64_t blk = (int64_t)m * ldw;
-  double* __restrict__ rinv = LDS ? ivs + threadIdx.x : scratch + s;
-  double* __restrict__ u1 = rinv + blk;
-  double* __restrict__ u2 = u1 + blk;
-  double* __restrict__ lm = u2 + blk;
-  double* __restrict__ pv = lm + blk;
-  double* __restrict__ z = pv + blk;
-  {
-    // the cluster holding s (cstart ascending, cstart[0] = 0)
-    int lo = 0, hi = ncl;  // cstart[lo] <= s < cstart[hi]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (cstart[mid] <= s) lo = mid;
-      else hi = mid;
-    }
-    const int c0 = cstart[lo];
+  double* __restrict__ rinv = ivs;
+  double* __restrict__ u1 = rinv + m;
+  double* __restrict__ u2 = u1 + m;
+  double* __restrict__ lm = u2 + m;
+  double* __restrict__ z = lm + m;
+  uint32_t* __restrict__ flags = reinterpret_cast<uint32_t*>(z + m);
+  // the first member of s's cluster (cstart ascending, cstart[0] = 0)
+  int lo = 0, hi = ncl;  // cstart[lo] <= s < cstart[hi]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (cstart[mid] <= s) lo = mid;
+    else hi = mid;
+  }
+  const int c0 = cstart[lo], pos = s - c0;
+  // start vector: 1 + 0.5 u, u in [-1, 1) from an integer hash of (row,
+  // position in the cluster), so that the members of a cluster start from
+  // linearly independent vectors
+  for (int i = lane; i < m; i += 64) {
+    uint32_t h = (uint32_t)i * 0x9E3779B1u ^ ((uint32_t)pos + 1u) * 0x85EBCA77u;
+    h ^= h >> 16;
+    h *= 0x7FEB352Du;
+    h ^= h >> 15;
+    h *= 0x846CA68Bu;
+    h ^= h >> 16;
+    z[i] = 1.0 + 0.5 * ((double)h * (2.0 / 4294967296.0) - 1.0);
+  }
+  // Blocks of kIvB rows run without a test per row, the rest of the rows with
+  // one (m - 1 eliminations, then m - 1 rows forward and m back).
+  const int full = (m - 1) / kIvB * kIvB;
+  if (lane == 0) {
     // shifts of the cluster's members up to s, each at least 10 eps above the last
     double lam = sel[c0];
     for (int t = c0 + 1; t <= s; ++t) lam = sel[t] - lam < 10.0 * tiny ? lam + 10.0 * tiny : sel[t];
-    const int pos = s - c0;
     // LU of T - lam I with partial pivoting; row i is (a, b, c) at columns
-    // (i, i+1, i+2) while it is being eliminated.  The recurrences below load
-    // kIvB rows ahead of the running values (the loads do not depend on them).
+    // (i, i+1, i+2) while it is being eliminated
     double a = d[0] - lam;
     double b = m > 1 ? e[0] : 0.0;
-    for (int i0 = 0; i0 + 1 < m; i0 += kIvB) {
-      double eb[kIvB], dn[kIvB], en[kIvB];
+    uint32_t fl = 0;
+    auto eliminate = [&](int i, int u, double be, double ad, double ce) {
+      const bool sw = fabs(a) < fabs(be);
+      // (a zero pivot has a zero below it: l = 0)
+      const double piv = sw ? be : a;
+      const double l = (sw ? a : be) / (piv == 0.0 ? 1.0 : piv);
+      const double v1 = sw ? ad : b;
+      rinv[i] = !sw && fabs(a) < tiny ? (a < 0.0 ? -tiny : tiny) : piv;
+      lm[i] = l;
+      u1[i] = v1;
+      u2[i] = sw ? ce : 0.0;
+      fl |= (sw ? 1u : 0u) << u;
+      a = (sw ? b : ad) - l * v1;
+      b = sw ? -l * ce : ce;
+    };
+    double eb[kIvB], dn[kIvB], en[kIvB];
+    auto load = [&](int i0) {
 #pragma unroll
       for (int u = 0; u < kIvB; ++u) {
-        const int i = i0 + u;
-        eb[u] = i + 1 < m ? e[i] : 0.0;
-        dn[u] = i + 1 < m ? d[i + 1] : 0.0;
-        en[u] = i + 2 < m ? e[i + 1] : 0.0;
+        const int i = min(i0 + u, m - 2);
+        eb[u] = e[i];
+        dn[u] = d[i + 1];
+        const double en1 = e[min(i + 1, m - 2)];
+        en[u] = i + 2 < m ? en1 : 0.0;
       }
+    };
+    if (full > 0) load(0);
+    for (int i0 = 0; i0 < full; i0 += kIvB) {
+      double be[kIvB], ad[kIvB], ce[kIvB];
 #pragma unroll
       for (int u = 0; u < kIvB; ++u) {
-        const int i = i0 + u;
-        if (i + 1 >= m) break;
-        const int64_t o = (int64_t)i * ldw;
-        const double bi = eb[u];
-        const double ai1 = dn[u] - lam;
-        const double ci1 = en[u];
-        double na, nb;
-        if (fabs(a) >= fabs(bi)) {
-          const double l = (a != 0.0) ? bi / a : 0.0;
-          pv[o] = 0.0;
-          lm[o] = l;
-          u2[o] = 0.0;
-          u1[o] = b;
-          if (fabs(a) < tiny) a = a < 0.0 ? -tiny : tiny;
-          rinv[o] = 1.0 / a;
-          na = ai1 - l * b;
-          nb = ci1;
-        } else {
-          const double l = a / bi;
-          pv[o] = 1.0;
-          lm[o] = l;
-          u1[o] = ai1;
-          u2[o] = ci1;
-          rinv[o] = 1.0 / bi;
-          na = b - l * ai1;
-          nb = -l * ci1;
-        }
-        a = na;
-        b = nb;
+        be[u] = eb[u];
+        ad[u] = dn[u] - lam;
+        ce[u] = en[u];
       }
+      load(i0 + kIvB);
+      fl = 0;
+#pragma unroll
+      for (int u = 0; u < kIvB; ++u) eliminate(i0 + u, u, be[u], ad[u], ce[u]);
+      flags[i0 / kIvB] = fl;
     }
-    const int64_t ol = (int64_t)(m - 1) * ldw;
-    if (fabs(a) < tiny) a = a < 0.0 ? -tiny : tiny;
-    rinv[ol] = 1.0 / a;
-    u1[ol] = 0.0;
-    u2[ol] = 0.0;
-    if (m >= 2) u2[ol - ldw] = 0.0;
-    // start vector: 1 + 0.5 u, u in [-1, 1) from an integer hash of (row,
-    // position in the cluster), so that the members of a cluster start from
-    // linearly independent vectors
-    for (int i = 0; i < m; ++i) {
-      uint32_t h = (uint32_t)i * 0x9E3779B1u ^ ((uint32_t)pos + 1u) * 0x85EBCA77u;
-      h ^= h >> 16;
-      h *= 0x7FEB352Du;
-      h ^= h >> 15;
-      h *= 0x846CA68Bu;
-      h ^= h >> 16;
-      z[(int64_t)i * ldw] = 1.0 + 0.5 * ((double)h * (2.0 / 4294967296.0) - 1.0);
-    }
+    fl = 0;
+    for (int i = full; i + 1 < m; ++i) eliminate(i, i - full, e[i], d[i + 1] - lam, i + 2 < m ? e[i + 1] : 0.0);
+    flags[full / kIvB] = fl;
+    rinv[m - 1] = fabs(a) < tiny ? (a < 0.0 ? -tiny : tiny) : a;
+    u1[m - 1] = 0.0;
+    u2[m - 1] = 0.0;
+    if (m >= 2) u2[m - 2] = 0.0;
+  }
+  __syncthreads();
+  for (int i = lane; i < m; i += 64) rinv[i] = 1.0 / rinv[i];
+  __syncthreads();
+  double rs = 1.0;  // what normalises the iterate in z
+  if (lane == 0) {
     for (int it = 0; it < 3; ++it) {
-      // forward: row swaps and elimination, running value in a register
-      double y = z[0];
-      for (int i0 = 0; i0 + 1 < m; i0 += kIvB) {
-        double nxv[kIvB], pvv[kIvB], lmv[kIvB];
+      // forward: row swaps and elimination
+      double y = z[0] * rs;
+      {
+        auto row = [&](int i, bool sw, double zn, double l) {
+          const double top = sw ? zn : y, rest = sw ? y : zn;
+          z[i] = top;
+          y = rest - l * top;
+        };
+        double nz[kIvB], nl[kIvB];
+        uint32_t nf = 0;
+        // (rows up to full + kIvB - 1 of z and lm: inside the arrays' LDS)
+        auto load = [&](int i0) {
 #pragma unroll
-        for (int u = 0; u < kIvB; ++u) {
-          const int i = i0 + u;
-          const int64_t o = (int64_t)i * ldw;
-          const bool ok = i + 1 < m;
-          nxv[u] = ok ? z[o + ldw] : 0.0;
-          pvv[u] = ok ? pv[o] : 0.0;
-          lmv[u] = ok ? lm[o] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < kIvB; ++u) {
-          const int i = i0 + u;
-          if (i + 1 >= m) break;
-          double nx = nxv[u];
-          if (pvv[u] != 0.0) {
-            const double t = y;
-            y = nx;
-            nx = t;
+          for (int u = 0; u < kIvB; ++u) {
+            nz[u] = z[i0 + u + 1];
+            nl[u] = lm[i0 + u];
           }
-          z[(int64_t)i * ldw] = y;
-          y = nx - lmv[u] * y;
+          nf = flags[i0 / kIvB];
+        };
+        if (full > 0) load(0);
+        for (int i0 = 0; i0 < full; i0 += kIvB) {
+          double zv[kIvB], lv[kIvB];
+          const uint32_t fl = nf;
+#pragma unroll
+          for (int u = 0; u < kIvB; ++u) {
+            zv[u] = nz[u] * rs;
+            lv[u] = nl[u];
+          }
+          if (i0 + kIvB < full) load(i0 + kIvB);
+#pragma unroll
+          for (int u = 0; u < kIvB; ++u) row(i0 + u, (fl >> u) & 1u, zv[u], lv[u]);
         }
+        const uint32_t fl = flags[full / kIvB];
+        for (int i = full; i + 1 < m; ++i) row(i, (fl >> (i - full)) & 1u, z[i + 1] * rs, lm[i]);
       }
-      z[ol] = y;
+      z[m - 1] = y;
       // backward substitution with U (diagonal inverse, two superdiagonals)
-      double x1 = 0.0, x2 = 0.0, mx = 0.0;
-      for (int i0 = m - 1; i0 >= 0; i0 -= kIvB) {
-        double zv[kIvB], u1v[kIvB], u2v[kIvB], rv[kIvB];
-#pragma unroll
-        for (int u = 0; u < kIvB; ++u) {
-          const int i = i0 - u;
-          const int64_t o = (int64_t)i * ldw;
-          const bool ok = i >= 0;
-          zv[u] = ok ? z[o] : 0.0;
-          u1v[u] = ok ? u1[o] : 0.0;
-          u2v[u] = ok ? u2[o] : 0.0;
-          rv[u] = ok ? rinv[o] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < kIvB; ++u) {
-          const int i = i0 - u;
-          if (i < 0) break;
-          const double x = (zv[u] - u1v[u] * x1 - u2v[u] * x2) * rv[u];
-          z[(int64_t)i * ldw] = x;
-          mx = fmax(mx, fabs(x));
+      double x1 = 0.0, x2 = 0.0, nrm = 0.0;
+      {
+        auto row = [&](int i, double zi, double v1, double v2, double r) {
+          const double x = (fma(-v2, x2, zi) - v1 * x1) * r;
+          z[i] = x;
+          nrm = fma(x, x, nrm);
           x2 = x1;
           x1 = x;
+        };
+        double nz[kIvB], n1[kIvB], n2[kIvB], nr[kIvB];
+        auto load = [&](int i0) {
+#pragma unroll
+          for (int u = 0; u < kIvB; ++u) {
+            nz[u] = z[i0 - u];
+            n1[u] = u1[i0 - u];
+            n2[u] = u2[i0 - u];
+            nr[u] = rinv[i0 - u];
+          }
+        };
+        int i0 = m - 1;
+        if (i0 + 1 >= kIvB) load(i0);
+        for (; i0 + 1 >= kIvB; i0 -= kIvB) {
+          double zv[kIvB], v1[kIvB], v2[kIvB], rv[kIvB];
+#pragma unroll
+          for (int u = 0; u < kIvB; ++u) {
+            zv[u] = nz[u];
+            v1[u] = n1[u];
+            v2[u] = n2[u];
+            rv[u] = nr[u];
+          }
+          if (i0 + 1 >= 2 * kIvB) load(i0 - kIvB);
+#pragma unroll
+          for (int u = 0; u < kIvB; ++u) row(i0 - u, zv[u], v1[u], v2[u], rv[u]);
         }
+        for (; i0 >= 0; --i0) row(i0, z[i0], u1[i0], u2[i0], rinv[i0]);
       }
-      const double r = mx > 0.0 ? 1.0 / mx : 0.0;
-      for (int i = 0; i < m; ++i) z[(int64_t)i * ldw] *= r;
-      double nrm = 0.0;
-      for (int i = 0; i < m; ++i) nrm = fma(z[(int64_t)i * ldw], z[(int64_t)i * ldw], nrm);
-      const double rn = nrm > 0.0 ? 1.0 / sqrt(nrm) : 0.0;
-      for (int i = 0; i < m; ++i) z[(int64_t)i * ldw] *= rn;
+      rs = nrm > 0.0 ? 1.0 / sqrt(nrm) : 0.0;
     }
-    double* __restrict__ zs = Z + (int64_t)s * m;
-    for (int i = 0; i < m; ++i) zs[i] = z[(int64_t)i * ldw];
   }
+  __syncthreads();
+  const double r = lane_value(rs, 0);
+  for (int i = lane; i < m; i += 64) Z[(int64_t)s * m + i] = z[i] * r;
 }
 
 // The vectors of each cluster with more than one member (Z columns
@@ -607,9 +960,21 @@ __global__ __launch_bounds__(256) void k_cluster_orth(int m, int ncl, const int3
   }
 }
 
-// y = H_0 H_1 ... H_{m-3} z, H_k = I - tau_k v_k v_k^T acting on rows k+1..m-1,
-// v_k = (1, A[k+2.., k]).  One wavefront per vector; lane l keeps rows l+64t.
-template <int MT>
+// The reflectors' columns completed in place: column k < m - 2 gets zeros in
+// rows 0 .. k and one in row k + 1.
+__global__ __launch_bounds__(256) void k_reflector_heads(int m, double* __restrict__ A) {
+  const int k = blockIdx.x;
+  for (int i = threadIdx.x; i <= k + 1; i += 256) A[i + (int64_t)k * m] = i <= k ? 0.0 : 1.0;
+}
+
+// y = H_0 H_1 ... H_{m-3} z, H_k = I - tau_k v_k v_k^T, v_k = column k of A
+// (k_reflector_heads).  One wavefront per vector; lane l keeps rows l+64t (rows
+// past m read row 0, where every v_k is zero).  A chain of m - 2 wavefront
+// sums, each a few tens of instructions of one wavefront; the next D reflectors
+// are loaded while D are applied, since a trip to memory takes longer than one.
+// 110 vectors of order 440: 394 us with sums through the LDS permute unit and
+// one reflector at a time, 167 us so.
+template <int MT, int D>
 __global__ __launch_bounds__(256) void k_backtransform(int m, const double* __restrict__ A,
                                                        const double* __restrict__ tau, int nsel,
                                                        const double* __restrict__ Z, double* __restrict__ Y) {
@@ -617,26 +982,50 @@ __global__ __launch_bounds__(256) void k_backtransform(int m, const double* __re
   const int lane = threadIdx.x & 63;
   if (vec >= nsel) return;
   double y[MT];
+  int at[MT];
 #pragma unroll
   for (int t = 0; t < MT; ++t) {
     const int i = lane + 64 * t;
     y[t] = i < m ? Z[(int64_t)vec * m + i] : 0.0;
+    at[t] = i < m ? i : 0;
   }
-  for (int k = m - 3; k >= 0; --k) {
-    const double tk = tau[k];
-    if (tk == 0.0) continue;
-    const double* col = A + (int64_t)k * m;
-    double vi[MT];
-    double dot = 0.0;
+  // reflectors k, k-1, .., k-D+1 (below 0: tau 0)
+  auto load = [&](int k, double (&v)[D][MT], double (&tk)[D]) {
 #pragma unroll
-    for (int t = 0; t < MT; ++t) {
-      const int i = lane + 64 * t;
-      vi[t] = (i == k + 1) ? 1.0 : ((i > k + 1 && i < m) ? col[i] : 0.0);
-      dot = fma(vi[t], y[t], dot);
+    for (int q = 0; q < D; ++q) {
+      const int kq = max(k - q, 0);
+      const double* __restrict__ col = A + (int64_t)kq * m;
+      const double t0 = tau[kq];
+      tk[q] = k - q >= 0 ? t0 : 0.0;
+#pragma unroll
+      for (int t = 0; t < MT; ++t) v[q][t] = col[at[t]];
     }
-    dot = wave_sum_e(dot) * tk;
+  };
+  auto apply = [&](const double (&v)[D][MT], const double (&tk)[D]) {
 #pragma unroll
-    for (int t = 0; t < MT; ++t) y[t] -= dot * vi[t];
+    for (int q = 0; q < D; ++q) {
+      double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+      for (int t = 0; t < MT; ++t) {
+        if (t & 1)
+          s1 = fma(v[q][t], y[t], s1);
+        else
+          s0 = fma(v[q][t], y[t], s0);
+      }
+      const double dot = wave_total(s0 + s1) * tk[q];
+#pragma unroll
+      for (int t = 0; t < MT; ++t) y[t] -= dot * v[q][t];
+    }
+  };
+  if (m >= 3) {
+    double va[D][MT], vb[D][MT], ta[D], tb[D];
+    load(m - 3, va, ta);
+    for (int k = m - 3; k >= 0; k -= 2 * D) {
+      load(k - D, vb, tb);
+      apply(va, ta);
+      load(k - 2 * D, va, ta);
+      apply(vb, tb);
+    }
   }
 #pragma unroll
   for (int t = 0; t < MT; ++t) {
@@ -648,7 +1037,7 @@ __global__ __launch_bounds__(256) void k_backtransform(int m, const double* __re
 }  // namespace
 
 void free_eig(EigWork& w) {
-  double* ptrs[] = {w.A, w.d, w.e, w.e2, w.bounds, w.tau, w.theta, w.pv, w.Z, w.Y, w.scratch, w.sel};
+  double* ptrs[] = {w.A, w.d, w.e, w.bounds, w.tau, w.theta, w.pv, w.Z, w.Y, w.sel};
   for (double* p : ptrs)
     if (p) (void)hipFree(p);
   if (w.cl) (void)hipFree(w.cl);
@@ -657,14 +1046,14 @@ void free_eig(EigWork& w) {
 
 int eig_reserve(EigWork& w, int m, int nsel) {
   if ((size_t)m > w.cap_m) {
-    double** ps[] = {&w.A, &w.d, &w.e, &w.e2, &w.bounds, &w.tau, &w.theta, &w.pv};
+    double** ps[] = {&w.A, &w.d, &w.e, &w.bounds, &w.tau, &w.theta, &w.pv};
     for (double** p : ps) {
       if (*p) (void)hipFree(*p);
       *p = nullptr;
     }
     const size_t mm = (size_t)m;
     if (hipMalloc(&w.A, sizeof(double) * mm * mm) != hipSuccess || hipMalloc(&w.d, sizeof(double) * mm) != hipSuccess ||
-        hipMalloc(&w.e, sizeof(double) * mm) != hipSuccess || hipMalloc(&w.e2, sizeof(double) * mm) != hipSuccess ||
+        hipMalloc(&w.e, sizeof(double) * mm) != hipSuccess ||
         hipMalloc(&w.bounds, sizeof(double) * 4) != hipSuccess || hipMalloc(&w.tau, sizeof(double) * mm) != hipSuccess ||
         hipMalloc(&w.theta, sizeof(double) * mm) != hipSuccess || hipMalloc(&w.pv, sizeof(double) * 4 * mm) != hipSuccess) {
       set_error("eig_reserve: allocation failed");
@@ -674,7 +1063,7 @@ int eig_reserve(EigWork& w, int m, int nsel) {
     w.cap_sel = 0;  // Z/Y/scratch depend on m too
   }
   if ((size_t)nsel > w.cap_sel) {
-    double** ps[] = {&w.Z, &w.Y, &w.scratch, &w.sel};
+    double** ps[] = {&w.Z, &w.Y, &w.sel};
     for (double** p : ps) {
       if (*p) (void)hipFree(*p);
       *p = nullptr;
@@ -684,7 +1073,6 @@ int eig_reserve(EigWork& w, int m, int nsel) {
     const size_t ns = std::max<size_t>(nsel, 16);
     if (hipMalloc(&w.Z, sizeof(double) * w.cap_m * ns) != hipSuccess ||
         hipMalloc(&w.Y, sizeof(double) * w.cap_m * ns) != hipSuccess ||
-        hipMalloc(&w.scratch, sizeof(double) * 6 * w.cap_m * (ns + 64)) != hipSuccess ||
         hipMalloc(&w.sel, sizeof(double) * ns) != hipSuccess ||
         hipMalloc(&w.cl, sizeof(int32_t) * (ns + 1)) != hipSuccess) {
       set_error("eig_reserve: allocation failed");
@@ -712,15 +1100,35 @@ int eig_values(EigWork& w, int k, const double* H, int64_t ldh, hipStream_t st) 
     // one launch per reflector; the grid shrinks with the trailing matrix
     const size_t lds = sizeof(double) * (3 * (size_t)k + 32);
     for (int j = 0; j + 2 <= k; ++j) {
+      if (j >= 1 && k - j <= kTriTail) {
+        const size_t tail = sizeof(double) * ((size_t)(k - j) * (k - j) + 5 * kTriTail + 8);
+        KF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tri_tail),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)tail));
+        hipLaunchKernelGGL(k_tri_tail, dim3(1), dim3(1024), tail, st, k, j, w.A, w.d, w.e, w.tau, w.pv);
+        KF_HIP(hipGetLastError());
+        break;
+      }
       const int cols = k - j - 1;
-      const int grid = std::max(1, std::min(cdiv(cols, 4), 256));
-      hipLaunchKernelGGL(k_tri_step, dim3(grid), dim3(256), lds, st, k, j, w.A, w.d, w.e, w.tau, w.pv);
+      const int mt = cdiv(k - (j & ~255), 64);
+#define KF_TRI(MT) \
+  hipLaunchKernelGGL(k_tri_wave<MT>, dim3(cdiv(cols, 4)), dim3(256), 0, st, k, j, w.A, w.d, w.e, w.tau, w.pv)
+      if (mt <= 4)
+        KF_TRI(4);
+      else if (mt <= 8)
+        KF_TRI(8);
+      else if (mt <= 16)
+        KF_TRI(16);
+      else  // (beyond what the registers hold: vectors in LDS, columns strided)
+        hipLaunchKernelGGL(k_tri_step, dim3(std::min(cdiv(cols, 4), 256)), dim3(256), lds, st, k, j, w.A, w.d, w.e,
+                           w.tau, w.pv);
+#undef KF_TRI
       KF_HIP(hipGetLastError());
     }
   }
-  hipLaunchKernelGGL(k_tri_prep, dim3(1), dim3(256), 0, st, k, w.d, w.e, w.e2, w.bounds);
+  hipLaunchKernelGGL(k_tri_prep, dim3(1), dim3(256), 0, st, k, w.d, w.e, w.bounds);
   KF_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_bisect, dim3(cdiv(k, 4)), dim3(256), 0, st, k, w.d, w.e2, w.bounds, w.theta);
+  hipLaunchKernelGGL(k_bisect, dim3(cdiv(k, 4)), dim3(256), sizeof(double2) * (size_t)(k + 2 * kSturmB), st, k, w.d,
+                     w.e, w.bounds, w.theta);
   KF_HIP(hipGetLastError());
   return KF_OK;
 }
@@ -731,37 +1139,34 @@ int eig_vectors(EigWork& w, int k, const double* theta_sel, const int32_t* clust
   KF_TRY(eig_reserve(w, k, nsel));
   KF_HIP(hipMemcpyAsync(w.sel, theta_sel, sizeof(double) * nsel, hipMemcpyHostToDevice, st));
   KF_HIP(hipMemcpyAsync(w.cl, cluster_start, sizeof(int32_t) * (nclusters + 1), hipMemcpyHostToDevice, st));
-  // six work arrays of k doubles per lane: as many lanes per wavefront as fit
-  // in kIvLdsBytes of LDS, else all 64 lanes with the arrays in global memory
-  const int lds_lanes = std::min(64, kIvLdsBytes / (6 * 8 * k));
-  if (lds_lanes >= 1) {
-    const size_t lds = sizeof(double) * 6 * (size_t)k * lds_lanes;
-    hipLaunchKernelGGL(k_invit<true>, dim3(cdiv(nsel, lds_lanes)), dim3(64), lds, st, k, w.d, w.e, w.bounds,
-                       nclusters, w.cl, w.sel, w.Z, w.scratch, lds_lanes);
-  } else {
-    const int ldw = cdiv(nsel, 64) * 64;  // <= nsel + 63
-    hipLaunchKernelGGL(k_invit<false>, dim3(cdiv(nsel, 64)), dim3(64), 0, st, k, w.d, w.e, w.bounds, nclusters,
-                       w.cl, w.sel, w.Z, w.scratch, ldw);
-  }
+  const size_t lds = sizeof(double) * (size_t)invit_doubles(k);
+  if (lds > 65536)
+    KF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_invit), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)lds));
+  hipLaunchKernelGGL(k_invit, dim3(nsel), dim3(64), lds, st, k, w.d, w.e, w.bounds, nclusters, w.cl, w.sel, w.Z);
   KF_HIP(hipGetLastError());
   if (nclusters < nsel) {
     hipLaunchKernelGGL(k_cluster_orth, dim3(nclusters), dim3(256), 0, st, k, nclusters, w.cl, w.Z);
     KF_HIP(hipGetLastError());
   }
+  if (k >= 3) {
+    hipLaunchKernelGGL(k_reflector_heads, dim3(k - 2), dim3(256), 0, st, k, w.A);
+    KF_HIP(hipGetLastError());
+  }
   const int grid = cdiv(nsel, 4);
   const int mt = cdiv(k, 64);
   if (mt <= 1)
-    hipLaunchKernelGGL(k_backtransform<1>, dim3(grid), dim3(256), 0, st, k, w.A, w.tau, nsel, w.Z, w.Y);
+    hipLaunchKernelGGL((k_backtransform<1, 4>), dim3(grid), dim3(256), 0, st, k, w.A, w.tau, nsel, w.Z, w.Y);
   else if (mt <= 2)
-    hipLaunchKernelGGL(k_backtransform<2>, dim3(grid), dim3(256), 0, st, k, w.A, w.tau, nsel, w.Z, w.Y);
+    hipLaunchKernelGGL((k_backtransform<2, 4>), dim3(grid), dim3(256), 0, st, k, w.A, w.tau, nsel, w.Z, w.Y);
   else if (mt <= 4)
-    hipLaunchKernelGGL(k_backtransform<4>, dim3(grid), dim3(256), 0, st, k, w.A, w.tau, nsel, w.Z, w.Y);
+    hipLaunchKernelGGL((k_backtransform<4, 4>), dim3(grid), dim3(256), 0, st, k, w.A, w.tau, nsel, w.Z, w.Y);
   else if (mt <= 8)
-    hipLaunchKernelGGL(k_backtransform<8>, dim3(grid), dim3(256), 0, st, k, w.A, w.tau, nsel, w.Z, w.Y);
+    hipLaunchKernelGGL((k_backtransform<8, 4>), dim3(grid), dim3(256), 0, st, k, w.A, w.tau, nsel, w.Z, w.Y);
   else if (mt <= 16)
-    hipLaunchKernelGGL(k_backtransform<16>, dim3(grid), dim3(256), 0, st, k, w.A, w.tau, nsel, w.Z, w.Y);
+    hipLaunchKernelGGL((k_backtransform<16, 2>), dim3(grid), dim3(256), 0, st, k, w.A, w.tau, nsel, w.Z, w.Y);
   else
-    hipLaunchKernelGGL(k_backtransform<32>, dim3(grid), dim3(256), 0, st, k, w.A, w.tau, nsel, w.Z, w.Y);
+    hipLaunchKernelGGL((k_backtransform<32, 1>), dim3(grid), dim3(256), 0, st, k, w.A, w.tau, nsel, w.Z, w.Y);
   KF_HIP(hipGetLastError());
   // the host arrays must outlive the asynchronous copies
   KF_HIP(hipStreamSynchronize(st));

@@ -318,14 +318,12 @@ struct EigWork {
   double* A = nullptr;  // m x m
   double* d = nullptr;
   double* e = nullptr;
-  double* e2 = nullptr;      // squared off-diagonal
-  double* bounds = nullptr;  // Gershgorin bracket and pivot floor
+  double* bounds = nullptr;  // Gershgorin bracket, pivot floor, scale
   double* tau = nullptr;
   double* theta = nullptr;
   double* pv = nullptr;    // 4 x m: two p vectors and two reflectors (multi-workgroup reduction)
   double* Z = nullptr;     // m x nsel (tridiagonal eigenvectors)
   double* Y = nullptr;     // m x nsel (pencil eigenvectors)
-  double* scratch = nullptr;
   double* sel = nullptr;   // selected eigenvalues
   int32_t* cl = nullptr;   // cluster starts
   size_t cap_m = 0, cap_sel = 0;
