@@ -91,6 +91,7 @@ inline bool use_band(const SellOp& A, int b, int lpr) {
 int lanes_per_row(const SellOp& A, int b);
 
 void free_sell(SellOp& op);
+void free_stencil(StencilOp& s);
 
 // Build a SELL operator from a device CSR: values scaled per row by
 // row_scale[i] (device array, or nullptr for 1), stored as float64
@@ -104,6 +105,9 @@ enum StencilForm { kStencilNone = 0, kStencilPadded = 1, kStencilExact = 2 };
 int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
                const double* d_row_scale, int val_bytes, int want_idx_bytes, hipStream_t st, SellOp& out,
                int stencil = kStencilNone);
+
+int build_stencil(int32_t n, int32_t ns, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
+                  const double* d_row_scale, int val_bytes, bool exact, hipStream_t st, StencilOp& out);
 
 // ---- fused leapfrog step ----------------------------------------------------
 enum StepMode { kMid = 0, kFirst = 1, kLast = 2, kFirstLast = 3, kMidAcc = 4 };
@@ -210,6 +214,18 @@ int launch_leapfrog_batch(const SellOp& A, int b, const int32_t* slice_problem, 
 // Batched load of the filter input into Y1 (and C = w0 I for L_p = 1).
 int launch_load_batch(int val_bytes, int64_t rows, int b, const int32_t* slice_problem, const BatchTables* tb,
                       const void* wtab, int lmax, void* Y1, hipStream_t st);
+
+// The same steps over the stencil form (A.st.width > 0), used by the launchers
+// above.
+int launch_stencil_step(const SellOp& A, int b, int mode, const void* cur, const void* prev, void* out, void* acc,
+                        double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap,
+                        hipStream_t st);
+int launch_stencil_step4(const SellOp& A, int b, int mode, const void* cur, const void* prev, void* out, void* acc,
+                         void* z, double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn,
+                         int remap, hipStream_t st);
+int launch_stencil_batch(const SellOp& A, int b, const int32_t* slice_problem, const BatchTables* tb, const void* wtab,
+                         int lmax, int ell, const void* cur, const void* prev, void* out, void* acc, int nslices,
+                         int remap, hipStream_t st);
 
 // dst (n x b row-major, stepping precision) = src[i*rs + j*cs] for j < bsrc, 0 beyond.
 int launch_load_block(int val_bytes, int32_t n, int b, int bsrc, const double* src, int64_t rs, int64_t cs,

@@ -1,0 +1,521 @@
+// The time step over stencil slices (StencilOp): the second-order step, the two
+// launches of the fourth-order one, the batched step, and the detection and
+// build of the form.
+
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <vector>
+
+#include "kf_device.h"
+#include "kf_internal.h"
+
+namespace kf {
+
+namespace {
+
+// ------------------------------------------------------------ stencil slices
+// One wavefront per slice merges its rows' sorted columns into the ascending
+// list of their offsets col - row.  FILL = false: width[slice] = the number of
+// offsets, or kStencilMax + 1 when there are more or when two rows store
+// different values at one offset.  FILL = true: writes the slice's offsets,
+// values and row masks at [slice * stride].
+template <typename VT, bool FILL>
+__global__ __launch_bounds__(256) void k_stencil(int32_t n, int32_t nslices, const int32_t* __restrict__ rowptr,
+                                                 const int32_t* __restrict__ col, const double* __restrict__ val,
+                                                 const double* __restrict__ rscale, int32_t* __restrict__ width,
+                                                 int stride, VT* __restrict__ oval, int32_t* __restrict__ ooff,
+                                                 uint64_t* __restrict__ omask) {
+  const int slice = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (slice >= nslices) return;
+  const int row = slice * 64 + lane;
+  int a = 0, b = 0;
+  double sc = 1.0;
+  if (row < n) {
+    a = rowptr[row];
+    b = rowptr[row + 1];
+    if (rscale) sc = rscale[row];
+  }
+  int cnt = 0;
+  while (cnt <= kStencilMax) {
+    const int mine = a < b ? col[a] - row : INT32_MAX;
+    int off = mine;
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) off = min(off, __shfl_xor(off, s));
+    if (off == INT32_MAX) break;
+    const bool has = mine == off;
+    const VT v = has ? (VT)(sc * val[a]) : (VT)0;
+    const unsigned long long m = __ballot(has);
+    const VT lead = __shfl(v, __ffsll(m) - 1);
+    if (__ballot(has && !(v == lead)) != 0ull) {
+      cnt = kStencilMax + 1;
+      break;
+    }
+    if (FILL && lane == 0) {
+      const int64_t o = (int64_t)slice * stride + cnt;
+      oval[o] = lead;
+      ooff[o] = off;
+      omask[o] = m;
+    }
+    ++cnt;
+    if (has) ++a;
+  }
+  if (!FILL) {
+    if (lane == 0) width[slice] = cnt;
+  } else {
+    for (int q = cnt + lane; q < stride; q += 64) {
+      const int64_t o = (int64_t)slice * stride + q;
+      oval[o] = (VT)0;
+      ooff[o] = 0;
+      omask[o] = 0ull;
+    }
+  }
+}
+
+// sum_j += (A x)(row, col0 + j) of a stencil slice.  The slice's entries are
+// the same for the whole wavefront, so they come through the scalar cache and
+// the only vector loads are the gathers, which do not wait for an index load.
+// Every load is issued before its sums; rows without an entry gather their own
+// element and multiply it by zero.  W: entries per slice when known (the
+// loop is then unrolled in full), 0: `stride` entries, a multiple of 4.
+template <typename T, int B, int BL, int LPR, int W>
+__device__ __forceinline__ void stencil_product(const T* __restrict__ val, const int32_t* __restrict__ off,
+                                                const uint64_t* __restrict__ mask, int stride, int slice, int rin,
+                                                int row, const T* __restrict__ x, int col0, T (&sum)[BL]) {
+  constexpr int U = W > 0 && BL * sizeof(T) <= 16 ? W : 4;
+  const int64_t base = (int64_t)slice * (W > 0 ? W : stride);
+  auto chunk = [&](int q0) {
+    T a[U];
+    int o[U];
+    uint64_t m[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (W > 0 && q0 + u >= W) continue;
+      a[u] = val[base + q0 + u];
+      o[u] = off[base + q0 + u];
+      m[u] = mask[base + q0 + u];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      // (the offsets stay in scalar registers ahead of the row tests)
+      if (W > 0 && q0 + u >= W) continue;
+      asm volatile("" : "+s"(o[u]));
+    }
+    Row<T, BL> xv[U];
+    bool has[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (W > 0 && q0 + u >= W) continue;
+      has[u] = LPR == 1 ? __builtin_amdgcn_inverse_ballot_w64(m[u]) : ((m[u] >> rin) & 1ull) != 0ull;
+      const int c = row + (has[u] ? o[u] : 0);
+      xv[u] = *reinterpret_cast<const Row<T, BL>*>(x + (int64_t)c * B + col0);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (W > 0 && q0 + u >= W) continue;
+      const T au = has[u] ? a[u] : (T)0;
+#pragma unroll
+      for (int j = 0; j < BL; ++j) sum[j] = fma(au, xv[u].v[j], sum[j]);
+    }
+  };
+  if constexpr (W > 0) {
+#pragma unroll
+    for (int q0 = 0; q0 < W; q0 += U) chunk(q0);
+  } else {
+    for (int q0 = 0; q0 < stride; q0 += U) chunk(q0);
+  }
+}
+
+// The fused step (k_leapfrog below) over stencil slices: no operator stream,
+// a row's traffic is its vector levels alone (25 instead of 86 MB per middle
+// step of the 96-cell cube in float64, whose levels then stay in the caches).
+// A filter application of 38 steps there: 541 us with the stored entries,
+// 266 us so (7.0 us a step, launch included); the 128-cell cube in float32,
+// 51 steps: 982 and 351 us.  Bound by launch latency and the caches.
+template <typename T, int B, int MODE, int LPR, int W>
+__global__ __launch_bounds__(256) void k_leapfrog_st(int32_t n, int32_t nslices, const T* __restrict__ val,
+                                                     const int32_t* __restrict__ soff,
+                                                     const uint64_t* __restrict__ mask, int stride,
+                                                     const T* __restrict__ cur, const T* prev, T* out,
+                                                     T* __restrict__ acc, double* __restrict__ rout, int64_t rs,
+                                                     int64_t cs, int bout, T wp, T wc, T wn, int remap) {
+  constexpr int BL = B / LPR;
+  constexpr int RW = 64 / LPR;
+  const int wg = remap ? xcd_map(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const int gw = __builtin_amdgcn_readfirstlane(wg * 4 + (int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63;
+  const int slice = (gw * RW) >> 6;
+  if (slice >= nslices) return;
+  const int rin = ((gw * RW) & 63) + lane / LPR;
+  const int row = slice * 64 + rin;
+  if (row >= n) return;
+  const int col0 = (lane % LPR) * BL;
+  const int64_t off = (int64_t)row * B + col0;
+  const Row<T, BL> yc = *reinterpret_cast<const Row<T, BL>*>(cur + off);
+  Row<T, BL> yp, r;
+  if (!(MODE & kFirst)) yp = *reinterpret_cast<const Row<T, BL>*>(prev + off);
+  if (MODE == kMidAcc || MODE == kLast) r = *reinterpret_cast<const Row<T, BL>*>(acc + off);
+  T sum[BL];
+#pragma unroll
+  for (int j = 0; j < BL; ++j) sum[j] = (T)0;
+  stencil_product<T, B, BL, LPR, W>(val, soff, mask, stride, slice, rin, row, cur, col0, sum);
+  if (MODE & kFirst) yp = yc;
+  Row<T, BL> nx;
+#pragma unroll
+  for (int j = 0; j < BL; ++j) nx.v[j] = (T)2 * yc.v[j] - yp.v[j] - sum[j];
+  if (!(MODE & kLast)) *reinterpret_cast<Row<T, BL>*>(out + off) = nx;
+  if (MODE == kMid) return;
+  if (MODE & kFirst) {
+#pragma unroll
+    for (int j = 0; j < BL; ++j) r.v[j] = fma(wn, nx.v[j], wc * yc.v[j]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < BL; ++j) r.v[j] = fma(wn, nx.v[j], fma(wc, yc.v[j], fma(wp, yp.v[j], r.v[j])));
+  }
+  if (MODE & kLast) {
+#pragma unroll
+    for (int j = 0; j < BL; ++j)
+      if (col0 + j < bout) rout[(int64_t)row * rs + (int64_t)(col0 + j) * cs] = (double)r.v[j];
+  } else {
+    *reinterpret_cast<Row<T, BL>*>(acc + off) = r;
+  }
+}
+
+// The two launches of a fourth-order step over stencil slices: MODE < 0 forms
+// z = A cur, else the update (see stencil_product).
+template <typename T, int B, int MODE, int LPR, int W>
+__global__ __launch_bounds__(256) void k_leapfrog4_st(int32_t n, int32_t nslices, const T* __restrict__ val,
+                                                      const int32_t* __restrict__ soff,
+                                                      const uint64_t* __restrict__ mask, int stride,
+                                                      const T* __restrict__ cur, const T* prev, T* out,
+                                                      T* __restrict__ acc, T* __restrict__ z,
+                                                      double* __restrict__ rout, int64_t rs, int64_t cs, int bout, T wp,
+                                                      T wc, T wn, int remap) {
+  constexpr int BL = B / LPR;
+  constexpr int RW = 64 / LPR;
+  using V = Row<T, BL>;
+  const int wg = remap ? xcd_map(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const int gw = __builtin_amdgcn_readfirstlane(wg * 4 + (int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63;
+  const int slice = (gw * RW) >> 6;
+  if (slice >= nslices) return;
+  const int rin = ((gw * RW) & 63) + lane / LPR;
+  const int row = slice * 64 + rin;
+  if (row >= n) return;
+  const int col0 = (lane % LPR) * BL;
+  const int64_t off = (int64_t)row * B + col0;
+  V yc, yp, zc, r;
+  if (MODE >= 0) {
+    yc = *reinterpret_cast<const V*>(cur + off);
+    zc = *reinterpret_cast<const V*>(z + off);
+    if (!(MODE & kFirst)) yp = *reinterpret_cast<const V*>(prev + off);
+    if (MODE == kMidAcc || MODE == kLast) r = *reinterpret_cast<const V*>(acc + off);
+  }
+  T sum[BL];
+#pragma unroll
+  for (int j = 0; j < BL; ++j) sum[j] = (T)0;
+  stencil_product<T, B, BL, LPR, W>(val, soff, mask, stride, slice, rin, row, MODE < 0 ? cur : z, col0, sum);
+  if (MODE < 0) {
+    V o;
+#pragma unroll
+    for (int j = 0; j < BL; ++j) o.v[j] = sum[j];
+    *reinterpret_cast<V*>(z + off) = o;
+    return;
+  }
+  if (MODE & kFirst) yp = yc;
+  constexpr T twelfth = (T)(1.0 / 12.0);
+  V nx;
+#pragma unroll
+  for (int j = 0; j < BL; ++j) nx.v[j] = fma(twelfth, sum[j], (T)2 * yc.v[j] - yp.v[j] - zc.v[j]);
+  if (!(MODE & kLast)) *reinterpret_cast<V*>(out + off) = nx;
+  if (MODE == kMid) return;
+  if (MODE & kFirst) {
+#pragma unroll
+    for (int j = 0; j < BL; ++j) r.v[j] = fma(wn, nx.v[j], wc * yc.v[j]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < BL; ++j) r.v[j] = fma(wn, nx.v[j], fma(wc, yc.v[j], fma(wp, yp.v[j], r.v[j])));
+  }
+  if (MODE & kLast) {
+#pragma unroll
+    for (int j = 0; j < BL; ++j)
+      if (col0 + j < bout) rout[(int64_t)row * rs + (int64_t)(col0 + j) * cs] = (double)r.v[j];
+  } else {
+    *reinterpret_cast<V*>(acc + off) = r;
+  }
+}
+
+// The batched step over stencil slices (see stencil_product).  The tables of
+// the slice's problem are scalar loads, as the slice's entries are.
+template <typename T, int B>
+__global__ __launch_bounds__(256) void k_leapfrog_batch_st(int32_t nslices, const T* __restrict__ val,
+                                                           const int32_t* __restrict__ soff,
+                                                           const uint64_t* __restrict__ mask, int stride,
+                                                           const int32_t* __restrict__ sp,
+                                                           const BatchTables* __restrict__ tb,
+                                                           const T* __restrict__ wtab, int lmax, int ell,
+                                                           const T* __restrict__ cur, const T* prev, T* out,
+                                                           T* __restrict__ acc, int remap) {
+  using V = Row<T, B>;
+  const int wg = remap ? xcd_map(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const int slice = __builtin_amdgcn_readfirstlane(wg * 4 + (int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63;
+  if (slice >= nslices) return;
+  const int p = sp[slice];
+  const int Lp = tb->L[p];
+  if (!tb->active[p] || ell > Lp - 1) return;
+  const int row = slice * 64 + lane;
+  const int local = row - (int)tb->row0[p];
+  if (local >= tb->n[p]) return;
+  const bool first = ell == 1, last = ell == Lp - 1;
+  // the accumulation schedule of the single-problem steps (step_plan)
+  const int u = ell >= 2 ? 1 + 3 * ((ell - 2) / 3) : 1;  // latest update before this step
+  const bool sums = first || last || ell - u == 3;
+  const V yc = reinterpret_cast<const V*>(cur)[row];
+  V yp = yc, r = yc;
+  if (!first) yp = reinterpret_cast<const V*>(prev)[row];
+  if (sums && !first) r = reinterpret_cast<const V*>(acc)[row];
+  T sum[B];
+#pragma unroll
+  for (int j = 0; j < B; ++j) sum[j] = (T)0;
+  stencil_product<T, B, B, 1, 0>(val, soff, mask, stride, slice, lane, row, cur, 0, sum);
+  V nx;
+#pragma unroll
+  for (int j = 0; j < B; ++j) nx.v[j] = (T)2 * yc.v[j] - yp.v[j] - sum[j];
+  if (!last) reinterpret_cast<V*>(out)[row] = nx;
+  if (!sums) return;
+  const T* __restrict__ wq = wtab + (int64_t)p * lmax;
+  if (first) {
+#pragma unroll
+    for (int j = 0; j < B; ++j) r.v[j] = fma(wq[1], nx.v[j], wq[0] * yc.v[j]);
+  } else {
+    const T wp = ell - 2 > u ? wq[ell - 2] : (T)0, wc = ell - 1 > u ? wq[ell - 1] : (T)0, wn = wq[ell];
+#pragma unroll
+    for (int j = 0; j < B; ++j) r.v[j] = fma(wn, nx.v[j], fma(wc, yc.v[j], fma(wp, yp.v[j], r.v[j])));
+  }
+  if (last) {
+    double* __restrict__ dst = tb->dst[p];
+    const int64_t ld = tb->ld[p];
+    const int bout = tb->bout[p];
+#pragma unroll
+    for (int j = 0; j < B; ++j)
+      if (j < bout) dst[local + (int64_t)j * ld] = (double)r.v[j];
+  } else {
+    reinterpret_cast<V*>(acc)[row] = r;
+  }
+}
+
+template <typename T, int B, int LPR, int W>
+int launch_st_w(const SellOp& A, int mode, const void* cur, const void* prev, void* out, void* acc, double* rout,
+                int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap, hipStream_t st) {
+#define KF_ST(M)                                                                                                     \
+  hipLaunchKernelGGL((k_leapfrog_st<T, B, M, LPR, W>), dim3(ceil_div64((int64_t)A.nslices * LPR, 4)), dim3(256), 0,    \
+                     st, A.n, A.nslices, static_cast<const T*>(A.st.val), A.st.off, A.st.mask, A.st.stride,             \
+                     static_cast<const T*>(cur), static_cast<const T*>(prev), static_cast<T*>(out),                     \
+                     static_cast<T*>(acc), rout, rs, cs, bout, (T)wp, (T)wc, (T)wn, remap)
+  switch (mode) {
+    case kMid: KF_ST(kMid); break;
+    case kFirst: KF_ST(kFirst); break;
+    case kMidAcc: KF_ST(kMidAcc); break;
+    case kLast: KF_ST(kLast); break;
+    default: KF_ST(kFirstLast); break;
+  }
+#undef KF_ST
+  KF_HIP(hipGetLastError());
+  return KF_OK;
+}
+
+template <typename T, int B, int LPR>
+int launch_st_l(const SellOp& A, int mode, const void* cur, const void* prev, void* out, void* acc, double* rout,
+                int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap, hipStream_t st) {
+  if (A.st.stride == 5)
+    return launch_st_w<T, B, LPR, 5>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+  if (A.st.stride == 7)
+    return launch_st_w<T, B, LPR, 7>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+  return launch_st_w<T, B, LPR, 0>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+}
+
+template <typename T, int B>
+int launch_st_b(const SellOp& A, int mode, const void* cur, const void* prev, void* out, void* acc, double* rout,
+                int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap, hipStream_t st) {
+  const int lpr = lanes_per_row(A, B);
+  if constexpr (B >= 4)
+    if (lpr == 4) return launch_st_l<T, B, 4>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+  if constexpr (B >= 2)
+    if (lpr == 2) return launch_st_l<T, B, 2>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+  return launch_st_l<T, B, 1>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+}
+
+// The fused step over stencil slices.
+template <typename T>
+int launch_st(const SellOp& A, int b, int mode, const void* cur, const void* prev, void* out, void* acc, double* rout,
+              int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap, hipStream_t st) {
+  switch (b) {
+    case 1: return launch_st_b<T, 1>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    case 2: return launch_st_b<T, 2>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    case 4: return launch_st_b<T, 4>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    case 8: return launch_st_b<T, 8>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    case 16: return launch_st_b<T, 16>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    default: set_error("leapfrog: block width must be 1, 2, 4, 8 or 16"); return KF_EINVAL;
+  }
+}
+
+template <typename T, int B, int LPR, int W>
+int launch_st4_w(const SellOp& A, int mode, const void* cur, const void* prev, void* out, void* acc, void* z,
+                 double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap,
+                 hipStream_t st) {
+#define KF_ST4(M)                                                                                                   \
+  hipLaunchKernelGGL((k_leapfrog4_st<T, B, M, LPR, W>), dim3(ceil_div64((int64_t)A.nslices * LPR, 4)), dim3(256), 0,  \
+                     st, A.n, A.nslices, static_cast<const T*>(A.st.val), A.st.off, A.st.mask, A.st.stride,            \
+                     static_cast<const T*>(cur), static_cast<const T*>(prev), static_cast<T*>(out),                    \
+                     static_cast<T*>(acc), static_cast<T*>(z), rout, rs, cs, bout, (T)wp, (T)wc, (T)wn, remap)
+  KF_ST4(-1);
+  switch (mode) {
+    case kMid: KF_ST4(kMid); break;
+    case kFirst: KF_ST4(kFirst); break;
+    case kMidAcc: KF_ST4(kMidAcc); break;
+    case kLast: KF_ST4(kLast); break;
+    default: KF_ST4(kFirstLast); break;
+  }
+#undef KF_ST4
+  KF_HIP(hipGetLastError());
+  return KF_OK;
+}
+
+// (16 bytes of a row per lane; as many lanes share it)
+template <typename T, int B>
+int launch_st4_b(const SellOp& A, int mode, const void* cur, const void* prev, void* out, void* acc, void* z,
+                 double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap,
+                 hipStream_t st) {
+  constexpr int LPR = B * sizeof(T) >= 64 ? 4 : (B * sizeof(T) >= 32 ? 2 : 1);
+  if (A.st.stride == 5)
+    return launch_st4_w<T, B, LPR, 5>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+  if (A.st.stride == 7)
+    return launch_st4_w<T, B, LPR, 7>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+  return launch_st4_w<T, B, LPR, 0>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+}
+
+template <typename T>
+int launch_st4(const SellOp& A, int b, int mode, const void* cur, const void* prev, void* out, void* acc, void* z,
+               double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap,
+               hipStream_t st) {
+  switch (b) {
+    case 1: return launch_st4_b<T, 1>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    case 2: return launch_st4_b<T, 2>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    case 4: return launch_st4_b<T, 4>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    case 8: return launch_st4_b<T, 8>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    case 16: return launch_st4_b<T, 16>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    default: set_error("fourth-order step: block width must be 1, 2, 4, 8 or 16"); return KF_EINVAL;
+  }
+}
+
+}  // namespace
+
+namespace {
+// The stencil form of an operator's slices, when it has one (else out.width
+// stays 0).
+template <typename VT>
+int build_stencil_t(int32_t n, int32_t ns, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
+                  const double* d_row_scale, bool exact, hipStream_t st, StencilOp& out) {
+  const int grid = ceil_div64(ns, 4);
+  int32_t* d_w = nullptr;
+  if (hipMalloc(&d_w, sizeof(int32_t) * (size_t)ns) != hipSuccess) {
+    set_error("build_sell: device allocation failed");
+    return KF_ENOMEM;
+  }
+  hipLaunchKernelGGL((k_stencil<VT, false>), dim3(grid), dim3(256), 0, st, n, ns, d_rowptr, d_col, d_val, d_row_scale,
+                     d_w, 0, (VT*)nullptr, (int32_t*)nullptr, (uint64_t*)nullptr);
+  std::vector<int32_t> w((size_t)ns);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = hipMemcpyAsync(w.data(), d_w, sizeof(int32_t) * (size_t)ns, hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  (void)hipFree(d_w);
+  if (e != hipSuccess) {
+    set_error(std::string("build_sell: ") + hipGetErrorString(e));
+    return KF_EHIP;
+  }
+  const int width = *std::max_element(w.begin(), w.end());
+  if (width < 1 || width > kStencilMax) return KF_OK;
+  // 5 and 7 entries (the 2D and 3D point stencils) have kernels of their own
+  // length; other lengths are padded to the loop's four entries
+  const int stride = exact && (width == 5 || width == 7) ? width : (width + 3) / 4 * 4;
+  const size_t tot = (size_t)ns * stride;
+  StencilOp s;
+  if (hipMalloc(&s.val, tot * sizeof(VT)) != hipSuccess || hipMalloc(&s.off, tot * sizeof(int32_t)) != hipSuccess ||
+      hipMalloc(&s.mask, tot * sizeof(uint64_t)) != hipSuccess) {
+    if (s.val) (void)hipFree(s.val);
+    if (s.off) (void)hipFree(s.off);
+    set_error("build_sell: device allocation failed");
+    return KF_ENOMEM;
+  }
+  s.width = width;
+  s.stride = stride;
+  out = s;
+  hipLaunchKernelGGL((k_stencil<VT, true>), dim3(grid), dim3(256), 0, st, n, ns, d_rowptr, d_col, d_val, d_row_scale,
+                     (int32_t*)nullptr, stride, (VT*)s.val, s.off, s.mask);
+  KF_HIP(hipGetLastError());
+  return KF_OK;
+}
+}  // namespace
+
+void free_stencil(StencilOp& s) {
+  if (s.val) (void)hipFree(s.val);
+  if (s.off) (void)hipFree(s.off);
+  if (s.mask) (void)hipFree(s.mask);
+  s = StencilOp();
+}
+
+int build_stencil(int32_t n, int32_t ns, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
+                  const double* d_row_scale, int val_bytes, bool exact, hipStream_t st, StencilOp& out) {
+  if (val_bytes == 8) return build_stencil_t<double>(n, ns, d_rowptr, d_col, d_val, d_row_scale, exact, st, out);
+  return build_stencil_t<float>(n, ns, d_rowptr, d_col, d_val, d_row_scale, exact, st, out);
+}
+
+int launch_stencil_step(const SellOp& A, int b, int mode, const void* cur, const void* prev, void* out, void* acc,
+                        double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap,
+                        hipStream_t st) {
+  if (A.val_bytes == 8)
+    return launch_st<double>(A, b, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+  return launch_st<float>(A, b, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+}
+
+int launch_stencil_step4(const SellOp& A, int b, int mode, const void* cur, const void* prev, void* out, void* acc,
+                         void* z, double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn,
+                         int remap, hipStream_t st) {
+  if (A.val_bytes == 8)
+    return launch_st4<double>(A, b, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+  return launch_st4<float>(A, b, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+}
+
+namespace {
+template <typename T>
+int launch_lfb_st(const SellOp& A, int b, const int32_t* sp, const BatchTables* tb, const void* wtab, int lmax, int ell,
+                  const void* cur, const void* prev, void* out, void* acc, int nslices, int remap, hipStream_t st) {
+#define KF_LFS(B)                                                                                                  \
+  hipLaunchKernelGGL((k_leapfrog_batch_st<T, B>), dim3(ceil_div64(nslices, 4)), dim3(256), 0, st, nslices,          \
+                     static_cast<const T*>(A.st.val), A.st.off, A.st.mask, A.st.stride, sp, tb,                     \
+                     static_cast<const T*>(wtab), lmax, ell, static_cast<const T*>(cur), static_cast<const T*>(prev), \
+                     static_cast<T*>(out), static_cast<T*>(acc), remap)
+  switch (b) {
+    case 1: KF_LFS(1); break;
+    case 2: KF_LFS(2); break;
+    case 4: KF_LFS(4); break;
+    case 8: KF_LFS(8); break;
+    case 16: KF_LFS(16); break;
+    default: set_error("batched leapfrog: block width must be 1, 2, 4, 8 or 16"); return KF_EINVAL;
+  }
+#undef KF_LFS
+  KF_HIP(hipGetLastError());
+  return KF_OK;
+}
+}  // namespace
+
+int launch_stencil_batch(const SellOp& A, int b, const int32_t* sp, const BatchTables* tb, const void* wtab, int lmax,
+                         int ell, const void* cur, const void* prev, void* out, void* acc, int nslices, int remap,
+                         hipStream_t st) {
+  if (A.val_bytes == 8) return launch_lfb_st<double>(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, nslices, remap, st);
+  return launch_lfb_st<float>(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, nslices, remap, st);
+}
+
+}  // namespace kf

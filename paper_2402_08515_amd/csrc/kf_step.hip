@@ -2,9 +2,9 @@
 // k_leapfrog, one step of the explicit two-step scheme of Section 2.3 (eq.
 // 2stepmethod) fused with the rectangle-rule accumulation of eq.
 // disc_filtercoeff, over a sliced-ELLPACK copy of A = tau^2 M^{-1} S, for one
-// problem or for a stack of independent problems; and the SELL build.  Where
-// every slice is a stencil (uniform meshes) the step reads that instead
-// (k_leapfrog_st).  Otherwise it is bound by HBM bandwidth: per step it streams the matrix once (value +
+// problem or for a stack of independent problems; and the SELL build.  (Where
+// the operator has a stencil form, the launchers here pass on to that.)  The
+// step is bound by HBM bandwidth: per step it streams the matrix once (value +
 // column index per stored entry) and five vector streams (cur gather, prev,
 // next, accumulator read and write).  A wavefront owns 64 rows of a slice
 // (LPR wavefronts for blocks with LPR lanes per row), so every matrix load of
@@ -18,27 +18,12 @@
 #include <cmath>
 #include <cstring>
 
+#include "kf_device.h"
 #include "kf_internal.h"
 
 namespace kf {
 
 namespace {
-
-inline int ceil_div64(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
-
-// Consecutive workgroup ids are dealt round-robin to the 8 XCDs; renumber
-// them so that each XCD receives one contiguous range of row slices and its
-// L2 keeps the neighbouring rows it gathers.
-__device__ __forceinline__ int xcd_map(int i, int nblk) {
-  const int q = nblk >> 3, r = nblk & 7;
-  const int x = i & 7, t = i >> 3;
-  return (x < r) ? x * (q + 1) + t : r * (q + 1) + (x - r) * q + t;
-}
-
-template <typename T, int B>
-struct alignas((B * sizeof(T)) >= 16 ? 16 : (B * sizeof(T))) Row {
-  T v[B];
-};
 
 // ---------------------------------------------------------------- SELL build
 __global__ __launch_bounds__(256) void k_sell_stats(int32_t n, int32_t nslices, const int32_t* __restrict__ rowptr,
@@ -99,174 +84,6 @@ __global__ __launch_bounds__(256) void k_sell_fill(int32_t n, int32_t nslices, c
       oval[pos] = (VT)0;
       oidx[pos] = relative ? (IT)0 : (IT)(row < n ? row : 0);
     }
-  }
-}
-
-// ------------------------------------------------------------ stencil slices
-// One wavefront per slice merges its rows' sorted columns into the ascending
-// list of their offsets col - row.  FILL = false: width[slice] = the number of
-// offsets, or kStencilMax + 1 when there are more or when two rows store
-// different values at one offset.  FILL = true: writes the slice's offsets,
-// values and row masks at [slice * stride].
-template <typename VT, bool FILL>
-__global__ __launch_bounds__(256) void k_stencil(int32_t n, int32_t nslices, const int32_t* __restrict__ rowptr,
-                                                 const int32_t* __restrict__ col, const double* __restrict__ val,
-                                                 const double* __restrict__ rscale, int32_t* __restrict__ width,
-                                                 int stride, VT* __restrict__ oval, int32_t* __restrict__ ooff,
-                                                 uint64_t* __restrict__ omask) {
-  const int slice = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (slice >= nslices) return;
-  const int row = slice * 64 + lane;
-  int a = 0, b = 0;
-  double sc = 1.0;
-  if (row < n) {
-    a = rowptr[row];
-    b = rowptr[row + 1];
-    if (rscale) sc = rscale[row];
-  }
-  int cnt = 0;
-  while (cnt <= kStencilMax) {
-    const int mine = a < b ? col[a] - row : INT32_MAX;
-    int off = mine;
-#pragma unroll
-    for (int s = 32; s > 0; s >>= 1) off = min(off, __shfl_xor(off, s));
-    if (off == INT32_MAX) break;
-    const bool has = mine == off;
-    const VT v = has ? (VT)(sc * val[a]) : (VT)0;
-    const unsigned long long m = __ballot(has);
-    const VT lead = __shfl(v, __ffsll(m) - 1);
-    if (__ballot(has && !(v == lead)) != 0ull) {
-      cnt = kStencilMax + 1;
-      break;
-    }
-    if (FILL && lane == 0) {
-      const int64_t o = (int64_t)slice * stride + cnt;
-      oval[o] = lead;
-      ooff[o] = off;
-      omask[o] = m;
-    }
-    ++cnt;
-    if (has) ++a;
-  }
-  if (!FILL) {
-    if (lane == 0) width[slice] = cnt;
-  } else {
-    for (int q = cnt + lane; q < stride; q += 64) {
-      const int64_t o = (int64_t)slice * stride + q;
-      oval[o] = (VT)0;
-      ooff[o] = 0;
-      omask[o] = 0ull;
-    }
-  }
-}
-
-// sum_j += (A x)(row, col0 + j) of a stencil slice.  The slice's entries are
-// the same for the whole wavefront, so they come through the scalar cache and
-// the only vector loads are the gathers, which do not wait for an index load.
-// Every load is issued before its sums; rows without an entry gather their own
-// element and multiply it by zero.  W: entries per slice when known (the
-// loop is then unrolled in full), 0: `stride` entries, a multiple of 4.
-template <typename T, int B, int BL, int LPR, int W>
-__device__ __forceinline__ void stencil_product(const T* __restrict__ val, const int32_t* __restrict__ off,
-                                                const uint64_t* __restrict__ mask, int stride, int slice, int rin,
-                                                int row, const T* __restrict__ x, int col0, T (&sum)[BL]) {
-  constexpr int U = W > 0 && BL * sizeof(T) <= 16 ? W : 4;
-  const int64_t base = (int64_t)slice * (W > 0 ? W : stride);
-  auto chunk = [&](int q0) {
-    T a[U];
-    int o[U];
-    uint64_t m[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (W > 0 && q0 + u >= W) continue;
-      a[u] = val[base + q0 + u];
-      o[u] = off[base + q0 + u];
-      m[u] = mask[base + q0 + u];
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      // (the offsets stay in scalar registers ahead of the row tests)
-      if (W > 0 && q0 + u >= W) continue;
-      asm volatile("" : "+s"(o[u]));
-    }
-    Row<T, BL> xv[U];
-    bool has[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (W > 0 && q0 + u >= W) continue;
-      has[u] = LPR == 1 ? __builtin_amdgcn_inverse_ballot_w64(m[u]) : ((m[u] >> rin) & 1ull) != 0ull;
-      const int c = row + (has[u] ? o[u] : 0);
-      xv[u] = *reinterpret_cast<const Row<T, BL>*>(x + (int64_t)c * B + col0);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (W > 0 && q0 + u >= W) continue;
-      const T au = has[u] ? a[u] : (T)0;
-#pragma unroll
-      for (int j = 0; j < BL; ++j) sum[j] = fma(au, xv[u].v[j], sum[j]);
-    }
-  };
-  if constexpr (W > 0) {
-#pragma unroll
-    for (int q0 = 0; q0 < W; q0 += U) chunk(q0);
-  } else {
-    for (int q0 = 0; q0 < stride; q0 += U) chunk(q0);
-  }
-}
-
-// The fused step (k_leapfrog below) over stencil slices: no operator stream,
-// a row's traffic is its vector levels alone (25 instead of 86 MB per middle
-// step of the 96-cell cube in float64, whose levels then stay in the caches).
-// A filter application of 38 steps there: 541 us with the stored entries,
-// 266 us so (7.0 us a step, launch included); the 128-cell cube in float32,
-// 51 steps: 982 and 351 us.  Bound by launch latency and the caches.
-template <typename T, int B, int MODE, int LPR, int W>
-__global__ __launch_bounds__(256) void k_leapfrog_st(int32_t n, int32_t nslices, const T* __restrict__ val,
-                                                     const int32_t* __restrict__ soff,
-                                                     const uint64_t* __restrict__ mask, int stride,
-                                                     const T* __restrict__ cur, const T* prev, T* out,
-                                                     T* __restrict__ acc, double* __restrict__ rout, int64_t rs,
-                                                     int64_t cs, int bout, T wp, T wc, T wn, int remap) {
-  constexpr int BL = B / LPR;
-  constexpr int RW = 64 / LPR;
-  const int wg = remap ? xcd_map(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-  const int gw = __builtin_amdgcn_readfirstlane(wg * 4 + (int)(threadIdx.x >> 6));
-  const int lane = threadIdx.x & 63;
-  const int slice = (gw * RW) >> 6;
-  if (slice >= nslices) return;
-  const int rin = ((gw * RW) & 63) + lane / LPR;
-  const int row = slice * 64 + rin;
-  if (row >= n) return;
-  const int col0 = (lane % LPR) * BL;
-  const int64_t off = (int64_t)row * B + col0;
-  const Row<T, BL> yc = *reinterpret_cast<const Row<T, BL>*>(cur + off);
-  Row<T, BL> yp, r;
-  if (!(MODE & kFirst)) yp = *reinterpret_cast<const Row<T, BL>*>(prev + off);
-  if (MODE == kMidAcc || MODE == kLast) r = *reinterpret_cast<const Row<T, BL>*>(acc + off);
-  T sum[BL];
-#pragma unroll
-  for (int j = 0; j < BL; ++j) sum[j] = (T)0;
-  stencil_product<T, B, BL, LPR, W>(val, soff, mask, stride, slice, rin, row, cur, col0, sum);
-  if (MODE & kFirst) yp = yc;
-  Row<T, BL> nx;
-#pragma unroll
-  for (int j = 0; j < BL; ++j) nx.v[j] = (T)2 * yc.v[j] - yp.v[j] - sum[j];
-  if (!(MODE & kLast)) *reinterpret_cast<Row<T, BL>*>(out + off) = nx;
-  if (MODE == kMid) return;
-  if (MODE & kFirst) {
-#pragma unroll
-    for (int j = 0; j < BL; ++j) r.v[j] = fma(wn, nx.v[j], wc * yc.v[j]);
-  } else {
-#pragma unroll
-    for (int j = 0; j < BL; ++j) r.v[j] = fma(wn, nx.v[j], fma(wc, yc.v[j], fma(wp, yp.v[j], r.v[j])));
-  }
-  if (MODE & kLast) {
-#pragma unroll
-    for (int j = 0; j < BL; ++j)
-      if (col0 + j < bout) rout[(int64_t)row * rs + (int64_t)(col0 + j) * cs] = (double)r.v[j];
-  } else {
-    *reinterpret_cast<Row<T, BL>*>(acc + off) = r;
   }
 }
 
@@ -473,70 +290,6 @@ __global__ __launch_bounds__(256) void k_leapfrog4(int32_t n, int32_t nslices, c
   }
 }
 
-// The two launches of a fourth-order step over stencil slices: MODE < 0 forms
-// z = A cur, else the update (see stencil_product).
-template <typename T, int B, int MODE, int LPR, int W>
-__global__ __launch_bounds__(256) void k_leapfrog4_st(int32_t n, int32_t nslices, const T* __restrict__ val,
-                                                      const int32_t* __restrict__ soff,
-                                                      const uint64_t* __restrict__ mask, int stride,
-                                                      const T* __restrict__ cur, const T* prev, T* out,
-                                                      T* __restrict__ acc, T* __restrict__ z,
-                                                      double* __restrict__ rout, int64_t rs, int64_t cs, int bout, T wp,
-                                                      T wc, T wn, int remap) {
-  constexpr int BL = B / LPR;
-  constexpr int RW = 64 / LPR;
-  using V = Row<T, BL>;
-  const int wg = remap ? xcd_map(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-  const int gw = __builtin_amdgcn_readfirstlane(wg * 4 + (int)(threadIdx.x >> 6));
-  const int lane = threadIdx.x & 63;
-  const int slice = (gw * RW) >> 6;
-  if (slice >= nslices) return;
-  const int rin = ((gw * RW) & 63) + lane / LPR;
-  const int row = slice * 64 + rin;
-  if (row >= n) return;
-  const int col0 = (lane % LPR) * BL;
-  const int64_t off = (int64_t)row * B + col0;
-  V yc, yp, zc, r;
-  if (MODE >= 0) {
-    yc = *reinterpret_cast<const V*>(cur + off);
-    zc = *reinterpret_cast<const V*>(z + off);
-    if (!(MODE & kFirst)) yp = *reinterpret_cast<const V*>(prev + off);
-    if (MODE == kMidAcc || MODE == kLast) r = *reinterpret_cast<const V*>(acc + off);
-  }
-  T sum[BL];
-#pragma unroll
-  for (int j = 0; j < BL; ++j) sum[j] = (T)0;
-  stencil_product<T, B, BL, LPR, W>(val, soff, mask, stride, slice, rin, row, MODE < 0 ? cur : z, col0, sum);
-  if (MODE < 0) {
-    V o;
-#pragma unroll
-    for (int j = 0; j < BL; ++j) o.v[j] = sum[j];
-    *reinterpret_cast<V*>(z + off) = o;
-    return;
-  }
-  if (MODE & kFirst) yp = yc;
-  constexpr T twelfth = (T)(1.0 / 12.0);
-  V nx;
-#pragma unroll
-  for (int j = 0; j < BL; ++j) nx.v[j] = fma(twelfth, sum[j], (T)2 * yc.v[j] - yp.v[j] - zc.v[j]);
-  if (!(MODE & kLast)) *reinterpret_cast<V*>(out + off) = nx;
-  if (MODE == kMid) return;
-  if (MODE & kFirst) {
-#pragma unroll
-    for (int j = 0; j < BL; ++j) r.v[j] = fma(wn, nx.v[j], wc * yc.v[j]);
-  } else {
-#pragma unroll
-    for (int j = 0; j < BL; ++j) r.v[j] = fma(wn, nx.v[j], fma(wc, yc.v[j], fma(wp, yp.v[j], r.v[j])));
-  }
-  if (MODE & kLast) {
-#pragma unroll
-    for (int j = 0; j < BL; ++j)
-      if (col0 + j < bout) rout[(int64_t)row * rs + (int64_t)(col0 + j) * cs] = (double)r.v[j];
-  } else {
-    *reinterpret_cast<V*>(acc + off) = r;
-  }
-}
-
 // ------------------------------------------------------- batched leapfrog
 // Many independent problems stacked into one block-diagonal operator: every
 // problem owns whole 64-row slices (rows padded to a multiple of 64), slice s
@@ -639,66 +392,6 @@ __global__ __launch_bounds__(256) void k_leapfrog_batch(int32_t nslices, const i
       if (j < bout) dst[local + (int64_t)j * ld] = (double)r.v[j];
   } else {
     *reinterpret_cast<Row<T, B>*>(acc + (int64_t)row * B) = r;
-  }
-}
-
-// The batched step over stencil slices (see stencil_product).  The tables of
-// the slice's problem are scalar loads, as the slice's entries are.
-template <typename T, int B>
-__global__ __launch_bounds__(256) void k_leapfrog_batch_st(int32_t nslices, const T* __restrict__ val,
-                                                           const int32_t* __restrict__ soff,
-                                                           const uint64_t* __restrict__ mask, int stride,
-                                                           const int32_t* __restrict__ sp,
-                                                           const BatchTables* __restrict__ tb,
-                                                           const T* __restrict__ wtab, int lmax, int ell,
-                                                           const T* __restrict__ cur, const T* prev, T* out,
-                                                           T* __restrict__ acc, int remap) {
-  using V = Row<T, B>;
-  const int wg = remap ? xcd_map(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-  const int slice = __builtin_amdgcn_readfirstlane(wg * 4 + (int)(threadIdx.x >> 6));
-  const int lane = threadIdx.x & 63;
-  if (slice >= nslices) return;
-  const int p = sp[slice];
-  const int Lp = tb->L[p];
-  if (!tb->active[p] || ell > Lp - 1) return;
-  const int row = slice * 64 + lane;
-  const int local = row - (int)tb->row0[p];
-  if (local >= tb->n[p]) return;
-  const bool first = ell == 1, last = ell == Lp - 1;
-  // the accumulation schedule of the single-problem steps (step_plan)
-  const int u = ell >= 2 ? 1 + 3 * ((ell - 2) / 3) : 1;  // latest update before this step
-  const bool sums = first || last || ell - u == 3;
-  const V yc = reinterpret_cast<const V*>(cur)[row];
-  V yp = yc, r = yc;
-  if (!first) yp = reinterpret_cast<const V*>(prev)[row];
-  if (sums && !first) r = reinterpret_cast<const V*>(acc)[row];
-  T sum[B];
-#pragma unroll
-  for (int j = 0; j < B; ++j) sum[j] = (T)0;
-  stencil_product<T, B, B, 1, 0>(val, soff, mask, stride, slice, lane, row, cur, 0, sum);
-  V nx;
-#pragma unroll
-  for (int j = 0; j < B; ++j) nx.v[j] = (T)2 * yc.v[j] - yp.v[j] - sum[j];
-  if (!last) reinterpret_cast<V*>(out)[row] = nx;
-  if (!sums) return;
-  const T* __restrict__ wq = wtab + (int64_t)p * lmax;
-  if (first) {
-#pragma unroll
-    for (int j = 0; j < B; ++j) r.v[j] = fma(wq[1], nx.v[j], wq[0] * yc.v[j]);
-  } else {
-    const T wp = ell - 2 > u ? wq[ell - 2] : (T)0, wc = ell - 1 > u ? wq[ell - 1] : (T)0, wn = wq[ell];
-#pragma unroll
-    for (int j = 0; j < B; ++j) r.v[j] = fma(wn, nx.v[j], fma(wc, yc.v[j], fma(wp, yp.v[j], r.v[j])));
-  }
-  if (last) {
-    double* __restrict__ dst = tb->dst[p];
-    const int64_t ld = tb->ld[p];
-    const int bout = tb->bout[p];
-#pragma unroll
-    for (int j = 0; j < B; ++j)
-      if (j < bout) dst[local + (int64_t)j * ld] = (double)r.v[j];
-  } else {
-    reinterpret_cast<V*>(acc)[row] = r;
   }
 }
 
@@ -839,61 +532,6 @@ int launch_lf_b(const SellOp& A, int mode, const void* cur, const void* prev, vo
   return launch_lf_bl<T, IT, B, 1>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
 }
 
-template <typename T, int B, int LPR, int W>
-int launch_st_w(const SellOp& A, int mode, const void* cur, const void* prev, void* out, void* acc, double* rout,
-                int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap, hipStream_t st) {
-#define KF_ST(M)                                                                                                     \
-  hipLaunchKernelGGL((k_leapfrog_st<T, B, M, LPR, W>), dim3(ceil_div64((int64_t)A.nslices * LPR, 4)), dim3(256), 0,    \
-                     st, A.n, A.nslices, static_cast<const T*>(A.st.val), A.st.off, A.st.mask, A.st.stride,             \
-                     static_cast<const T*>(cur), static_cast<const T*>(prev), static_cast<T*>(out),                     \
-                     static_cast<T*>(acc), rout, rs, cs, bout, (T)wp, (T)wc, (T)wn, remap)
-  switch (mode) {
-    case kMid: KF_ST(kMid); break;
-    case kFirst: KF_ST(kFirst); break;
-    case kMidAcc: KF_ST(kMidAcc); break;
-    case kLast: KF_ST(kLast); break;
-    default: KF_ST(kFirstLast); break;
-  }
-#undef KF_ST
-  KF_HIP(hipGetLastError());
-  return KF_OK;
-}
-
-template <typename T, int B, int LPR>
-int launch_st_l(const SellOp& A, int mode, const void* cur, const void* prev, void* out, void* acc, double* rout,
-                int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap, hipStream_t st) {
-  if (A.st.stride == 5)
-    return launch_st_w<T, B, LPR, 5>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
-  if (A.st.stride == 7)
-    return launch_st_w<T, B, LPR, 7>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
-  return launch_st_w<T, B, LPR, 0>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
-}
-
-template <typename T, int B>
-int launch_st_b(const SellOp& A, int mode, const void* cur, const void* prev, void* out, void* acc, double* rout,
-                int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap, hipStream_t st) {
-  const int lpr = lanes_per_row(A, B);
-  if constexpr (B >= 4)
-    if (lpr == 4) return launch_st_l<T, B, 4>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
-  if constexpr (B >= 2)
-    if (lpr == 2) return launch_st_l<T, B, 2>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
-  return launch_st_l<T, B, 1>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
-}
-
-// The fused step over stencil slices.
-template <typename T>
-int launch_st(const SellOp& A, int b, int mode, const void* cur, const void* prev, void* out, void* acc, double* rout,
-              int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap, hipStream_t st) {
-  switch (b) {
-    case 1: return launch_st_b<T, 1>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
-    case 2: return launch_st_b<T, 2>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
-    case 4: return launch_st_b<T, 4>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
-    case 8: return launch_st_b<T, 8>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
-    case 16: return launch_st_b<T, 16>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
-    default: set_error("leapfrog: block width must be 1, 2, 4, 8 or 16"); return KF_EINVAL;
-  }
-}
-
 template <typename T, typename IT>
 int launch_lf_t(const SellOp& A, int b, int mode, const void* cur, const void* prev, void* out, void* acc,
                 double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap, hipStream_t st) {
@@ -934,55 +572,6 @@ int launch_lf4_b(const SellOp& A, int mode, const void* cur, const void* prev, v
 #undef KF_LF4
   KF_HIP(hipGetLastError());
   return KF_OK;
-}
-
-template <typename T, int B, int LPR, int W>
-int launch_st4_w(const SellOp& A, int mode, const void* cur, const void* prev, void* out, void* acc, void* z,
-                 double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap,
-                 hipStream_t st) {
-#define KF_ST4(M)                                                                                                   \
-  hipLaunchKernelGGL((k_leapfrog4_st<T, B, M, LPR, W>), dim3(ceil_div64((int64_t)A.nslices * LPR, 4)), dim3(256), 0,  \
-                     st, A.n, A.nslices, static_cast<const T*>(A.st.val), A.st.off, A.st.mask, A.st.stride,            \
-                     static_cast<const T*>(cur), static_cast<const T*>(prev), static_cast<T*>(out),                    \
-                     static_cast<T*>(acc), static_cast<T*>(z), rout, rs, cs, bout, (T)wp, (T)wc, (T)wn, remap)
-  KF_ST4(-1);
-  switch (mode) {
-    case kMid: KF_ST4(kMid); break;
-    case kFirst: KF_ST4(kFirst); break;
-    case kMidAcc: KF_ST4(kMidAcc); break;
-    case kLast: KF_ST4(kLast); break;
-    default: KF_ST4(kFirstLast); break;
-  }
-#undef KF_ST4
-  KF_HIP(hipGetLastError());
-  return KF_OK;
-}
-
-// (16 bytes of a row per lane; as many lanes share it)
-template <typename T, int B>
-int launch_st4_b(const SellOp& A, int mode, const void* cur, const void* prev, void* out, void* acc, void* z,
-                 double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap,
-                 hipStream_t st) {
-  constexpr int LPR = B * sizeof(T) >= 64 ? 4 : (B * sizeof(T) >= 32 ? 2 : 1);
-  if (A.st.stride == 5)
-    return launch_st4_w<T, B, LPR, 5>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
-  if (A.st.stride == 7)
-    return launch_st4_w<T, B, LPR, 7>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
-  return launch_st4_w<T, B, LPR, 0>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
-}
-
-template <typename T>
-int launch_st4(const SellOp& A, int b, int mode, const void* cur, const void* prev, void* out, void* acc, void* z,
-               double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap,
-               hipStream_t st) {
-  switch (b) {
-    case 1: return launch_st4_b<T, 1>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
-    case 2: return launch_st4_b<T, 2>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
-    case 4: return launch_st4_b<T, 4>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
-    case 8: return launch_st4_b<T, 8>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
-    case 16: return launch_st4_b<T, 16>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
-    default: set_error("fourth-order step: block width must be 1, 2, 4, 8 or 16"); return KF_EINVAL;
-  }
 }
 
 template <typename T, typename IT>
@@ -1201,134 +790,6 @@ __global__ __launch_bounds__(1024) void k_leapfrog_mp_reg(int32_t n, int32_t nsl
   }
 }
 
-// ------------------------------------- several steps per launch over stencils
-// The time loop of problems too small to fill a launch: a step of one launch
-// takes 3 to 4 us whatever its size, most of it launch and dependent-load
-// latency.  A workgroup owns a range of row slices and advances it s steps in
-// one launch; y_l of those rows, and of the hb slices a step reaches on either
-// side for each later step, lie in LDS (two copies, written in turn), and each
-// wavefront keeps the levels y_{l-1}, y_l and the weighted sum of its slices
-// (wave, wave + 16, ...: at most R) in registers, with the places of their
-// stencil neighbours in LDS; absent neighbours point at a zero.  A step then
-// is W LDS reads, W products and one LDS write per row and one barrier.  The
-// halo slices are computed by every workgroup that needs them; with the whole
-// problem in one workgroup there are none.  The weighted sum takes one term
-// per step, in the same order as three terms every third step: results are
-// those of one step per launch, bit for bit.  A workgroup carries B columns
-// (at most 16 bytes) of a row of `groups` times as many: wider blocks are
-// independent groups of columns along the grid's y.
-// Measured, us per filter application, one step per launch and so: 64-cell
-// square (63 slices) fp64 257 -> 45; 128 cells 535 -> 114; 256 cells 1072 ->
-// 322, its block of 4 in float32 1021 -> 463; 20-cell cube 91 -> 44.  Bound by
-// a launch's latency (about 4 us) and the LDS reads of the halo slices.
-//   first: y_{-1} = y_0 = x (x in ysrc), the sum starts at w_0 x; else i0, i1
-//          hold y_{l0-1}, y_{l0} and acc the sum
-//   last:  the sum goes to rout; otherwise y_{l0+s-1}, y_{l0+s} go to o0g,
-//          o1g and the sum to acc.  o0g, o1g are not i0, i1 unless there is
-//          one workgroup.
-// w.w[j] is the weight of y_{l0+j}.
-template <typename T, int B, int W, int R>
-__global__ __launch_bounds__(1024) void k_steps_st(int32_t n, int32_t nslices, const T* __restrict__ sval,
-                                                   const int32_t* __restrict__ soff, const uint64_t* __restrict__ smask,
-                                                   const T* ysrc, const T* i0, const T* i1, T* o0g, T* o1g, T* acc, double* __restrict__ rout, int64_t rs, int64_t cs,
-                                                   int bout, int groups, StepWeights w, int s, int own,
-                                                   int hb, int first, int last) {
-  using V = Row<T, B>;
-  extern __shared__ __align__(16) unsigned char steps_raw[];
-  const int wg = xcd_map(blockIdx.x, gridDim.x);
-  const int o0 = wg * own, o1 = min(nslices, o0 + own);
-  const int w0 = max(0, o0 - s * hb), w1 = min(nslices, o1 + s * hb);
-  const int rows = (w1 - w0) * 64;  // of one level in LDS; row `rows` is the zero
-  V* lds = reinterpret_cast<V*>(steps_raw);
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int step2 = rows + 1;  // distance of the two copies
-  if (threadIdx.x < 2) {
-    V zero;
-#pragma unroll
-    for (int j = 0; j < B; ++j) zero.v[j] = (T)0;
-    lds[threadIdx.x * step2 + rows] = zero;
-  }
-  const int grp = blockIdx.y;
-  V yc[R], yp[R], ra[R];
-  uint32_t at[R][(W + 1) / 2];  // two neighbours' LDS rows per register
-#pragma unroll
-  for (int k = 0; k < R; ++k) {
-    const int sl = w0 + wave + 16 * k;
-    if (sl >= w1) break;
-    const int row = sl * 64 + lane;
-#pragma unroll
-    for (int j = 0; j < B; ++j) yc[k].v[j] = yp[k].v[j] = ra[k].v[j] = (T)0;
-    if (row < n) {
-      yc[k] = reinterpret_cast<const V*>(first ? ysrc : i1)[(int64_t)row * groups + grp];
-      yp[k] = first ? yc[k] : reinterpret_cast<const V*>(i0)[(int64_t)row * groups + grp];
-      if (sl >= o0 && sl < o1) {
-        if (first) {
-#pragma unroll
-          for (int j = 0; j < B; ++j) ra[k].v[j] = (T)w.w[0] * yc[k].v[j];
-        } else {
-          ra[k] = reinterpret_cast<const V*>(acc)[(int64_t)row * groups + grp];
-        }
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < W; ++q) {
-      const bool has = __builtin_amdgcn_inverse_ballot_w64(smask[(int64_t)sl * W + q]);
-      const int c = row - w0 * 64 + soff[(int64_t)sl * W + q];
-      const uint32_t a = has && c >= 0 && c < rows ? (uint32_t)c : (uint32_t)rows;
-      at[k][q >> 1] = q & 1 ? at[k][q >> 1] | a << 16 : a;
-    }
-    lds[row - w0 * 64] = yc[k];
-  }
-  __syncthreads();
-  int cur = 0;
-  for (int j = 0; j < s; ++j) {
-    const T wn = (T)w.w[j + 1];
-    // the slices the later steps still read
-    const int a0 = o0 - (s - 1 - j) * hb, a1 = o1 + (s - 1 - j) * hb;
-    const V* __restrict__ src = lds + cur * step2;
-    V* __restrict__ dst = lds + (cur ^ 1) * step2;
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-      const int sl = w0 + wave + 16 * k;
-      if (sl >= w1 || sl < a0 || sl >= a1) continue;
-      V x[W];
-#pragma unroll
-      for (int q = 0; q < W; ++q) x[q] = src[q & 1 ? at[k][q >> 1] >> 16 : at[k][q >> 1] & 0xFFFFu];
-      V nx;
-#pragma unroll
-      for (int c = 0; c < B; ++c) {
-        T sum = (T)0;
-#pragma unroll
-        for (int q = 0; q < W; ++q) sum = fma(sval[(int64_t)sl * W + q], x[q].v[c], sum);
-        nx.v[c] = (T)2 * yc[k].v[c] - yp[k].v[c] - sum;
-        ra[k].v[c] = fma(wn, nx.v[c], ra[k].v[c]);
-      }
-      yp[k] = yc[k];
-      yc[k] = nx;
-      dst[sl * 64 + lane - w0 * 64] = nx;
-    }
-    __syncthreads();
-    cur ^= 1;
-  }
-#pragma unroll
-  for (int k = 0; k < R; ++k) {
-    const int sl = w0 + wave + 16 * k;
-    if (sl < o0 || sl >= o1) continue;
-    const int row = sl * 64 + lane;
-    if (row >= n) continue;
-    if (last) {
-#pragma unroll
-      for (int j = 0; j < B; ++j)
-        if (grp * B + j < bout) rout[(int64_t)row * rs + (int64_t)(grp * B + j) * cs] = (double)ra[k].v[j];
-    } else {
-      const int64_t o = (int64_t)row * groups + grp;
-      reinterpret_cast<V*>(o0g)[o] = yp[k];
-      reinterpret_cast<V*>(o1g)[o] = yc[k];
-      reinterpret_cast<V*>(acc)[o] = ra[k];
-    }
-  }
-}
-
 }  // namespace
 
 
@@ -1336,58 +797,9 @@ void free_sell(SellOp& op) {
   if (op.slice_ptr) (void)hipFree(op.slice_ptr);
   if (op.val) (void)hipFree(op.val);
   if (op.idx) (void)hipFree(op.idx);
-  if (op.st.val) (void)hipFree(op.st.val);
-  if (op.st.off) (void)hipFree(op.st.off);
-  if (op.st.mask) (void)hipFree(op.st.mask);
+  free_stencil(op.st);
   op = SellOp();
 }
-
-namespace {
-// The stencil form of an operator's slices, when it has one (else out.width
-// stays 0).
-template <typename VT>
-int build_stencil(int32_t n, int32_t ns, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
-                  const double* d_row_scale, bool exact, hipStream_t st, StencilOp& out) {
-  const int grid = ceil_div64(ns, 4);
-  int32_t* d_w = nullptr;
-  if (hipMalloc(&d_w, sizeof(int32_t) * (size_t)ns) != hipSuccess) {
-    set_error("build_sell: device allocation failed");
-    return KF_ENOMEM;
-  }
-  hipLaunchKernelGGL((k_stencil<VT, false>), dim3(grid), dim3(256), 0, st, n, ns, d_rowptr, d_col, d_val, d_row_scale,
-                     d_w, 0, (VT*)nullptr, (int32_t*)nullptr, (uint64_t*)nullptr);
-  std::vector<int32_t> w((size_t)ns);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = hipMemcpyAsync(w.data(), d_w, sizeof(int32_t) * (size_t)ns, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  (void)hipFree(d_w);
-  if (e != hipSuccess) {
-    set_error(std::string("build_sell: ") + hipGetErrorString(e));
-    return KF_EHIP;
-  }
-  const int width = *std::max_element(w.begin(), w.end());
-  if (width < 1 || width > kStencilMax) return KF_OK;
-  // 5 and 7 entries (the 2D and 3D point stencils) have kernels of their own
-  // length; other lengths are padded to the loop's four entries
-  const int stride = exact && (width == 5 || width == 7) ? width : (width + 3) / 4 * 4;
-  const size_t tot = (size_t)ns * stride;
-  StencilOp s;
-  if (hipMalloc(&s.val, tot * sizeof(VT)) != hipSuccess || hipMalloc(&s.off, tot * sizeof(int32_t)) != hipSuccess ||
-      hipMalloc(&s.mask, tot * sizeof(uint64_t)) != hipSuccess) {
-    if (s.val) (void)hipFree(s.val);
-    if (s.off) (void)hipFree(s.off);
-    set_error("build_sell: device allocation failed");
-    return KF_ENOMEM;
-  }
-  s.width = width;
-  s.stride = stride;
-  out = s;
-  hipLaunchKernelGGL((k_stencil<VT, true>), dim3(grid), dim3(256), 0, st, n, ns, d_rowptr, d_col, d_val, d_row_scale,
-                     (int32_t*)nullptr, stride, (VT*)s.val, s.off, s.mask);
-  KF_HIP(hipGetLastError());
-  return KF_OK;
-}
-}  // namespace
 
 int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
                const double* d_row_scale, int val_bytes, int want_idx_bytes, hipStream_t st, SellOp& out, int stencil) {
@@ -1462,12 +874,8 @@ int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d
     hipLaunchKernelGGL((k_sell_fill<float, int32_t>), dim3(grid), dim3(256), 0, st, n, ns, out.slice_ptr, d_rowptr,
                        d_col, d_val, d_row_scale, (float*)out.val, (int32_t*)out.idx);
   KF_HIP(hipGetLastError());
-  if (stencil) {
-    if (val_bytes == 8)
-      KF_TRY(build_stencil<double>(n, ns, d_rowptr, d_col, d_val, d_row_scale, stencil == kStencilExact, st, out.st));
-    else
-      KF_TRY(build_stencil<float>(n, ns, d_rowptr, d_col, d_val, d_row_scale, stencil == kStencilExact, st, out.st));
-  }
+  if (stencil)
+    KF_TRY(build_stencil(n, ns, d_rowptr, d_col, d_val, d_row_scale, val_bytes, stencil == kStencilExact, st, out.st));
   KF_HIP(hipStreamSynchronize(st));
   (void)nnz;
   return KF_OK;
@@ -1488,11 +896,8 @@ int lanes_per_row(const SellOp& A, int b) {
 int launch_leapfrog(const SellOp& A, int b, int mode, const void* cur, const void* prev, void* out, void* acc,
                     double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int xcd_remap,
                     hipStream_t st) {
-  if (A.st.width > 0) {
-    if (A.val_bytes == 8)
-      return launch_st<double>(A, b, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, xcd_remap, st);
-    return launch_st<float>(A, b, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, xcd_remap, st);
-  }
+  if (A.st.width > 0)
+    return launch_stencil_step(A, b, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, xcd_remap, st);
   if (A.val_bytes == 8) {
     if (A.idx_bytes == 2)
       return launch_lf_t<double, int16_t>(A, b, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, xcd_remap,
@@ -1603,11 +1008,8 @@ int launch_leapfrog_mp(const SellOp& A, const MultiStepPlan& pl, int l0, int s, 
 int launch_leapfrog4(const SellOp& A, int b, int mode, const void* cur, const void* prev, void* out, void* acc, void* z,
                      double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int xcd_remap,
                      hipStream_t st) {
-  if (A.st.width > 0) {
-    if (A.val_bytes == 8)
-      return launch_st4<double>(A, b, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, xcd_remap, st);
-    return launch_st4<float>(A, b, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, xcd_remap, st);
-  }
+  if (A.st.width > 0)
+    return launch_stencil_step4(A, b, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, xcd_remap, st);
   if (A.val_bytes == 8) {
     if (A.idx_bytes == 2)
       return launch_lf4_t<double, int16_t>(A, b, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn,
@@ -1620,106 +1022,6 @@ int launch_leapfrog4(const SellOp& A, int b, int mode, const void* cur, const vo
                                         st);
   return launch_lf4_t<float, int32_t>(A, b, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, xcd_remap,
                                       st);
-}
-
-namespace {
-// arguments of one k_steps_st launch that its dispatch only passes on
-struct StepsArgs {
-  const void *ysrc, *i0, *i1;
-  void *o0, *o1, *acc;
-  double* rout;
-  int64_t rs, cs;
-  int bout, groups, s;
-  bool first, last;
-};
-
-template <typename T, int B, int W, int R>
-int launch_steps_r(const SellOp& A, const StepsPlan& pl, const StepsArgs& g, const StepWeights& w, hipStream_t st) {
-  const int win = std::min(A.nslices, pl.own + 2 * g.s * pl.hb);
-  const size_t lds = (size_t)2 * (win * 64 + 1) * B * sizeof(T);
-  KF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_steps_st<T, B, W, R>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL((k_steps_st<T, B, W, R>), dim3(ceil_div64(A.nslices, pl.own), g.groups), dim3(1024), lds, st, A.n,
-                     A.nslices, static_cast<const T*>(A.st.val), A.st.off, A.st.mask, static_cast<const T*>(g.ysrc),
-                     static_cast<const T*>(g.i0), static_cast<const T*>(g.i1), static_cast<T*>(g.o0),
-                     static_cast<T*>(g.o1), static_cast<T*>(g.acc), g.rout, g.rs, g.cs, g.bout, g.groups, w, g.s, pl.own,
-                     pl.hb, g.first ? 1 : 0, g.last ? 1 : 0);
-  KF_HIP(hipGetLastError());
-  return KF_OK;
-}
-
-template <typename T, int B, int W>
-int launch_steps_w(const SellOp& A, const StepsPlan& pl, const StepsArgs& g, const StepWeights& w, hipStream_t st) {
-  const int per = (std::min(A.nslices, pl.own + 2 * g.s * pl.hb) + 15) / 16;  // slices of a wavefront
-  if (per <= 2) return launch_steps_r<T, B, W, 2>(A, pl, g, w, st);
-  if (per <= 4) return launch_steps_r<T, B, W, 4>(A, pl, g, w, st);
-  return launch_steps_r<T, B, W, steps_max_r(B * sizeof(T))>(A, pl, g, w, st);
-}
-
-template <typename T, int B>
-int launch_steps_b(const SellOp& A, const StepsPlan& pl, const StepsArgs& g, const StepWeights& w, hipStream_t st) {
-  if (A.st.stride == 5) return launch_steps_w<T, B, 5>(A, pl, g, w, st);
-  return launch_steps_w<T, B, 7>(A, pl, g, w, st);
-}
-}  // namespace
-
-int launch_steps(const SellOp& A, const StepsPlan& pl, int b, int s, bool first, bool last, const void* ysrc,
-                 const void* i0, const void* i1, void* o0, void* o1, void* acc, double* rout, int64_t rs, int64_t cs,
-                 int bout, const StepWeights& w, hipStream_t st) {
-  if (pl.s < 1 || s < 1 || s > pl.s || (A.st.stride != 5 && A.st.stride != 7)) {
-    set_error("several steps per launch: no plan for this operator");
-    return KF_EINVAL;
-  }
-  const int cols = std::min(b, 16 / A.val_bytes);
-  const StepsArgs g{ysrc, i0, i1, o0, o1, acc, rout, rs, cs, bout, b / cols, s, first, last};
-  if (A.val_bytes == 8) return cols == 1 ? launch_steps_b<double, 1>(A, pl, g, w, st) : launch_steps_b<double, 2>(A, pl, g, w, st);
-  if (cols == 1) return launch_steps_b<float, 1>(A, pl, g, w, st);
-  return cols == 2 ? launch_steps_b<float, 2>(A, pl, g, w, st) : launch_steps_b<float, 4>(A, pl, g, w, st);
-}
-
-// The rule: the time of a filter application by the figures measured on
-// squares of 32 to 600 and cubes of 13 to 33 cells (within 10 % of every
-// measurement while a wavefront has at most four slices), in us:
-//   a launch        3.7 + 0.03 per slice of the window (0.06 for 16-byte rows)
-//   one of its steps  0.12 + 0.014 per slice computed (0.022), 15 % more with
-//                   more than four slices per wavefront
-// with at most one workgroup per compute unit, against 4.0 per step of a
-// launch of its own, which larger problems exceed.  The plan is taken where it
-// is at least 15 % better; e.g. the 600-cell square in float32 (4 steps, 2.55
-// us each) and the 33-cell cube (3 steps, 3.1 us) are, the 48-cell cube, whose
-// band is 35 slices, is not.
-StepsPlan plan_steps(const SellOp& A, int b, int L, size_t lds_bytes) {
-  StepsPlan best;
-  if ((A.st.stride != 5 && A.st.stride != 7) || A.st.width != A.st.stride || L < 3) return best;
-  constexpr int kCus = 256;
-  const int cols = std::min(b, 16 / A.val_bytes), groups = b / cols, rb = cols * A.val_bytes;
-  const int hb = (A.max_off + 63) / 64, ns = A.nslices;
-  const int win_max = std::min<int64_t>(16 * steps_max_r(rb), ((int64_t)lds_bytes / (2 * rb) - 1) / 64);
-  const double load = rb > 8 ? 0.06 : 0.03, slice = rb > 8 ? 0.022 : 0.014;
-  double t_best = 0.85 * 4.0 * (L - 1);
-  const int own_min = (int)(((int64_t)ns * groups + kCus - 1) / kCus);
-  if (own_min > win_max || groups > kCus) return best;
-  for (int i = 0; i < 4; ++i) {
-    const int own = i == 3 ? ns : std::min(ns, own_min << i);
-    const bool whole = own >= ns;
-    for (int s = 1; s <= std::min(kStepsMax, L - 1); ++s) {
-      const int win = std::min(ns, own + 2 * s * hb);
-      if (win > win_max) break;
-      const double avg = std::min<double>(ns, own + (double)(s - 1) * hb);
-      double step = 0.12 + slice * avg;
-      if (win > 64) step *= 1.15;
-      const int launches = (L - 1 + s - 1) / s;
-      const double t = launches * (3.7 + load * win) + (L - 1) * step;
-      if (t < t_best) {
-        t_best = t;
-        best.s = s;
-        best.own = whole ? ns : own;
-        best.hb = hb;
-      }
-    }
-    if (whole) break;
-  }
-  return best;
 }
 
 StepPlan step_plan(int l, int L) {
@@ -1772,37 +1074,12 @@ int launch_lfb_t(const SellOp& A, int b, const int32_t* sp, const BatchTables* t
 }
 }  // namespace
 
-namespace {
-template <typename T>
-int launch_lfb_st(const SellOp& A, int b, const int32_t* sp, const BatchTables* tb, const void* wtab, int lmax, int ell,
-                  const void* cur, const void* prev, void* out, void* acc, int nslices, int remap, hipStream_t st) {
-#define KF_LFS(B)                                                                                                  \
-  hipLaunchKernelGGL((k_leapfrog_batch_st<T, B>), dim3(ceil_div64(nslices, 4)), dim3(256), 0, st, nslices,          \
-                     static_cast<const T*>(A.st.val), A.st.off, A.st.mask, A.st.stride, sp, tb,                     \
-                     static_cast<const T*>(wtab), lmax, ell, static_cast<const T*>(cur), static_cast<const T*>(prev), \
-                     static_cast<T*>(out), static_cast<T*>(acc), remap)
-  switch (b) {
-    case 1: KF_LFS(1); break;
-    case 2: KF_LFS(2); break;
-    case 4: KF_LFS(4); break;
-    case 8: KF_LFS(8); break;
-    case 16: KF_LFS(16); break;
-    default: set_error("batched leapfrog: block width must be 1, 2, 4, 8 or 16"); return KF_EINVAL;
-  }
-#undef KF_LFS
-  KF_HIP(hipGetLastError());
-  return KF_OK;
-}
-}  // namespace
-
 int launch_leapfrog_batch(const SellOp& A, int b, const int32_t* sp, const BatchTables* tb, const void* wtab, int lmax,
                           int ell, const void* cur, const void* prev, void* out, void* acc, int nslices, int remap,
                           hipStream_t st) {
   if (nslices <= 0 || nslices > A.nslices) nslices = A.nslices;
   if (A.st.width > 0)
-    return A.val_bytes == 8
-               ? launch_lfb_st<double>(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, nslices, remap, st)
-               : launch_lfb_st<float>(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, nslices, remap, st);
+    return launch_stencil_batch(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, nslices, remap, st);
 #define KF_LFB(T, IT)                                                                                               \
   return A.nt_loads ? launch_lfb_t<T, IT, true>(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, nslices, remap, \
                                                 st)                                                                 \

@@ -1,0 +1,245 @@
+// Several time steps per launch over stencil slices: the kernel, the rule that
+// chooses it and its launcher.
+
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "kf_device.h"
+#include "kf_internal.h"
+
+namespace kf {
+
+namespace {
+
+// ------------------------------------- several steps per launch over stencils
+// The time loop of problems too small to fill a launch: a step of one launch
+// takes 3 to 4 us whatever its size, most of it launch and dependent-load
+// latency.  A workgroup owns a range of row slices and advances it s steps in
+// one launch; y_l of those rows, and of the hb slices a step reaches on either
+// side for each later step, lie in LDS (two copies, written in turn), and each
+// wavefront keeps the levels y_{l-1}, y_l and the weighted sum of its slices
+// (wave, wave + 16, ...: at most R) in registers, with the places of their
+// stencil neighbours in LDS; absent neighbours point at a zero.  A step then
+// is W LDS reads, W products and one LDS write per row and one barrier.  The
+// halo slices are computed by every workgroup that needs them; with the whole
+// problem in one workgroup there are none.  The weighted sum takes one term
+// per step, in the same order as three terms every third step: results are
+// those of one step per launch, bit for bit.  A workgroup carries B columns
+// (at most 16 bytes) of a row of `groups` times as many: wider blocks are
+// independent groups of columns along the grid's y.
+// Measured, us per filter application, one step per launch and so: 64-cell
+// square (63 slices) fp64 257 -> 45; 128 cells 535 -> 114; 256 cells 1072 ->
+// 322, its block of 4 in float32 1021 -> 463; 20-cell cube 91 -> 44.  Bound by
+// a launch's latency (about 4 us) and the LDS reads of the halo slices.
+//   first: y_{-1} = y_0 = x (x in ysrc), the sum starts at w_0 x; else i0, i1
+//          hold y_{l0-1}, y_{l0} and acc the sum
+//   last:  the sum goes to rout; otherwise y_{l0+s-1}, y_{l0+s} go to o0g,
+//          o1g and the sum to acc.  o0g, o1g are not i0, i1 unless there is
+//          one workgroup.
+// w.w[j] is the weight of y_{l0+j}.
+template <typename T, int B, int W, int R>
+__global__ __launch_bounds__(1024) void k_steps_st(int32_t n, int32_t nslices, const T* __restrict__ sval,
+                                                   const int32_t* __restrict__ soff, const uint64_t* __restrict__ smask,
+                                                   const T* ysrc, const T* i0, const T* i1, T* o0g, T* o1g, T* acc, double* __restrict__ rout, int64_t rs, int64_t cs,
+                                                   int bout, int groups, StepWeights w, int s, int own,
+                                                   int hb, int first, int last) {
+  using V = Row<T, B>;
+  extern __shared__ __align__(16) unsigned char steps_raw[];
+  const int wg = xcd_map(blockIdx.x, gridDim.x);
+  const int o0 = wg * own, o1 = min(nslices, o0 + own);
+  const int w0 = max(0, o0 - s * hb), w1 = min(nslices, o1 + s * hb);
+  const int rows = (w1 - w0) * 64;  // of one level in LDS; row `rows` is the zero
+  V* lds = reinterpret_cast<V*>(steps_raw);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int step2 = rows + 1;  // distance of the two copies
+  if (threadIdx.x < 2) {
+    V zero;
+#pragma unroll
+    for (int j = 0; j < B; ++j) zero.v[j] = (T)0;
+    lds[threadIdx.x * step2 + rows] = zero;
+  }
+  const int grp = blockIdx.y;
+  V yc[R], yp[R], ra[R];
+  uint32_t at[R][(W + 1) / 2];  // two neighbours' LDS rows per register
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int sl = w0 + wave + 16 * k;
+    if (sl >= w1) break;
+    const int row = sl * 64 + lane;
+#pragma unroll
+    for (int j = 0; j < B; ++j) yc[k].v[j] = yp[k].v[j] = ra[k].v[j] = (T)0;
+    if (row < n) {
+      yc[k] = reinterpret_cast<const V*>(first ? ysrc : i1)[(int64_t)row * groups + grp];
+      yp[k] = first ? yc[k] : reinterpret_cast<const V*>(i0)[(int64_t)row * groups + grp];
+      if (sl >= o0 && sl < o1) {
+        if (first) {
+#pragma unroll
+          for (int j = 0; j < B; ++j) ra[k].v[j] = (T)w.w[0] * yc[k].v[j];
+        } else {
+          ra[k] = reinterpret_cast<const V*>(acc)[(int64_t)row * groups + grp];
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+      const bool has = __builtin_amdgcn_inverse_ballot_w64(smask[(int64_t)sl * W + q]);
+      const int c = row - w0 * 64 + soff[(int64_t)sl * W + q];
+      const uint32_t a = has && c >= 0 && c < rows ? (uint32_t)c : (uint32_t)rows;
+      at[k][q >> 1] = q & 1 ? at[k][q >> 1] | a << 16 : a;
+    }
+    lds[row - w0 * 64] = yc[k];
+  }
+  __syncthreads();
+  int cur = 0;
+  for (int j = 0; j < s; ++j) {
+    const T wn = (T)w.w[j + 1];
+    // the slices the later steps still read
+    const int a0 = o0 - (s - 1 - j) * hb, a1 = o1 + (s - 1 - j) * hb;
+    const V* __restrict__ src = lds + cur * step2;
+    V* __restrict__ dst = lds + (cur ^ 1) * step2;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const int sl = w0 + wave + 16 * k;
+      if (sl >= w1 || sl < a0 || sl >= a1) continue;
+      V x[W];
+#pragma unroll
+      for (int q = 0; q < W; ++q) x[q] = src[q & 1 ? at[k][q >> 1] >> 16 : at[k][q >> 1] & 0xFFFFu];
+      V nx;
+#pragma unroll
+      for (int c = 0; c < B; ++c) {
+        T sum = (T)0;
+#pragma unroll
+        for (int q = 0; q < W; ++q) sum = fma(sval[(int64_t)sl * W + q], x[q].v[c], sum);
+        nx.v[c] = (T)2 * yc[k].v[c] - yp[k].v[c] - sum;
+        ra[k].v[c] = fma(wn, nx.v[c], ra[k].v[c]);
+      }
+      yp[k] = yc[k];
+      yc[k] = nx;
+      dst[sl * 64 + lane - w0 * 64] = nx;
+    }
+    __syncthreads();
+    cur ^= 1;
+  }
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int sl = w0 + wave + 16 * k;
+    if (sl < o0 || sl >= o1) continue;
+    const int row = sl * 64 + lane;
+    if (row >= n) continue;
+    if (last) {
+#pragma unroll
+      for (int j = 0; j < B; ++j)
+        if (grp * B + j < bout) rout[(int64_t)row * rs + (int64_t)(grp * B + j) * cs] = (double)ra[k].v[j];
+    } else {
+      const int64_t o = (int64_t)row * groups + grp;
+      reinterpret_cast<V*>(o0g)[o] = yp[k];
+      reinterpret_cast<V*>(o1g)[o] = yc[k];
+      reinterpret_cast<V*>(acc)[o] = ra[k];
+    }
+  }
+}
+
+}  // namespace
+
+namespace {
+// arguments of one k_steps_st launch that its dispatch only passes on
+struct StepsArgs {
+  const void *ysrc, *i0, *i1;
+  void *o0, *o1, *acc;
+  double* rout;
+  int64_t rs, cs;
+  int bout, groups, s;
+  bool first, last;
+};
+
+template <typename T, int B, int W, int R>
+int launch_steps_r(const SellOp& A, const StepsPlan& pl, const StepsArgs& g, const StepWeights& w, hipStream_t st) {
+  const int win = std::min(A.nslices, pl.own + 2 * g.s * pl.hb);
+  const size_t lds = (size_t)2 * (win * 64 + 1) * B * sizeof(T);
+  KF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_steps_st<T, B, W, R>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL((k_steps_st<T, B, W, R>), dim3(ceil_div64(A.nslices, pl.own), g.groups), dim3(1024), lds, st, A.n,
+                     A.nslices, static_cast<const T*>(A.st.val), A.st.off, A.st.mask, static_cast<const T*>(g.ysrc),
+                     static_cast<const T*>(g.i0), static_cast<const T*>(g.i1), static_cast<T*>(g.o0),
+                     static_cast<T*>(g.o1), static_cast<T*>(g.acc), g.rout, g.rs, g.cs, g.bout, g.groups, w, g.s, pl.own,
+                     pl.hb, g.first ? 1 : 0, g.last ? 1 : 0);
+  KF_HIP(hipGetLastError());
+  return KF_OK;
+}
+
+template <typename T, int B, int W>
+int launch_steps_w(const SellOp& A, const StepsPlan& pl, const StepsArgs& g, const StepWeights& w, hipStream_t st) {
+  const int per = (std::min(A.nslices, pl.own + 2 * g.s * pl.hb) + 15) / 16;  // slices of a wavefront
+  if (per <= 2) return launch_steps_r<T, B, W, 2>(A, pl, g, w, st);
+  if (per <= 4) return launch_steps_r<T, B, W, 4>(A, pl, g, w, st);
+  return launch_steps_r<T, B, W, steps_max_r(B * sizeof(T))>(A, pl, g, w, st);
+}
+
+template <typename T, int B>
+int launch_steps_b(const SellOp& A, const StepsPlan& pl, const StepsArgs& g, const StepWeights& w, hipStream_t st) {
+  if (A.st.stride == 5) return launch_steps_w<T, B, 5>(A, pl, g, w, st);
+  return launch_steps_w<T, B, 7>(A, pl, g, w, st);
+}
+}  // namespace
+
+int launch_steps(const SellOp& A, const StepsPlan& pl, int b, int s, bool first, bool last, const void* ysrc,
+                 const void* i0, const void* i1, void* o0, void* o1, void* acc, double* rout, int64_t rs, int64_t cs,
+                 int bout, const StepWeights& w, hipStream_t st) {
+  if (pl.s < 1 || s < 1 || s > pl.s || (A.st.stride != 5 && A.st.stride != 7)) {
+    set_error("several steps per launch: no plan for this operator");
+    return KF_EINVAL;
+  }
+  const int cols = std::min(b, 16 / A.val_bytes);
+  const StepsArgs g{ysrc, i0, i1, o0, o1, acc, rout, rs, cs, bout, b / cols, s, first, last};
+  if (A.val_bytes == 8) return cols == 1 ? launch_steps_b<double, 1>(A, pl, g, w, st) : launch_steps_b<double, 2>(A, pl, g, w, st);
+  if (cols == 1) return launch_steps_b<float, 1>(A, pl, g, w, st);
+  return cols == 2 ? launch_steps_b<float, 2>(A, pl, g, w, st) : launch_steps_b<float, 4>(A, pl, g, w, st);
+}
+
+// The rule: the time of a filter application by the figures measured on
+// squares of 32 to 600 and cubes of 13 to 33 cells (within 10 % of every
+// measurement while a wavefront has at most four slices), in us:
+//   a launch        3.7 + 0.03 per slice of the window (0.06 for 16-byte rows)
+//   one of its steps  0.12 + 0.014 per slice computed (0.022), 15 % more with
+//                   more than four slices per wavefront
+// with at most one workgroup per compute unit, against 4.0 per step of a
+// launch of its own, which larger problems exceed.  The plan is taken where it
+// is at least 15 % better; e.g. the 600-cell square in float32 (4 steps, 2.55
+// us each) and the 33-cell cube (3 steps, 3.1 us) are, the 48-cell cube, whose
+// band is 35 slices, is not.
+StepsPlan plan_steps(const SellOp& A, int b, int L, size_t lds_bytes) {
+  StepsPlan best;
+  if ((A.st.stride != 5 && A.st.stride != 7) || A.st.width != A.st.stride || L < 3) return best;
+  constexpr int kCus = 256;
+  const int cols = std::min(b, 16 / A.val_bytes), groups = b / cols, rb = cols * A.val_bytes;
+  const int hb = (A.max_off + 63) / 64, ns = A.nslices;
+  const int win_max = std::min<int64_t>(16 * steps_max_r(rb), ((int64_t)lds_bytes / (2 * rb) - 1) / 64);
+  const double load = rb > 8 ? 0.06 : 0.03, slice = rb > 8 ? 0.022 : 0.014;
+  double t_best = 0.85 * 4.0 * (L - 1);
+  const int own_min = (int)(((int64_t)ns * groups + kCus - 1) / kCus);
+  if (own_min > win_max || groups > kCus) return best;
+  for (int i = 0; i < 4; ++i) {
+    const int own = i == 3 ? ns : std::min(ns, own_min << i);
+    const bool whole = own >= ns;
+    for (int s = 1; s <= std::min(kStepsMax, L - 1); ++s) {
+      const int win = std::min(ns, own + 2 * s * hb);
+      if (win > win_max) break;
+      const double avg = std::min<double>(ns, own + (double)(s - 1) * hb);
+      double step = 0.12 + slice * avg;
+      if (win > 64) step *= 1.15;
+      const int launches = (L - 1 + s - 1) / s;
+      const double t = launches * (3.7 + load * win) + (L - 1) * step;
+      if (t < t_best) {
+        t_best = t;
+        best.s = s;
+        best.own = whole ? ns : own;
+        best.hb = hb;
+      }
+    }
+    if (whole) break;
+  }
+  return best;
+}
+
+}  // namespace kf
