@@ -33,15 +33,19 @@ void set_error(const std::string& msg);
 
 constexpr int kSlice = 64;  // SELL slice height = wavefront width
 
-// The slices of an operator whose rows repeat: in every slice the stored
-// entries with the same offset col - row have the same value (uniform meshes
-// and materials, any ordering).  A slice is then the list of its offsets in
-// ascending order, each with one value and a 64-bit mask of the rows that
-// store it: `width` entries per slice at [slice * stride], the tail with empty
-// masks.  Lossless: value, order of summation and result are the row's own.
+// The slices of an operator as stencils: a slice is the list of its rows'
+// offsets col - row in ascending order, each with a 64-bit mask of the rows
+// that store it and either one value for all of them (where in every slice the
+// entries with the same offset have the same value: uniform meshes and
+// materials) or, with row_values, a value per row (any values on a mesh whose
+// numbering keeps the offsets of 64 consecutive rows alike).  `width` is the
+// longest list; a slice has `stride` entries at [slice * stride], the tail with
+// empty masks, and row values at [(slice * stride + entry) * 64 + row].
+// Lossless: value, order of summation and result are the row's own.
 struct StencilOp {
   int width = 0;   // entries of the longest slice; 0: not built
   int stride = 0;  // entries stored per slice
+  bool row_values = false;
   void* val = nullptr;  // in the operator's precision
   int32_t* off = nullptr;
   uint64_t* mask = nullptr;
@@ -96,10 +100,10 @@ void free_stencil(StencilOp& s);
 // Build a SELL operator from a device CSR: values scaled per row by
 // row_scale[i] (device array, or nullptr for 1), stored as float64
 // (val_bytes 8) or float32 (val_bytes 4).  want_idx_bytes 0 chooses 2 when
-// every |col - row| < 32768.  stencil: also build out.st when every slice is
-// a stencil of at most kStencilMax offsets; its stride is a multiple of 4, or
-// with kStencilExact the width itself for the lengths that have kernels of
-// their own (5 and 7).
+// every |col - row| < 32768.  stencil: also build out.st when every slice has
+// at most kStencilMax offsets; its stride is a multiple of 4, or with
+// kStencilExact the width itself for the lengths that have kernels of their
+// own.
 constexpr int kStencilMax = 32;
 enum StencilForm { kStencilNone = 0, kStencilPadded = 1, kStencilExact = 2 };
 int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
@@ -107,7 +111,8 @@ int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d
                int stencil = kStencilNone);
 
 int build_stencil(int32_t n, int32_t ns, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
-                  const double* d_row_scale, int val_bytes, bool exact, hipStream_t st, StencilOp& out);
+                  const double* d_row_scale, int val_bytes, int64_t nstored, int idx_bytes, bool exact, hipStream_t st,
+                  StencilOp& out);
 
 // ---- fused leapfrog step ----------------------------------------------------
 enum StepMode { kMid = 0, kFirst = 1, kLast = 2, kFirstLast = 3, kMidAcc = 4 };
@@ -166,8 +171,10 @@ int launch_leapfrog_mp(const SellOp& A, const MultiStepPlan& pl, int l0, int s, 
 // travel as a kernel argument.
 constexpr int kStepsMax = 64;  // steps of one launch
 // row slices per wavefront for rows of rb bytes (16: LDS ends before more, and
-// their registers would spill)
-constexpr int steps_max_r(size_t rb) { return rb > 8 ? 5 : 8; }
+// their registers would spill) and row_width row values (0: none)
+constexpr int steps_max_r(size_t rb, int row_width) {
+  return row_width > 8 ? 2 : (row_width > 0 ? 4 : (rb > 8 ? 5 : 8));
+}
 struct StepWeights {
   double w[kStepsMax + 1];
 };

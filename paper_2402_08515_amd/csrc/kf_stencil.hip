@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdlib>
+#include <string>
 #include <vector>
 
 #include "kf_device.h"
@@ -16,11 +18,12 @@ namespace {
 
 // ------------------------------------------------------------ stencil slices
 // One wavefront per slice merges its rows' sorted columns into the ascending
-// list of their offsets col - row.  FILL = false: width[slice] = the number of
-// offsets, or kStencilMax + 1 when there are more or when two rows store
-// different values at one offset.  FILL = true: writes the slice's offsets,
-// values and row masks at [slice * stride].
-template <typename VT, bool FILL>
+// list of their offsets col - row.  FORM 0: width[slice] = the number of
+// offsets (kStencilMax + 1 when there are more), negative when two rows store
+// different values at one offset.  FORM 1 writes the slice's offsets, row masks
+// and one value per offset at [slice * stride], FORM 2 a value per offset and
+// row at [(slice * stride + offset) * 64 + row] (0 where the row has no entry).
+template <typename VT, int FORM>
 __global__ __launch_bounds__(256) void k_stencil(int32_t n, int32_t nslices, const int32_t* __restrict__ rowptr,
                                                  const int32_t* __restrict__ col, const double* __restrict__ val,
                                                  const double* __restrict__ rscale, int32_t* __restrict__ width,
@@ -38,6 +41,7 @@ __global__ __launch_bounds__(256) void k_stencil(int32_t n, int32_t nslices, con
     if (rscale) sc = rscale[row];
   }
   int cnt = 0;
+  bool uniform = true;
   while (cnt <= kStencilMax) {
     const int mine = a < b ? col[a] - row : INT32_MAX;
     int off = mine;
@@ -48,42 +52,46 @@ __global__ __launch_bounds__(256) void k_stencil(int32_t n, int32_t nslices, con
     const VT v = has ? (VT)(sc * val[a]) : (VT)0;
     const unsigned long long m = __ballot(has);
     const VT lead = __shfl(v, __ffsll(m) - 1);
-    if (__ballot(has && !(v == lead)) != 0ull) {
-      cnt = kStencilMax + 1;
-      break;
-    }
-    if (FILL && lane == 0) {
+    if (__ballot(has && !(v == lead)) != 0ull) uniform = false;
+    if (FORM > 0) {
       const int64_t o = (int64_t)slice * stride + cnt;
-      oval[o] = lead;
-      ooff[o] = off;
-      omask[o] = m;
+      if (lane == 0) {
+        if (FORM == 1) oval[o] = lead;
+        ooff[o] = off;
+        omask[o] = m;
+      }
+      if (FORM == 2) oval[o * 64 + lane] = v;
     }
     ++cnt;
     if (has) ++a;
   }
-  if (!FILL) {
-    if (lane == 0) width[slice] = cnt;
+  if (FORM == 0) {
+    if (lane == 0) width[slice] = uniform ? cnt : -cnt;
   } else {
-    for (int q = cnt + lane; q < stride; q += 64) {
-      const int64_t o = (int64_t)slice * stride + q;
-      oval[o] = (VT)0;
-      ooff[o] = 0;
-      omask[o] = 0ull;
+    for (; cnt < stride; ++cnt) {
+      const int64_t o = (int64_t)slice * stride + cnt;
+      if (lane == 0) {
+        if (FORM == 1) oval[o] = (VT)0;
+        ooff[o] = 0;
+        omask[o] = 0ull;
+      }
+      if (FORM == 2) oval[o * 64 + lane] = (VT)0;
     }
   }
 }
 
 // sum_j += (A x)(row, col0 + j) of a stencil slice.  The slice's entries are
 // the same for the whole wavefront, so they come through the scalar cache and
-// the only vector loads are the gathers, which do not wait for an index load.
-// Every load is issued before its sums; rows without an entry gather their own
-// element and multiply it by zero.  W: entries per slice when known (the
-// loop is then unrolled in full), 0: `stride` entries, a multiple of 4.
-template <typename T, int B, int BL, int LPR, int W>
+// the vector loads are the gathers, which do not wait for an index load, and
+// with ROWV the values of the rows.  Every load of a chunk is issued before its
+// sums; rows without an entry gather their own element and multiply it by
+// zero.  W: entries per slice when known (the loop is then unrolled in full),
+// 0: `stride` entries, a multiple of 4.
+template <typename T, int B, int BL, int LPR, int W, bool ROWV>
 __device__ __forceinline__ void stencil_product(const T* __restrict__ val, const int32_t* __restrict__ off,
                                                 const uint64_t* __restrict__ mask, int stride, int slice, int rin,
                                                 int row, const T* __restrict__ x, int col0, T (&sum)[BL]) {
-  constexpr int U = W > 0 && BL * sizeof(T) <= 16 ? W : 4;
+  constexpr int U = W > 0 && BL * sizeof(T) <= 16 ? W : (W == 15 ? 5 : 4);
   const int64_t base = (int64_t)slice * (W > 0 ? W : stride);
   auto chunk = [&](int q0) {
     T a[U];
@@ -92,7 +100,7 @@ __device__ __forceinline__ void stencil_product(const T* __restrict__ val, const
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (W > 0 && q0 + u >= W) continue;
-      a[u] = val[base + q0 + u];
+      a[u] = ROWV ? val[(base + q0 + u) * 64 + rin] : val[base + q0 + u];
       o[u] = off[base + q0 + u];
       m[u] = mask[base + q0 + u];
     }
@@ -114,7 +122,7 @@ __device__ __forceinline__ void stencil_product(const T* __restrict__ val, const
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (W > 0 && q0 + u >= W) continue;
-      const T au = has[u] ? a[u] : (T)0;
+      const T au = ROWV || has[u] ? a[u] : (T)0;
 #pragma unroll
       for (int j = 0; j < BL; ++j) sum[j] = fma(au, xv[u].v[j], sum[j]);
     }
@@ -127,13 +135,17 @@ __device__ __forceinline__ void stencil_product(const T* __restrict__ val, const
   }
 }
 
-// The fused step (k_leapfrog below) over stencil slices: no operator stream,
-// a row's traffic is its vector levels alone (25 instead of 86 MB per middle
+// The fused step (k_leapfrog) over stencil slices.  With one value per offset
+// there is no operator stream, a row's traffic is its vector levels alone (25 instead of 86 MB per middle
 // step of the 96-cell cube in float64, whose levels then stay in the caches).
 // A filter application of 38 steps there: 541 us with the stored entries,
 // 266 us so (7.0 us a step, launch included); the 128-cell cube in float32,
-// 51 steps: 982 and 351 us.  Bound by launch latency and the caches.
-template <typename T, int B, int MODE, int LPR, int W>
+// 51 steps: 982 and 351 us.  Bound by launch latency and by the trip of the
+// levels through the Infinity Cache.  With a value per row (ROWV) the step
+// saves the index stream and the wait for it: 16 vectors in float32 on the
+// horn of 144,789 rows, 452 steps, 5.49 and 3.98 ms (15 entries in flight;
+// five at a time 4.07).
+template <typename T, int B, int MODE, int LPR, int W, bool ROWV>
 __global__ __launch_bounds__(256) void k_leapfrog_st(int32_t n, int32_t nslices, const T* __restrict__ val,
                                                      const int32_t* __restrict__ soff,
                                                      const uint64_t* __restrict__ mask, int stride,
@@ -159,7 +171,7 @@ __global__ __launch_bounds__(256) void k_leapfrog_st(int32_t n, int32_t nslices,
   T sum[BL];
 #pragma unroll
   for (int j = 0; j < BL; ++j) sum[j] = (T)0;
-  stencil_product<T, B, BL, LPR, W>(val, soff, mask, stride, slice, rin, row, cur, col0, sum);
+  stencil_product<T, B, BL, LPR, W, ROWV>(val, soff, mask, stride, slice, rin, row, cur, col0, sum);
   if (MODE & kFirst) yp = yc;
   Row<T, BL> nx;
 #pragma unroll
@@ -184,7 +196,7 @@ __global__ __launch_bounds__(256) void k_leapfrog_st(int32_t n, int32_t nslices,
 
 // The two launches of a fourth-order step over stencil slices: MODE < 0 forms
 // z = A cur, else the update (see stencil_product).
-template <typename T, int B, int MODE, int LPR, int W>
+template <typename T, int B, int MODE, int LPR, int W, bool ROWV>
 __global__ __launch_bounds__(256) void k_leapfrog4_st(int32_t n, int32_t nslices, const T* __restrict__ val,
                                                       const int32_t* __restrict__ soff,
                                                       const uint64_t* __restrict__ mask, int stride,
@@ -215,7 +227,7 @@ __global__ __launch_bounds__(256) void k_leapfrog4_st(int32_t n, int32_t nslices
   T sum[BL];
 #pragma unroll
   for (int j = 0; j < BL; ++j) sum[j] = (T)0;
-  stencil_product<T, B, BL, LPR, W>(val, soff, mask, stride, slice, rin, row, MODE < 0 ? cur : z, col0, sum);
+  stencil_product<T, B, BL, LPR, W, ROWV>(val, soff, mask, stride, slice, rin, row, MODE < 0 ? cur : z, col0, sum);
   if (MODE < 0) {
     V o;
 #pragma unroll
@@ -248,7 +260,7 @@ __global__ __launch_bounds__(256) void k_leapfrog4_st(int32_t n, int32_t nslices
 
 // The batched step over stencil slices (see stencil_product).  The tables of
 // the slice's problem are scalar loads, as the slice's entries are.
-template <typename T, int B>
+template <typename T, int B, bool ROWV>
 __global__ __launch_bounds__(256) void k_leapfrog_batch_st(int32_t nslices, const T* __restrict__ val,
                                                            const int32_t* __restrict__ soff,
                                                            const uint64_t* __restrict__ mask, int stride,
@@ -279,7 +291,7 @@ __global__ __launch_bounds__(256) void k_leapfrog_batch_st(int32_t nslices, cons
   T sum[B];
 #pragma unroll
   for (int j = 0; j < B; ++j) sum[j] = (T)0;
-  stencil_product<T, B, B, 1, 0>(val, soff, mask, stride, slice, lane, row, cur, 0, sum);
+  stencil_product<T, B, B, 1, 0, ROWV>(val, soff, mask, stride, slice, lane, row, cur, 0, sum);
   V nx;
 #pragma unroll
   for (int j = 0; j < B; ++j) nx.v[j] = (T)2 * yc.v[j] - yp.v[j] - sum[j];
@@ -306,11 +318,11 @@ __global__ __launch_bounds__(256) void k_leapfrog_batch_st(int32_t nslices, cons
   }
 }
 
-template <typename T, int B, int LPR, int W>
+template <typename T, int B, int LPR, int W, bool ROWV>
 int launch_st_w(const SellOp& A, int mode, const void* cur, const void* prev, void* out, void* acc, double* rout,
                 int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap, hipStream_t st) {
 #define KF_ST(M)                                                                                                     \
-  hipLaunchKernelGGL((k_leapfrog_st<T, B, M, LPR, W>), dim3(ceil_div64((int64_t)A.nslices * LPR, 4)), dim3(256), 0,    \
+  hipLaunchKernelGGL((k_leapfrog_st<T, B, M, LPR, W, ROWV>), dim3(ceil_div64((int64_t)A.nslices * LPR, 4)), dim3(256), 0,    \
                      st, A.n, A.nslices, static_cast<const T*>(A.st.val), A.st.off, A.st.mask, A.st.stride,             \
                      static_cast<const T*>(cur), static_cast<const T*>(prev), static_cast<T*>(out),                     \
                      static_cast<T*>(acc), rout, rs, cs, bout, (T)wp, (T)wc, (T)wn, remap)
@@ -329,11 +341,16 @@ int launch_st_w(const SellOp& A, int mode, const void* cur, const void* prev, vo
 template <typename T, int B, int LPR>
 int launch_st_l(const SellOp& A, int mode, const void* cur, const void* prev, void* out, void* acc, double* rout,
                 int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap, hipStream_t st) {
+  if (A.st.row_values) {
+    if (A.st.stride == 15)
+      return launch_st_w<T, B, LPR, 15, true>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    return launch_st_w<T, B, LPR, 0, true>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+  }
   if (A.st.stride == 5)
-    return launch_st_w<T, B, LPR, 5>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    return launch_st_w<T, B, LPR, 5, false>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
   if (A.st.stride == 7)
-    return launch_st_w<T, B, LPR, 7>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
-  return launch_st_w<T, B, LPR, 0>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    return launch_st_w<T, B, LPR, 7, false>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
+  return launch_st_w<T, B, LPR, 0, false>(A, mode, cur, prev, out, acc, rout, rs, cs, bout, wp, wc, wn, remap, st);
 }
 
 template <typename T, int B>
@@ -361,12 +378,12 @@ int launch_st(const SellOp& A, int b, int mode, const void* cur, const void* pre
   }
 }
 
-template <typename T, int B, int LPR, int W>
+template <typename T, int B, int LPR, int W, bool ROWV>
 int launch_st4_w(const SellOp& A, int mode, const void* cur, const void* prev, void* out, void* acc, void* z,
                  double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap,
                  hipStream_t st) {
 #define KF_ST4(M)                                                                                                   \
-  hipLaunchKernelGGL((k_leapfrog4_st<T, B, M, LPR, W>), dim3(ceil_div64((int64_t)A.nslices * LPR, 4)), dim3(256), 0,  \
+  hipLaunchKernelGGL((k_leapfrog4_st<T, B, M, LPR, W, ROWV>), dim3(ceil_div64((int64_t)A.nslices * LPR, 4)), dim3(256), 0,  \
                      st, A.n, A.nslices, static_cast<const T*>(A.st.val), A.st.off, A.st.mask, A.st.stride,            \
                      static_cast<const T*>(cur), static_cast<const T*>(prev), static_cast<T*>(out),                    \
                      static_cast<T*>(acc), static_cast<T*>(z), rout, rs, cs, bout, (T)wp, (T)wc, (T)wn, remap)
@@ -389,11 +406,17 @@ int launch_st4_b(const SellOp& A, int mode, const void* cur, const void* prev, v
                  double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn, int remap,
                  hipStream_t st) {
   constexpr int LPR = B * sizeof(T) >= 64 ? 4 : (B * sizeof(T) >= 32 ? 2 : 1);
+  if (A.st.row_values) {
+    if (A.st.stride == 15)
+      return launch_st4_w<T, B, LPR, 15, true>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap,
+                                               st);
+    return launch_st4_w<T, B, LPR, 0, true>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+  }
   if (A.st.stride == 5)
-    return launch_st4_w<T, B, LPR, 5>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    return launch_st4_w<T, B, LPR, 5, false>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
   if (A.st.stride == 7)
-    return launch_st4_w<T, B, LPR, 7>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
-  return launch_st4_w<T, B, LPR, 0>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+    return launch_st4_w<T, B, LPR, 7, false>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
+  return launch_st4_w<T, B, LPR, 0, false>(A, mode, cur, prev, out, acc, z, rout, rs, cs, bout, wp, wc, wn, remap, st);
 }
 
 template <typename T>
@@ -414,18 +437,20 @@ int launch_st4(const SellOp& A, int b, int mode, const void* cur, const void* pr
 
 namespace {
 // The stencil form of an operator's slices, when it has one (else out.width
-// stays 0).
+// stays 0): one value per offset where every slice is uniform, a value per row
+// where that does not take more memory than the stored entries (nstored of
+// them with ib bytes of index) would.
 template <typename VT>
 int build_stencil_t(int32_t n, int32_t ns, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
-                  const double* d_row_scale, bool exact, hipStream_t st, StencilOp& out) {
+                    const double* d_row_scale, int64_t nstored, int ib, bool exact, hipStream_t st, StencilOp& out) {
   const int grid = ceil_div64(ns, 4);
   int32_t* d_w = nullptr;
   if (hipMalloc(&d_w, sizeof(int32_t) * (size_t)ns) != hipSuccess) {
     set_error("build_sell: device allocation failed");
     return KF_ENOMEM;
   }
-  hipLaunchKernelGGL((k_stencil<VT, false>), dim3(grid), dim3(256), 0, st, n, ns, d_rowptr, d_col, d_val, d_row_scale,
-                     d_w, 0, (VT*)nullptr, (int32_t*)nullptr, (uint64_t*)nullptr);
+  hipLaunchKernelGGL((k_stencil<VT, 0>), dim3(grid), dim3(256), 0, st, n, ns, d_rowptr, d_col, d_val, d_row_scale, d_w,
+                     0, (VT*)nullptr, (int32_t*)nullptr, (uint64_t*)nullptr);
   std::vector<int32_t> w((size_t)ns);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpyAsync(w.data(), d_w, sizeof(int32_t) * (size_t)ns, hipMemcpyDeviceToHost, st);
@@ -435,41 +460,55 @@ int build_stencil_t(int32_t n, int32_t ns, const int32_t* d_rowptr, const int32_
     set_error(std::string("build_sell: ") + hipGetErrorString(e));
     return KF_EHIP;
   }
-  const int width = *std::max_element(w.begin(), w.end());
+  int width = 0;
+  bool row_values = false;
+  for (int32_t v : w) {
+    width = std::max(width, std::abs(v));
+    row_values |= v < 0;
+  }
   if (width < 1 || width > kStencilMax) return KF_OK;
-  // 5 and 7 entries (the 2D and 3D point stencils) have kernels of their own
-  // length; other lengths are padded to the loop's four entries
-  const int stride = exact && (width == 5 || width == 7) ? width : (width + 3) / 4 * 4;
+  // 5 and 7 entries (the 2D and 3D point stencils) and, with row values, 15
+  // (linear tetrahedra around a vertex of a structured mesh) have kernels of
+  // their own length; other lengths are padded to the loop's four entries
+  const bool own = exact && (row_values ? width == 15 : width == 5 || width == 7);
+  const int stride = own ? width : (width + 3) / 4 * 4;
   const size_t tot = (size_t)ns * stride;
-  StencilOp s;
-  if (hipMalloc(&s.val, tot * sizeof(VT)) != hipSuccess || hipMalloc(&s.off, tot * sizeof(int32_t)) != hipSuccess ||
-      hipMalloc(&s.mask, tot * sizeof(uint64_t)) != hipSuccess) {
-    if (s.val) (void)hipFree(s.val);
-    if (s.off) (void)hipFree(s.off);
+  const size_t vals = row_values ? tot * 64 : tot;
+  if (row_values && vals * sizeof(VT) + tot * 12 > (size_t)nstored * (sizeof(VT) + ib)) return KF_OK;
+  // one allocation: masks, values, offsets
+  char* mem = nullptr;
+  if (hipMalloc(&mem, tot * sizeof(uint64_t) + vals * sizeof(VT) + tot * sizeof(int32_t)) != hipSuccess) {
     set_error("build_sell: device allocation failed");
     return KF_ENOMEM;
   }
-  s.width = width;
-  s.stride = stride;
-  out = s;
-  hipLaunchKernelGGL((k_stencil<VT, true>), dim3(grid), dim3(256), 0, st, n, ns, d_rowptr, d_col, d_val, d_row_scale,
-                     (int32_t*)nullptr, stride, (VT*)s.val, s.off, s.mask);
+  out.mask = reinterpret_cast<uint64_t*>(mem);
+  out.val = mem + tot * sizeof(uint64_t);
+  out.off = reinterpret_cast<int32_t*>(mem + tot * sizeof(uint64_t) + vals * sizeof(VT));
+  out.width = width;
+  out.stride = stride;
+  out.row_values = row_values;
+  if (row_values)
+    hipLaunchKernelGGL((k_stencil<VT, 2>), dim3(grid), dim3(256), 0, st, n, ns, d_rowptr, d_col, d_val, d_row_scale,
+                       (int32_t*)nullptr, stride, (VT*)out.val, out.off, out.mask);
+  else
+    hipLaunchKernelGGL((k_stencil<VT, 1>), dim3(grid), dim3(256), 0, st, n, ns, d_rowptr, d_col, d_val, d_row_scale,
+                       (int32_t*)nullptr, stride, (VT*)out.val, out.off, out.mask);
   KF_HIP(hipGetLastError());
   return KF_OK;
 }
 }  // namespace
 
 void free_stencil(StencilOp& s) {
-  if (s.val) (void)hipFree(s.val);
-  if (s.off) (void)hipFree(s.off);
-  if (s.mask) (void)hipFree(s.mask);
+  if (s.mask) (void)hipFree(s.mask);  // (the three arrays are one allocation)
   s = StencilOp();
 }
 
 int build_stencil(int32_t n, int32_t ns, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
-                  const double* d_row_scale, int val_bytes, bool exact, hipStream_t st, StencilOp& out) {
-  if (val_bytes == 8) return build_stencil_t<double>(n, ns, d_rowptr, d_col, d_val, d_row_scale, exact, st, out);
-  return build_stencil_t<float>(n, ns, d_rowptr, d_col, d_val, d_row_scale, exact, st, out);
+                  const double* d_row_scale, int val_bytes, int64_t nstored, int idx_bytes, bool exact, hipStream_t st,
+                  StencilOp& out) {
+  if (val_bytes == 8)
+    return build_stencil_t<double>(n, ns, d_rowptr, d_col, d_val, d_row_scale, nstored, idx_bytes, exact, st, out);
+  return build_stencil_t<float>(n, ns, d_rowptr, d_col, d_val, d_row_scale, nstored, idx_bytes, exact, st, out);
 }
 
 int launch_stencil_step(const SellOp& A, int b, int mode, const void* cur, const void* prev, void* out, void* acc,
@@ -493,7 +532,7 @@ template <typename T>
 int launch_lfb_st(const SellOp& A, int b, const int32_t* sp, const BatchTables* tb, const void* wtab, int lmax, int ell,
                   const void* cur, const void* prev, void* out, void* acc, int nslices, int remap, hipStream_t st) {
 #define KF_LFS(B)                                                                                                  \
-  hipLaunchKernelGGL((k_leapfrog_batch_st<T, B>), dim3(ceil_div64(nslices, 4)), dim3(256), 0, st, nslices,          \
+  hipLaunchKernelGGL((A.st.row_values ? k_leapfrog_batch_st<T, B, true> : k_leapfrog_batch_st<T, B, false>), dim3(ceil_div64(nslices, 4)), dim3(256), 0, st, nslices,          \
                      static_cast<const T*>(A.st.val), A.st.off, A.st.mask, A.st.stride, sp, tb,                     \
                      static_cast<const T*>(wtab), lmax, ell, static_cast<const T*>(cur), static_cast<const T*>(prev), \
                      static_cast<T*>(out), static_cast<T*>(acc), remap)

@@ -875,7 +875,8 @@ int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d
                        d_col, d_val, d_row_scale, (float*)out.val, (int32_t*)out.idx);
   KF_HIP(hipGetLastError());
   if (stencil)
-    KF_TRY(build_stencil(n, ns, d_rowptr, d_col, d_val, d_row_scale, val_bytes, stencil == kStencilExact, st, out.st));
+    KF_TRY(build_stencil(n, ns, d_rowptr, d_col, d_val, d_row_scale, val_bytes, out.nstored, ib,
+                         stencil == kStencilExact, st, out.st));
   KF_HIP(hipStreamSynchronize(st));
   (void)nnz;
   return KF_OK;

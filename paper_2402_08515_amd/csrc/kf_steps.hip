@@ -21,7 +21,8 @@ namespace {
 // wavefront keeps the levels y_{l-1}, y_l and the weighted sum of its slices
 // (wave, wave + 16, ...: at most R) in registers, with the places of their
 // stencil neighbours in LDS; absent neighbours point at a zero.  A step then
-// is W LDS reads, W products and one LDS write per row and one barrier.  The
+// is W LDS reads, W products and one LDS write per row and one barrier.  Row
+// values (ROWV) stay in registers through all steps, which limits R.  The
 // halo slices are computed by every workgroup that needs them; with the whole
 // problem in one workgroup there are none.  The weighted sum takes one term
 // per step, in the same order as three terms every third step: results are
@@ -38,7 +39,7 @@ namespace {
 //          o1g and the sum to acc.  o0g, o1g are not i0, i1 unless there is
 //          one workgroup.
 // w.w[j] is the weight of y_{l0+j}.
-template <typename T, int B, int W, int R>
+template <typename T, int B, int W, int R, bool ROWV>
 __global__ __launch_bounds__(1024) void k_steps_st(int32_t n, int32_t nslices, const T* __restrict__ sval,
                                                    const int32_t* __restrict__ soff, const uint64_t* __restrict__ smask,
                                                    const T* ysrc, const T* i0, const T* i1, T* o0g, T* o1g, T* acc, double* __restrict__ rout, int64_t rs, int64_t cs,
@@ -102,16 +103,29 @@ __global__ __launch_bounds__(1024) void k_steps_st(int32_t n, int32_t nslices, c
     for (int k = 0; k < R; ++k) {
       const int sl = w0 + wave + 16 * k;
       if (sl >= w1 || sl < a0 || sl >= a1) continue;
-      V x[W];
-#pragma unroll
-      for (int q = 0; q < W; ++q) x[q] = src[q & 1 ? at[k][q >> 1] >> 16 : at[k][q >> 1] & 0xFFFFu];
       V nx;
+      T sum[B];
+#pragma unroll
+      for (int c = 0; c < B; ++c) sum[c] = (T)0;
+      constexpr int U = ROWV ? (W == 15 ? 5 : 4) : W;
+#pragma unroll
+      for (int q0 = 0; q0 < W; q0 += U) {
+        V x[U];
+        T av[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int q = q0 + u;
+          av[u] = ROWV ? sval[((int64_t)sl * W + q) * 64 + lane] : sval[(int64_t)sl * W + q];
+          x[u] = src[q & 1 ? at[k][q >> 1] >> 16 : at[k][q >> 1] & 0xFFFFu];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int c = 0; c < B; ++c) sum[c] = fma(av[u], x[u].v[c], sum[c]);
+      }
 #pragma unroll
       for (int c = 0; c < B; ++c) {
-        T sum = (T)0;
-#pragma unroll
-        for (int q = 0; q < W; ++q) sum = fma(sval[(int64_t)sl * W + q], x[q].v[c], sum);
-        nx.v[c] = (T)2 * yc[k].v[c] - yp[k].v[c] - sum;
+        nx.v[c] = (T)2 * yc[k].v[c] - yp[k].v[c] - sum[c];
         ra[k].v[c] = fma(wn, nx.v[c], ra[k].v[c]);
       }
       yp[k] = yc[k];
@@ -153,13 +167,13 @@ struct StepsArgs {
   bool first, last;
 };
 
-template <typename T, int B, int W, int R>
+template <typename T, int B, int W, int R, bool ROWV>
 int launch_steps_r(const SellOp& A, const StepsPlan& pl, const StepsArgs& g, const StepWeights& w, hipStream_t st) {
   const int win = std::min(A.nslices, pl.own + 2 * g.s * pl.hb);
   const size_t lds = (size_t)2 * (win * 64 + 1) * B * sizeof(T);
-  KF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_steps_st<T, B, W, R>),
+  KF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_steps_st<T, B, W, R, ROWV>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL((k_steps_st<T, B, W, R>), dim3(ceil_div64(A.nslices, pl.own), g.groups), dim3(1024), lds, st, A.n,
+  hipLaunchKernelGGL((k_steps_st<T, B, W, R, ROWV>), dim3(ceil_div64(A.nslices, pl.own), g.groups), dim3(1024), lds, st, A.n,
                      A.nslices, static_cast<const T*>(A.st.val), A.st.off, A.st.mask, static_cast<const T*>(g.ysrc),
                      static_cast<const T*>(g.i0), static_cast<const T*>(g.i1), static_cast<T*>(g.o0),
                      static_cast<T*>(g.o1), static_cast<T*>(g.acc), g.rout, g.rs, g.cs, g.bout, g.groups, w, g.s, pl.own,
@@ -168,25 +182,40 @@ int launch_steps_r(const SellOp& A, const StepsPlan& pl, const StepsArgs& g, con
   return KF_OK;
 }
 
-template <typename T, int B, int W>
+template <typename T, int B, int W, bool ROWV>
 int launch_steps_w(const SellOp& A, const StepsPlan& pl, const StepsArgs& g, const StepWeights& w, hipStream_t st) {
   const int per = (std::min(A.nslices, pl.own + 2 * g.s * pl.hb) + 15) / 16;  // slices of a wavefront
-  if (per <= 2) return launch_steps_r<T, B, W, 2>(A, pl, g, w, st);
-  if (per <= 4) return launch_steps_r<T, B, W, 4>(A, pl, g, w, st);
-  return launch_steps_r<T, B, W, steps_max_r(B * sizeof(T))>(A, pl, g, w, st);
+  if (per <= 2) return launch_steps_r<T, B, W, 2, ROWV>(A, pl, g, w, st);
+  constexpr int RM = steps_max_r(B * sizeof(T), ROWV ? W : 0);
+  if constexpr (RM > 2) {
+    if (RM == 4 || per <= 4) return launch_steps_r<T, B, W, 4, ROWV>(A, pl, g, w, st);
+    return launch_steps_r<T, B, W, RM, ROWV>(A, pl, g, w, st);
+  }
+  set_error("several steps per launch: window too wide");
+  return KF_EINVAL;
 }
 
 template <typename T, int B>
 int launch_steps_b(const SellOp& A, const StepsPlan& pl, const StepsArgs& g, const StepWeights& w, hipStream_t st) {
-  if (A.st.stride == 5) return launch_steps_w<T, B, 5>(A, pl, g, w, st);
-  return launch_steps_w<T, B, 7>(A, pl, g, w, st);
+  if (A.st.row_values)
+    return A.st.stride == 15 ? launch_steps_w<T, B, 15, true>(A, pl, g, w, st)
+                             : launch_steps_w<T, B, 8, true>(A, pl, g, w, st);
+  return A.st.stride == 5 ? launch_steps_w<T, B, 5, false>(A, pl, g, w, st)
+                          : launch_steps_w<T, B, 7, false>(A, pl, g, w, st);
+}
+}  // namespace
+
+namespace {
+// the lengths of stencils that k_steps_st is built for
+bool has_steps(const StencilOp& st) {
+  return st.row_values ? st.stride == 8 || st.stride == 15 : (st.stride == 5 || st.stride == 7) && st.width == st.stride;
 }
 }  // namespace
 
 int launch_steps(const SellOp& A, const StepsPlan& pl, int b, int s, bool first, bool last, const void* ysrc,
                  const void* i0, const void* i1, void* o0, void* o1, void* acc, double* rout, int64_t rs, int64_t cs,
                  int bout, const StepWeights& w, hipStream_t st) {
-  if (pl.s < 1 || s < 1 || s > pl.s || (A.st.stride != 5 && A.st.stride != 7)) {
+  if (pl.s < 1 || s < 1 || s > pl.s || !has_steps(A.st)) {
     set_error("several steps per launch: no plan for this operator");
     return KF_EINVAL;
   }
@@ -207,15 +236,23 @@ int launch_steps(const SellOp& A, const StepsPlan& pl, int b, int s, bool first,
 // launch of its own, which larger problems exceed.  The plan is taken where it
 // is at least 15 % better; e.g. the 600-cell square in float32 (4 steps, 2.55
 // us each) and the 33-cell cube (3 steps, 3.1 us) are, the 48-cell cube, whose
-// band is 35 slices, is not.
+// band is 35 slices, is not.  With row values (horns of 5 to 16 cells, jittered
+// squares and cubes, within 20 %) a launch takes 3.7 + 0.06 per slice of the
+// window, whose values it reads, and a step per slice and entry 0.0073 in
+// float64, 0.005 in float32, 0.008 with several groups of columns, which leave
+// fewer compute units to each: 5 x 109-cell horn, one vector in float64, 4.0 ->
+// 1.4 us a step; 16 x 200 cells 4.2 -> 3.3, its block of 16 in float32 not.
 StepsPlan plan_steps(const SellOp& A, int b, int L, size_t lds_bytes) {
   StepsPlan best;
-  if ((A.st.stride != 5 && A.st.stride != 7) || A.st.width != A.st.stride || L < 3) return best;
+  if (!has_steps(A.st) || L < 3) return best;
   constexpr int kCus = 256;
   const int cols = std::min(b, 16 / A.val_bytes), groups = b / cols, rb = cols * A.val_bytes;
   const int hb = (A.max_off + 63) / 64, ns = A.nslices;
-  const int win_max = std::min<int64_t>(16 * steps_max_r(rb), ((int64_t)lds_bytes / (2 * rb) - 1) / 64);
-  const double load = rb > 8 ? 0.06 : 0.03, slice = rb > 8 ? 0.022 : 0.014;
+  const int win_max = std::min<int64_t>(16 * steps_max_r(rb, A.st.row_values ? A.st.stride : 0), ((int64_t)lds_bytes / (2 * rb) - 1) / 64);
+  const bool rv = A.st.row_values;
+  const double load = rv || rb > 8 ? 0.06 : 0.03;
+  const double slice = rv ? A.st.stride * (groups > 1 ? 0.008 : (A.val_bytes == 8 ? 0.0073 : 0.005))
+                          : (rb > 8 ? 0.022 : 0.014);
   double t_best = 0.85 * 4.0 * (L - 1);
   const int own_min = (int)(((int64_t)ns * groups + kCus - 1) / kCus);
   if (own_min > win_max || groups > kCus) return best;
@@ -226,7 +263,7 @@ StepsPlan plan_steps(const SellOp& A, int b, int L, size_t lds_bytes) {
       const int win = std::min(ns, own + 2 * s * hb);
       if (win > win_max) break;
       const double avg = std::min<double>(ns, own + (double)(s - 1) * hb);
-      double step = 0.12 + slice * avg;
+      double step = (rv ? 0.0 : 0.12) + slice * avg;
       if (win > 64) step *= 1.15;
       const int launches = (L - 1 + s - 1) / s;
       const double t = launches * (3.7 + load * win) + (L - 1) * step;

@@ -1,5 +1,5 @@
-"""Operators whose slices are stencils (every stored offset of a 64-row slice
-has one value) against the same operator in its stored-entry form
+"""Operators whose slices are stencils (lists of offsets with one value each,
+or with a value per row) against the same operator in its stored-entry form
 (index_bytes fixed), bit for bit: the stencil form keeps the values and the
 order of summation of every row, so no tolerance is needed."""
 
@@ -8,7 +8,8 @@ import pytest
 import scipy.sparse as sp
 
 from synth import start_block
-from synth.grids import grid_problem
+from synth.grids import grid_problem, jittered_problem
+from synth.horn import horn_pencil
 
 pytestmark = pytest.mark.gpu
 
@@ -25,7 +26,11 @@ def _matrix(kind):
     if kind.startswith("grid"):
         S, m, _ = grid_problem(int(kind[4]), int(kind[6:]))
         return S, m
-    if kind == "broken":  # one row of one slice has a value of its own: no stencil
+    if kind.startswith("jitter"):  # linear triangles / tetrahedra: 7 / 15 offsets, a value per row
+        return jittered_problem(int(kind[6]), int(kind[8:]), 0.2, 3)
+    if kind == "horn":
+        return horn_pencil(5, 9, 0.05, 2)
+    if kind == "broken":  # one row of one slice has a value of its own
         S = _band(200, [1, 9])
         S[70, 70] = 5.0
         return S, np.full(200, 0.5)
@@ -43,7 +48,8 @@ def _matrix(kind):
     # rows x neighbours on one side: slice widths 1, 3, 5, 7 (the unrolled
     # lengths), 9, 31 and 33 (one past the longest stencil); less than a
     # slice, one slice, one row more, several
-    ["1x1", "63x1", "64x2", "65x3", "130x4", "200x15", "200x16", "grid2_23", "grid3_9", "broken", "mass"],
+    ["1x1", "63x1", "64x2", "65x3", "130x4", "200x15", "200x16", "grid2_23", "grid3_9", "broken", "mass",
+     "jitter2_7", "jitter2_20", "jitter3_3", "jitter3_9", "horn"],
 )
 def test_stencil_slices_match_stored_entries_bitwise(kind, b, precision):
     import torch
@@ -129,7 +135,7 @@ def test_several_steps_per_launch_bitwise(dim, n, b, precision):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
-@pytest.mark.parametrize("kind", ["63x1", "65x3", "200x15", "grid2_23", "grid3_9", "broken"])
+@pytest.mark.parametrize("kind", ["63x1", "65x3", "200x15", "grid2_23", "grid3_9", "broken", "jitter2_20", "jitter3_9"])
 def test_fourth_order_step_over_stencils_bitwise(kind, precision):
     import torch
 
@@ -143,3 +149,33 @@ def test_fourth_order_step_over_stencils_bitwise(kind, precision):
             out = [kf.Problem(S, m, 0.3 / tau, 0.6 / tau, tau, L, precision=precision, index_bytes=ib, stepper=4)
                    .apply_filter(x) for ib in (0, 4)]
             assert torch.equal(out[0], out[1]), (b, L)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("b", [1, 2, 3, 16])
+@pytest.mark.parametrize(
+    "kind",
+    # 7 and 15 offsets with row values: less than a slice, one workgroup, few
+    # and many halo slices, and (the last two) too wide a band for it
+    ["jitter2_6", "jitter2_30", "jitter2_120", "jitter3_3", "jitter3_8", "jitter3_14", "horn5x40", "horn8x60", "horn16x30",
+     "jitter3_24"],
+)
+def test_several_steps_per_launch_with_row_values_bitwise(kind, b, precision):
+    import torch
+
+    from paper_2402_08515_amd import kf
+
+    print(f"case row-value steps kind={kind} b={b} {precision}", flush=True)
+    S, m = horn_pencil(*(int(v) for v in kind[4:].split("x")), 0.05, 2) if kind.startswith("horn") else _matrix(kind)
+    tau = 1.8 / np.sqrt((np.abs(S).sum(1).A1 / m).max())
+    x = torch.from_numpy(start_block(S.shape[0], b, 13)).cuda()
+    for L in (3, 24, 130):
+        out = []
+        for ib in (0, 4):
+            P = kf.Problem(S, m, 0.3 / tau, 0.5 / tau, tau, L, precision=precision, index_bytes=ib)
+            out.append(P.apply_filter(x))
+            if ib == 0:
+                y = torch.empty_like(x)
+                P.apply_filter_noalloc(x, y)
+                assert torch.equal(y, out[0]), L
+        assert torch.equal(out[0], out[1]), (L, (out[0] - out[1]).abs().max())
