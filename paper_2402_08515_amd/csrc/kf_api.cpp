@@ -149,6 +149,7 @@ struct BatchStack {
   StepBufs sb;
   BatchTables h_tb{};    // per-member tables of the next launch (active members of this stack)
   BatchTables* d_tb = nullptr;
+  BatchWg* d_wg = nullptr;  // several steps per launch: the workgroups' plans
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   int graph_bk = 0;
@@ -167,9 +168,19 @@ struct kf_batch {
   int lmax = 1;
   int64_t rows = 0;
   hipEvent_t ev[2] = {nullptr, nullptr};
-  // members are stacked by decreasing L: at step ell the members still
-  // stepping own the first prefix[ell] row slices
-  std::vector<int> prefix;
+  // Stacked first are the members that always step one step per launch, then
+  // (from slice m0 on) those that may take several, by decreasing L within
+  // either group: at step ell the members still stepping own the first
+  // left[ell].na row slices and the left[ell].nm from m0 on.
+  std::vector<BatchRange> left;
+  struct Many {
+    int q;          // member
+    int64_t slice0;
+    BatchMember m;
+  };
+  std::vector<Many> many;  // the second group
+  hipStream_t st_many = nullptr;  // and its stream and events (beside the first group's)
+  hipEvent_t fork[2] = {nullptr, nullptr};
   int autotune = 0;
   // members passed the same operator arrays (slices of one problem's
   // spectrum) share a group: they share the operator's eigenvalue
@@ -3246,6 +3257,8 @@ void free_stack(BatchStack& k) {
   k.d_tb = nullptr;
   dfree(k.wtab);
   k.wtab = nullptr;
+  dfree(k.d_wg);
+  k.d_wg = nullptr;
   free_step_buffers(k.sb);
 }
 
@@ -3257,12 +3270,69 @@ void free_batch(kf_batch* bt) {
   dfree(bt->d_sp);
   for (hipEvent_t e : bt->ev)
     if (e) (void)hipEventDestroy(e);
+  for (hipEvent_t e : bt->fork)
+    if (e) (void)hipEventDestroy(e);
+  if (bt->st_many) (void)hipStreamDestroy(bt->st_many);
   if (bt->st) (void)hipStreamDestroy(bt->st);
   delete bt;
 }
 
-// Record the batched filter application of a stack (load + lmax-1 fused
-// steps) for block width bk once; replays read the per-problem tables from
+// The longest slice (entries) of each member of bt->many in a stack's stencil.
+int member_widths(kf_batch* bt, const SellOp& A, std::vector<int>& width) {
+  std::vector<uint64_t> mask;
+  for (const kf_batch::Many& q : bt->many) {
+    const size_t stride = (size_t)A.st.stride;
+    mask.resize((size_t)q.m.nslices * stride);
+    KF_HIP(hipMemcpy(mask.data(), A.st.mask + (size_t)q.slice0 * stride, mask.size() * sizeof(uint64_t), hipMemcpyDeviceToHost));
+    int w = 0;
+    for (size_t i = 0; i < mask.size(); ++i)
+      if (mask[i]) w = std::max(w, (int)(i % stride) + 1);
+    width.push_back(w);
+  }
+  return KF_OK;
+}
+
+// The plans of the members that take several steps per launch in a stack at
+// block width bk, its workgroups (k.d_wg) and buffers for the rows from m0 on;
+// wgs stays empty where one of the members is better off, or can only be
+// stepped, one step per launch, and where there is no memory for the buffers.
+int plan_many(kf_batch* bt, BatchStack& k, int bk, std::vector<BatchWg>& wgs, int& win, int& launches) {
+  if (bt->many.empty() || k.A.st.width == 0 || k.A.st.row_values) return KF_OK;
+  std::vector<BatchMember> m;
+  for (const kf_batch::Many& q : bt->many) m.push_back(q.m);
+  const std::vector<StepsPlan> plans = plan_batch(m, k.A.val_bytes, bk, lds_per_workgroup());
+  if (plans.empty()) return KF_OK;
+  std::vector<int> width;
+  KF_TRY(member_widths(bt, k.A, width));
+  win = launches = 0;
+  std::vector<BatchWg> out;
+  for (size_t i = 0; i < m.size(); ++i) {
+    if (width[i] > kBatchStepsWidth) return KF_OK;
+    const StepsPlan& pl = plans[i];
+    win = std::max(win, std::min(m[i].nslices, pl.own + 2 * pl.s * pl.hb));
+    launches = std::max(launches, (m[i].L - 1 + pl.s - 1) / pl.s);
+    for (int o0 = 0; o0 < m[i].nslices; o0 += pl.own)
+      out.push_back({bt->many[i].q, (int32_t)bt->many[i].slice0, m[i].nslices, o0, pl.own, pl.hb, pl.s, width[i]});
+  }
+  const size_t bytes = (size_t)(bt->rows - bt->many[0].slice0 * 64) * bk * k.A.val_bytes;
+  dfree(k.sb.Y2);
+  dfree(k.sb.Y3);
+  dfree(k.d_wg);
+  k.sb.Y2 = k.sb.Y3 = nullptr;
+  k.d_wg = nullptr;
+  if (hipMalloc(&k.sb.Y2, bytes) != hipSuccess || hipMalloc(&k.sb.Y3, bytes) != hipSuccess ||
+      hipMalloc(&k.d_wg, out.size() * sizeof(BatchWg)) != hipSuccess) {
+    (void)hipGetLastError();
+    return KF_OK;
+  }
+  KF_HIP(hipMemcpy(k.d_wg, out.data(), out.size() * sizeof(BatchWg), hipMemcpyHostToDevice));
+  wgs = std::move(out);
+  return KF_OK;
+}
+
+// Record the batched filter application of a stack (load, then lmax-1 fused
+// steps, and beside them the launches of the members that take several steps
+// each) for block width bk once; replays read the per-problem tables from
 // device memory.
 int ensure_batch_graph(kf_batch* bt, BatchStack& k, int bk) {
   if (k.exec && k.graph_bk == bk) return KF_OK;
@@ -3299,7 +3369,7 @@ int ensure_batch_graph(kf_batch* bt, BatchStack& k, int bk) {
           KF_HIP(hipEventRecord(bt->ev[0], st));
           for (int t = 0; t < 10; ++t)
             KF_TRY(launch_leapfrog_batch(k.A, bk, bt->d_sp, k.d_tb, k.wtab, bt->lmax, 2, k.sb.Y1, k.sb.Y0, k.sb.Y0,
-                                         k.sb.R, 0, remap, st));
+                                         k.sb.R, BatchRange{k.A.nslices, 0, 0}, remap, st));
           KF_HIP(hipEventRecord(bt->ev[1], st));
         }
         KF_HIP(hipEventSynchronize(bt->ev[1]));
@@ -3315,12 +3385,36 @@ int ensure_batch_graph(kf_batch* bt, BatchStack& k, int bk) {
     k.A.nt_loads = best_nt;
     k.tuned = true;
   }
+  std::vector<BatchWg> wgs;
+  int win = 0, launches = 0;
+  KF_TRY(plan_many(bt, k, bk, wgs, win, launches));
   KF_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
   int rc = launch_load_batch(k.A.val_bytes, bt->rows, bk, bt->d_sp, k.d_tb, k.wtab, bt->lmax, k.sb.Y1, st);
+  // beside the rest (which has nothing to do where every member takes several)
+  const bool fork = !wgs.empty() && bt->many[0].slice0 > 0;
+  hipStream_t sm = fork ? bt->st_many : st;
+  const auto link = [&](hipEvent_t e, hipStream_t from, hipStream_t to) {
+    return hipEventRecord(e, from) == hipSuccess && hipStreamWaitEvent(to, e, 0) == hipSuccess;
+  };
+  if (rc == KF_OK && fork && !link(bt->fork[0], st, sm)) rc = fail(KF_EHIP, "kf_batch: graph capture failed");
   void* Y[2] = {k.sb.Y0, k.sb.Y1};
-  for (int l = 1; l < bt->lmax && rc == KF_OK; ++l)
+  for (int l = 1; l < bt->lmax && rc == KF_OK; ++l) {
+    BatchRange r = bt->left[(size_t)l];
+    if (!wgs.empty()) r.nm = 0;
     rc = launch_leapfrog_batch(k.A, bk, bt->d_sp, k.d_tb, k.wtab, bt->lmax, l, Y[l & 1], Y[(l + 1) & 1],
-                               Y[(l + 1) & 1], k.sb.R, bt->prefix[(size_t)l], k.remap, st);
+                               Y[(l + 1) & 1], k.sb.R, r, k.remap, st);
+  }
+  // (after the longer chain: a graph is submitted branch by branch)
+  if (!wgs.empty()) {
+    const int64_t base = bt->many[0].slice0 * 64;
+    void* Ya[2] = {k.sb.Y2, k.sb.Y0};
+    void* Yb[2] = {k.sb.Y3, k.sb.Y1};
+    for (int i = 0; i < launches && rc == KF_OK; ++i)
+      rc = launch_steps_batch(k.A, k.d_wg, (int)wgs.size(), win, bk, k.d_tb, k.wtab, bt->lmax, i, k.sb.Y1,
+                              Ya[(i + 1) & 1], Yb[(i + 1) & 1], Ya[i & 1], Yb[i & 1], k.sb.R, i & 1 ? base : 0,
+                              i & 1 ? 0 : base, sm);
+  }
+  if (rc == KF_OK && fork && !link(bt->fork[1], sm, st)) rc = fail(KF_EHIP, "kf_batch: graph capture failed");
   hipGraph_t g = nullptr;
   const hipError_t e = hipStreamEndCapture(st, &g);
   if (rc != KF_OK) {
@@ -3432,11 +3526,32 @@ int kf_create_batch(int32_t P, const kf_problem_desc* descs, const kf_options* o
         }
       }
     }
-    // members stacked by decreasing L (stable): the members still stepping
-    // at step ell own a prefix of the stacked rows
+    // the members that may take several steps per launch, smallest first for
+    // as long as all of them are better off so
+    std::vector<char> is_many((size_t)P, 0);
+    {
+      std::vector<int> small;
+      for (int q = 0; q < P; ++q) {
+        const SellOp& A = bt->probs[(size_t)q]->A;
+        if (o.multistep == 0 && A.st.width > 0 && A.st.width <= kBatchStepsWidth && !A.st.row_values) small.push_back(q);
+      }
+      const auto op = [&](int q) -> const SellOp& { return bt->probs[(size_t)q]->A; };
+      std::stable_sort(small.begin(), small.end(), [&](int a, int b) { return op(a).nslices < op(b).nslices; });
+      std::vector<BatchMember> m;
+      for (int q : small) {
+        m.push_back({op(q).nslices, (op(q).max_off + 63) / 64, descs[q].L});
+        if (plan_batch(m, op(q).val_bytes, 16 / op(q).val_bytes, lds_per_workgroup()).empty())
+          m.pop_back();
+        else
+          is_many[(size_t)q] = 1;
+      }
+    }
+    // stacked in these two groups, by decreasing L (stable) in each
     std::vector<int> ord((size_t)P);
     for (int q = 0; q < P; ++q) ord[(size_t)q] = q;
-    std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) { return descs[a].L > descs[b].L; });
+    std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) {
+      return is_many[(size_t)a] != is_many[(size_t)b] ? is_many[(size_t)a] < is_many[(size_t)b] : descs[a].L > descs[b].L;
+    });
     std::vector<int64_t> slices_of((size_t)P, 0);
     BatchTables& tb0 = bt->stk[0].h_tb;
     for (int32_t oi = 0; oi < P && rc == KF_OK; ++oi) {
@@ -3462,6 +3577,10 @@ int kf_create_batch(int32_t P, const kf_problem_desc* descs, const kf_options* o
       for (int64_t i = n; i < padded; ++i) rowptr.push_back((int32_t)col.size());
       for (int64_t s = 0; s < padded / 64; ++s) sp.push_back(q);
       slices_of[(size_t)q] = padded / 64;
+      if (is_many[(size_t)q]) {
+        const SellOp& A = bt->probs[(size_t)q]->A;
+        bt->many.push_back({q, row0 / 64, {(int)(padded / 64), (A.max_off + 63) / 64, d.L}});
+      }
       tb0.row0[q] = row0;
       tb0.n[q] = n;
       tb0.L[q] = d.L;
@@ -3470,11 +3589,20 @@ int kf_create_batch(int32_t P, const kf_problem_desc* descs, const kf_options* o
     }
     if (rc) break;
     bt->rows = row0;
-    bt->prefix.assign((size_t)bt->lmax + 1, 0);
+    bt->left.assign((size_t)bt->lmax + 1, BatchRange());
     for (int ell = 0; ell <= bt->lmax; ++ell) {
-      int64_t cnt = 0;
-      for (int oi = 0; oi < P && descs[ord[(size_t)oi]].L - 1 >= ell; ++oi) cnt += slices_of[(size_t)ord[(size_t)oi]];
-      bt->prefix[(size_t)ell] = (int)std::max<int64_t>(cnt, 1);
+      BatchRange& r = bt->left[(size_t)ell];
+      r.m0 = bt->many.empty() ? 0 : (int)bt->many[0].slice0;
+      for (int q = 0; q < P; ++q)
+        if (descs[q].L - 1 >= ell) (is_many[(size_t)q] ? r.nm : r.na) += (int)slices_of[(size_t)q];
+    }
+    if (!bt->many.empty())
+      for (hipEvent_t& e : bt->fork)
+        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) rc = KF_EHIP;
+    if (!bt->many.empty() && hipStreamCreateWithFlags(&bt->st_many, hipStreamNonBlocking) != hipSuccess) rc = KF_EHIP;
+    if (rc) {
+      rc = fail(KF_EHIP, "kf_create_batch: stream creation failed");
+      break;
     }
     HostCsr hs;
     hs.rowptr = std::move(rowptr);

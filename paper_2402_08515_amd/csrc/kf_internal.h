@@ -212,12 +212,33 @@ struct BatchTables {
   double* dst[kMaxBatch];
 };
 
-// One batched fused step (step index ell >= 1) over the first nslices row
-// slices of the stacked operator (0: all; members are stacked by decreasing
-// L, so the members still stepping at ell form a prefix).
+// One batched fused step (step index ell >= 1) over the row slices of `r`
+// (members are stacked by decreasing L within either range, so those still
+// stepping at ell are at its start).
+struct BatchRange {
+  int na = 0;  // the first na slices
+  int m0 = 0;  // and nm slices from m0 on
+  int nm = 0;
+};
 int launch_leapfrog_batch(const SellOp& A, int b, const int32_t* slice_problem, const BatchTables* tb,
                           const void* wtab, int lmax, int ell, const void* cur, const void* prev, void* out, void* acc,
-                          int nslices, int remap, hipStream_t st);
+                          const BatchRange& r, int remap, hipStream_t st);
+// Several steps per launch for members of a batch (k_steps_batch).  plan_batch
+// gives each member its plan (as plan_steps; empty: not worth it);
+// launch_steps_batch is launch i of all of them, with the slices and plan of
+// each workgroup in device memory.  win is the widest window, own + 2 s hb.
+struct BatchMember {
+  int nslices, hb, L;
+};
+struct BatchWg {
+  int32_t p, slice0, nslices, o0, own, hb, s;
+  int32_t width;  // entries of the member's longest slice
+};
+constexpr int kBatchStepsWidth = 7;  // longest slice of such a member
+std::vector<StepsPlan> plan_batch(const std::vector<BatchMember>& m, int val_bytes, int b, size_t lds_bytes);
+int launch_steps_batch(const SellOp& A, const BatchWg* wgs, int nwg, int win, int b, const BatchTables* tb,
+                       const void* wtab, int lmax, int i, const void* ysrc, const void* i0, const void* i1, void* o0,
+                       void* o1, void* acc, int64_t ibase, int64_t obase, hipStream_t st);
 // Batched load of the filter input into Y1 (and C = w0 I for L_p = 1).
 int launch_load_batch(int val_bytes, int64_t rows, int b, const int32_t* slice_problem, const BatchTables* tb,
                       const void* wtab, int lmax, void* Y1, hipStream_t st);
@@ -231,8 +252,8 @@ int launch_stencil_step4(const SellOp& A, int b, int mode, const void* cur, cons
                          void* z, double* rout, int64_t rs, int64_t cs, int bout, double wp, double wc, double wn,
                          int remap, hipStream_t st);
 int launch_stencil_batch(const SellOp& A, int b, const int32_t* slice_problem, const BatchTables* tb, const void* wtab,
-                         int lmax, int ell, const void* cur, const void* prev, void* out, void* acc, int nslices,
-                         int remap, hipStream_t st);
+                         int lmax, int ell, const void* cur, const void* prev, void* out, void* acc,
+                         const BatchRange& r, int remap, hipStream_t st);
 
 // dst (n x b row-major, stepping precision) = src[i*rs + j*cs] for j < bsrc, 0 beyond.
 int launch_load_block(int val_bytes, int32_t n, int b, int bsrc, const double* src, int64_t rs, int64_t cs,

@@ -261,7 +261,7 @@ __global__ __launch_bounds__(256) void k_leapfrog4_st(int32_t n, int32_t nslices
 // The batched step over stencil slices (see stencil_product).  The tables of
 // the slice's problem are scalar loads, as the slice's entries are.
 template <typename T, int B, bool ROWV>
-__global__ __launch_bounds__(256) void k_leapfrog_batch_st(int32_t nslices, const T* __restrict__ val,
+__global__ __launch_bounds__(256) void k_leapfrog_batch_st(BatchRange rg, const T* __restrict__ val,
                                                            const int32_t* __restrict__ soff,
                                                            const uint64_t* __restrict__ mask, int stride,
                                                            const int32_t* __restrict__ sp,
@@ -271,9 +271,10 @@ __global__ __launch_bounds__(256) void k_leapfrog_batch_st(int32_t nslices, cons
                                                            T* __restrict__ acc, int remap) {
   using V = Row<T, B>;
   const int wg = remap ? xcd_map(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-  const int slice = __builtin_amdgcn_readfirstlane(wg * 4 + (int)(threadIdx.x >> 6));
+  const int at = __builtin_amdgcn_readfirstlane(wg * 4 + (int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
-  if (slice >= nslices) return;
+  if (at >= rg.na + rg.nm) return;
+  const int slice = at < rg.na ? at : at - rg.na + rg.m0;
   const int p = sp[slice];
   const int Lp = tb->L[p];
   if (!tb->active[p] || ell > Lp - 1) return;
@@ -530,9 +531,9 @@ int launch_stencil_step4(const SellOp& A, int b, int mode, const void* cur, cons
 namespace {
 template <typename T>
 int launch_lfb_st(const SellOp& A, int b, const int32_t* sp, const BatchTables* tb, const void* wtab, int lmax, int ell,
-                  const void* cur, const void* prev, void* out, void* acc, int nslices, int remap, hipStream_t st) {
+                  const void* cur, const void* prev, void* out, void* acc, const BatchRange& r, int remap, hipStream_t st) {
 #define KF_LFS(B)                                                                                                  \
-  hipLaunchKernelGGL((A.st.row_values ? k_leapfrog_batch_st<T, B, true> : k_leapfrog_batch_st<T, B, false>), dim3(ceil_div64(nslices, 4)), dim3(256), 0, st, nslices,          \
+  hipLaunchKernelGGL((A.st.row_values ? k_leapfrog_batch_st<T, B, true> : k_leapfrog_batch_st<T, B, false>), dim3(ceil_div64(r.na + r.nm, 4)), dim3(256), 0, st, r, \
                      static_cast<const T*>(A.st.val), A.st.off, A.st.mask, A.st.stride, sp, tb,                     \
                      static_cast<const T*>(wtab), lmax, ell, static_cast<const T*>(cur), static_cast<const T*>(prev), \
                      static_cast<T*>(out), static_cast<T*>(acc), remap)
@@ -551,10 +552,10 @@ int launch_lfb_st(const SellOp& A, int b, const int32_t* sp, const BatchTables* 
 }  // namespace
 
 int launch_stencil_batch(const SellOp& A, int b, const int32_t* sp, const BatchTables* tb, const void* wtab, int lmax,
-                         int ell, const void* cur, const void* prev, void* out, void* acc, int nslices, int remap,
+                         int ell, const void* cur, const void* prev, void* out, void* acc, const BatchRange& r, int remap,
                          hipStream_t st) {
-  if (A.val_bytes == 8) return launch_lfb_st<double>(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, nslices, remap, st);
-  return launch_lfb_st<float>(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, nslices, remap, st);
+  if (A.val_bytes == 8) return launch_lfb_st<double>(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, r, remap, st);
+  return launch_lfb_st<float>(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, r, remap, st);
 }
 
 }  // namespace kf

@@ -299,7 +299,7 @@ __global__ __launch_bounds__(256) void k_leapfrog4(int32_t n, int32_t nslices, c
 // columns) live in device memory and are refreshed before each replay, so the
 // launch sequence can be captured once in a graph.
 template <typename T, typename IT, int B, bool NT>
-__global__ __launch_bounds__(256) void k_leapfrog_batch(int32_t nslices, const int64_t* __restrict__ sptr,
+__global__ __launch_bounds__(256) void k_leapfrog_batch(BatchRange rg, const int64_t* __restrict__ sptr,
                                                         const T* __restrict__ val, const IT* __restrict__ idx,
                                                         const int32_t* __restrict__ sp, const BatchTables* __restrict__ tb,
                                                         const T* __restrict__ wtab, int lmax, int ell,
@@ -307,9 +307,10 @@ __global__ __launch_bounds__(256) void k_leapfrog_batch(int32_t nslices, const i
                                                         T* __restrict__ acc, int remap) {
   constexpr bool relative = sizeof(IT) == 2;
   const int wg = remap ? xcd_map(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-  const int slice = wg * 4 + (threadIdx.x >> 6);
+  const int at = wg * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  if (slice >= nslices) return;
+  if (at >= rg.na + rg.nm) return;
+  const int slice = at < rg.na ? at : at - rg.na + rg.m0;
   const int p = sp[slice];
   const int Lp = tb->L[p];
   if (!tb->active[p] || ell > Lp - 1) return;
@@ -1036,8 +1037,8 @@ StepPlan step_plan(int l, int L) {
 namespace {
 template <typename T, typename IT, bool NT>
 int launch_lfb_t(const SellOp& A, int b, const int32_t* sp, const BatchTables* tb, const void* wtab, int lmax, int ell,
-                 const void* cur, const void* prev, void* out, void* acc, int nslices, int remap, hipStream_t st) {
-  const int grid = ceil_div64(nslices, 4);
+                 const void* cur, const void* prev, void* out, void* acc, const BatchRange& r, int remap, hipStream_t st) {
+  const int grid = ceil_div64(r.na + r.nm, 4);
   const T* v = static_cast<const T*>(A.val);
   const IT* ix = static_cast<const IT*>(A.idx);
   const T* w = static_cast<const T*>(wtab);
@@ -1047,23 +1048,23 @@ int launch_lfb_t(const SellOp& A, int b, const int32_t* sp, const BatchTables* t
   T* a = static_cast<T*>(acc);
   switch (b) {
     case 1:
-      hipLaunchKernelGGL((k_leapfrog_batch<T, IT, 1, NT>), dim3(grid), dim3(256), 0, st, nslices, A.slice_ptr, v, ix, sp,
+      hipLaunchKernelGGL((k_leapfrog_batch<T, IT, 1, NT>), dim3(grid), dim3(256), 0, st, r, A.slice_ptr, v, ix, sp,
                          tb, w, lmax, ell, c, pr, o, a, remap);
       break;
     case 2:
-      hipLaunchKernelGGL((k_leapfrog_batch<T, IT, 2, NT>), dim3(grid), dim3(256), 0, st, nslices, A.slice_ptr, v, ix, sp,
+      hipLaunchKernelGGL((k_leapfrog_batch<T, IT, 2, NT>), dim3(grid), dim3(256), 0, st, r, A.slice_ptr, v, ix, sp,
                          tb, w, lmax, ell, c, pr, o, a, remap);
       break;
     case 4:
-      hipLaunchKernelGGL((k_leapfrog_batch<T, IT, 4, NT>), dim3(grid), dim3(256), 0, st, nslices, A.slice_ptr, v, ix, sp,
+      hipLaunchKernelGGL((k_leapfrog_batch<T, IT, 4, NT>), dim3(grid), dim3(256), 0, st, r, A.slice_ptr, v, ix, sp,
                          tb, w, lmax, ell, c, pr, o, a, remap);
       break;
     case 8:
-      hipLaunchKernelGGL((k_leapfrog_batch<T, IT, 8, NT>), dim3(grid), dim3(256), 0, st, nslices, A.slice_ptr, v, ix, sp,
+      hipLaunchKernelGGL((k_leapfrog_batch<T, IT, 8, NT>), dim3(grid), dim3(256), 0, st, r, A.slice_ptr, v, ix, sp,
                          tb, w, lmax, ell, c, pr, o, a, remap);
       break;
     case 16:
-      hipLaunchKernelGGL((k_leapfrog_batch<T, IT, 16, NT>), dim3(grid), dim3(256), 0, st, nslices, A.slice_ptr, v, ix,
+      hipLaunchKernelGGL((k_leapfrog_batch<T, IT, 16, NT>), dim3(grid), dim3(256), 0, st, r, A.slice_ptr, v, ix,
                          sp, tb, w, lmax, ell, c, pr, o, a, remap);
       break;
     default:
@@ -1076,15 +1077,15 @@ int launch_lfb_t(const SellOp& A, int b, const int32_t* sp, const BatchTables* t
 }  // namespace
 
 int launch_leapfrog_batch(const SellOp& A, int b, const int32_t* sp, const BatchTables* tb, const void* wtab, int lmax,
-                          int ell, const void* cur, const void* prev, void* out, void* acc, int nslices, int remap,
+                          int ell, const void* cur, const void* prev, void* out, void* acc, const BatchRange& r, int remap,
                           hipStream_t st) {
-  if (nslices <= 0 || nslices > A.nslices) nslices = A.nslices;
+  if (r.na + r.nm <= 0) return KF_OK;
   if (A.st.width > 0)
-    return launch_stencil_batch(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, nslices, remap, st);
+    return launch_stencil_batch(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, r, remap, st);
 #define KF_LFB(T, IT)                                                                                               \
-  return A.nt_loads ? launch_lfb_t<T, IT, true>(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, nslices, remap, \
+  return A.nt_loads ? launch_lfb_t<T, IT, true>(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, r, remap, \
                                                 st)                                                                 \
-                    : launch_lfb_t<T, IT, false>(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, nslices, remap, st)
+                    : launch_lfb_t<T, IT, false>(A, b, sp, tb, wtab, lmax, ell, cur, prev, out, acc, r, remap, st)
   if (A.val_bytes == 8) {
     if (A.idx_bytes == 2) KF_LFB(double, int16_t);
     KF_LFB(double, int32_t);

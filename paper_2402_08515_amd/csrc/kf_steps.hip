@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "kf_device.h"
 #include "kf_internal.h"
@@ -38,17 +39,15 @@ namespace {
 //   last:  the sum goes to rout; otherwise y_{l0+s-1}, y_{l0+s} go to o0g,
 //          o1g and the sum to acc.  o0g, o1g are not i0, i1 unless there is
 //          one workgroup.
-// w.w[j] is the weight of y_{l0+j}.
-template <typename T, int B, int W, int R, bool ROWV>
-__global__ __launch_bounds__(1024) void k_steps_st(int32_t n, int32_t nslices, const T* __restrict__ sval,
-                                                   const int32_t* __restrict__ soff, const uint64_t* __restrict__ smask,
-                                                   const T* ysrc, const T* i0, const T* i1, T* o0g, T* o1g, T* acc, double* __restrict__ rout, int64_t rs, int64_t cs,
-                                                   int bout, int groups, StepWeights w, int s, int own,
-                                                   int hb, int first, int last) {
+// wt(j) is the weight of y_{l0+j}; own slices are [o0, o1).
+template <typename T, int B, int W, int R, bool ROWV, class Weight>
+__device__ __forceinline__ void steps_body(int32_t n, int32_t nslices, const T* __restrict__ sval,
+                                           const int32_t* __restrict__ soff, const uint64_t* __restrict__ smask,
+                                           int stride, const T* ysrc, const T* i0, const T* i1, T* o0g, T* o1g, T* acc,
+                                           double* __restrict__ rout, int64_t rs, int64_t cs, int bout, int groups,
+                                           Weight wt, int s, int o0, int o1, int hb, bool first, bool last) {
   using V = Row<T, B>;
   extern __shared__ __align__(16) unsigned char steps_raw[];
-  const int wg = xcd_map(blockIdx.x, gridDim.x);
-  const int o0 = wg * own, o1 = min(nslices, o0 + own);
   const int w0 = max(0, o0 - s * hb), w1 = min(nslices, o1 + s * hb);
   const int rows = (w1 - w0) * 64;  // of one level in LDS; row `rows` is the zero
   V* lds = reinterpret_cast<V*>(steps_raw);
@@ -76,7 +75,7 @@ __global__ __launch_bounds__(1024) void k_steps_st(int32_t n, int32_t nslices, c
       if (sl >= o0 && sl < o1) {
         if (first) {
 #pragma unroll
-          for (int j = 0; j < B; ++j) ra[k].v[j] = (T)w.w[0] * yc[k].v[j];
+          for (int j = 0; j < B; ++j) ra[k].v[j] = wt(0) * yc[k].v[j];
         } else {
           ra[k] = reinterpret_cast<const V*>(acc)[(int64_t)row * groups + grp];
         }
@@ -84,8 +83,8 @@ __global__ __launch_bounds__(1024) void k_steps_st(int32_t n, int32_t nslices, c
     }
 #pragma unroll
     for (int q = 0; q < W; ++q) {
-      const bool has = __builtin_amdgcn_inverse_ballot_w64(smask[(int64_t)sl * W + q]);
-      const int c = row - w0 * 64 + soff[(int64_t)sl * W + q];
+      const bool has = __builtin_amdgcn_inverse_ballot_w64(smask[(int64_t)sl * stride + q]);
+      const int c = row - w0 * 64 + soff[(int64_t)sl * stride + q];
       const uint32_t a = has && c >= 0 && c < rows ? (uint32_t)c : (uint32_t)rows;
       at[k][q >> 1] = q & 1 ? at[k][q >> 1] | a << 16 : a;
     }
@@ -94,7 +93,7 @@ __global__ __launch_bounds__(1024) void k_steps_st(int32_t n, int32_t nslices, c
   __syncthreads();
   int cur = 0;
   for (int j = 0; j < s; ++j) {
-    const T wn = (T)w.w[j + 1];
+    const T wn = wt(j + 1);
     // the slices the later steps still read
     const int a0 = o0 - (s - 1 - j) * hb, a1 = o1 + (s - 1 - j) * hb;
     const V* __restrict__ src = lds + cur * step2;
@@ -115,7 +114,7 @@ __global__ __launch_bounds__(1024) void k_steps_st(int32_t n, int32_t nslices, c
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int q = q0 + u;
-          av[u] = ROWV ? sval[((int64_t)sl * W + q) * 64 + lane] : sval[(int64_t)sl * W + q];
+          av[u] = ROWV ? sval[((int64_t)sl * stride + q) * 64 + lane] : sval[(int64_t)sl * stride + q];
           x[u] = src[q & 1 ? at[k][q >> 1] >> 16 : at[k][q >> 1] & 0xFFFFu];
         }
 #pragma unroll
@@ -152,6 +151,53 @@ __global__ __launch_bounds__(1024) void k_steps_st(int32_t n, int32_t nslices, c
       reinterpret_cast<V*>(acc)[o] = ra[k];
     }
   }
+}
+
+template <typename T, int B, int W, int R, bool ROWV>
+__global__ __launch_bounds__(1024) void k_steps_st(int32_t n, int32_t nslices, const T* __restrict__ sval,
+                                                   const int32_t* __restrict__ soff, const uint64_t* __restrict__ smask,
+                                                   const T* ysrc, const T* i0, const T* i1, T* o0g, T* o1g, T* acc,
+                                                   double* __restrict__ rout, int64_t rs, int64_t cs, int bout,
+                                                   int groups, StepWeights w, int s, int own, int hb, int first,
+                                                   int last) {
+  const int o0 = xcd_map(blockIdx.x, gridDim.x) * own;
+  steps_body<T, B, W, R, ROWV>(n, nslices, sval, soff, smask, W, ysrc, i0, i1, o0g, o1g, acc, rout, rs, cs, bout,
+                               groups, [&](int j) { return (T)w.w[j]; }, s, o0, min(nslices, o0 + own), hb, first != 0,
+                               last != 0);
+}
+
+// The same for the members of a batch that plan_batch took: wgs[] says which
+// member, slices and plan each workgroup has; launch i advances every member
+// from step i * s on until its L - 1 steps are done.  i0, i1 and o0, o1 hold
+// the stack's rows from ibase and obase on.
+// Bound by a launch's latency, as k_steps_st is, and by the compute units it
+// shares with the one-step launches beside it: 16 members of 18800 slices,
+// float32 blocks of 4, of which 2148 slices of small members set the number
+// of steps (199), 1180 -> 968 us an application, 1087 with the two kinds of
+// launches one after another.
+template <typename T, int B, int R>
+__global__ __launch_bounds__(1024) void k_steps_batch(const BatchWg* __restrict__ wgs, const T* __restrict__ sval,
+                                                      const int32_t* __restrict__ soff,
+                                                      const uint64_t* __restrict__ smask, int stride,
+                                                      const BatchTables* __restrict__ tb, const T* __restrict__ wtab,
+                                                      int lmax, int i, const T* ysrc, const T* i0, const T* i1, T* o0,
+                                                      T* o1, T* acc, int64_t ibase, int64_t obase, int groups) {
+  const BatchWg g = wgs[xcd_map(blockIdx.x, gridDim.x)];
+  const int l0 = i * g.s, left = tb->L[g.p] - 1 - l0;
+  if (!tb->active[g.p] || left <= 0) return;
+  const int64_t row0 = (int64_t)g.slice0 * 64, b = (int64_t)groups * B;
+  const int64_t so = (int64_t)g.slice0 * stride, in = (row0 - ibase) * b, out = (row0 - obase) * b;
+  const T* __restrict__ wq = wtab + (int64_t)g.p * lmax + l0;
+  const auto run = [&](auto width) {
+    steps_body<T, B, decltype(width)::value, R, false>(
+        tb->n[g.p], g.nslices, sval + so, soff + so, smask + so, stride, ysrc + row0 * b, i0 + in, i1 + in, o0 + out,
+        o1 + out, acc + row0 * b, tb->dst[g.p], 1, tb->ld[g.p], tb->bout[g.p], groups,
+        [&](int j) { return wq[j]; }, min(g.s, left), g.o0, min(g.nslices, g.o0 + g.own), g.hb, i == 0, left <= g.s);
+  };
+  if (g.width <= 5)
+    run(std::integral_constant<int, 5>());
+  else
+    run(std::integral_constant<int, 7>());
 }
 
 }  // namespace
@@ -206,6 +252,8 @@ int launch_steps_b(const SellOp& A, const StepsPlan& pl, const StepsArgs& g, con
 }  // namespace
 
 namespace {
+constexpr int kCus = 256;  // compute units: workgroups of a launch
+
 // the lengths of stencils that k_steps_st is built for
 bool has_steps(const StencilOp& st) {
   return st.row_values ? st.stride == 8 || st.stride == 15 : (st.stride == 5 || st.stride == 7) && st.width == st.stride;
@@ -242,20 +290,15 @@ int launch_steps(const SellOp& A, const StepsPlan& pl, int b, int s, bool first,
 // float64, 0.005 in float32, 0.008 with several groups of columns, which leave
 // fewer compute units to each: 5 x 109-cell horn, one vector in float64, 4.0 ->
 // 1.4 us a step; 16 x 200 cells 4.2 -> 3.3, its block of 16 in float32 not.
-StepsPlan plan_steps(const SellOp& A, int b, int L, size_t lds_bytes) {
+namespace {
+StepsPlan plan_of(int ns, int hb, bool rv, int stride, int val_bytes, int b, int L, size_t lds_bytes, int own_min) {
   StepsPlan best;
-  if (!has_steps(A.st) || L < 3) return best;
-  constexpr int kCus = 256;
-  const int cols = std::min(b, 16 / A.val_bytes), groups = b / cols, rb = cols * A.val_bytes;
-  const int hb = (A.max_off + 63) / 64, ns = A.nslices;
-  const int win_max = std::min<int64_t>(16 * steps_max_r(rb, A.st.row_values ? A.st.stride : 0), ((int64_t)lds_bytes / (2 * rb) - 1) / 64);
-  const bool rv = A.st.row_values;
+  const int cols = std::min(b, 16 / val_bytes), groups = b / cols, rb = cols * val_bytes;
+  const int win_max = std::min<int64_t>(16 * steps_max_r(rb, rv ? stride : 0), ((int64_t)lds_bytes / (2 * rb) - 1) / 64);
   const double load = rv || rb > 8 ? 0.06 : 0.03;
-  const double slice = rv ? A.st.stride * (groups > 1 ? 0.008 : (A.val_bytes == 8 ? 0.0073 : 0.005))
-                          : (rb > 8 ? 0.022 : 0.014);
+  const double slice = rv ? stride * (groups > 1 ? 0.008 : (val_bytes == 8 ? 0.0073 : 0.005)) : (rb > 8 ? 0.022 : 0.014);
   double t_best = 0.85 * 4.0 * (L - 1);
-  const int own_min = (int)(((int64_t)ns * groups + kCus - 1) / kCus);
-  if (own_min > win_max || groups > kCus) return best;
+  if (L < 3 || own_min > win_max || groups > kCus) return best;
   for (int i = 0; i < 4; ++i) {
     const int own = i == 3 ? ns : std::min(ns, own_min << i);
     const bool whole = own >= ns;
@@ -277,6 +320,78 @@ StepsPlan plan_steps(const SellOp& A, int b, int L, size_t lds_bytes) {
     if (whole) break;
   }
   return best;
+}
+}  // namespace
+
+StepsPlan plan_steps(const SellOp& A, int b, int L, size_t lds_bytes) {
+  if (!has_steps(A.st)) return StepsPlan();
+  const int groups = b / std::min(b, 16 / A.val_bytes);
+  return plan_of(A.nslices, (A.max_off + 63) / 64, A.st.row_values, A.st.stride, A.val_bytes, b, L, lds_bytes,
+                 (int)ceil_div64((int64_t)A.nslices * groups, kCus));
+}
+
+// Members of a batch side by side in one launch: each as alone, with so many
+// slices a workgroup that all of them have a compute unit to themselves.
+// Empty: one of them is not better off than with one step per launch.
+std::vector<StepsPlan> plan_batch(const std::vector<BatchMember>& m, int val_bytes, int b, size_t lds_bytes) {
+  const int groups = b / std::min(b, 16 / val_bytes);
+  int64_t total = 0;
+  for (const BatchMember& q : m) total += q.nslices;
+  std::vector<StepsPlan> plans(m.size());
+  for (int own_min = std::max(1, (int)ceil_div64(total * groups, kCus));; ++own_min) {
+    int64_t wgs = 0;
+    for (size_t i = 0; i < m.size(); ++i) {
+      plans[i] = plan_of(m[i].nslices, m[i].hb, false, 0, val_bytes, b, m[i].L, lds_bytes, own_min);
+      if (plans[i].s == 0) return {};
+      wgs += (int64_t)ceil_div64(m[i].nslices, plans[i].own) * groups;
+    }
+    if (wgs <= kCus) return plans;
+  }
+}
+
+namespace {
+template <typename T, int B>
+int launch_steps_batch_b(const SellOp& A, const BatchWg* wgs, int nwg, int win, int groups, const BatchTables* tb,
+                         const void* wtab, int lmax, int i, const void* ysrc, const void* i0, const void* i1, void* o0,
+                         void* o1, void* acc, int64_t ibase, int64_t obase, hipStream_t st) {
+  const size_t lds = (size_t)2 * (win * 64 + 1) * B * sizeof(T);
+  constexpr int RM = steps_max_r(B * sizeof(T), 0);
+  if (win > 16 * RM) {
+    set_error("several steps per launch: window too wide");
+    return KF_EINVAL;
+  }
+#define KF_SB(R)                                                                                                     \
+  do {                                                                                                               \
+    KF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_steps_batch<T, B, R>),                               \
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));                               \
+    hipLaunchKernelGGL((k_steps_batch<T, B, R>), dim3(nwg, groups), dim3(1024), lds, st, wgs,                        \
+                       static_cast<const T*>(A.st.val), A.st.off, A.st.mask, A.st.stride, tb,                        \
+                       static_cast<const T*>(wtab), lmax, i, static_cast<const T*>(ysrc), static_cast<const T*>(i0), \
+                       static_cast<const T*>(i1), static_cast<T*>(o0), static_cast<T*>(o1), static_cast<T*>(acc),    \
+                       ibase, obase, groups);                                                                        \
+  } while (0)
+  if (win <= 32)
+    KF_SB(2);
+  else if (win <= 64)
+    KF_SB(4);
+  else
+    KF_SB(RM);
+#undef KF_SB
+  KF_HIP(hipGetLastError());
+  return KF_OK;
+}
+}  // namespace
+
+int launch_steps_batch(const SellOp& A, const BatchWg* wgs, int nwg, int win, int b, const BatchTables* tb,
+                       const void* wtab, int lmax, int i, const void* ysrc, const void* i0, const void* i1, void* o0,
+                       void* o1, void* acc, int64_t ibase, int64_t obase, hipStream_t st) {
+  const int cols = std::min(b, 16 / A.val_bytes), groups = b / cols;
+#define KF_SB(T, B) \
+  launch_steps_batch_b<T, B>(A, wgs, nwg, win, groups, tb, wtab, lmax, i, ysrc, i0, i1, o0, o1, acc, ibase, obase, st)
+  if (A.val_bytes == 8) return cols == 1 ? KF_SB(double, 1) : KF_SB(double, 2);
+  if (cols == 1) return KF_SB(float, 1);
+  return cols == 2 ? KF_SB(float, 2) : KF_SB(float, 4);
+#undef KF_SB
 }
 
 }  // namespace kf
