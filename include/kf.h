@@ -516,6 +516,9 @@ int kf_destroy_batch(kf_batch* bt);
  * dimension n_p), 1 <= b <= 16.  Synchronous. */
 int kf_batch_apply_filter(kf_batch* bt, const double* const* x, double* const* y, int32_t b);
 
+/* The same for ROW-major blocks, the layout of kf_apply_filter. */
+int kf_batch_apply_filter_rows(kf_batch* bt, const double* const* x, double* const* y, int32_t b);
+
 /* Algorithm 2.5 (with the block remedy of Section 4.4) for every member,
  * exactly as kf_solve, with the time loops of all members (eq. 2stepmethod,
  * eq. disc_filtercoeff) advancing in one batched launch sequence.

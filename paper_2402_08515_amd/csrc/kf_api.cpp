@@ -3673,7 +3673,8 @@ int kf_destroy_batch(kf_batch* bt) {
   return KF_OK;
 }
 
-int kf_batch_apply_filter(kf_batch* bt, const double* const* x, double* const* y, int32_t b) {
+namespace {
+int batch_apply_filter(kf_batch* bt, const double* const* x, double* const* y, int32_t b, bool row_major) {
   if (!bt || !x || !y) return fail(KF_EINVAL, "kf_batch_apply_filter: NULL argument");
   if (b < 1 || b > 16) return fail(KF_EINVAL, "kf_batch_apply_filter: b must lie in [1, 16]");
   BatchTables& tb = bt->stk[0].h_tb;
@@ -3681,15 +3682,26 @@ int kf_batch_apply_filter(kf_batch* bt, const double* const* x, double* const* y
     if (!x[q] || !y[q]) return fail(KF_EINVAL, "kf_batch_apply_filter: NULL block");
     tb.active[q] = 1;
     tb.src[q] = x[q];
-    tb.lds[q] = tb.n[q];
+    tb.lds[q] = row_major ? 1 : tb.n[q];
+    tb.srs[q] = row_major ? b : 1;
     tb.bsrc[q] = b;
     tb.dst[q] = y[q];
-    tb.ld[q] = tb.n[q];
+    tb.ld[q] = row_major ? 1 : tb.n[q];
+    tb.drs[q] = row_major ? b : 1;
     tb.bout[q] = b;
   }
   KF_TRY(run_batch_filter(bt, bt->stk[0], pow2ceil(b)));
   KF_HIP(hipStreamSynchronize(bt->st));
   return KF_OK;
+}
+}  // namespace
+
+int kf_batch_apply_filter(kf_batch* bt, const double* const* x, double* const* y, int32_t b) {
+  return batch_apply_filter(bt, x, y, b, false);
+}
+
+int kf_batch_apply_filter_rows(kf_batch* bt, const double* const* x, double* const* y, int32_t b) {
+  return batch_apply_filter(bt, x, y, b, true);
 }
 
 int kf_solve_batch(kf_batch* bt, const double* const* starts, int32_t b, int32_t m_max, double tol,
@@ -3743,9 +3755,11 @@ int kf_solve_batch(kf_batch* bt, const double* const* starts, int32_t b, int32_t
       tb.active[q] = 1;
       tb.src[q] = p->B + (int64_t)s.q0 * p->ldb;
       tb.lds[q] = p->ldb;
+      tb.srs[q] = 1;
       tb.bsrc[q] = s.qn;
       tb.dst[q] = p->B + (int64_t)s.cur * p->ldb;
       tb.ld[q] = p->ldb;
+      tb.drs[q] = 1;
       tb.bout[q] = bk;
     }
     if (!any[0] && !any[1]) break;

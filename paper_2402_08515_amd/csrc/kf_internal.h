@@ -208,6 +208,8 @@ struct BatchTables {
   int32_t bout[kMaxBatch];  // destination columns written
   int64_t lds[kMaxBatch];   // source column stride
   int64_t ld[kMaxBatch];    // destination column stride
+  int64_t srs[kMaxBatch];   // source row stride
+  int64_t drs[kMaxBatch];   // destination row stride
   const double* src[kMaxBatch];
   double* dst[kMaxBatch];
 };

@@ -309,11 +309,11 @@ __global__ __launch_bounds__(256) void k_leapfrog_batch_st(BatchRange rg, const 
   }
   if (last) {
     double* __restrict__ dst = tb->dst[p];
-    const int64_t ld = tb->ld[p];
+    const int64_t ld = tb->ld[p], drs = tb->drs[p];
     const int bout = tb->bout[p];
 #pragma unroll
     for (int j = 0; j < B; ++j)
-      if (j < bout) dst[local + (int64_t)j * ld] = (double)r.v[j];
+      if (j < bout) dst[local * drs + (int64_t)j * ld] = (double)r.v[j];
   } else {
     reinterpret_cast<V*>(acc)[row] = r;
   }

@@ -386,11 +386,11 @@ __global__ __launch_bounds__(256) void k_leapfrog_batch(BatchRange rg, const int
   }
   if (last) {
     double* __restrict__ dst = tb->dst[p];
-    const int64_t ld = tb->ld[p];
+    const int64_t ld = tb->ld[p], drs = tb->drs[p];
     const int bout = tb->bout[p];
 #pragma unroll
     for (int j = 0; j < B; ++j)
-      if (j < bout) dst[local + (int64_t)j * ld] = (double)r.v[j];
+      if (j < bout) dst[local * drs + (int64_t)j * ld] = (double)r.v[j];
   } else {
     *reinterpret_cast<Row<T, B>*>(acc + (int64_t)row * B) = r;
   }
@@ -409,14 +409,15 @@ __global__ __launch_bounds__(256) void k_load_batch(int64_t rows, int b, const i
   const int local = (int)(row - tb->row0[p]);
   const bool on = tb->active[p] && local < tb->n[p];
   const double* __restrict__ src = tb->src[p];
-  const int64_t lds = tb->lds[p];
+  const int64_t lds = tb->lds[p], srs = tb->srs[p];
   const int bsrc = tb->bsrc[p];
-  for (int j = 0; j < b; ++j) Y1[row * b + j] = (on && j < bsrc) ? (T)src[local + (int64_t)j * lds] : (T)0;
+  for (int j = 0; j < b; ++j) Y1[row * b + j] = (on && j < bsrc) ? (T)src[local * srs + (int64_t)j * lds] : (T)0;
   if (on && tb->L[p] == 1) {
     const double w0 = (double)wtab[(int64_t)p * lmax];
     double* __restrict__ dst = tb->dst[p];
-    const int64_t ld = tb->ld[p];
-    for (int j = 0; j < tb->bout[p]; ++j) dst[local + (int64_t)j * ld] = j < bsrc ? w0 * src[local + (int64_t)j * lds] : 0.0;
+    const int64_t ld = tb->ld[p], drs = tb->drs[p];
+    for (int j = 0; j < tb->bout[p]; ++j)
+      dst[local * drs + (int64_t)j * ld] = j < bsrc ? w0 * src[local * srs + (int64_t)j * lds] : 0.0;
   }
 }
 

@@ -191,7 +191,7 @@ __global__ __launch_bounds__(1024) void k_steps_batch(const BatchWg* __restrict_
   const auto run = [&](auto width) {
     steps_body<T, B, decltype(width)::value, R, false>(
         tb->n[g.p], g.nslices, sval + so, soff + so, smask + so, stride, ysrc + row0 * b, i0 + in, i1 + in, o0 + out,
-        o1 + out, acc + row0 * b, tb->dst[g.p], 1, tb->ld[g.p], tb->bout[g.p], groups,
+        o1 + out, acc + row0 * b, tb->dst[g.p], tb->drs[g.p], tb->ld[g.p], tb->bout[g.p], groups,
         [&](int j) { return wq[j]; }, min(g.s, left), g.o0, min(g.nslices, g.o0 + g.own), g.hb, i == 0, left <= g.s);
   };
   if (g.width <= 5)

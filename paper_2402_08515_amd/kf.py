@@ -157,6 +157,7 @@ _SIGNATURES = {
     "kf_destroy_batch": (C.c_int, [C.c_void_p]),
     "kf_batch_set_weights": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_int32]),
     "kf_batch_apply_filter": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32]),
+    "kf_batch_apply_filter_rows": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32]),
     "kf_solve_batch": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_double, C.c_void_p]),
     "kf_mlp_param_count": (C.c_int32, []),
     "kf_mlp_create": (C.c_int, [C.c_void_p, C.POINTER(C.c_void_p)]),
@@ -473,12 +474,12 @@ class Batch:
         """ys[p] = C_p xs[p] for device blocks xs[p] of shape (n_p, b),
         float64; one batched application."""
         b = int(xs[0].shape[1])
-        cols = [x.t().contiguous() for x in xs]  # column-major n x b
-        outs = [torch.empty_like(c) for c in cols]
-        xp = (C.c_void_p * self.P)(*[c.data_ptr() for c in cols])
+        rows = [x.contiguous() for x in xs]
+        outs = [torch.empty_like(r) for r in rows]
+        xp = (C.c_void_p * self.P)(*[r.data_ptr() for r in rows])
         yp = (C.c_void_p * self.P)(*[o.data_ptr() for o in outs])
-        _check(lib().kf_batch_apply_filter(self._h, C.cast(xp, C.c_void_p), C.cast(yp, C.c_void_p), b))
-        return [o.t().contiguous() for o in outs]
+        _check(lib().kf_batch_apply_filter_rows(self._h, C.cast(xp, C.c_void_p), C.cast(yp, C.c_void_p), b))
+        return outs
 
     def solve(self, starts, m_max: int, tol: float):
         arrs = [np.ascontiguousarray(v[:, None] if v.ndim == 1 else v, dtype=np.float64) for v in starts]

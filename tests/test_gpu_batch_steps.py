@@ -48,3 +48,32 @@ def test_batch_with_several_steps_per_launch_bitwise(name, b, precision):
         for (_, n, L), y, r in zip(BATCHES[name], got, ref):
             assert torch.equal(y, r), (rep, n, L, (y - r).abs().max())
         torch.ones(1 << 20, device="cuda").sum().item()
+
+
+@pytest.mark.parametrize("b", [1, 3, 4])
+def test_column_major_blocks_equal_row_major_ones(b):
+    """The two layouts of a batch's blocks (members with no step, one step and
+    several, stored entries too): only the addresses differ."""
+    import ctypes as C
+
+    import torch
+
+    from paper_2402_08515_amd import kf
+
+    print(f"case batch layouts b={b}", flush=True)
+    for options in ({}, {"index_bytes": 4}):
+        members = []
+        for n, L in ((20, 1), (33, 2), (90, 23)):
+            S, m = grid_problem(2, n)[:2]
+            tau = 1.8 / (8.0 * n * n) ** 0.5
+            members.append((S, m, 0.3 / tau, 0.5 / tau, tau, L, 0))
+        bt = kf.Batch(members, **options)
+        xs = [torch.from_numpy(start_block(S.shape[0], b, i)).cuda() for i, (S, *_rest) in enumerate(members)]
+        wide = [torch.cat([x, x], 1)[:, :b] for x in xs]  # rows further apart than b
+        cols = [x.t().contiguous() for x in xs]
+        outs = [torch.zeros_like(c) for c in cols]
+        xp, yp = ((C.c_void_p * len(xs))(*[t.data_ptr() for t in ts]) for ts in (cols, outs))
+        torch.cuda.synchronize()
+        assert kf.lib().kf_batch_apply_filter(bt._h, C.cast(xp, C.c_void_p), C.cast(yp, C.c_void_p), b) == 0
+        for y, w, o in zip(bt.apply_filter(xs), bt.apply_filter(wide), outs):
+            assert torch.equal(y, o.t()) and torch.equal(w, y)
