@@ -180,8 +180,10 @@ struct StepWeights {
 };
 struct StepsPlan {
   int s = 0, own = 0, hb = 0;
+  bool order4 = false;  // fourth-order steps
+  int reach() const { return order4 ? 2 * hb : hb; }  // slices a step reaches
 };
-StepsPlan plan_steps(const SellOp& A, int b, int L, size_t lds_bytes);
+StepsPlan plan_steps(const SellOp& A, int b, int L, size_t lds_bytes, bool order4);
 int launch_steps(const SellOp& A, const StepsPlan& pl, int b, int s, bool first, bool last, const void* ysrc,
                  const void* i0, const void* i1, void* o0, void* o1, void* acc, double* rout, int64_t rs, int64_t cs,
                  int bout, const StepWeights& w, hipStream_t st);

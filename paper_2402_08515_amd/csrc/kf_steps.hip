@@ -33,14 +33,20 @@ namespace {
 // Measured, us per filter application, one step per launch and so: 64-cell
 // square (63 slices) fp64 257 -> 45; 128 cells 535 -> 114; 256 cells 1072 ->
 // 322, its block of 4 in float32 1021 -> 463; 20-cell cube 91 -> 44.  Bound by
-// a launch's latency (about 4 us) and the LDS reads of the halo slices.
+// a launch's latency (about 4 us) and the LDS reads of the halo slices.  The
+// fourth-order step, us a step, two launches each and so (fp64, one vector):
+// 20-cell square 8.4 -> 0.57, 128 cells 8.4 -> 1.7, 500 cells 8.5 -> 4.3,
+// 25-cell cube 8.4 -> 4.3; 11 x 34-cell horn 8.5 -> 4.5.
 //   first: y_{-1} = y_0 = x (x in ysrc), the sum starts at w_0 x; else i0, i1
 //          hold y_{l0-1}, y_{l0} and acc the sum
 //   last:  the sum goes to rout; otherwise y_{l0+s-1}, y_{l0+s} go to o0g,
 //          o1g and the sum to acc.  o0g, o1g are not i0, i1 unless there is
 //          one workgroup.
 // wt(j) is the weight of y_{l0+j}; own slices are [o0, o1).
-template <typename T, int B, int W, int R, bool ROWV, class Weight>
+// O4: the fourth-order step, z = A y first and then y_{l+1} = 2 y_l - y_{l-1} -
+// z + A z / 12; a step reaches twice as far, the second copy in LDS holds z,
+// and y is written in place.
+template <typename T, int B, int W, int R, bool ROWV, bool O4, class Weight>
 __device__ __forceinline__ void steps_body(int32_t n, int32_t nslices, const T* __restrict__ sval,
                                            const int32_t* __restrict__ soff, const uint64_t* __restrict__ smask,
                                            int stride, const T* ysrc, const T* i0, const T* i1, T* o0g, T* o1g, T* acc,
@@ -48,7 +54,8 @@ __device__ __forceinline__ void steps_body(int32_t n, int32_t nslices, const T* 
                                            Weight wt, int s, int o0, int o1, int hb, bool first, bool last) {
   using V = Row<T, B>;
   extern __shared__ __align__(16) unsigned char steps_raw[];
-  const int w0 = max(0, o0 - s * hb), w1 = min(nslices, o1 + s * hb);
+  const int reach = O4 ? 2 * hb : hb;
+  const int w0 = max(0, o0 - s * reach), w1 = min(nslices, o1 + s * reach);
   const int rows = (w1 - w0) * 64;  // of one level in LDS; row `rows` is the zero
   V* lds = reinterpret_cast<V*>(steps_raw);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
@@ -91,42 +98,68 @@ __device__ __forceinline__ void steps_body(int32_t n, int32_t nslices, const T* 
     lds[row - w0 * 64] = yc[k];
   }
   __syncthreads();
+  // sum = (A x)[own row of slice sl], x a level in LDS
+  const auto product = [&](int k, int sl, const V* __restrict__ src, int j, T (&sum)[B]) {
+#pragma unroll
+    for (int c = 0; c < B; ++c) sum[c] = (T)0;
+    constexpr int U = ROWV ? (W == 15 ? 5 : 4) : W;
+#pragma unroll
+    for (int q0 = 0; q0 < W; q0 += U) {
+      V x[U];
+      T av[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int q = q0 + u;
+        av[u] = ROWV ? sval[((int64_t)sl * stride + q) * 64 + lane] : sval[(int64_t)sl * stride + q];
+        uint32_t pair = at[k][q >> 1];
+        // (the places are unpacked here; unpacked once for all steps, which
+        // the two products of a step invite, they take too many registers)
+        if (O4) asm("" : "+v"(pair) : "s"(j));
+        x[u] = src[q & 1 ? pair >> 16 : pair & 0xFFFFu];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int c = 0; c < B; ++c) sum[c] = fma(av[u], x[u].v[c], sum[c]);
+    }
+  };
   int cur = 0;
   for (int j = 0; j < s; ++j) {
     const T wn = wt(j + 1);
     // the slices the later steps still read
-    const int a0 = o0 - (s - 1 - j) * hb, a1 = o1 + (s - 1 - j) * hb;
-    const V* __restrict__ src = lds + cur * step2;
-    V* __restrict__ dst = lds + (cur ^ 1) * step2;
+    const int a0 = o0 - (s - 1 - j) * reach, a1 = o1 + (s - 1 - j) * reach;
+    const V* __restrict__ src = lds + (O4 ? step2 : cur * step2);
+    V* __restrict__ dst = lds + (O4 ? 0 : (cur ^ 1) * step2);
+    if constexpr (O4) {
+      V* __restrict__ z = lds + step2;
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        const int sl = w0 + wave + 16 * k;
+        if (sl >= w1 || sl < a0 - hb || sl >= a1 + hb) continue;
+        V o;
+        product(k, sl, dst, j, o.v);
+        z[sl * 64 + lane - w0 * 64] = o;
+      }
+      __syncthreads();
+    }
 #pragma unroll
     for (int k = 0; k < R; ++k) {
       const int sl = w0 + wave + 16 * k;
       if (sl >= w1 || sl < a0 || sl >= a1) continue;
       V nx;
       T sum[B];
+      product(k, sl, src, j, sum);
+      if constexpr (O4) {
+        constexpr T twelfth = (T)(1.0 / 12.0);
+        const V z = src[sl * 64 + lane - w0 * 64];
 #pragma unroll
-      for (int c = 0; c < B; ++c) sum[c] = (T)0;
-      constexpr int U = ROWV ? (W == 15 ? 5 : 4) : W;
+        for (int c = 0; c < B; ++c) nx.v[c] = fma(twelfth, sum[c], (T)2 * yc[k].v[c] - yp[k].v[c] - z.v[c]);
+      } else {
 #pragma unroll
-      for (int q0 = 0; q0 < W; q0 += U) {
-        V x[U];
-        T av[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int q = q0 + u;
-          av[u] = ROWV ? sval[((int64_t)sl * stride + q) * 64 + lane] : sval[(int64_t)sl * stride + q];
-          x[u] = src[q & 1 ? at[k][q >> 1] >> 16 : at[k][q >> 1] & 0xFFFFu];
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-          for (int c = 0; c < B; ++c) sum[c] = fma(av[u], x[u].v[c], sum[c]);
+        for (int c = 0; c < B; ++c) nx.v[c] = (T)2 * yc[k].v[c] - yp[k].v[c] - sum[c];
       }
 #pragma unroll
-      for (int c = 0; c < B; ++c) {
-        nx.v[c] = (T)2 * yc[k].v[c] - yp[k].v[c] - sum[c];
-        ra[k].v[c] = fma(wn, nx.v[c], ra[k].v[c]);
-      }
+      for (int c = 0; c < B; ++c) ra[k].v[c] = fma(wn, nx.v[c], ra[k].v[c]);
       yp[k] = yc[k];
       yc[k] = nx;
       dst[sl * 64 + lane - w0 * 64] = nx;
@@ -153,7 +186,7 @@ __device__ __forceinline__ void steps_body(int32_t n, int32_t nslices, const T* 
   }
 }
 
-template <typename T, int B, int W, int R, bool ROWV>
+template <typename T, int B, int W, int R, bool ROWV, bool O4>
 __global__ __launch_bounds__(1024) void k_steps_st(int32_t n, int32_t nslices, const T* __restrict__ sval,
                                                    const int32_t* __restrict__ soff, const uint64_t* __restrict__ smask,
                                                    const T* ysrc, const T* i0, const T* i1, T* o0g, T* o1g, T* acc,
@@ -161,7 +194,7 @@ __global__ __launch_bounds__(1024) void k_steps_st(int32_t n, int32_t nslices, c
                                                    int groups, StepWeights w, int s, int own, int hb, int first,
                                                    int last) {
   const int o0 = xcd_map(blockIdx.x, gridDim.x) * own;
-  steps_body<T, B, W, R, ROWV>(n, nslices, sval, soff, smask, W, ysrc, i0, i1, o0g, o1g, acc, rout, rs, cs, bout,
+  steps_body<T, B, W, R, ROWV, O4>(n, nslices, sval, soff, smask, W, ysrc, i0, i1, o0g, o1g, acc, rout, rs, cs, bout,
                                groups, [&](int j) { return (T)w.w[j]; }, s, o0, min(nslices, o0 + own), hb, first != 0,
                                last != 0);
 }
@@ -189,7 +222,7 @@ __global__ __launch_bounds__(1024) void k_steps_batch(const BatchWg* __restrict_
   const int64_t so = (int64_t)g.slice0 * stride, in = (row0 - ibase) * b, out = (row0 - obase) * b;
   const T* __restrict__ wq = wtab + (int64_t)g.p * lmax + l0;
   const auto run = [&](auto width) {
-    steps_body<T, B, decltype(width)::value, R, false>(
+    steps_body<T, B, decltype(width)::value, R, false, false>(
         tb->n[g.p], g.nslices, sval + so, soff + so, smask + so, stride, ysrc + row0 * b, i0 + in, i1 + in, o0 + out,
         o1 + out, acc + row0 * b, tb->dst[g.p], tb->drs[g.p], tb->ld[g.p], tb->bout[g.p], groups,
         [&](int j) { return wq[j]; }, min(g.s, left), g.o0, min(g.nslices, g.o0 + g.own), g.hb, i == 0, left <= g.s);
@@ -213,13 +246,13 @@ struct StepsArgs {
   bool first, last;
 };
 
-template <typename T, int B, int W, int R, bool ROWV>
+template <typename T, int B, int W, int R, bool ROWV, bool O4>
 int launch_steps_r(const SellOp& A, const StepsPlan& pl, const StepsArgs& g, const StepWeights& w, hipStream_t st) {
-  const int win = std::min(A.nslices, pl.own + 2 * g.s * pl.hb);
+  const int win = std::min(A.nslices, pl.own + 2 * g.s * pl.reach());
   const size_t lds = (size_t)2 * (win * 64 + 1) * B * sizeof(T);
-  KF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_steps_st<T, B, W, R, ROWV>),
+  KF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_steps_st<T, B, W, R, ROWV, O4>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL((k_steps_st<T, B, W, R, ROWV>), dim3(ceil_div64(A.nslices, pl.own), g.groups), dim3(1024), lds, st, A.n,
+  hipLaunchKernelGGL((k_steps_st<T, B, W, R, ROWV, O4>), dim3(ceil_div64(A.nslices, pl.own), g.groups), dim3(1024), lds, st, A.n,
                      A.nslices, static_cast<const T*>(A.st.val), A.st.off, A.st.mask, static_cast<const T*>(g.ysrc),
                      static_cast<const T*>(g.i0), static_cast<const T*>(g.i1), static_cast<T*>(g.o0),
                      static_cast<T*>(g.o1), static_cast<T*>(g.acc), g.rout, g.rs, g.cs, g.bout, g.groups, w, g.s, pl.own,
@@ -228,26 +261,35 @@ int launch_steps_r(const SellOp& A, const StepsPlan& pl, const StepsArgs& g, con
   return KF_OK;
 }
 
-template <typename T, int B, int W, bool ROWV>
+template <typename T, int B, int W, bool ROWV, bool O4>
 int launch_steps_w(const SellOp& A, const StepsPlan& pl, const StepsArgs& g, const StepWeights& w, hipStream_t st) {
-  const int per = (std::min(A.nslices, pl.own + 2 * g.s * pl.hb) + 15) / 16;  // slices of a wavefront
-  if (per <= 2) return launch_steps_r<T, B, W, 2, ROWV>(A, pl, g, w, st);
+  const int per = (std::min(A.nslices, pl.own + 2 * g.s * pl.reach()) + 15) / 16;  // slices of a wavefront
+  if (per <= 2) return launch_steps_r<T, B, W, 2, ROWV, O4>(A, pl, g, w, st);
   constexpr int RM = steps_max_r(B * sizeof(T), ROWV ? W : 0);
   if constexpr (RM > 2) {
-    if (RM == 4 || per <= 4) return launch_steps_r<T, B, W, 4, ROWV>(A, pl, g, w, st);
-    return launch_steps_r<T, B, W, RM, ROWV>(A, pl, g, w, st);
+    if (RM == 4 || per <= 4) return launch_steps_r<T, B, W, 4, ROWV, O4>(A, pl, g, w, st);
+    return launch_steps_r<T, B, W, RM, ROWV, O4>(A, pl, g, w, st);
   }
   set_error("several steps per launch: window too wide");
   return KF_EINVAL;
 }
 
-template <typename T, int B>
+template <typename T, int B, bool O4>
 int launch_steps_b(const SellOp& A, const StepsPlan& pl, const StepsArgs& g, const StepWeights& w, hipStream_t st) {
   if (A.st.row_values)
-    return A.st.stride == 15 ? launch_steps_w<T, B, 15, true>(A, pl, g, w, st)
-                             : launch_steps_w<T, B, 8, true>(A, pl, g, w, st);
-  return A.st.stride == 5 ? launch_steps_w<T, B, 5, false>(A, pl, g, w, st)
-                          : launch_steps_w<T, B, 7, false>(A, pl, g, w, st);
+    return A.st.stride == 15 ? launch_steps_w<T, B, 15, true, O4>(A, pl, g, w, st)
+                             : launch_steps_w<T, B, 8, true, O4>(A, pl, g, w, st);
+  return A.st.stride == 5 ? launch_steps_w<T, B, 5, false, O4>(A, pl, g, w, st)
+                          : launch_steps_w<T, B, 7, false, O4>(A, pl, g, w, st);
+}
+
+template <bool O4>
+int launch_steps_o(const SellOp& A, const StepsPlan& pl, int cols, const StepsArgs& g, const StepWeights& w,
+                   hipStream_t st) {
+  if (A.val_bytes == 8)
+    return cols == 1 ? launch_steps_b<double, 1, O4>(A, pl, g, w, st) : launch_steps_b<double, 2, O4>(A, pl, g, w, st);
+  if (cols == 1) return launch_steps_b<float, 1, O4>(A, pl, g, w, st);
+  return cols == 2 ? launch_steps_b<float, 2, O4>(A, pl, g, w, st) : launch_steps_b<float, 4, O4>(A, pl, g, w, st);
 }
 }  // namespace
 
@@ -269,9 +311,7 @@ int launch_steps(const SellOp& A, const StepsPlan& pl, int b, int s, bool first,
   }
   const int cols = std::min(b, 16 / A.val_bytes);
   const StepsArgs g{ysrc, i0, i1, o0, o1, acc, rout, rs, cs, bout, b / cols, s, first, last};
-  if (A.val_bytes == 8) return cols == 1 ? launch_steps_b<double, 1>(A, pl, g, w, st) : launch_steps_b<double, 2>(A, pl, g, w, st);
-  if (cols == 1) return launch_steps_b<float, 1>(A, pl, g, w, st);
-  return cols == 2 ? launch_steps_b<float, 2>(A, pl, g, w, st) : launch_steps_b<float, 4>(A, pl, g, w, st);
+  return pl.order4 ? launch_steps_o<true>(A, pl, cols, g, w, st) : launch_steps_o<false>(A, pl, cols, g, w, st);
 }
 
 // The rule: the time of a filter application by the figures measured on
@@ -281,7 +321,9 @@ int launch_steps(const SellOp& A, const StepsPlan& pl, int b, int s, bool first,
 //   one of its steps  0.12 + 0.014 per slice computed (0.022), 15 % more with
 //                   more than four slices per wavefront
 // with at most one workgroup per compute unit, against 4.0 per step of a
-// launch of its own, which larger problems exceed.  The plan is taken where it
+// launch of its own, which larger problems exceed, and 7.0 per fourth-order
+// step of two launches (5.7 to 8.5 measured, as the host keeps up), which is
+// two products here: the 33-cell cube takes 6.9 so and is left to them.  The plan is taken where it
 // is at least 15 % better; e.g. the 600-cell square in float32 (4 steps, 2.55
 // us each) and the 33-cell cube (3 steps, 3.1 us) are, the 48-cell cube, whose
 // band is 35 slices, is not.  With row values (horns of 5 to 16 cells, jittered
@@ -291,22 +333,27 @@ int launch_steps(const SellOp& A, const StepsPlan& pl, int b, int s, bool first,
 // fewer compute units to each: 5 x 109-cell horn, one vector in float64, 4.0 ->
 // 1.4 us a step; 16 x 200 cells 4.2 -> 3.3, its block of 16 in float32 not.
 namespace {
-StepsPlan plan_of(int ns, int hb, bool rv, int stride, int val_bytes, int b, int L, size_t lds_bytes, int own_min) {
+StepsPlan plan_of(int ns, int hb, bool rv, int stride, int val_bytes, int b, int L, size_t lds_bytes, int own_min,
+                  bool order4) {
   StepsPlan best;
+  best.order4 = order4;
+  best.hb = hb;
   const int cols = std::min(b, 16 / val_bytes), groups = b / cols, rb = cols * val_bytes;
   const int win_max = std::min<int64_t>(16 * steps_max_r(rb, rv ? stride : 0), ((int64_t)lds_bytes / (2 * rb) - 1) / 64);
   const double load = rv || rb > 8 ? 0.06 : 0.03;
   const double slice = rv ? stride * (groups > 1 ? 0.008 : (val_bytes == 8 ? 0.0073 : 0.005)) : (rb > 8 ? 0.022 : 0.014);
-  double t_best = 0.85 * 4.0 * (L - 1);
+  const int reach = best.reach();
+  double t_best = 0.85 * (order4 ? 7.0 : 4.0) * (L - 1);
   if (L < 3 || own_min > win_max || groups > kCus) return best;
   for (int i = 0; i < 4; ++i) {
     const int own = i == 3 ? ns : std::min(ns, own_min << i);
     const bool whole = own >= ns;
     for (int s = 1; s <= std::min(kStepsMax, L - 1); ++s) {
-      const int win = std::min(ns, own + 2 * s * hb);
+      const int win = std::min(ns, own + 2 * s * reach);
       if (win > win_max) break;
-      const double avg = std::min<double>(ns, own + (double)(s - 1) * hb);
+      const double avg = std::min<double>(ns, own + (double)(s - 1) * reach);
       double step = (rv ? 0.0 : 0.12) + slice * avg;
+      if (order4) step += (rv ? 0.0 : 0.12) + slice * std::min<double>(ns, avg + 2.0 * hb);
       if (win > 64) step *= 1.15;
       const int launches = (L - 1 + s - 1) / s;
       const double t = launches * (3.7 + load * win) + (L - 1) * step;
@@ -314,7 +361,6 @@ StepsPlan plan_of(int ns, int hb, bool rv, int stride, int val_bytes, int b, int
         t_best = t;
         best.s = s;
         best.own = whole ? ns : own;
-        best.hb = hb;
       }
     }
     if (whole) break;
@@ -323,11 +369,11 @@ StepsPlan plan_of(int ns, int hb, bool rv, int stride, int val_bytes, int b, int
 }
 }  // namespace
 
-StepsPlan plan_steps(const SellOp& A, int b, int L, size_t lds_bytes) {
+StepsPlan plan_steps(const SellOp& A, int b, int L, size_t lds_bytes, bool order4) {
   if (!has_steps(A.st)) return StepsPlan();
   const int groups = b / std::min(b, 16 / A.val_bytes);
   return plan_of(A.nslices, (A.max_off + 63) / 64, A.st.row_values, A.st.stride, A.val_bytes, b, L, lds_bytes,
-                 (int)ceil_div64((int64_t)A.nslices * groups, kCus));
+                 (int)ceil_div64((int64_t)A.nslices * groups, kCus), order4);
 }
 
 // Members of a batch side by side in one launch: each as alone, with so many
@@ -341,7 +387,7 @@ std::vector<StepsPlan> plan_batch(const std::vector<BatchMember>& m, int val_byt
   for (int own_min = std::max(1, (int)ceil_div64(total * groups, kCus));; ++own_min) {
     int64_t wgs = 0;
     for (size_t i = 0; i < m.size(); ++i) {
-      plans[i] = plan_of(m[i].nslices, m[i].hb, false, 0, val_bytes, b, m[i].L, lds_bytes, own_min);
+      plans[i] = plan_of(m[i].nslices, m[i].hb, false, 0, val_bytes, b, m[i].L, lds_bytes, own_min, false);
       if (plans[i].s == 0) return {};
       wgs += (int64_t)ceil_div64(m[i].nslices, plans[i].own) * groups;
     }

@@ -179,3 +179,35 @@ def test_several_steps_per_launch_with_row_values_bitwise(kind, b, precision):
                 P.apply_filter_noalloc(x, y)
                 assert torch.equal(y, out[0]), L
         assert torch.equal(out[0], out[1]), (L, (out[0] - out[1]).abs().max())
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("b", [1, 3, 4, 16])
+@pytest.mark.parametrize(
+    "kind",
+    # one workgroup; several with halos of one, a few and many slices; a value
+    # per row with 7 and 15 offsets
+    ["grid2_5", "grid2_33", "grid2_64", "grid2_140", "grid2_257", "grid3_9", "grid3_20", "grid3_27", "jitter2_40",
+     "jitter3_9", "horn"],
+)
+def test_several_fourth_order_steps_per_launch_bitwise(kind, b, precision):
+    """As above for the fourth-order step, whose two products take twice the
+    halo: against two launches per step over the stored entries."""
+    import torch
+
+    from paper_2402_08515_amd import kf
+
+    print(f"case fourth-order steps {kind} b={b} {precision}", flush=True)
+    S, m = _matrix(kind)
+    tau = 1.8 / np.sqrt(np.abs(S).sum(1).max() / m.min())
+    x = torch.from_numpy(start_block(S.shape[0], b, 13)).cuda()
+    for L in (3, 24, 70):  # one launch, several, a remainder
+        out = []
+        for ib in (0, 4):
+            P = kf.Problem(S, m, 0.3 / tau, 0.5 / tau, tau, L, precision=precision, index_bytes=ib, stepper=4)
+            out.append(P.apply_filter(x))
+            if ib == 0:
+                y = torch.empty_like(x)
+                P.apply_filter_noalloc(x, y)
+                assert torch.equal(y, out[0]), L
+        assert torch.equal(out[0], out[1]), (L, (out[0] - out[1]).abs().max())
