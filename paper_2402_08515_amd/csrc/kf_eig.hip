@@ -465,6 +465,7 @@ __global__ __launch_bounds__(256) void k_tri_wave(int m, int k, double* __restri
 // sums.  Three barriers and the LDS traffic of the matrix per reflector, 2.6 us
 // on average, against 3.6 us for a launch of k_tri_wave.
 constexpr int kTriTail = 128;
+constexpr size_t tri_tail_lds(int n) { return sizeof(double) * ((size_t)n * n + 5 * kTriTail + 8); }
 __global__ __launch_bounds__(1024) void k_tri_tail(int m, int k0, double* __restrict__ A, double* __restrict__ d,
                                                    double* __restrict__ e, double* __restrict__ tau,
                                                    const double* __restrict__ pv) {
@@ -737,6 +738,7 @@ __global__ __launch_bounds__(256) void k_bisect(int m, const double* __restrict_
 // divisions per row, several lanes' arrays interleaved and separate passes for
 // the norms, 232 us so.
 constexpr int kIvB = 8;
+constexpr int kEigMax = 2048;  // largest order
 // doubles of LDS: five arrays and one flag word per kIvB rows
 __host__ __device__ constexpr int invit_doubles(int m) { return 5 * m + (m / kIvB + 2) / 2 + 1; }
 __global__ __launch_bounds__(64) void k_invit(int m, const double* __restrict__ d, const double* __restrict__ e,
@@ -1085,7 +1087,7 @@ int eig_reserve(EigWork& w, int m, int nsel) {
 
 int eig_values(EigWork& w, int k, const double* H, int64_t ldh, hipStream_t st) {
   if (k < 1) return KF_OK;
-  if (k > 2048) {
+  if (k > kEigMax) {
     set_error("eigensolver: projected pencil larger than 2048");
     return KF_EINVAL;
   }
@@ -1101,9 +1103,9 @@ int eig_values(EigWork& w, int k, const double* H, int64_t ldh, hipStream_t st) 
     const size_t lds = sizeof(double) * (3 * (size_t)k + 32);
     for (int j = 0; j + 2 <= k; ++j) {
       if (j >= 1 && k - j <= kTriTail) {
-        const size_t tail = sizeof(double) * ((size_t)(k - j) * (k - j) + 5 * kTriTail + 8);
+        const size_t tail = tri_tail_lds(k - j);
         KF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tri_tail),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)tail));
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)tri_tail_lds(kTriTail)));
         hipLaunchKernelGGL(k_tri_tail, dim3(1), dim3(1024), tail, st, k, j, w.A, w.d, w.e, w.tau, w.pv);
         KF_HIP(hipGetLastError());
         break;
@@ -1140,9 +1142,9 @@ int eig_vectors(EigWork& w, int k, const double* theta_sel, const int32_t* clust
   KF_HIP(hipMemcpyAsync(w.sel, theta_sel, sizeof(double) * nsel, hipMemcpyHostToDevice, st));
   KF_HIP(hipMemcpyAsync(w.cl, cluster_start, sizeof(int32_t) * (nclusters + 1), hipMemcpyHostToDevice, st));
   const size_t lds = sizeof(double) * (size_t)invit_doubles(k);
-  if (lds > 65536)
+  if (lds > 65536)  // (the limit of every order: other threads launch this kernel too)
     KF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_invit), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)lds));
+                               (int)(sizeof(double) * invit_doubles(kEigMax))));
   hipLaunchKernelGGL(k_invit, dim3(nsel), dim3(64), lds, st, k, w.d, w.e, w.bounds, nclusters, w.cl, w.sel, w.Z);
   KF_HIP(hipGetLastError());
   if (nclusters < nsel) {

@@ -246,12 +246,17 @@ struct StepsArgs {
   bool first, last;
 };
 
+// The dynamic LDS any launch of a form with R slices per wavefront asks for:
+// its limit is set to this whatever the launch needs, as other threads launch
+// the same kernels.
+constexpr int steps_lds_limit(int r, size_t rb) { return (int)std::min<size_t>(160 << 10, 2 * (16 * r * 64 + 1) * rb); }
+
 template <typename T, int B, int W, int R, bool ROWV, bool O4>
 int launch_steps_r(const SellOp& A, const StepsPlan& pl, const StepsArgs& g, const StepWeights& w, hipStream_t st) {
   const int win = std::min(A.nslices, pl.own + 2 * g.s * pl.reach());
   const size_t lds = (size_t)2 * (win * 64 + 1) * B * sizeof(T);
   KF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_steps_st<T, B, W, R, ROWV, O4>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+                             hipFuncAttributeMaxDynamicSharedMemorySize, steps_lds_limit(R, sizeof(T) * B)));
   hipLaunchKernelGGL((k_steps_st<T, B, W, R, ROWV, O4>), dim3(ceil_div64(A.nslices, pl.own), g.groups), dim3(1024), lds, st, A.n,
                      A.nslices, static_cast<const T*>(A.st.val), A.st.off, A.st.mask, static_cast<const T*>(g.ysrc),
                      static_cast<const T*>(g.i0), static_cast<const T*>(g.i1), static_cast<T*>(g.o0),
@@ -409,7 +414,7 @@ int launch_steps_batch_b(const SellOp& A, const BatchWg* wgs, int nwg, int win, 
 #define KF_SB(R)                                                                                                     \
   do {                                                                                                               \
     KF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_steps_batch<T, B, R>),                               \
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));                               \
+                               hipFuncAttributeMaxDynamicSharedMemorySize, steps_lds_limit(R, sizeof(T) * B)));        \
     hipLaunchKernelGGL((k_steps_batch<T, B, R>), dim3(nwg, groups), dim3(1024), lds, st, wgs,                        \
                        static_cast<const T*>(A.st.val), A.st.off, A.st.mask, A.st.stride, tb,                        \
                        static_cast<const T*>(wtab), lmax, i, static_cast<const T*>(ysrc), static_cast<const T*>(i0), \
