@@ -110,9 +110,13 @@ int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d
                const double* d_row_scale, int val_bytes, int want_idx_bytes, hipStream_t st, SellOp& out,
                int stencil = kStencilNone);
 
+// The number of distinct offsets of every slice (negative: values differ
+// within an offset) into d_w[ns], and the stencil form from them (on the host).
+int launch_stencil_widths(int32_t n, int32_t ns, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
+                          const double* d_row_scale, int val_bytes, int32_t* d_w, hipStream_t st);
 int build_stencil(int32_t n, int32_t ns, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
-                  const double* d_row_scale, int val_bytes, int64_t nstored, int idx_bytes, bool exact, hipStream_t st,
-                  StencilOp& out);
+                  const double* d_row_scale, const int32_t* widths, int val_bytes, int64_t nstored, int idx_bytes,
+                  bool exact, hipStream_t st, StencilOp& out);
 
 // ---- fused leapfrog step ----------------------------------------------------
 enum StepMode { kMid = 0, kFirst = 1, kLast = 2, kFirstLast = 3, kMidAcc = 4 };

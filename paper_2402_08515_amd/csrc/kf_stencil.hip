@@ -443,29 +443,14 @@ namespace {
 // them with ib bytes of index) would.
 template <typename VT>
 int build_stencil_t(int32_t n, int32_t ns, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
-                    const double* d_row_scale, int64_t nstored, int ib, bool exact, hipStream_t st, StencilOp& out) {
+                    const double* d_row_scale, const int32_t* w, int64_t nstored, int ib, bool exact, hipStream_t st,
+                    StencilOp& out) {
   const int grid = ceil_div64(ns, 4);
-  int32_t* d_w = nullptr;
-  if (hipMalloc(&d_w, sizeof(int32_t) * (size_t)ns) != hipSuccess) {
-    set_error("build_sell: device allocation failed");
-    return KF_ENOMEM;
-  }
-  hipLaunchKernelGGL((k_stencil<VT, 0>), dim3(grid), dim3(256), 0, st, n, ns, d_rowptr, d_col, d_val, d_row_scale, d_w,
-                     0, (VT*)nullptr, (int32_t*)nullptr, (uint64_t*)nullptr);
-  std::vector<int32_t> w((size_t)ns);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = hipMemcpyAsync(w.data(), d_w, sizeof(int32_t) * (size_t)ns, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  (void)hipFree(d_w);
-  if (e != hipSuccess) {
-    set_error(std::string("build_sell: ") + hipGetErrorString(e));
-    return KF_EHIP;
-  }
   int width = 0;
   bool row_values = false;
-  for (int32_t v : w) {
-    width = std::max(width, std::abs(v));
-    row_values |= v < 0;
+  for (int32_t i = 0; i < ns; ++i) {
+    width = std::max(width, std::abs(w[i]));
+    row_values |= w[i] < 0;
   }
   if (width < 1 || width > kStencilMax) return KF_OK;
   // 5 and 7 entries (the 2D and 3D point stencils) and, with row values, 15
@@ -504,12 +489,24 @@ void free_stencil(StencilOp& s) {
   s = StencilOp();
 }
 
-int build_stencil(int32_t n, int32_t ns, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
-                  const double* d_row_scale, int val_bytes, int64_t nstored, int idx_bytes, bool exact, hipStream_t st,
-                  StencilOp& out) {
+int launch_stencil_widths(int32_t n, int32_t ns, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
+                          const double* d_row_scale, int val_bytes, int32_t* d_w, hipStream_t st) {
   if (val_bytes == 8)
-    return build_stencil_t<double>(n, ns, d_rowptr, d_col, d_val, d_row_scale, nstored, idx_bytes, exact, st, out);
-  return build_stencil_t<float>(n, ns, d_rowptr, d_col, d_val, d_row_scale, nstored, idx_bytes, exact, st, out);
+    hipLaunchKernelGGL((k_stencil<double, 0>), dim3(ceil_div64(ns, 4)), dim3(256), 0, st, n, ns, d_rowptr, d_col, d_val,
+                       d_row_scale, d_w, 0, (double*)nullptr, (int32_t*)nullptr, (uint64_t*)nullptr);
+  else
+    hipLaunchKernelGGL((k_stencil<float, 0>), dim3(ceil_div64(ns, 4)), dim3(256), 0, st, n, ns, d_rowptr, d_col, d_val,
+                       d_row_scale, d_w, 0, (float*)nullptr, (int32_t*)nullptr, (uint64_t*)nullptr);
+  KF_HIP(hipGetLastError());
+  return KF_OK;
+}
+
+int build_stencil(int32_t n, int32_t ns, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
+                  const double* d_row_scale, const int32_t* widths, int val_bytes, int64_t nstored, int idx_bytes,
+                  bool exact, hipStream_t st, StencilOp& out) {
+  if (val_bytes == 8)
+    return build_stencil_t<double>(n, ns, d_rowptr, d_col, d_val, d_row_scale, widths, nstored, idx_bytes, exact, st, out);
+  return build_stencil_t<float>(n, ns, d_rowptr, d_col, d_val, d_row_scale, widths, nstored, idx_bytes, exact, st, out);
 }
 
 int launch_stencil_step(const SellOp& A, int b, int mode, const void* cur, const void* prev, void* out, void* acc,

@@ -812,12 +812,22 @@ int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d
   }
   const int32_t ns = ceil_div64(n, kSlice);
   int32_t* d_stats = nullptr;
-  KF_HIP(hipMalloc(&d_stats, sizeof(int32_t) * 2 * (size_t)ns));
+  if (val_bytes != 4 && val_bytes != 8) {
+    set_error("build_sell: value width must be 4 or 8");
+    return KF_EINVAL;
+  }
+  const size_t nstat = (stencil ? 3 : 2) * (size_t)ns;  // widths, offsets and the stencils' widths
+  KF_HIP(hipMalloc(&d_stats, sizeof(int32_t) * nstat));
   const int grid = ceil_div64((int64_t)ns * kSlice, 256);
   hipLaunchKernelGGL(k_sell_stats, dim3(grid), dim3(256), 0, st, n, ns, d_rowptr, d_col, d_stats, d_stats + ns);
-  std::vector<int32_t> h(2 * (size_t)ns);
+  std::vector<int32_t> h(nstat);
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = hipMemcpyAsync(h.data(), d_stats, sizeof(int32_t) * 2 * ns, hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess && stencil &&
+      launch_stencil_widths(n, ns, d_rowptr, d_col, d_val, d_row_scale, val_bytes, d_stats + 2 * (size_t)ns, st)) {
+    (void)hipFree(d_stats);
+    return KF_EHIP;
+  }
+  if (e == hipSuccess) e = hipMemcpyAsync(h.data(), d_stats, sizeof(int32_t) * nstat, hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   (void)hipFree(d_stats);
   if (e != hipSuccess) {
@@ -841,10 +851,6 @@ int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d
   }
   if (ib != 2 && ib != 4) {
     set_error("build_sell: index width must be 0, 2 or 4");
-    return KF_EINVAL;
-  }
-  if (val_bytes != 4 && val_bytes != 8) {
-    set_error("build_sell: value width must be 4 or 8");
     return KF_EINVAL;
   }
   const int64_t tot = std::max<int64_t>(ptr[ns], kSlice);
@@ -877,8 +883,8 @@ int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d
                        d_col, d_val, d_row_scale, (float*)out.val, (int32_t*)out.idx);
   KF_HIP(hipGetLastError());
   if (stencil)
-    KF_TRY(build_stencil(n, ns, d_rowptr, d_col, d_val, d_row_scale, val_bytes, out.nstored, ib,
-                         stencil == kStencilExact, st, out.st));
+    KF_TRY(build_stencil(n, ns, d_rowptr, d_col, d_val, d_row_scale, h.data() + 2 * (size_t)ns, val_bytes, out.nstored,
+                         ib, stencil == kStencilExact, st, out.st));
   KF_HIP(hipStreamSynchronize(st));
   (void)nnz;
   return KF_OK;
