@@ -3297,7 +3297,9 @@ int member_widths(kf_batch* bt, const SellOp& A, std::vector<int>& width) {
 // wgs stays empty where one of the members is better off, or can only be
 // stepped, one step per launch, and where there is no memory for the buffers.
 int plan_many(kf_batch* bt, BatchStack& k, int bk, std::vector<BatchWg>& wgs, int& win, int& launches) {
-  if (bt->many.empty() || k.A.st.width == 0 || k.A.st.row_values) return KF_OK;
+  // (the kernel reads a slice's list to its own length, 5 or 7: shorter lists,
+  // stored in fours, are left to the one-step kernel)
+  if (bt->many.empty() || k.A.st.stride < kBatchStepsWidth || k.A.st.row_values) return KF_OK;
   std::vector<BatchMember> m;
   for (const kf_batch::Many& q : bt->many) m.push_back(q.m);
   const std::vector<StepsPlan> plans = plan_batch(m, k.A.val_bytes, bk, lds_per_workgroup());

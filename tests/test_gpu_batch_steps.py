@@ -3,7 +3,9 @@ launch, beside the members that take one, against the stored-entry form of the
 same batch (index_bytes fixed: one step per launch), bit for bit: the same
 operations in the same order, so no tolerance is needed."""
 
+import numpy as np
 import pytest
+import scipy.sparse as sp
 
 from synth import start_block
 from synth.grids import grid_problem, jittered_problem
@@ -14,12 +16,16 @@ pytestmark = pytest.mark.gpu
 # halos of one and of many slices, with no step, one step, less than a launch's
 # steps and several launches of them; "mixed" beside cubes too large for it,
 # "small" with no other member, "uneven" with a member whose slices hold a value
-# per row, which keeps the batch at one step per launch.
+# per row and "wide" with one that has more offsets than the stencil form takes,
+# which both keep the batch at one step per launch (of the members in two groups),
+# as lists shorter than the kernel's do ("chain", three offsets).
 BATCHES = {
     "mixed": [("square", 5, 3), ("square", 64, 60), ("cube", 52, 40), ("square", 91, 33), ("square", 64, 1),
               ("square", 33, 130), ("cube", 17, 24), ("square", 64, 2), ("cube", 40, 7), ("square", 187, 90)],
     "small": [("square", 140, 41), ("cube", 9, 66)],
     "uneven": [("square", 33, 12), ("jitter", 20, 21)],
+    "wide": [("square", 33, 12), ("band", 300, 21), ("square", 64, 30)],
+    "chain": [("chain", 300, 33), ("chain", 64, 12)],
 }
 
 
@@ -35,7 +41,12 @@ def test_batch_with_several_steps_per_launch_bitwise(name, b, precision):
     members = []
     for mesh, n, L in BATCHES[name]:
         dim = 3 if mesh == "cube" else 2
-        S, m = jittered_problem(2, n, 0.2, 3) if mesh == "jitter" else grid_problem(dim, n)[:2]
+        if mesh in ("band", "chain"):  # 33 offsets, 3
+            r = 16 if mesh == "band" else 1
+            S = sp.csr_matrix(sp.diags([4.0] + [-0.8 / r] * (2 * r), list(range(r + 1)) + list(range(-r, 0)), shape=(n, n)))
+            m = np.full(n, 0.5)
+        else:
+            S, m = jittered_problem(2, n, 0.2, 3) if mesh == "jitter" else grid_problem(dim, n)[:2]
         tau = 1.8 / (abs(S).sum(1).max() / m.min()) ** 0.5
         members.append((S, m, 0.3 / tau, 0.5 / tau, tau, L, 0))
     free = kf.Batch(members, precision=precision)
