@@ -37,7 +37,19 @@ void set_error(const std::string& msg) { g_err = msg; }
 using namespace kf;
 
 // time-stepping buffers (n x cap blocks)
+// The launches of a filter application that touch nothing but the step buffers,
+// recorded once for one operator, block width and set of weights.
+struct StepGraph {
+  hipGraph_t graph = nullptr;
+  hipGraphExec_t exec = nullptr;
+  const void* op = nullptr;  // the operator's stencil arrays
+  int bk = 0, remap = 0, lpr = 0;
+  std::vector<double> w;
+  bool failed = false;  // could not be recorded: not tried again
+};
+
 struct StepBufs {
+  StepGraph g;
   void* Y0 = nullptr;
   void* Y1 = nullptr;
   void* R = nullptr;
@@ -333,6 +345,12 @@ void dfree(void* p) {
   if (p) (void)hipFree(p);
 }
 
+void drop_graph(StepGraph& g) {
+  if (g.exec) (void)hipGraphExecDestroy(g.exec);
+  if (g.graph) (void)hipGraphDestroy(g.graph);
+  g = StepGraph();
+}
+
 int ensure_step_buffers(kf_problem* p, StepBufs& sb, int bk, int vb, bool second_pair = false) {
   const bool needz = p->opt.stepper == 4;
   const bool need23 = second_pair || (p->opt.multistep != 0 && bk == 1);
@@ -343,6 +361,7 @@ int ensure_step_buffers(kf_problem* p, StepBufs& sb, int bk, int vb, bool second
   dfree(sb.Z);
   dfree(sb.Y2);
   dfree(sb.Y3);
+  drop_graph(sb.g);  // (the frees have waited for its last launch)
   sb = StepBufs();
   const size_t bytes = (size_t)p->n * bk * vb;
   if (hipMalloc(&sb.Y0, bytes) != hipSuccess || hipMalloc(&sb.Y1, bytes) != hipSuccess ||
@@ -413,6 +432,7 @@ void free_step_buffers(StepBufs& sb) {
   dfree(sb.Z);
   dfree(sb.Y2);
   dfree(sb.Y3);
+  drop_graph(sb.g);  // (the frees have waited for its last launch)
   sb = StepBufs();
 }
 
@@ -447,6 +467,57 @@ int device_weights(kf_problem* p, const std::vector<double>& w, const double** o
   }
   *out = p->d_w;
   return KF_OK;
+}
+
+// The recorded steps 3 .. L - 2 of an application (step(l, stream) launches
+// one), or null: launch them.  The host needs 3 to 4 us for a launch, a small
+// problem's step 2.4 to 3: replayed, 39 steps of the 41-cell cube take 97
+// instead of 147 us (107 instead of 225 where each application is waited for),
+// its fourth-order steps in blocks of 3 232 instead of 339, 60 cells 132
+// instead of 155; where a level has 7 MB (96 cells) the steps outlast the
+// host, 284 and 290.  Recorded at the second application with the same
+// weights: a single one does not pay for it.
+template <class Step>
+hipGraphExec_t step_graph(kf_problem* p, const SellOp& A, StepBufs& sb, int bk, const std::vector<double>& w,
+                          const Step& step) {
+  constexpr int kMinSteps = 8;
+  constexpr int64_t kMaxLevel = 4 << 20;
+  const int L = (int)w.size();
+  if (A.st.width == 0 || L - 4 < kMinSteps || (int64_t)A.n * bk * A.val_bytes > kMaxLevel) return nullptr;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(p->st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return nullptr;  // the caller records these launches
+  }
+  StepGraph& g = sb.g;
+  int lb = 0;
+  while ((1 << lb) < bk) ++lb;
+  if (g.op != A.st.mask || g.bk != bk || g.remap != p->opt.xcd_remap || g.lpr != A.lpr[lb] || g.w != w) {
+    if (g.exec) (void)hipStreamSynchronize(p->st);
+    drop_graph(g);
+    g.op = A.st.mask;
+    g.bk = bk;
+    g.remap = p->opt.xcd_remap;
+    g.lpr = A.lpr[lb];
+    g.w = w;
+    return nullptr;
+  }
+  if (g.exec || g.failed) return g.exec;
+  // on a stream of its own: the problem's may be the default stream, which
+  // cannot be recorded
+  hipStream_t cap = nullptr;
+  g.failed = true;
+  if (hipStreamCreateWithFlags(&cap, hipStreamNonBlocking) == hipSuccess &&
+      hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) == hipSuccess) {
+    int rc = KF_OK;
+    for (int l = 3; l <= L - 2 && rc == KF_OK; ++l) rc = step(l, cap);
+    const bool ended = hipStreamEndCapture(cap, &g.graph) == hipSuccess;
+    g.failed = rc != KF_OK || !ended || hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0) != hipSuccess;
+    if (g.failed) g.exec = nullptr;
+  }
+  if (cap) (void)hipStreamDestroy(cap);
+  if (g.failed) (void)hipGetLastError();
+  return g.exec;
 }
 
 // C applied to bsrc columns of src (strides srs between rows, scs between
@@ -513,19 +584,28 @@ int run_filter(kf_problem* p, const SellOp& A, StepBufs& sb, const double* src, 
   }
   void* Y[2] = {sb.Y0, sb.Y1};
   auto wt = [&](int i) { return i < 0 ? 0.0 : w[(size_t)i]; };
-  for (int l = 1; l < L; ++l) {
+  auto step = [&](int l, hipStream_t on) {
     const StepPlan sp = step_plan(l, L);
     // step l reads y_l (cur) and y_{l-1} (prev) and writes y_{l+1} over
     // y_{l-1}, except at l = 2 where y_1 is the source itself
     const void* cur = l == 1 ? y0 : Y[l & 1];
     void* nxt = Y[(l + 1) & 1];
     const void* prv = l == 2 ? y0 : nxt;
+    double* out = l == L - 1 ? dst : nullptr;
     if (p->opt.stepper == 4)
-      KF_TRY(launch_leapfrog4(A, bk, sp.mode, cur, prv, nxt, sb.R, sb.Z, dst, drs, dcs, bout, wt(sp.ip), wt(sp.ic),
-                              wt(sp.in), p->opt.xcd_remap, st));
-    else
-      KF_TRY(launch_leapfrog(A, bk, sp.mode, cur, prv, nxt, sb.R, dst, drs, dcs, bout, wt(sp.ip), wt(sp.ic),
-                             wt(sp.in), p->opt.xcd_remap, st));
+      return launch_leapfrog4(A, bk, sp.mode, cur, prv, nxt, sb.R, sb.Z, out, drs, dcs, bout, wt(sp.ip), wt(sp.ic),
+                              wt(sp.in), p->opt.xcd_remap, on);
+    return launch_leapfrog(A, bk, sp.mode, cur, prv, nxt, sb.R, out, drs, dcs, bout, wt(sp.ip), wt(sp.ic), wt(sp.in),
+                           p->opt.xcd_remap, on);
+  };
+  hipGraphExec_t exec = nullptr;
+  if (may_alloc) exec = step_graph(p, A, sb, bk, w, step);
+  for (int l = 1; l < L; ++l) {
+    if (exec && l == 3) {
+      KF_HIP(hipGraphLaunch(exec, st));
+      l = L - 1;
+    }
+    KF_TRY(step(l, st));
   }
   return KF_OK;
 }
