@@ -480,10 +480,8 @@ int device_weights(kf_problem* p, const std::vector<double>& w, const double** o
 template <class Step>
 hipGraphExec_t step_graph(kf_problem* p, const SellOp& A, StepBufs& sb, int bk, const std::vector<double>& w,
                           const Step& step) {
-  constexpr int kMinSteps = 8;
-  constexpr int64_t kMaxLevel = 4 << 20;
   const int L = (int)w.size();
-  if (A.st.width == 0 || L - 4 < kMinSteps || (int64_t)A.n * bk * A.val_bytes > kMaxLevel) return nullptr;
+  if (A.st.width == 0 || !step_replay(A.n, bk, A.val_bytes, L)) return nullptr;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(p->st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
     (void)hipGetLastError();
@@ -530,7 +528,7 @@ int run_filter(kf_problem* p, const SellOp& A, StepBufs& sb, const double* src, 
   hipStream_t st = p->st;
   if (L == 1) return launch_scale_copy(p->n, bout, std::min(bsrc, bout), src, srs, scs, w[0], dst, drs, dcs, st);
   StepsPlan steps;
-  if (p->opt.multistep == 0 && A.st.width > 0) steps = plan_steps(A, bk, L, lds_per_workgroup(), p->opt.stepper == 4);
+  if (p->opt.multistep == 0 && A.st.width > 0) steps = plan_steps(A, bk, L, lds_per_workgroup(), p->opt.stepper == 4, may_alloc);
   if (may_alloc) {
     KF_TRY(ensure_step_buffers(p, sb, bk, A.val_bytes, steps.s > 0 && steps.own < A.nslices && steps.s < L - 1));
   } else if (sb.cap < bk || sb.vb != A.val_bytes || !sb.Y0 || !sb.Y1 || !sb.R || (p->opt.stepper == 4 && !sb.Z)) {
@@ -1835,7 +1833,7 @@ int tune_block(kf_problem* p, SellOp& A, StepBufs& sb, int bk) {
   if (A.lpr_tuned & (1 << lb)) return KF_OK;
   // (several steps per launch have no such choice)
   if (p->opt.multistep == 0 && A.st.width > 0 &&
-      plan_steps(A, bk, p->L, lds_per_workgroup(), p->opt.stepper == 4).s > 0)
+      plan_steps(A, bk, p->L, lds_per_workgroup(), p->opt.stepper == 4, true).s > 0)
     return KF_OK;
   double best = 1e300;
   int best_l = 1, best_b = 0;

@@ -187,7 +187,12 @@ struct StepsPlan {
   bool order4 = false;  // fourth-order steps
   int reach() const { return order4 ? 2 * hb : hb; }  // slices a step reaches
 };
-StepsPlan plan_steps(const SellOp& A, int b, int L, size_t lds_bytes, bool order4);
+StepsPlan plan_steps(const SellOp& A, int b, int L, size_t lds_bytes, bool order4, bool replay);
+// Whether an application's one-step launches are replayed from a recording
+// (where the caller's path may record at all): enough of them, and short ones.
+inline bool step_replay(int32_t n, int b, int val_bytes, int L) {
+  return L - 4 >= 8 && (int64_t)n * b * val_bytes <= (4 << 20);
+}
 int launch_steps(const SellOp& A, const StepsPlan& pl, int b, int s, bool first, bool last, const void* ysrc,
                  const void* i0, const void* i1, void* o0, void* o1, void* acc, double* rout, int64_t rs, int64_t cs,
                  int bout, const StepWeights& w, hipStream_t st);

@@ -325,30 +325,35 @@ int launch_steps(const SellOp& A, const StepsPlan& pl, int b, int s, bool first,
 //   a launch        3.7 + 0.03 per slice of the window (0.06 for 16-byte rows)
 //   one of its steps  0.12 + 0.014 per slice computed (0.022), 15 % more with
 //                   more than four slices per wavefront
-// with at most one workgroup per compute unit, against 4.0 per step of a
-// launch of its own, which larger problems exceed, and 7.0 per fourth-order
-// step of two launches (5.7 to 8.5 measured, as the host keeps up), which is
-// two products here: the 33-cell cube takes 6.9 so and is left to them.  The plan is taken where it
-// is at least 15 % better; e.g. the 600-cell square in float32 (4 steps, 2.55
-// us each) and the 33-cell cube (3 steps, 3.1 us) are, the 48-cell cube, whose
-// band is 35 slices, is not.  With row values (horns of 5 to 16 cells, jittered
-// squares and cubes, within 20 %) a launch takes 3.7 + 0.06 per slice of the
-// window, whose values it reads, and a step per slice and entry 0.0073 in
-// float64, 0.005 in float32, 0.008 with several groups of columns, which leave
-// fewer compute units to each: 5 x 109-cell horn, one vector in float64, 4.0 ->
-// 1.4 us a step; 16 x 200 cells 4.2 -> 3.3, its block of 16 in float32 not.
+// with at most one workgroup per compute unit, and 0.035 (0.02) more per slice of
+// the window for each further group of columns, which reads a part of every
+// row.  The plan is taken where it is at least 10 % below one step per launch,
+// us a step (MB: of a level, n b values):
+//   replayed from a recording (step_replay)  2.1 + 0.4 MB, with row values 2.75
+//     in float64 and 2.45 in float32 instead of 2.1; fourth-order steps, two
+//     launches each, 4.1 + 0.7 MB, with row values 5.6 and 4.85
+//   else at least what the host needs: 3.8 a launch
+// E.g. (taken | left, us a step so and with one step per launch) 23-cell cube
+// 2.16 and 2.20 | 26 cells 2.43 and 2.22, 33 cells 3.15 and 2.25; the 400-cell
+// square, one vector 2.08 and 2.62 | its block of 4 in float32 3.16 and 2.92;
+// 20-cell cube, block of 4 in float32 | 2.32 and 2.28; horn of 11 x 34 cells
+// 2.28 and 2.72 | 16 x 60 cells 3.02 and 2.73.
+// With row values (horns of 5 to 16 cells, jittered squares and cubes, within
+// 20 %) a launch takes 3.7 + 0.06 per slice of the window, whose values it
+// reads, and a step per slice and entry 0.0073 in float64, 0.005 in float32,
+// 0.008 with several groups of columns, which leave fewer compute units to each.
 namespace {
 StepsPlan plan_of(int ns, int hb, bool rv, int stride, int val_bytes, int b, int L, size_t lds_bytes, int own_min,
-                  bool order4) {
+                  bool order4, double step_us) {
   StepsPlan best;
   best.order4 = order4;
   best.hb = hb;
   const int cols = std::min(b, 16 / val_bytes), groups = b / cols, rb = cols * val_bytes;
   const int win_max = std::min<int64_t>(16 * steps_max_r(rb, rv ? stride : 0), ((int64_t)lds_bytes / (2 * rb) - 1) / 64);
-  const double load = rv || rb > 8 ? 0.06 : 0.03;
+  const double load = (rv || rb > 8 ? 0.06 : 0.03) + (rv ? 0.02 : 0.035) * (groups - 1);
   const double slice = rv ? stride * (groups > 1 ? 0.008 : (val_bytes == 8 ? 0.0073 : 0.005)) : (rb > 8 ? 0.022 : 0.014);
   const int reach = best.reach();
-  double t_best = 0.85 * (order4 ? 7.0 : 4.0) * (L - 1);
+  double t_best = step_us * (L - 1);
   if (L < 3 || own_min > win_max || groups > kCus) return best;
   for (int i = 0; i < 4; ++i) {
     const int own = i == 3 ? ns : std::min(ns, own_min << i);
@@ -374,16 +379,21 @@ StepsPlan plan_of(int ns, int hb, bool rv, int stride, int val_bytes, int b, int
 }
 }  // namespace
 
-StepsPlan plan_steps(const SellOp& A, int b, int L, size_t lds_bytes, bool order4) {
+StepsPlan plan_steps(const SellOp& A, int b, int L, size_t lds_bytes, bool order4, bool replay) {
   if (!has_steps(A.st)) return StepsPlan();
+  const bool rv = A.st.row_values, f64 = A.val_bytes == 8;
+  const double mb = 1e-6 * A.n * b * A.val_bytes;
+  double one = order4 ? (rv ? (f64 ? 5.6 : 4.85) : 4.1) + 0.7 * mb : (rv ? (f64 ? 2.75 : 2.45) : 2.1) + 0.4 * mb;
+  if (!replay || !step_replay(A.n, b, A.val_bytes, L)) one = std::max(one, order4 ? 7.6 : 3.8);
   const int groups = b / std::min(b, 16 / A.val_bytes);
   return plan_of(A.nslices, (A.max_off + 63) / 64, A.st.row_values, A.st.stride, A.val_bytes, b, L, lds_bytes,
-                 (int)ceil_div64((int64_t)A.nslices * groups, kCus), order4);
+                 (int)ceil_div64((int64_t)A.nslices * groups, kCus), order4, 0.9 * one);
 }
 
 // Members of a batch side by side in one launch: each as alone, with so many
 // slices a workgroup that all of them have a compute unit to themselves.
-// Empty: one of them is not better off than with one step per launch.
+// Empty: one of them is not better off than with one step per launch (about 4
+// us in a batch).
 std::vector<StepsPlan> plan_batch(const std::vector<BatchMember>& m, int val_bytes, int b, size_t lds_bytes) {
   const int groups = b / std::min(b, 16 / val_bytes);
   int64_t total = 0;
@@ -392,7 +402,8 @@ std::vector<StepsPlan> plan_batch(const std::vector<BatchMember>& m, int val_byt
   for (int own_min = std::max(1, (int)ceil_div64(total * groups, kCus));; ++own_min) {
     int64_t wgs = 0;
     for (size_t i = 0; i < m.size(); ++i) {
-      plans[i] = plan_of(m[i].nslices, m[i].hb, false, 0, val_bytes, b, m[i].L, lds_bytes, own_min, false);
+      plans[i] = plan_of(m[i].nslices, m[i].hb, false, 0, val_bytes, b, m[i].L, lds_bytes, own_min, false,
+                         0.85 * 4.0);
       if (plans[i].s == 0) return {};
       wgs += (int64_t)ceil_div64(m[i].nslices, plans[i].own) * groups;
     }
