@@ -796,9 +796,7 @@ __global__ __launch_bounds__(1024) void k_leapfrog_mp_reg(int32_t n, int32_t nsl
 
 
 void free_sell(SellOp& op) {
-  if (op.slice_ptr) (void)hipFree(op.slice_ptr);
-  if (op.val) (void)hipFree(op.val);
-  if (op.idx) (void)hipFree(op.idx);
+  if (op.slice_ptr) (void)hipFree(op.slice_ptr);  // (the three arrays are one allocation)
   free_stencil(op.st);
   op = SellOp();
 }
@@ -861,13 +859,16 @@ int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d
   out.val_bytes = val_bytes;
   out.max_width = maxw;
   out.max_off = maxoff;
-  if (hipMalloc(&out.slice_ptr, sizeof(int64_t) * (ns + 1)) != hipSuccess ||
-      hipMalloc(&out.val, (size_t)tot * val_bytes) != hipSuccess ||
-      hipMalloc(&out.idx, (size_t)tot * ib) != hipSuccess) {
+  const auto padded = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
+  const size_t ptr_bytes = padded(sizeof(int64_t) * (ns + 1)), sell_bytes = padded((size_t)tot * val_bytes);
+  if (hipMalloc(&out.slice_ptr, ptr_bytes + sell_bytes + (size_t)tot * ib) != hipSuccess) {
+    out.slice_ptr = nullptr;
     free_sell(out);
     set_error("build_sell: device allocation failed");
     return KF_ENOMEM;
   }
+  out.val = reinterpret_cast<char*>(out.slice_ptr) + ptr_bytes;
+  out.idx = static_cast<char*>(out.val) + sell_bytes;
   KF_HIP(hipMemcpyAsync(out.slice_ptr, ptr.data(), sizeof(int64_t) * (ns + 1), hipMemcpyHostToDevice, st));
   if (val_bytes == 8 && ib == 2)
     hipLaunchKernelGGL((k_sell_fill<double, int16_t>), dim3(grid), dim3(256), 0, st, n, ns, out.slice_ptr, d_rowptr,
