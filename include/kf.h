@@ -145,9 +145,10 @@ typedef struct kf_options {
                             0 = automatic (2 when every |col - row| < 32768),
                             2 or 4.  With 0 here, nt_loads 0, gather_unroll 0
                             and block_band 0 or -1, an operator whose rows
-                            repeat (in every 64 consecutive rows the entries
-                            at one offset col - row have one value, as on
-                            uniform meshes) is stepped as stencils instead of
+                            repeat (in every 64 consecutive rows at most 32
+                            offsets col - row occur, with one value each, as
+                            on uniform meshes, or a value per row, as on
+                            jittered ones) is stepped as stencils instead of
                             stored entries, with the same results */
   int32_t xcd_remap;     /* 1: map consecutive row slices to the same XCD */
   int32_t nt_loads;      /* 1: stream the operator with non-temporal loads in
@@ -207,8 +208,9 @@ typedef struct kf_options {
                             weighted sum in LDS and advances s steps per
                             launch.  0 = one step per launch (default),
                             except that operators stepped as stencils (see
-                            index_bytes) take several, for blocks too, where
-                            that is faster; the results are the same;
+                            index_bytes) take several, for blocks and the
+                            fourth-order scheme too, where that is faster;
+                            the results are the same;
                             s > 0 = s steps per launch; -1 = the whole filter
                             in one launch.  KF_EINVAL from the solve or
                             filter call when the band does not fit;

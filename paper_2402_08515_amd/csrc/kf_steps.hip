@@ -15,8 +15,8 @@ namespace {
 
 // ------------------------------------- several steps per launch over stencils
 // The time loop of problems too small to fill a launch: a step of one launch
-// takes 3 to 4 us whatever its size, most of it launch and dependent-load
-// latency.  A workgroup owns a range of row slices and advances it s steps in
+// takes 3 to 4 us whatever its size (2.1 replayed from a recording), most of it
+// launch and dependent-load latency.  A workgroup owns a range of row slices and advances it s steps in
 // one launch; y_l of those rows, and of the hb slices a step reaches on either
 // side for each later step, lie in LDS (two copies, written in turn), and each
 // wavefront keeps the levels y_{l-1}, y_l and the weighted sum of its slices
@@ -30,7 +30,7 @@ namespace {
 // those of one step per launch, bit for bit.  A workgroup carries B columns
 // (at most 16 bytes) of a row of `groups` times as many: wider blocks are
 // independent groups of columns along the grid's y.
-// Measured, us per filter application, one step per launch and so: 64-cell
+// Measured, us per filter application, one launched step each and so: 64-cell
 // square (63 slices) fp64 257 -> 45; 128 cells 535 -> 114; 256 cells 1072 ->
 // 322, its block of 4 in float32 1021 -> 463; 20-cell cube 91 -> 44.  Bound by
 // a launch's latency (about 4 us) and the LDS reads of the halo slices.  The
