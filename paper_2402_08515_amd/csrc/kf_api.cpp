@@ -43,7 +43,7 @@ struct StepGraph {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   const void* op = nullptr;  // the operator's stencil arrays
-  int bk = 0, remap = 0, lpr = 0;
+  int bk = 0, remap = 0, lpr = 0, uses = 0;
   std::vector<double> w;
   bool failed = false;  // could not be recorded: not tried again
 };
@@ -475,11 +475,13 @@ int device_weights(kf_problem* p, const std::vector<double>& w, const double** o
 // instead of 147 us (107 instead of 225 where each application is waited for),
 // its fourth-order steps in blocks of 3 232 instead of 339, 60 cells 132
 // instead of 155; where a level has 7 MB (96 cells) the steps outlast the
-// host, 284 and 290.  Recorded at the second application with the same
-// weights: a single one does not pay for it.
+// host, 284 and 290.  Recording 39 steps takes 0.6 ms, what six applications
+// gain: it is done at the record_at-th application with the same weights, the
+// second of a solve, which will run many, the sixth where the caller applies
+// the filter.
 template <class Step>
 hipGraphExec_t step_graph(kf_problem* p, const SellOp& A, StepBufs& sb, int bk, const std::vector<double>& w,
-                          const Step& step) {
+                          int record_at, const Step& step) {
   const int L = (int)w.size();
   if (A.st.width == 0 || !step_replay(A.n, bk, A.val_bytes, L)) return nullptr;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -498,9 +500,11 @@ hipGraphExec_t step_graph(kf_problem* p, const SellOp& A, StepBufs& sb, int bk, 
     g.remap = p->opt.xcd_remap;
     g.lpr = A.lpr[lb];
     g.w = w;
+    g.uses = 1;
     return nullptr;
   }
   if (g.exec || g.failed) return g.exec;
+  if (++g.uses < record_at) return nullptr;
   // on a stream of its own: the problem's may be the default stream, which
   // cannot be recorded
   hipStream_t cap = nullptr;
@@ -523,7 +527,7 @@ hipGraphExec_t step_graph(kf_problem* p, const SellOp& A, StepBufs& sb, int bk, 
 // result go to dst (strides drs, dcs).  Asynchronous.
 int run_filter(kf_problem* p, const SellOp& A, StepBufs& sb, const double* src, int64_t srs, int64_t scs, int bsrc,
                int bk, double* dst, int64_t drs, int64_t dcs, int bout, const std::vector<double>& w,
-               bool may_alloc = true) {
+               bool may_alloc = true, int record_at = 2) {
   const int L = (int)w.size();
   hipStream_t st = p->st;
   if (L == 1) return launch_scale_copy(p->n, bout, std::min(bsrc, bout), src, srs, scs, w[0], dst, drs, dcs, st);
@@ -597,7 +601,7 @@ int run_filter(kf_problem* p, const SellOp& A, StepBufs& sb, const double* src, 
                            p->opt.xcd_remap, on);
   };
   hipGraphExec_t exec = nullptr;
-  if (may_alloc) exec = step_graph(p, A, sb, bk, w, step);
+  if (may_alloc) exec = step_graph(p, A, sb, bk, w, record_at, step);
   for (int l = 1; l < L; ++l) {
     if (exec && l == 3) {
       KF_HIP(hipGraphLaunch(exec, st));
@@ -2523,7 +2527,7 @@ int kf_apply_filter(kf_problem* p, const double* x, double* y, int32_t b) {
   if (b < 1 || b > 16) return fail(KF_EINVAL, "kf_apply_filter: b must lie in [1, 16]");
   const int bk = pow2ceil(b);
   KF_TRY(tune_block(p, p->A, p->sb, bk));
-  return run_filter(p, p->A, p->sb, x, b, 1, b, bk, y, b, 1, b, p->w);
+  return run_filter(p, p->A, p->sb, x, b, 1, b, bk, y, b, 1, b, p->w, true, 6);
 }
 
 int kf_apply_filter_noalloc(kf_problem* p, const double* x, double* y, int32_t b) {

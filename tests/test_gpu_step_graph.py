@@ -34,8 +34,8 @@ def test_replayed_steps_bitwise(kind, b, precision, stepper, stream):
         for L in (11, 12, 30):  # too few steps to record, the fewest, more
             P = kf.Problem(S, m, 0.3 / tau, 0.5 / tau, tau, L, precision=precision, stepper=stepper)
             y = torch.empty((S.shape[0], b), dtype=torch.float64, device="cuda")
-            for rep in range(5):  # launched, recorded, replayed; then again after new weights
-                if rep == 3:
+            for rep in range(15):  # launched, recorded (the sixth), replayed; then again after new weights
+                if rep == 7:
                     P.set_weights(np.linspace(1.0, 0.1, L))
                 x = torch.from_numpy(start_block(S.shape[0], b, rep)).cuda()
                 got = P.apply_filter(x)
@@ -44,11 +44,11 @@ def test_replayed_steps_bitwise(kind, b, precision, stepper, stream):
             # another width in between, and the first again
             x1 = torch.from_numpy(start_block(S.shape[0], 1, 7)).cuda()
             y1 = torch.empty_like(x1)
-            for _ in range(3):
+            for _ in range(7):
                 P.apply_filter_noalloc(x1, y1)
                 assert torch.equal(P.apply_filter(x1), y1), L
             P.apply_filter_noalloc(x, y)
-            for _ in range(3):
+            for _ in range(7):
                 assert torch.equal(P.apply_filter(x), y), L
         torch.cuda.synchronize()
 
@@ -67,7 +67,7 @@ def test_applications_under_the_callers_capture():
     with torch.cuda.stream(s):
         P = kf.Problem(S, m, 0.3 / tau, 0.5 / tau, tau, 30)
         x = torch.from_numpy(start_block(S.shape[0], 1, 1)).cuda()
-        want = [P.apply_filter(x) for _ in range(3)][-1]
+        want = [P.apply_filter(x) for _ in range(7)][-1]
         torch.cuda.synchronize()
         g = torch.cuda.CUDAGraph()
         with torch.cuda.graph(g, stream=s):
