@@ -600,7 +600,8 @@ __device__ __forceinline__ int sturm_count(int m, const double2* __restrict__ de
 
 // The same count from the sign changes of p_j = (d_j - x) p_{j-1} -
 // e_{j-1}^2 p_{j-2}, one dependent multiply-add per row; entries and x scaled by
-// a power of two to at most one (`scale` for x and d), so that in eight rows
+// a power of two to at most one (`scale` for x and d, e^2 by it twice: its
+// square is infinite where the entries are below 2^-512), so that in eight rows
 // |p| grows at most by 3^8, and brought back by a power of two every eight rows.
 // Rounds differently from the ratios, so it is for points many roundings
 // away from the eigenvalue sought, where the counts agree.
@@ -608,7 +609,6 @@ __device__ __forceinline__ int sturm_count_far(int m, const double2* __restrict_
   int cnt = 0;
   double p1 = 1.0, p2 = 0.0;
   x *= scale;
-  const double scale2 = scale * scale;
   double2 cur[kSturmB], nxt[kSturmB];
 #pragma unroll
   for (int u = 0; u < kSturmB; ++u) cur[u] = de[u];
@@ -617,7 +617,7 @@ __device__ __forceinline__ int sturm_count_far(int m, const double2* __restrict_
     for (int u = 0; u < kSturmB; ++u) nxt[u] = de[j0 + kSturmB + u];
 #pragma unroll
     for (int u = 0; u < kSturmB; ++u) {
-      double p = fma(fma(cur[u].x, scale, -x), p1, -(cur[u].y * scale2) * p2);
+      double p = fma(fma(cur[u].x, scale, -x), p1, -(cur[u].y * scale * scale) * p2);
       p = p == 0.0 ? -0x1p-200 * p1 : p;
       if (j0 + u < m) cnt += (int)((uint32_t)(__double2hiint(p) ^ __double2hiint(p1)) >> 31);
       p2 = p1;

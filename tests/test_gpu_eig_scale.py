@@ -1,0 +1,36 @@
+"""The eigensolver on matrices far from norm one.  Scaling by a power of two
+is exact, so eigenvalues scale with it; the tolerances are those of the same
+matrices at norm one (a few roundings of the bisection)."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _second_difference(k):
+    return 2.0 * np.eye(k) - np.diag(np.ones(k - 1), 1) - np.diag(np.ones(k - 1), -1)
+
+
+# (2^-514: the power of two that brings the matrix to norm one has an infinite
+# square; off-diagonals are powers of two, so that their squares are exact
+# although subnormal)
+@pytest.mark.parametrize("exponent", [-536, -520, -514, -513, -512, -500, -100, 0, 100, 500])
+@pytest.mark.parametrize("k", [20, 50, 300])
+def test_eigenvalues_scale_with_the_matrix(k, exponent):
+    from paper_2402_08515_amd import kf
+
+    print(f"case sym_eig scale 2^{exponent} k={k}", flush=True)
+    T, s = _second_difference(k), 2.0**exponent
+    theta = kf.sym_eig(T * s) / s
+    np.testing.assert_allclose(theta, np.linalg.eigvalsh(T), atol=1e-13)
+
+
+@pytest.mark.parametrize("exponent", [-900, -600, -530, 530, 600, 900])
+@pytest.mark.parametrize("k", [20, 50, 300])
+def test_diagonal_matrices_of_any_scale(k, exponent):
+    from paper_2402_08515_amd import kf
+
+    print(f"case sym_eig diagonal scale 2^{exponent} k={k}", flush=True)
+    d = np.sort(np.random.default_rng(k).uniform(1.0, 2.0, size=k))
+    np.testing.assert_allclose(kf.sym_eig(np.diag(d[::-1]) * 2.0**exponent), d * 2.0**exponent, rtol=1e-14)
