@@ -603,6 +603,9 @@ __device__ __forceinline__ int sturm_count(int m, const double2* __restrict__ de
 // a power of two to at most one (`scale` for x and d, e^2 by it twice: its
 // square is infinite where the entries are below 2^-512), so that in eight rows
 // |p| grows at most by 3^8, and brought back by a power of two every eight rows.
+// A pivot p_j / p_{j-1} of less than 2^-60 counts as -2^-60, as the ratios' pivots
+// below their floor count as minus it: eight rows shrink |p| at most by 2^480,
+// and a run of diagonal entries equal to x does not take it to zero.
 // Rounds differently from the ratios, so it is for points many roundings
 // away from the eigenvalue sought, where the counts agree.
 __device__ __forceinline__ int sturm_count_far(int m, const double2* __restrict__ de, double x, double scale) {
@@ -618,7 +621,8 @@ __device__ __forceinline__ int sturm_count_far(int m, const double2* __restrict_
 #pragma unroll
     for (int u = 0; u < kSturmB; ++u) {
       double p = fma(fma(cur[u].x, scale, -x), p1, -(cur[u].y * scale * scale) * p2);
-      p = p == 0.0 ? -0x1p-200 * p1 : p;
+      const double least = -0x1p-60 * p1;
+      p = fabs(p) < fabs(least) ? least : p;
       if (j0 + u < m) cnt += (int)((uint32_t)(__double2hiint(p) ^ __double2hiint(p1)) >> 31);
       p2 = p1;
       p1 = p;

@@ -34,3 +34,24 @@ def test_diagonal_matrices_of_any_scale(k, exponent):
     print(f"case sym_eig diagonal scale 2^{exponent} k={k}", flush=True)
     d = np.sort(np.random.default_rng(k).uniform(1.0, 2.0, size=k))
     np.testing.assert_allclose(kf.sym_eig(np.diag(d[::-1]) * 2.0**exponent), d * 2.0**exponent, rtol=1e-14)
+
+
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("k", [50, 300])
+def test_repeated_diagonal_entries_at_a_section_point(k, fused):
+    """The bisection's first points depend on the extreme entries alone: runs
+    of diagonal entries equal to some of them (rounded as a product and a sum,
+    or once) give it pivots of zero row after row."""
+    from fractions import Fraction
+
+    from paper_2402_08515_amd import kf
+
+    print(f"case sym_eig section points k={k} fused={fused}", flush=True)
+    d = np.linspace(1.0, 2.0, k)
+    widen = 2.0 * np.finfo(float).eps * 2.0
+    lo, hi = 1.0 - widen - np.finfo(float).tiny, 2.0 + widen + np.finfo(float).tiny
+    h = (hi - lo) / 65.0
+    for i, point in enumerate((20, 41)):
+        x = float(Fraction(lo) + point * Fraction(h)) if fused else lo + point * h
+        d[8 + 16 * i : 24 + 16 * i] = x
+    np.testing.assert_allclose(kf.sym_eig(np.diag(d)), np.sort(d), rtol=1e-14)
