@@ -738,7 +738,10 @@ __global__ __launch_bounds__(256) void k_bisect(int m, const double* __restrict_
 // and latency of a single wavefront's chain: one division per row in the
 // factorisation, one multiply-add per row forward and two operations backward;
 // the rows are read kIvB ahead, with the normalisation of an iterate applied
-// by the next sweep's reads.  110 vectors of order 440: 560 us with two
+// by the next sweep's reads.  The squares of its norm are taken of the iterate
+// times a power of two of about the matrix's norm: its entries are about the
+// norm's inverse over eps, whose squares leave the range of a double where the
+// norm is below 2^-460 or above 2^560.  110 vectors of order 440: 560 us with two
 // divisions per row, several lanes' arrays interleaved and separate passes for
 // the norms, 232 us so.
 constexpr int kIvB = 8;
@@ -843,6 +846,7 @@ __global__ __launch_bounds__(64) void k_invit(int m, const double* __restrict__ 
   for (int i = lane; i < m; i += 64) rinv[i] = 1.0 / rinv[i];
   __syncthreads();
   double rs = 1.0;  // what normalises the iterate in z
+  const double unit = 1.0 / bounds[3];  // (an exact power of two)
   if (lane == 0) {
     for (int it = 0; it < 3; ++it) {
       // forward: row swaps and elimination
@@ -887,7 +891,7 @@ __global__ __launch_bounds__(64) void k_invit(int m, const double* __restrict__ 
         auto row = [&](int i, double zi, double v1, double v2, double r) {
           const double x = (fma(-v2, x2, zi) - v1 * x1) * r;
           z[i] = x;
-          nrm = fma(x, x, nrm);
+          nrm = fma(x * unit, x * unit, nrm);
           x2 = x1;
           x1 = x;
         };
@@ -918,7 +922,7 @@ __global__ __launch_bounds__(64) void k_invit(int m, const double* __restrict__ 
         }
         for (; i0 >= 0; --i0) row(i0, z[i0], u1[i0], u2[i0], rinv[i0]);
       }
-      rs = nrm > 0.0 ? 1.0 / sqrt(nrm) : 0.0;
+      rs = nrm > 0.0 ? unit / sqrt(nrm) : 0.0;
     }
   }
   __syncthreads();

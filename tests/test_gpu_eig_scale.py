@@ -55,3 +55,34 @@ def test_repeated_diagonal_entries_at_a_section_point(k, fused):
         x = float(Fraction(lo) + point * Fraction(h)) if fused else lo + point * h
         d[8 + 16 * i : 24 + 16 * i] = x
     np.testing.assert_allclose(kf.sym_eig(np.diag(d)), np.sort(d), rtol=1e-14)
+
+
+@pytest.mark.parametrize("exponent", [-500, -480, -400, 0, 400, 500])
+@pytest.mark.parametrize("k", [20, 50, 300])
+def test_eigenvectors_scale_with_the_matrix(k, exponent):
+    """Vectors of a part of the spectrum: unit norm, orthogonal, and
+    eigenvectors of the matrix brought back to norm one (tolerances of the
+    eigensolver's other tests)."""
+    from paper_2402_08515_amd import kf
+
+    print(f"case sym_eig vectors scale 2^{exponent} k={k}", flush=True)
+    T, s = _second_difference(k), 2.0**exponent
+    theta, Y = kf.sym_eig(T * s, 1.0 * s, 3.0 * s, vectors=True)
+    sel = theta[(theta >= 1.0 * s) & (theta <= 3.0 * s)] / s
+    assert Y.shape == (k, sel.size) and sel.size >= k // 4
+    assert np.abs(T @ Y - Y * sel).max() <= 1e-11 * 4.0
+    assert np.abs(Y.T @ Y - np.eye(sel.size)).max() <= 1e-10
+
+
+@pytest.mark.parametrize("exponent", [-900, -600, 600, 900])
+@pytest.mark.parametrize("k", [20, 50, 300])
+def test_eigenvectors_of_diagonal_matrices_of_any_scale(k, exponent):
+    from paper_2402_08515_amd import kf
+
+    print(f"case sym_eig diagonal vectors scale 2^{exponent} k={k}", flush=True)
+    d, s = np.linspace(1.0, 2.0, k), 2.0**exponent
+    theta, Y = kf.sym_eig(np.diag(d) * s, 1.2 * s, 1.8 * s, vectors=True)
+    sel = theta[(theta >= 1.2 * s) & (theta <= 1.8 * s)] / s
+    assert Y.shape == (k, sel.size) and sel.size >= k // 2
+    assert np.abs(d[:, None] * Y - Y * sel).max() <= 1e-11 * 2.0
+    assert np.abs(Y.T @ Y - np.eye(sel.size)).max() <= 1e-10
