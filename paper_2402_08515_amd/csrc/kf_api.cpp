@@ -36,7 +36,6 @@ void set_error(const std::string& msg) { g_err = msg; }
 
 using namespace kf;
 
-// time-stepping buffers (n x cap blocks)
 // The launches of a filter application that touch nothing but the step buffers,
 // recorded once for one operator, block width and set of weights.
 struct StepGraph {
@@ -48,6 +47,7 @@ struct StepGraph {
   bool failed = false;  // could not be recorded: not tried again
 };
 
+// time-stepping buffers (n x cap blocks; the second pair n x pair)
 struct StepBufs {
   StepGraph g;
   void* Y0 = nullptr;
@@ -56,8 +56,9 @@ struct StepBufs {
   void* Z = nullptr;  // fourth-order stepper: z = A y
   void* Y2 = nullptr;  // several steps per launch: the second pair of levels
   void* Y3 = nullptr;
-  int cap = 0;  // block width held
-  int vb = 0;   // value bytes
+  int cap = 0;   // block width held
+  int pair = 0;  // block width the second pair holds
+  int vb = 0;    // value bytes
 };
 
 namespace kf {
@@ -351,25 +352,61 @@ void drop_graph(StepGraph& g) {
   g = StepGraph();
 }
 
-int ensure_step_buffers(kf_problem* p, StepBufs& sb, int bk, int vb, bool second_pair = false) {
-  const bool needz = p->opt.stepper == 4;
-  const bool need23 = second_pair || (p->opt.multistep != 0 && bk == 1);
-  if (sb.cap >= bk && sb.vb == vb && (!needz || sb.Z) && (!need23 || sb.Y3)) return KF_OK;
-  dfree(sb.Y0);
-  dfree(sb.Y1);
-  dfree(sb.R);
-  dfree(sb.Z);
+size_t lds_per_workgroup();
+
+// Whether a plan's launches alternate between two pairs of levels: not with
+// all rows in one workgroup or all steps in one launch.
+bool needs_pair(const StepsPlan& pl, const SellOp& A, int L) {
+  return pl.s > 0 && pl.own < A.nslices && pl.s < L - 1;
+}
+
+// The widest block up to cap columns that needs the second pair (0: none).
+int pair_width(const kf_problem* p, const SellOp& A, int cap) {
+  if (p->opt.multistep != 0) return 1;
+  for (int bk = cap; bk >= 1; bk /= 2)
+    if (needs_pair(plan_steps(A, bk, p->L, lds_per_workgroup(), p->opt.stepper == 4, true), A, p->L)) return bk;
+  return 0;
+}
+
+bool alloc_pair(const kf_problem* p, StepBufs& sb, int width) {
+  const size_t bytes = (size_t)p->n * width * sb.vb;
+  if (hipMalloc(&sb.Y2, bytes) == hipSuccess && hipMalloc(&sb.Y3, bytes) == hipSuccess) {
+    sb.pair = width;
+    return true;
+  }
+  (void)hipGetLastError();
   dfree(sb.Y2);
-  dfree(sb.Y3);
-  drop_graph(sb.g);  // (the frees have waited for its last launch)
-  sb = StepBufs();
-  const size_t bytes = (size_t)p->n * bk * vb;
-  if (hipMalloc(&sb.Y0, bytes) != hipSuccess || hipMalloc(&sb.Y1, bytes) != hipSuccess ||
-      hipMalloc(&sb.R, bytes) != hipSuccess || (needz && hipMalloc(&sb.Z, bytes) != hipSuccess) ||
-      (need23 && (hipMalloc(&sb.Y2, bytes) != hipSuccess || hipMalloc(&sb.Y3, bytes) != hipSuccess)))
+  sb.Y2 = sb.Y3 = nullptr;
+  return false;
+}
+
+// Buffers for blocks of bk columns.  They only grow, and everything that any
+// width up to theirs needs comes with them: a caller that has applied its
+// widest block may alternate widths, or record an application and replay it
+// later, and nothing is allocated and no buffer moves.
+int ensure_step_buffers(kf_problem* p, const SellOp& A, StepBufs& sb, int bk) {
+  const bool needz = p->opt.stepper == 4;
+  if (sb.cap < bk || sb.vb != A.val_bytes || (needz && !sb.Z)) {
+    const int cap = sb.vb == A.val_bytes ? std::max(bk, sb.cap) : bk;
+    dfree(sb.Y0);
+    dfree(sb.Y1);
+    dfree(sb.R);
+    dfree(sb.Z);
+    dfree(sb.Y2);
+    dfree(sb.Y3);
+    drop_graph(sb.g);  // (the frees have waited for its last launch)
+    sb = StepBufs();
+    sb.vb = A.val_bytes;
+    const size_t bytes = (size_t)p->n * cap * sb.vb;
+    if (hipMalloc(&sb.Y0, bytes) != hipSuccess || hipMalloc(&sb.Y1, bytes) != hipSuccess ||
+        hipMalloc(&sb.R, bytes) != hipSuccess || (needz && hipMalloc(&sb.Z, bytes) != hipSuccess))
+      return fail(KF_ENOMEM, "kf: time-stepping buffers");
+    sb.cap = cap;
+    // (without the pair: one step per launch)
+    if (const int pair = pair_width(p, A, cap)) (void)alloc_pair(p, sb, pair);
+  }
+  if (p->opt.multistep != 0 && bk == 1 && sb.pair < 1 && !alloc_pair(p, sb, 1))
     return fail(KF_ENOMEM, "kf: time-stepping buffers");
-  sb.cap = bk;
-  sb.vb = vb;
   return KF_OK;
 }
 
@@ -419,6 +456,7 @@ int scratch_step_buffers(int32_t n, int bk, int vb, StepBufs& sb, int nbuf, bool
   if (second_pair && (size_t)(nbuf + 2) * one <= kScratchBytes) {
     sb.Y2 = c + nbuf * one;
     sb.Y3 = c + (nbuf + 1) * one;
+    sb.pair = bk;
   }
   sb.cap = bk;
   sb.vb = vb;
@@ -534,7 +572,7 @@ int run_filter(kf_problem* p, const SellOp& A, StepBufs& sb, const double* src, 
   StepsPlan steps;
   if (p->opt.multistep == 0 && A.st.width > 0) steps = plan_steps(A, bk, L, lds_per_workgroup(), p->opt.stepper == 4, may_alloc);
   if (may_alloc) {
-    KF_TRY(ensure_step_buffers(p, sb, bk, A.val_bytes, steps.s > 0 && steps.own < A.nslices && steps.s < L - 1));
+    KF_TRY(ensure_step_buffers(p, A, sb, bk));
   } else if (sb.cap < bk || sb.vb != A.val_bytes || !sb.Y0 || !sb.Y1 || !sb.R || (p->opt.stepper == 4 && !sb.Z)) {
     return fail(KF_EINVAL, "kf: time-stepping buffers too small");
   }
@@ -568,7 +606,7 @@ int run_filter(kf_problem* p, const SellOp& A, StepBufs& sb, const double* src, 
     }
     return KF_OK;
   }
-  if (steps.s > 0 && (steps.own >= A.nslices || steps.s >= L - 1 || sb.Y3)) {
+  if (steps.s > 0 && (!needs_pair(steps, A, L) || sb.pair >= bk)) {
     // (one workgroup reads every level before it writes, so one pair serves)
     void* P0[2] = {sb.Y0, sb.Y1};
     void* P1[2] = {steps.own >= A.nslices ? sb.Y0 : sb.Y2, steps.own >= A.nslices ? sb.Y1 : sb.Y3};
@@ -1790,7 +1828,7 @@ bool copies_beyond_block(const std::vector<double>& acc, int b) {
 // given XCD mapping; returns microseconds per step.
 int time_variant(kf_problem* p, const SellOp& A, StepBufs& sb, int remap, int reps, double* us, int bk = 1) {
   hipStream_t st = p->st;
-  KF_TRY(ensure_step_buffers(p, sb, bk, A.val_bytes));
+  KF_TRY(ensure_step_buffers(p, A, sb, bk));
   const size_t bytes = (size_t)p->n * bk * A.val_bytes;
   KF_HIP(hipMemsetAsync(sb.Y0, 0, bytes, st));
   KF_HIP(hipMemsetAsync(sb.Y1, 0, bytes, st));
