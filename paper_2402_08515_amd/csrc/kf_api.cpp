@@ -37,19 +37,19 @@ void set_error(const std::string& msg) { g_err = msg; }
 using namespace kf;
 
 // The launches of a filter application that touch nothing but the step buffers,
-// recorded once for one operator, block width and set of weights.
+// recorded once for one operator, set of weights and block width.
 struct StepGraph {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   const void* op = nullptr;  // the operator's stencil arrays
-  int bk = 0, remap = 0, lpr = 0, uses = 0;
+  int remap = 0, lpr = 0, uses = 0;
   std::vector<double> w;
   bool failed = false;  // could not be recorded: not tried again
 };
 
 // time-stepping buffers (n x cap blocks; the second pair n x pair)
 struct StepBufs {
-  StepGraph g;
+  StepGraph g[5];  // block widths 1, 2, .., 16
   void* Y0 = nullptr;
   void* Y1 = nullptr;
   void* R = nullptr;
@@ -346,6 +346,12 @@ void dfree(void* p) {
   if (p) (void)hipFree(p);
 }
 
+int log2_width(int bk) {
+  int lb = 0;
+  while ((1 << lb) < bk && lb < 4) ++lb;
+  return lb;
+}
+
 void drop_graph(StepGraph& g) {
   if (g.exec) (void)hipGraphExecDestroy(g.exec);
   if (g.graph) (void)hipGraphDestroy(g.graph);
@@ -394,7 +400,7 @@ int ensure_step_buffers(kf_problem* p, const SellOp& A, StepBufs& sb, int bk) {
     dfree(sb.Z);
     dfree(sb.Y2);
     dfree(sb.Y3);
-    drop_graph(sb.g);  // (the frees have waited for its last launch)
+    for (StepGraph& g : sb.g) drop_graph(g);  // (the frees have waited for their last launches)
     sb = StepBufs();
     sb.vb = A.val_bytes;
     const size_t bytes = (size_t)p->n * cap * sb.vb;
@@ -470,7 +476,7 @@ void free_step_buffers(StepBufs& sb) {
   dfree(sb.Z);
   dfree(sb.Y2);
   dfree(sb.Y3);
-  drop_graph(sb.g);  // (the frees have waited for its last launch)
+  for (StepGraph& g : sb.g) drop_graph(g);  // (the frees have waited for their last launches)
   sb = StepBufs();
 }
 
@@ -514,9 +520,12 @@ int device_weights(kf_problem* p, const std::vector<double>& w, const double** o
 // its fourth-order steps in blocks of 3 232 instead of 339, 60 cells 132
 // instead of 155; where a level has 7 MB (96 cells) the steps outlast the
 // host, 284 and 290.  Recording 39 steps takes 0.6 ms, what six applications
-// gain: it is done at the record_at-th application with the same weights, the
-// second of a solve, which will run many, the sixth where the caller applies
-// the filter.
+// gain: it is done at the record_at-th application with the same weights and
+// width, the second of a solve, which will run many, the sixth where the caller
+// applies the filter and in the subspace iterations, which may end early.  Each
+// width has a recording of its own: an iteration over 36 columns applies blocks
+// of 16, 16 and 4.
+constexpr int kRecordSolve = 2, kRecordOther = 6;
 template <class Step>
 hipGraphExec_t step_graph(kf_problem* p, const SellOp& A, StepBufs& sb, int bk, const std::vector<double>& w,
                           int record_at, const Step& step) {
@@ -527,14 +536,12 @@ hipGraphExec_t step_graph(kf_problem* p, const SellOp& A, StepBufs& sb, int bk, 
     (void)hipGetLastError();
     return nullptr;  // the caller records these launches
   }
-  StepGraph& g = sb.g;
-  int lb = 0;
-  while ((1 << lb) < bk) ++lb;
-  if (g.op != A.st.mask || g.bk != bk || g.remap != p->opt.xcd_remap || g.lpr != A.lpr[lb] || g.w != w) {
+  const int lb = log2_width(bk);
+  StepGraph& g = sb.g[lb];
+  if (g.op != A.st.mask || g.remap != p->opt.xcd_remap || g.lpr != A.lpr[lb] || g.w != w) {
     if (g.exec) (void)hipStreamSynchronize(p->st);
     drop_graph(g);
     g.op = A.st.mask;
-    g.bk = bk;
     g.remap = p->opt.xcd_remap;
     g.lpr = A.lpr[lb];
     g.w = w;
@@ -565,12 +572,13 @@ hipGraphExec_t step_graph(kf_problem* p, const SellOp& A, StepBufs& sb, int bk, 
 // result go to dst (strides drs, dcs).  Asynchronous.
 int run_filter(kf_problem* p, const SellOp& A, StepBufs& sb, const double* src, int64_t srs, int64_t scs, int bsrc,
                int bk, double* dst, int64_t drs, int64_t dcs, int bout, const std::vector<double>& w,
-               bool may_alloc = true, int record_at = 2) {
+               bool may_alloc = true, int record_at = kRecordOther) {
   const int L = (int)w.size();
   hipStream_t st = p->st;
   if (L == 1) return launch_scale_copy(p->n, bout, std::min(bsrc, bout), src, srs, scs, w[0], dst, drs, dcs, st);
   StepsPlan steps;
-  if (p->opt.multistep == 0 && A.st.width > 0) steps = plan_steps(A, bk, L, lds_per_workgroup(), p->opt.stepper == 4, may_alloc);
+  if (p->opt.multistep == 0 && A.st.width > 0)
+    steps = plan_steps(A, bk, L, lds_per_workgroup(), p->opt.stepper == 4, may_alloc && !sb.g[log2_width(bk)].failed);
   if (may_alloc) {
     KF_TRY(ensure_step_buffers(p, A, sb, bk));
   } else if (sb.cap < bk || sb.vb != A.val_bytes || !sb.Y0 || !sb.Y1 || !sb.R || (p->opt.stepper == 4 && !sb.Z)) {
@@ -1870,8 +1878,7 @@ int time_variant_min(kf_problem* p, const SellOp& A, StepBufs& sb, int remap, in
 // Called outside the timed regions of a solve (it records ev[0], ev[1]).
 int tune_block(kf_problem* p, SellOp& A, StepBufs& sb, int bk) {
   if (!p->opt.autotune || bk < 2) return KF_OK;
-  int lb = 0;
-  while ((1 << lb) < bk && lb < 4) ++lb;
+  const int lb = log2_width(bk);
   if (A.lpr_tuned & (1 << lb)) return KF_OK;
   // (several steps per launch have no such choice)
   if (p->opt.multistep == 0 && A.st.width > 0 &&
@@ -2565,7 +2572,7 @@ int kf_apply_filter(kf_problem* p, const double* x, double* y, int32_t b) {
   if (b < 1 || b > 16) return fail(KF_EINVAL, "kf_apply_filter: b must lie in [1, 16]");
   const int bk = pow2ceil(b);
   KF_TRY(tune_block(p, p->A, p->sb, bk));
-  return run_filter(p, p->A, p->sb, x, b, 1, b, bk, y, b, 1, b, p->w, true, 6);
+  return run_filter(p, p->A, p->sb, x, b, 1, b, bk, y, b, 1, b, p->w);
 }
 
 int kf_apply_filter_noalloc(kf_problem* p, const double* x, double* y, int32_t b) {
@@ -3031,7 +3038,7 @@ int solve_after_filter(kf_problem* p, SolveState& s) {
   const std::function<int()> ahead = [&]() -> int {
     KF_HIP(hipEventRecord(p->ev[5], st));
     KF_TRY(run_filter(p, *s.Aop, *s.sbop, p->B + (int64_t)s.cur * ldb, 1, ldb, s.bk, s.bk, p->B + (int64_t)cur1 * ldb, 1,
-                      ldb, s.bk, p->w));
+                      ldb, s.bk, p->w, true, kRecordSolve));
     KF_HIP(hipEventRecord(p->ev[6], st));
     return KF_OK;
   };
@@ -3164,7 +3171,7 @@ int solve_loop(kf_problem* p, SolveState& s) {
     } else {
       KF_HIP(hipEventRecord(p->ev[0], p->st));
       KF_TRY(run_filter(p, *s.Aop, *s.sbop, p->B + (int64_t)s.q0 * ldb, 1, ldb, s.qn, s.bk,
-                        p->B + (int64_t)s.cur * ldb, 1, ldb, s.bk, p->w));
+                        p->B + (int64_t)s.cur * ldb, 1, ldb, s.bk, p->w, true, kRecordSolve));
       KF_HIP(hipEventRecord(p->ev[1], p->st));
     }
     KF_TRY(solve_after_filter(p, s));

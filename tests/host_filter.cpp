@@ -167,9 +167,9 @@ struct Case {
     rt.live.erase((char*)x.data());
     check(rt.live.empty(), "blocks left behind");
   }
-  // y = C x for b columns as kf_apply_filter (record_at 6) or a solve does
-  int apply(int b, int record_at = 6) {
-    return run_filter(&p, p.A, p.sb, x.data(), b, 1, b, pow2ceil(b), x.data(), b, 1, b, p.w, true, record_at);
+  // y = C x for b columns
+  int apply(int b) {
+    return run_filter(&p, p.A, p.sb, x.data(), b, 1, b, pow2ceil(b), x.data(), b, 1, b, p.w);
   }
   std::vector<void*> blocks() const { return {p.sb.Y0, p.sb.Y1, p.sb.R, p.sb.Z, p.sb.Y2, p.sb.Y3}; }
 };
@@ -214,6 +214,28 @@ void no_second_pair(int which) {
   check(rt.several == 0 && rt.launches == kSteps - 1, "not one step per launch");
 }
 
+// A subspace iteration over 36 columns, in chunks, none of which takes several
+// steps per launch: each width is recorded once and replayed from then on, the
+// stream is never waited for; new weights are recorded anew.
+void chunks() {
+  Case c;
+  const auto iterate = [&](int times) {
+    for (int i = 0; i < times; ++i)
+      for (int b : {16, 16, 4}) check(c.apply(b) == KF_OK, "refused");
+  };
+  iterate(12);
+  check(rt.recordings == 2, "not one recording per width");
+  check(rt.dropped == 0 && rt.waits == 0, "a recording was dropped");
+  check(rt.replays >= 2 * 12 + 12 - 10, "recordings not replayed");
+  c.p.w.assign(kSteps, 0.25);
+  const int replays = rt.replays;
+  iterate(2);  // (fewer applications than a recording pays for)
+  check(rt.recordings == 2 && rt.replays == replays, "recordings of other weights replayed");
+  check(rt.dropped == 2, "recordings of other weights kept");
+  iterate(10);
+  check(rt.recordings == 4, "new weights not recorded");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -223,6 +245,7 @@ int main(int argc, char** argv) {
   else if (s == "wide_then_recorded") wide_then_recorded();
   else if (s == "no_second_pair_1") no_second_pair(1);
   else if (s == "no_second_pair_2") no_second_pair(2);
+  else if (s == "chunks") chunks();
   else check(false, "no such scenario");
   return errors ? 1 : 0;
 }

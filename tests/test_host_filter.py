@@ -36,3 +36,7 @@ def _run(program, scenario):
 )
 def test_step_buffers(program, scenario):
     _run(program, scenario)
+
+
+def test_recordings_of_alternating_widths(program):
+    _run(program, "chunks")
