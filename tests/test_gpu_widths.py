@@ -44,24 +44,3 @@ def test_a_recorded_width_survives_the_others(precision, stepper):
             for b in (8, 1, 3, 16):
                 assert torch.equal(P.apply_filter(x[b]), want[b]), (rep, b)
         torch.cuda.synchronize()
-
-
-def test_alternating_widths_keep_their_memory():
-    """Device memory in use after the first round of widths is that after
-    every further one."""
-    import torch
-
-    from paper_2402_08515_amd import kf
-
-    S, m, _ = grid_problem(2, 600)
-    tau = 1.8 / np.sqrt(8.0 * 600 * 600)
-    P = kf.Problem(S, m, 0.3 / tau, 0.5 / tau, tau, 20, precision="mixed")
-    x = {b: torch.from_numpy(start_block(S.shape[0], b, b)).cuda() for b in (1, 16)}
-    y = {b: torch.empty_like(v) for b, v in x.items()}
-    used = []
-    for _ in range(3):
-        for b in (16, 1):
-            y[b].copy_(P.apply_filter(x[b]))
-            torch.cuda.synchronize()
-            used.append(torch.cuda.mem_get_info()[0])
-    assert len(set(used[1:])) == 1, used
