@@ -1789,7 +1789,7 @@ int refine_mixed(kf_problem* p, int k, double tol, const CheckOut& in, bool want
   const int64_t ld = p->ldb;
   const int nc = (int)in.cand_theta.size();
   out = in;
-  if (nc == 0 || !p->A64.val) return KF_OK;
+  if (nc == 0 || p->A64.n == 0) return KF_OK;
   if (nc > 2048) return fail(KF_EINVAL, "kf_solve: refinement block larger than 2048 columns");
   KF_TRY(ensure_refine(p, nc, k));
   // X = B * (eigenvectors of the last check's candidates, ew.Y), into Vx
@@ -2137,9 +2137,11 @@ int kf_create(const kf_csr* S, const double* m_diag, double omega_min, double om
     }
     const int vb = o.precision == KF_MIXED ? 4 : 8;
     const int stencil = layout_is_free(o) ? kStencilExact : kStencilNone;
-    rc = build_sell(p->n, p->nnz, dc.rowptr, dc.col, dc.val, d_scale, vb, o.index_bytes, p->st, p->A, stencil);
+    rc = build_sell(p->n, p->nnz, dc.rowptr, dc.col, dc.val, d_scale, vb, o.index_bytes, p->st, p->A, stencil,
+                    o.multistep != 0);
     if (!rc && o.precision == KF_MIXED && o.refine)
-      rc = build_sell(p->n, p->nnz, dc.rowptr, dc.col, dc.val, d_scale, 8, o.index_bytes, p->st, p->A64, stencil);
+      rc = build_sell(p->n, p->nnz, dc.rowptr, dc.col, dc.val, d_scale, 8, o.index_bytes, p->st, p->A64, stencil,
+                      o.multistep != 0);
     if (!rc) rc = build_sell(p->n, p->nnz, dc.rowptr, dc.col, dc.val, nullptr, 8, o.index_bytes, p->st, p->S);
     if (rc) {
       dfree(d_scale);
@@ -2764,7 +2766,7 @@ int solve_begin(kf_problem* p, const double* start, int32_t b, int32_t m_max, do
   // Krylov loop accepts at ten times that floor and the float64 refinement
   // takes the pairs to tol.  Candidates are taken from the interval widened
   // by 5% of its width.
-  s.refine = p->opt.precision == KF_MIXED && p->opt.refine && p->A64.val;
+  s.refine = p->opt.precision == KF_MIXED && p->opt.refine && p->A64.n > 0;
   const double floor32 = 5.96e-8 * 4.0 / (p->tau * p->tau) / std::max(p->omega_min * p->omega_min, 1e-300);
   s.tol_loop = s.refine ? std::max(tol, std::min(1e-3, 10.0 * floor32)) : tol;
   s.margin = s.refine ? 0.05 * (p->omega_max - p->omega_min) : 0.0;
@@ -3285,7 +3287,7 @@ int kf_subspace_solve(kf_problem* p, const double* start, int32_t ncols, int32_t
   double* X = p->Vx;
   double* Q = p->Yy;
   const bool mixed = p->opt.precision == KF_MIXED;
-  const bool has64 = p->A64.val != nullptr;
+  const bool has64 = p->A64.n > 0;
   const int target = p->opt.target;
   SubspaceStats s32, s64;
   CheckOut chk;
@@ -3752,7 +3754,7 @@ int kf_create_batch(int32_t P, const kf_problem_desc* descs, const kf_options* o
       BatchStack& k = bt->stk[ks];
       const int vb = (mixed && ks == 0) ? 4 : 8;
       rc = build_sell((int32_t)bt->rows, (int64_t)hs.col.size(), dc.rowptr, dc.col, dc.val, nullptr, vb, o.index_bytes,
-                      bt->st, k.A, layout_is_free(o) ? kStencilPadded : kStencilNone);
+                      bt->st, k.A, layout_is_free(o) ? kStencilPadded : kStencilNone, false);
       if (rc) break;
       k.A.nt_loads = o.nt_loads ? 1 : 0;
       if ((rc = dalloc(&k.d_tb, 1))) break;

@@ -103,12 +103,13 @@ void free_stencil(StencilOp& s);
 // every |col - row| < 32768.  stencil: also build out.st when every slice has
 // at most kStencilMax offsets; its stride is a multiple of 4, or with
 // kStencilExact the width itself for the lengths that have kernels of their
-// own.
+// own.  Without `entries` an operator that has this form gets no stored entries
+// (only the steps with the caller's own number of steps per launch read both).
 constexpr int kStencilMax = 32;
 enum StencilForm { kStencilNone = 0, kStencilPadded = 1, kStencilExact = 2 };
 int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
                const double* d_row_scale, int val_bytes, int want_idx_bytes, hipStream_t st, SellOp& out,
-               int stencil = kStencilNone);
+               int stencil = kStencilNone, bool entries = true);
 
 // The number of distinct offsets of every slice (negative: values differ
 // within an offset) into d_w[ns], and the stencil form from them (on the host).

@@ -802,7 +802,8 @@ void free_sell(SellOp& op) {
 }
 
 int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d_col, const double* d_val,
-               const double* d_row_scale, int val_bytes, int want_idx_bytes, hipStream_t st, SellOp& out, int stencil) {
+               const double* d_row_scale, int val_bytes, int want_idx_bytes, hipStream_t st, SellOp& out, int stencil,
+               bool entries) {
   free_sell(out);
   if (n <= 0) {
     set_error("build_sell: empty matrix");
@@ -859,6 +860,17 @@ int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d
   out.val_bytes = val_bytes;
   out.max_width = maxw;
   out.max_off = maxoff;
+  const auto stencil_form = [&]() {
+    return build_stencil(n, ns, d_rowptr, d_col, d_val, d_row_scale, h.data() + 2 * (size_t)ns, val_bytes, out.nstored,
+                         ib, stencil == kStencilExact, st, out.st);
+  };
+  if (stencil && !entries) {
+    KF_TRY(stencil_form());
+    if (out.st.width > 0) {
+      KF_HIP(hipStreamSynchronize(st));
+      return KF_OK;
+    }
+  }
   const auto padded = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
   const size_t ptr_bytes = padded(sizeof(int64_t) * (ns + 1)), sell_bytes = padded((size_t)tot * val_bytes);
   if (hipMalloc(&out.slice_ptr, ptr_bytes + sell_bytes + (size_t)tot * ib) != hipSuccess) {
@@ -883,9 +895,7 @@ int build_sell(int32_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d
     hipLaunchKernelGGL((k_sell_fill<float, int32_t>), dim3(grid), dim3(256), 0, st, n, ns, out.slice_ptr, d_rowptr,
                        d_col, d_val, d_row_scale, (float*)out.val, (int32_t*)out.idx);
   KF_HIP(hipGetLastError());
-  if (stencil)
-    KF_TRY(build_stencil(n, ns, d_rowptr, d_col, d_val, d_row_scale, h.data() + 2 * (size_t)ns, val_bytes, out.nstored,
-                         ib, stencil == kStencilExact, st, out.st));
+  if (stencil && entries) KF_TRY(stencil_form());
   KF_HIP(hipStreamSynchronize(st));
   (void)nnz;
   return KF_OK;
