@@ -163,6 +163,7 @@ struct BatchStack {
   BatchTables h_tb{};    // per-member tables of the next launch (active members of this stack)
   BatchTables* d_tb = nullptr;
   BatchWg* d_wg = nullptr;  // several steps per launch: the workgroups' plans
+  size_t wg_cap = 0;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   int graph_bk = 0;
@@ -190,6 +191,7 @@ struct kf_batch {
     int q;          // member
     int64_t slice0;
     BatchMember m;
+    int width;  // entries of its longest slice
   };
   std::vector<Many> many;  // the second group
   hipStream_t st_many = nullptr;  // and its stream and events (beside the first group's)
@@ -3388,6 +3390,7 @@ void free_stack(BatchStack& k) {
   k.wtab = nullptr;
   dfree(k.d_wg);
   k.d_wg = nullptr;
+  k.wg_cap = 0;
   free_step_buffers(k.sb);
 }
 
@@ -3406,21 +3409,6 @@ void free_batch(kf_batch* bt) {
   delete bt;
 }
 
-// The longest slice (entries) of each member of bt->many in a stack's stencil.
-int member_widths(kf_batch* bt, const SellOp& A, std::vector<int>& width) {
-  std::vector<uint64_t> mask;
-  for (const kf_batch::Many& q : bt->many) {
-    const size_t stride = (size_t)A.st.stride;
-    mask.resize((size_t)q.m.nslices * stride);
-    KF_HIP(hipMemcpy(mask.data(), A.st.mask + (size_t)q.slice0 * stride, mask.size() * sizeof(uint64_t), hipMemcpyDeviceToHost));
-    int w = 0;
-    for (size_t i = 0; i < mask.size(); ++i)
-      if (mask[i]) w = std::max(w, (int)(i % stride) + 1);
-    width.push_back(w);
-  }
-  return KF_OK;
-}
-
 // The plans of the members that take several steps per launch in a stack at
 // block width bk, its workgroups (k.d_wg) and buffers for the rows from m0 on;
 // wgs stays empty where one of the members is better off, or can only be
@@ -3433,29 +3421,40 @@ int plan_many(kf_batch* bt, BatchStack& k, int bk, std::vector<BatchWg>& wgs, in
   for (const kf_batch::Many& q : bt->many) m.push_back(q.m);
   const std::vector<StepsPlan> plans = plan_batch(m, k.A.val_bytes, bk, lds_per_workgroup());
   if (plans.empty()) return KF_OK;
-  std::vector<int> width;
-  KF_TRY(member_widths(bt, k.A, width));
   win = launches = 0;
   std::vector<BatchWg> out;
   for (size_t i = 0; i < m.size(); ++i) {
-    if (width[i] > kBatchStepsWidth) return KF_OK;
+    if (bt->many[i].width > kBatchStepsWidth) return KF_OK;
     const StepsPlan& pl = plans[i];
     win = std::max(win, std::min(m[i].nslices, pl.own + 2 * pl.s * pl.hb));
     launches = std::max(launches, (m[i].L - 1 + pl.s - 1) / pl.s);
     for (int o0 = 0; o0 < m[i].nslices; o0 += pl.own)
-      out.push_back({bt->many[i].q, (int32_t)bt->many[i].slice0, m[i].nslices, o0, pl.own, pl.hb, pl.s, width[i]});
+      out.push_back({bt->many[i].q, (int32_t)bt->many[i].slice0, m[i].nslices, o0, pl.own, pl.hb, pl.s, bt->many[i].width});
   }
-  const size_t bytes = (size_t)(bt->rows - bt->many[0].slice0 * 64) * bk * k.A.val_bytes;
-  dfree(k.sb.Y2);
-  dfree(k.sb.Y3);
-  dfree(k.d_wg);
-  k.sb.Y2 = k.sb.Y3 = nullptr;
-  k.d_wg = nullptr;
-  if (hipMalloc(&k.sb.Y2, bytes) != hipSuccess || hipMalloc(&k.sb.Y3, bytes) != hipSuccess ||
-      hipMalloc(&k.d_wg, out.size() * sizeof(BatchWg)) != hipSuccess) {
-    (void)hipGetLastError();
-    return KF_OK;
+  // (as wide as the first pair, so that narrower blocks find them in place)
+  if (k.sb.pair < bk) {
+    dfree(k.sb.Y2);
+    dfree(k.sb.Y3);
+    k.sb.Y2 = k.sb.Y3 = nullptr;
+    k.sb.pair = 0;
+    const size_t bytes = (size_t)(bt->rows - bt->many[0].slice0 * 64) * k.sb.cap * k.A.val_bytes;
+    if (hipMalloc(&k.sb.Y2, bytes) != hipSuccess || hipMalloc(&k.sb.Y3, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return KF_OK;
+    }
+    k.sb.pair = k.sb.cap;
   }
+  if (k.wg_cap < out.size()) {
+    dfree(k.d_wg);
+    k.d_wg = nullptr;
+    k.wg_cap = 0;
+    if (hipMalloc(&k.d_wg, out.size() * sizeof(BatchWg)) != hipSuccess) {
+      (void)hipGetLastError();
+      return KF_OK;
+    }
+    k.wg_cap = out.size();
+  }
+  KF_HIP(hipStreamSynchronize(bt->st));  // (the last replay may still read the plans)
   KF_HIP(hipMemcpy(k.d_wg, out.data(), out.size() * sizeof(BatchWg), hipMemcpyHostToDevice));
   wgs = std::move(out);
   return KF_OK;
@@ -3710,7 +3709,7 @@ int kf_create_batch(int32_t P, const kf_problem_desc* descs, const kf_options* o
       slices_of[(size_t)q] = padded / 64;
       if (is_many[(size_t)q]) {
         const SellOp& A = bt->probs[(size_t)q]->A;
-        bt->many.push_back({q, row0 / 64, {(int)(padded / 64), (A.max_off + 63) / 64, d.L}});
+        bt->many.push_back({q, row0 / 64, {(int)(padded / 64), (A.max_off + 63) / 64, d.L}, A.st.width});
       }
       tb0.row0[q] = row0;
       tb0.n[q] = n;

@@ -22,7 +22,7 @@ struct Runtime {
   int mallocs = 0, frees = 0, refuse = 0;  // refuse: the refuse-th allocation from now fails
   bool capturing = false;                  // the caller records the problem's stream
   int launches = 0, several = 0, loads = 0;
-  int recordings = 0, dropped = 0, replays = 0, waits = 0;
+  int recordings = 0, dropped = 0, replays = 0, waits = 0, copies_back = 0;
   std::set<int> wide;  // block widths with several steps per launch
   bool recording = false;
 } rt;
@@ -91,6 +91,11 @@ hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, c
 hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return ++rt.replays, hipSuccess; }
 hipError_t hipGraphExecDestroy(hipGraphExec_t) { return ++rt.dropped, hipSuccess; }
 hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipMemcpy(void* dst, const void* src, size_t n, hipMemcpyKind kind) {
+  if (kind == hipMemcpyDeviceToHost) ++rt.copies_back;
+  std::memcpy(dst, src, n);
+  return hipSuccess;
+}
 }
 
 namespace kf {
@@ -104,6 +109,32 @@ StepPlan step_plan(int l, int L) {
   StepPlan sp{};
   sp.mode = l == 1 ? kFirst : l == L - 1 ? kLast : kMid;
   return sp;
+}
+std::vector<StepsPlan> plan_batch(const std::vector<BatchMember>& m, int, int b, size_t) {
+  StepsPlan pl;
+  pl.s = 8, pl.own = b > 2 ? 4 : 2, pl.hb = 1;  // (fewer columns, more workgroups)
+  return rt.wide.count(b) ? std::vector<StepsPlan>(m.size(), pl) : std::vector<StepsPlan>();
+}
+int launch_load_batch(int vb, int64_t rows, int b, const int32_t*, const BatchTables*, const void*, int, void* Y1,
+                      hipStream_t) {
+  check_live(Y1, (size_t)rows * b * vb, "batch: load");
+  return KF_OK;
+}
+int launch_leapfrog_batch(const SellOp&, int, const int32_t*, const BatchTables*, const void*, int, int, const void*,
+                          const void*, void*, void*, const BatchRange&, int, hipStream_t) {
+  ++rt.launches;
+  return KF_OK;
+}
+int launch_steps_batch(const SellOp& A, const BatchWg* wgs, int nwg, int, int b, const BatchTables*, const void*, int, int,
+                       const void* ysrc, const void*, const void*, void* o0, void* o1, void*, int64_t, int64_t,
+                       hipStream_t) {
+  const size_t bytes = (size_t)A.nslices * 64 * b * A.val_bytes;
+  ++rt.several;
+  check_live(wgs, nwg * sizeof(BatchWg), "batch: plans");
+  check_live(ysrc, bytes, "batch: in");
+  check_live(o0, bytes, "batch: out");
+  check_live(o1, bytes, "batch: out");
+  return KF_OK;
 }
 int lanes_per_row(const SellOp&, int) { return 1; }
 int launch_load_block(int vb, int32_t n, int b, int, const double*, int64_t, int64_t, void* dst, hipStream_t) {
@@ -236,6 +267,40 @@ void chunks() {
   check(rt.recordings == 4, "new weights not recorded");
 }
 
+// Widths in turn on a batch of one member that takes several steps per launch:
+// nothing is copied back, and nothing allocated or freed after the widest.
+void batch_widths() {
+  rt.wide = {1, 2, 4};
+  kf_batch bt;
+  BatchStack& k = bt.stk[0];
+  std::vector<uint64_t> mask((size_t)kSlices * 8, 1);  // (16 slices, lists of 8 entries, 5 of them used)
+  for (size_t i = 0; i < mask.size(); ++i)
+    if (i % 8 >= 5) mask[i] = 0;
+  k.A.n = kSlices * 64;
+  k.A.nslices = kSlices;
+  k.A.val_bytes = 8;
+  k.A.st.width = 5;
+  k.A.st.stride = 8;
+  k.A.st.mask = mask.data();
+  bt.P = 1;
+  bt.rows = kSlices * 64;
+  bt.lmax = kSteps;
+  bt.left.assign(kSteps + 1, BatchRange());
+  kf_batch::Many one{};
+  one.m = {kSlices, 1, kSteps};
+  one.width = 5;
+  bt.many.push_back(one);
+  for (int b : {8, 1}) check(ensure_batch_graph(&bt, k, b) == KF_OK, "refused");
+  const int mallocs = rt.mallocs, frees = rt.frees;
+  for (int b : {8, 4, 1, 8, 2}) check(ensure_batch_graph(&bt, k, b) == KF_OK, "refused");
+  check(rt.several > 0, "one step per launch throughout");
+  check(rt.copies_back == 0, "copies back to the host");
+  check(rt.mallocs == mallocs && rt.frees == frees, "allocations after the widest block");
+  free_step_buffers(k.sb);
+  dfree(k.d_wg);
+  check(rt.live.empty(), "blocks left behind");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -246,6 +311,7 @@ int main(int argc, char** argv) {
   else if (s == "no_second_pair_1") no_second_pair(1);
   else if (s == "no_second_pair_2") no_second_pair(2);
   else if (s == "chunks") chunks();
+  else if (s == "batch_widths") batch_widths();
   else check(false, "no such scenario");
   return errors ? 1 : 0;
 }

@@ -40,3 +40,7 @@ def test_step_buffers(program, scenario):
 
 def test_recordings_of_alternating_widths(program):
     _run(program, "chunks")
+
+
+def test_block_widths_of_a_batch(program):
+    _run(program, "batch_widths")
