@@ -86,12 +86,18 @@ __global__ __launch_bounds__(256) void k_stencil(int32_t n, int32_t nslices, con
 // with ROWV the values of the rows.  Every load of a chunk is issued before its
 // sums; rows without an entry gather their own element and multiply it by
 // zero.  W: entries per slice when known (the loop is then unrolled in full),
-// 0: `stride` entries, a multiple of 4.
+// 0: `stride` entries, a multiple of 4, the last ones without rows where the
+// list is shorter.  Where a lane has 64 bytes of a row or more those are left
+// out: a batch gathered 8 rows for 5 or 7 of them, and was slower so than over
+// stored entries.  Batched application, blocks of 16 in float64: 3 members 1732
+// -> 1349 us (stored entries 1584), 16 members 13.98 -> 11.87 ms (14.21).  Below
+// 64 bytes the branches cost what they save.
 template <typename T, int B, int BL, int LPR, int W, bool ROWV>
 __device__ __forceinline__ void stencil_product(const T* __restrict__ val, const int32_t* __restrict__ off,
                                                 const uint64_t* __restrict__ mask, int stride, int slice, int rin,
                                                 int row, const T* __restrict__ x, int col0, T (&sum)[BL]) {
   constexpr int U = W > 0 && BL * sizeof(T) <= 16 ? W : (W == 15 ? 5 : 4);
+  constexpr bool leave_out = W == 0 && BL * sizeof(T) >= 64;
   const int64_t base = (int64_t)slice * (W > 0 ? W : stride);
   auto chunk = [&](int q0) {
     T a[U];
@@ -117,11 +123,12 @@ __device__ __forceinline__ void stencil_product(const T* __restrict__ val, const
       if (W > 0 && q0 + u >= W) continue;
       has[u] = LPR == 1 ? __builtin_amdgcn_inverse_ballot_w64(m[u]) : ((m[u] >> rin) & 1ull) != 0ull;
       const int c = row + (has[u] ? o[u] : 0);
-      xv[u] = *reinterpret_cast<const Row<T, BL>*>(x + (int64_t)c * B + col0);
+      if (!leave_out || m[u] != 0) xv[u] = *reinterpret_cast<const Row<T, BL>*>(x + (int64_t)c * B + col0);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (W > 0 && q0 + u >= W) continue;
+      if (leave_out && m[u] == 0) continue;
       const T au = ROWV || has[u] ? a[u] : (T)0;
 #pragma unroll
       for (int j = 0; j < BL; ++j) sum[j] = fma(au, xv[u].v[j], sum[j]);
@@ -299,14 +306,23 @@ __global__ __launch_bounds__(256) void k_leapfrog_batch_st(BatchRange rg, const 
   // the accumulation schedule of the single-problem steps (step_plan)
   const int u = ell >= 2 ? 1 + 3 * ((ell - 2) / 3) : 1;  // latest update before this step
   const bool sums = first || last || ell - u == 3;
-  const V yc = reinterpret_cast<const V*>(cur)[row];
-  V yp = yc, r = yc;
-  if (!first) yp = reinterpret_cast<const V*>(prev)[row];
-  if (sums && !first) r = reinterpret_cast<const V*>(acc)[row];
+  V yc, yp, r;
+  const auto own_rows = [&]() {
+    yc = yp = r = reinterpret_cast<const V*>(cur)[row];
+    if (!first) yp = reinterpret_cast<const V*>(prev)[row];
+    if (sums && !first) r = reinterpret_cast<const V*>(acc)[row];
+  };
+  // (as in k_leapfrog_st; 5 % on blocks of 16 in float64)
+  constexpr bool early = sizeof(V) < 64;
+  if (early) own_rows();
   T sum[B];
 #pragma unroll
   for (int j = 0; j < B; ++j) sum[j] = (T)0;
   stencil_product<T, B, B, 1, 0, ROWV>(val, soff, mask, stride, slice, lane, row, cur, 0, sum);
+  if (!early) {
+    asm volatile("" ::: "memory");
+    own_rows();
+  }
   V nx;
 #pragma unroll
   for (int j = 0; j < B; ++j) nx.v[j] = (T)2 * yc.v[j] - yp.v[j] - sum[j];
