@@ -25,6 +25,8 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -919,13 +921,23 @@ int kf_mlp_train(kf_mlp* net, const double* samples, int32_t n, const int32_t* o
     }
   }
   if (epoch_loss) {
-    std::vector<float> Jh((size_t)nJ);
-    KF_HIP(hipMemcpyAsync(Jh.data(), net->Jrun, sizeof(float) * (size_t)nJ, hipMemcpyDeviceToHost, net->st));
-    KF_HIP(hipStreamSynchronize(net->st));
-    for (int e = 0; e < epochs; ++e) {
-      double acc = 0.0;
-      for (int64_t i = 0; i < (int64_t)steps * batch; ++i) acc += Jh[(size_t)((int64_t)e * steps * batch + i)];
-      epoch_loss[e] = acc / ((double)steps * batch);
+    // (a long run's losses come back 16 MB at a time)
+    const int64_t per = (int64_t)steps * batch, most = std::min<int64_t>(nJ, 1 << 22);
+    float* Jh = new (std::nothrow) float[(size_t)most];
+    if (!Jh) return mfail(KF_ENOMEM, "kf_mlp_train: host allocation");
+    std::unique_ptr<float[]> hold(Jh);
+    double acc = 0.0;
+    for (int64_t i = 0; i < nJ; ++i) {
+      if (i % most == 0) {
+        KF_HIP(hipMemcpyAsync(Jh, net->Jrun + i, sizeof(float) * (size_t)std::min(most, nJ - i), hipMemcpyDeviceToHost,
+                              net->st));
+        KF_HIP(hipStreamSynchronize(net->st));
+      }
+      acc += Jh[i % most];
+      if ((i + 1) % per == 0) {
+        epoch_loss[i / per] = acc / ((double)steps * batch);
+        acc = 0.0;
+      }
     }
   }
   KF_HIP(hipStreamSynchronize(net->st));
