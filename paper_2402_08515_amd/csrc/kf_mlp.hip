@@ -926,18 +926,19 @@ int kf_mlp_train(kf_mlp* net, const double* samples, int32_t n, const int32_t* o
     float* Jh = new (std::nothrow) float[(size_t)most];
     if (!Jh) return mfail(KF_ENOMEM, "kf_mlp_train: host allocation");
     std::unique_ptr<float[]> hold(Jh);
-    double acc = 0.0;
-    for (int64_t i = 0; i < nJ; ++i) {
-      if (i % most == 0) {
-        KF_HIP(hipMemcpyAsync(Jh, net->Jrun + i, sizeof(float) * (size_t)std::min(most, nJ - i), hipMemcpyDeviceToHost,
-                              net->st));
-        KF_HIP(hipStreamSynchronize(net->st));
+    int64_t from = 0, to = 0;  // the losses in the block
+    for (int e = 0; e < epochs; ++e) {
+      double acc = 0.0;
+      for (int64_t i = e * per, end = i + per; i < end;) {
+        if (i == to) {
+          from = to;
+          to = std::min(nJ, from + most);
+          KF_HIP(hipMemcpyAsync(Jh, net->Jrun + from, sizeof(float) * (size_t)(to - from), hipMemcpyDeviceToHost, net->st));
+          KF_HIP(hipStreamSynchronize(net->st));
+        }
+        for (const int64_t stop = std::min(end, to); i < stop; ++i) acc += Jh[i - from];
       }
-      acc += Jh[i % most];
-      if ((i + 1) % per == 0) {
-        epoch_loss[i / per] = acc / ((double)steps * batch);
-        acc = 0.0;
-      }
+      epoch_loss[e] = acc / ((double)steps * batch);
     }
   }
   KF_HIP(hipStreamSynchronize(net->st));
