@@ -208,8 +208,9 @@ typedef struct kf_options {
                             weighted sum in LDS and advances s steps per
                             launch.  0 = one step per launch (default),
                             except that operators stepped as stencils (see
-                            index_bytes) take several, for blocks and the
-                            fourth-order scheme too, where that is faster;
+                            index_bytes) of 5 or 7 offsets, or with a value per
+                            row of 5 to 8 or 15, take several, for blocks and
+                            the fourth-order scheme too, where that is faster;
                             the results are the same;
                             s > 0 = s steps per launch; -1 = the whole filter
                             in one launch.  KF_EINVAL from the solve or

@@ -517,16 +517,16 @@ int device_weights(kf_problem* p, const std::vector<double>& w, const double** o
 
 // The recorded steps 3 .. L - 2 of an application (step(l, stream) launches
 // one), or null: launch them.  The host needs 3 to 4 us for a launch, a small
-// problem's step 2.4 to 3: replayed, 39 steps of the 41-cell cube take 97
-// instead of 147 us (107 instead of 225 where each application is waited for),
-// its fourth-order steps in blocks of 3 232 instead of 339, 60 cells 132
-// instead of 155; where a level has 7 MB (96 cells) the steps outlast the
-// host, 284 and 290.  Recording 39 steps takes 0.6 ms, what six applications
-// gain: it is done at the record_at-th application with the same weights and
-// width, the second of a solve, which will run many, the sixth where the caller
-// applies the filter and in the subspace iterations, which may end early.  Each
-// width has a recording of its own: an iteration over 36 columns applies blocks
-// of 16, 16 and 4.
+// problem's step 2.4 to 3: replayed, 39 steps of the 41-cell cube take 92
+// instead of 112 us (108 instead of 159 where each application is waited for),
+// 41 of its fourth-order steps in blocks of 3 233 instead of 253, 39 on 60 cells
+// 126 instead of 131; where a level has 7 MB (96 cells) the steps outlast the
+// host, 284 and 290.  Recording 39 steps takes 0.5 ms, what 10 to 25 applications
+// of the 41-cell cube gain: it is done at the record_at-th application with the
+// same weights and width, the second of a solve, which will run many, the sixth
+// where the caller applies the filter and in the subspace iterations, which may
+// end before it pays.  Each width has a recording of its own: an iteration over
+// 36 columns applies blocks of 16, 16 and 4.
 constexpr int kRecordSolve = 2, kRecordOther = 6;
 template <class Step>
 hipGraphExec_t step_graph(kf_problem* p, const SellOp& A, StepBufs& sb, int bk, const std::vector<double>& w,

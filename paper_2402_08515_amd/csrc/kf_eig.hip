@@ -7,7 +7,7 @@
 //   1. Householder reduction of H to tridiagonal form (one launch per
 //      reflector, the last 128 and small matrices in one workgroup; the
 //      reflectors stay in the lower triangle of the work matrix);
-//   2. all eigenvalues by Sturm-count bisection, one lane per eigenvalue;
+//   2. all eigenvalues by Sturm-count bisection, one wavefront per eigenvalue;
 //   3. eigenvectors for the selected eigenvalues only, by inverse iteration
 //      on the tridiagonal matrix (LU with partial pivoting), re-orthogonalised
 //      inside clusters of nearly equal values;

@@ -23,7 +23,8 @@ namespace {
 // (wave, wave + 16, ...: at most R) in registers, with the places of their
 // stencil neighbours in LDS; absent neighbours point at a zero.  A step then
 // is W LDS reads, W products and one LDS write per row and one barrier.  Row
-// values (ROWV) stay in registers through all steps, which limits R.  The
+// values (ROWV) are read again in every step, from the caches; kept in registers
+// through all steps, as four slices of 15 each would be, they spill.  The
 // halo slices are computed by every workgroup that needs them; with the whole
 // problem in one workgroup there are none.  The weighted sum takes one term
 // per step, in the same order as three terms every third step: results are
@@ -319,7 +320,9 @@ int launch_steps(const SellOp& A, const StepsPlan& pl, int b, int s, bool first,
   return pl.order4 ? launch_steps_o<true>(A, pl, cols, g, w, st) : launch_steps_o<false>(A, pl, cols, g, w, st);
 }
 
-// The rule: the time of a filter application by the figures measured on
+// The rule, for the lists the kernel is built for (5 or 7 offsets, with row
+// values up to 8 stored in 8, or 15; other lists take one step per launch): the
+// time of a filter application by the figures measured on
 // squares of 32 to 600 and cubes of 13 to 33 cells (within 10 % of every
 // measurement while a wavefront has at most four slices), in us:
 //   a launch        3.7 + 0.03 per slice of the window (0.06 for 16-byte rows)
