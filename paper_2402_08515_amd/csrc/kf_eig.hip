@@ -738,10 +738,11 @@ __global__ __launch_bounds__(256) void k_bisect(int m, const double* __restrict_
 // and latency of a single wavefront's chain: one division per row in the
 // factorisation, one multiply-add per row forward and two operations backward;
 // the rows are read kIvB ahead, with the normalisation of an iterate applied
-// by the next sweep's reads.  The squares of its norm are taken of the iterate
-// times a power of two of about the matrix's norm: its entries are about the
-// norm's inverse over eps, whose squares leave the range of a double where the
-// norm is below 2^-460 or above 2^560.  110 vectors of order 440: 560 us with two
+// by the next sweep's reads.  Pivots are kept
+// at eps times the norm at least, a swapped row's off-diagonal too.  Where the
+// squares of an iterate's norm leave the range of a double (its entries are about
+// 1 / (eps norm)) they are summed again, of the iterate times a power of two.
+// 110 vectors of order 440: 560 us with two
 // divisions per row, several lanes' arrays interleaved and separate passes for
 // the norms, 232 us so.
 constexpr int kIvB = 8;
@@ -800,7 +801,7 @@ __global__ __launch_bounds__(64) void k_invit(int m, const double* __restrict__ 
       const double piv = sw ? be : a;
       const double l = (sw ? a : be) / (piv == 0.0 ? 1.0 : piv);
       const double v1 = sw ? ad : b;
-      rinv[i] = !sw && fabs(a) < tiny ? (a < 0.0 ? -tiny : tiny) : piv;
+      rinv[i] = fabs(piv) < tiny ? (piv < 0.0 ? -tiny : tiny) : piv;
       lm[i] = l;
       u1[i] = v1;
       u2[i] = sw ? ce : 0.0;
@@ -846,7 +847,6 @@ __global__ __launch_bounds__(64) void k_invit(int m, const double* __restrict__ 
   for (int i = lane; i < m; i += 64) rinv[i] = 1.0 / rinv[i];
   __syncthreads();
   double rs = 1.0;  // what normalises the iterate in z
-  const double unit = 1.0 / bounds[3];  // (an exact power of two)
   if (lane == 0) {
     for (int it = 0; it < 3; ++it) {
       // forward: row swaps and elimination
@@ -891,7 +891,7 @@ __global__ __launch_bounds__(64) void k_invit(int m, const double* __restrict__ 
         auto row = [&](int i, double zi, double v1, double v2, double r) {
           const double x = (fma(-v2, x2, zi) - v1 * x1) * r;
           z[i] = x;
-          nrm = fma(x * unit, x * unit, nrm);
+          nrm = fma(x, x, nrm);
           x2 = x1;
           x1 = x;
         };
@@ -921,6 +921,19 @@ __global__ __launch_bounds__(64) void k_invit(int m, const double* __restrict__ 
           for (int u = 0; u < kIvB; ++u) row(i0 - u, zv[u], v1[u], v2[u], rv[u]);
         }
         for (; i0 >= 0; --i0) row(i0, z[i0], u1[i0], u2[i0], rinv[i0]);
+      }
+      double unit = 1.0;
+      if (!(nrm > 0x1p-900 && nrm < 0x1p1000)) {
+        double mx = 0.0;
+        for (int i = 0; i < m; ++i) mx = fmax(mx, fabs(z[i]));
+        int ex = 0;
+        (void)frexp(mx, &ex);
+        unit = ldexp(1.0, min(max(-ex, -1000), 1000));
+        nrm = 0.0;
+        for (int i = 0; i < m; ++i) {
+          const double x = z[i] * unit;
+          nrm = fma(x, x, nrm);
+        }
       }
       rs = nrm > 0.0 ? unit / sqrt(nrm) : 0.0;
     }

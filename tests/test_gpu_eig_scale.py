@@ -86,3 +86,20 @@ def test_eigenvectors_of_diagonal_matrices_of_any_scale(k, exponent):
     assert Y.shape == (k, sel.size) and sel.size >= k // 2
     assert np.abs(d[:, None] * Y - Y * sel).max() <= 1e-11 * 2.0
     assert np.abs(Y.T @ Y - np.eye(sel.size)).max() <= 1e-10
+
+
+@pytest.mark.parametrize("off", [1e-100, 1e-160, 1e-200, 1e-290])
+@pytest.mark.parametrize("k", [3, 20, 50, 300])
+def test_eigenvectors_beside_tiny_off_diagonals(k, off):
+    """Where a shift equals a diagonal entry, the off-diagonal below it is the
+    pivot and its inverse the largest entry of the iterate, however tiny."""
+    from paper_2402_08515_amd import kf
+
+    print(f"case sym_eig off-diagonal {off} k={k}", flush=True)
+    d = np.random.default_rng(k).standard_normal(k)
+    A = np.diag(d) + np.diag(np.full(k - 1, off), 1) + np.diag(np.full(k - 1, off), -1)
+    theta, Y = kf.sym_eig(A, -10.0, 10.0, vectors=True)
+    np.testing.assert_allclose(theta, np.sort(d), atol=1e-14)
+    assert Y.shape == (k, k)
+    assert np.abs(A @ Y - Y * theta).max() <= 1e-11 * np.abs(d).max()
+    assert np.abs(Y.T @ Y - np.eye(k)).max() <= 1e-10
